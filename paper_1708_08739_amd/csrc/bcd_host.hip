@@ -128,12 +128,12 @@ void Workspace::release() {
   dfree(S.dout);
   dfree(S.vis);
   dfree(S.fr);
-  dfree(S.rec);
-  dfree(S.bt);
+  dfree(S.msk);
   dfree(S.items);
   dfree(S.imask);
   dfree(S.cnt);
   dfree(S.off);
+  dfree(S.tail);
   dfree(S.tmin);
   dfree(S.tgt_of);
   dfree(S.res);
@@ -205,8 +205,8 @@ bcd_status Workspace::ensure_batch(int G_) {
   // the previous width's arrays, or what an earlier call that failed part
   // way left allocated (every free is a no-op on a null pointer)
   release_weighted();
-  dfree(S.sig); dfree(S.psi); dfree(S.dout); dfree(S.vis); dfree(S.fr); dfree(S.rec); dfree(S.bt);
-  dfree(S.items); dfree(S.imask); dfree(S.cnt); dfree(S.off); dfree(S.tmin);
+  dfree(S.sig); dfree(S.psi); dfree(S.dout); dfree(S.vis); dfree(S.fr); dfree(S.msk);
+  dfree(S.items); dfree(S.imask); dfree(S.cnt); dfree(S.off); dfree(S.tail); dfree(S.tmin);
   dfree(S.tgt_of); dfree(S.res); dfree(S.ctr); dfree(S.acc); dfree(S.flags); dfree(S.ovl);
   dfree(d_items0); dfree(d_masks0); dfree(d_dest0); dfree(d_lane_slot); hfree(h_items0); hfree(h_masks0);
   hfree(h_dest0); hfree(h_res);
@@ -225,21 +225,26 @@ bcd_status Workspace::ensure_batch(int G_) {
     STCHK(dalloc(&S.vis, GN));
     STCHK(dalloc(&S.fr, 3 * GN));
   } else {
-    STCHK(dalloc(&S.rec, GN));
+    STCHK(dalloc(&S.msk, M_COUNT * GN));
   }
-  STCHK(dalloc(&S.bt, 2 * GN));
   S.P = std::min(kMaxParts, G);
+  S.NL = lists(S.P);
+  S.H = graph->heavy;
   S.capP = ((uint64_t)GN * 16 + (uint64_t)S.P - 1) / (uint64_t)S.P;
-  S.cap = S.capP * (uint64_t)S.P;
-  STCHK(dalloc(&S.items, S.cap));
-  STCHK(dalloc(&S.imask, S.cap));
-  const size_t levels = ((size_t)n + kLevelChunkMax + 4) * kMaxParts;
+  // a (group, vertex) is an item at most once per level and on at most 64
+  // levels, so the heavy lists cannot overflow
+  S.capH = (uint64_t)((G + S.P - 1) / S.P) * S.H * kLanes;
+  S.hbase = S.capP * (uint64_t)S.P;
+  STCHK(dalloc(&S.items, S.hbase + S.capH * S.P));
+  STCHK(dalloc(&S.imask, S.hbase + S.capH * S.P));
+  const size_t levels = ((size_t)n + kLevelChunkMax + 4) * kMaxLists;
   STCHK(dalloc(&S.cnt, levels));
   STCHK(dalloc(&S.off, levels));
+  STCHK(dalloc(&S.tail, (size_t)4 * kMaxLists * kTailStride));
   STCHK(dalloc(&S.tmin, 4));
   STCHK(dalloc(&S.tgt_of, (size_t)n));
   STCHK(dalloc(&S.flags, 4));
-  STCHK(dalloc(&S.ovl, (size_t)G));
+  STCHK(dalloc(&S.ovl, 2 * (size_t)G));
   S.ctr_slots = kCtrSlots;
   STCHK(dalloc(&S.ctr, (size_t)kCtrSlots * C_COUNT));
   STCHK(dalloc(&S.acc, (size_t)C_COUNT));
@@ -260,15 +265,13 @@ bcd_status Workspace::ensure_batch(int G_) {
   HIPCHK(hipMemsetAsync(S.sig, 0, GN * kLanes * sizeof(uint64_t), stream));
   if (S.vis) HIPCHK(hipMemsetAsync(S.vis, 0, GN * sizeof(uint64_t), stream));
   if (S.fr) HIPCHK(hipMemsetAsync(S.fr, 0, 3 * GN * sizeof(uint64_t), stream));
-  if (S.rec) HIPCHK(hipMemsetAsync(S.rec, 0, GN * sizeof(MaskRec), stream));
-  HIPCHK(hipMemsetAsync(S.bt, 0, 2 * GN * sizeof(LevMask), stream));
+  if (S.msk) HIPCHK(hipMemsetAsync(S.msk, 0, M_COUNT * GN * sizeof(uint64_t), stream));
   HIPCHK(hipMemsetAsync(S.cnt, 0, levels * sizeof(uint32_t), stream));
   HIPCHK(hipMemsetAsync(S.off, 0, levels * sizeof(uint64_t), stream));
   HIPCHK(hipMemsetAsync(S.tgt_of, 0xFF, (size_t)n * sizeof(int32_t), stream));
   HIPCHK(hipMemsetAsync(S.flags, 0, 4 * sizeof(uint32_t), stream));
   HIPCHK(hipMemsetAsync(S.ctr, 0, (size_t)kCtrSlots * C_COUNT * sizeof(uint64_t), stream));
   HIPCHK(hipStreamSynchronize(stream));
-  S.epoch = 0;
   sig_zero = true;
   batch_ready = true;
   return BCD_OK;
@@ -277,22 +280,26 @@ bcd_status Workspace::ensure_batch(int G_) {
 
 void Workspace::stage_sources(const int32_t *src, int k) {
   for (int i = 0; i < k; ++i) {
-    h_items0[i] = (uint32_t)((uint64_t)(i / kLanes) * (uint64_t)n + (uint64_t)src[i]);
+    h_items0[i] = (uint32_t)((uint64_t)(i / kLanes) * (uint64_t)n + (uint64_t)graph->rank[(size_t)src[i]]);
     h_masks0[i] = 1ull << (i % kLanes);
   }
   staged = k;
   stage_sources_dest(k);
 }
 
-// Level-0 slot of every staged item in its group's partition.
+// Level-0 slot of every staged item in its list of its group's partition.
 void Workspace::stage_sources_dest(int k) {
-  uint32_t fill[kMaxParts] = {0};
-  const int P = batch_parts(k);
+  uint32_t fill[kMaxLists] = {0};
+  BatchState T = S;
+  T.P = batch_parts(k);
+  T.NL = lists(T.P);
   for (int i = 0; i < k; ++i) {
-    const int p = (i / kLanes) % P;
-    h_dest0[i] = (uint32_t)((uint64_t)p * S.capP + fill[p]++);
+    const int p = (i / kLanes) % T.P;
+    const uint64_t v = h_items0[i] - (uint64_t)(i / kLanes) * (uint64_t)n;
+    const int l = v < T.H ? T.P + p : p;
+    h_dest0[i] = (uint32_t)(list_begin(T, l) + fill[l]++);
   }
-  for (int p = 0; p < kMaxParts; ++p) h_cnt0[p] = fill[p];
+  for (int l = 0; l < kMaxLists; ++l) h_cnt0[l] = fill[l];
 }
 
 bcd_status Workspace::ensure_res(size_t need) {
@@ -337,12 +344,12 @@ bcd_status Workspace::grow_items() {
   dfree(S.items);
   dfree(S.imask);
   S.capP = ncapP;
-  S.cap = S.capP * (uint64_t)S.P;
+  S.hbase = S.capP * (uint64_t)S.P;
   // if an allocation fails the workspace must not be reused as it stands:
   // the next ensure_batch rebuilds every array
   batch_ready = false;
-  STCHK(dalloc(&S.items, S.cap));
-  STCHK(dalloc(&S.imask, S.cap));
+  STCHK(dalloc(&S.items, S.hbase + S.capH * S.P));
+  STCHK(dalloc(&S.imask, S.hbase + S.capH * S.P));
   batch_ready = true;
   return BCD_OK;
 }
@@ -356,8 +363,8 @@ bcd_status Workspace::reset_batch_dense() {
   sig_zero = true;
   if (S.vis) HIPCHK(hipMemsetAsync(S.vis, 0, GN * sizeof(uint64_t), stream));
   if (S.fr) HIPCHK(hipMemsetAsync(S.fr, 0, 3 * GN * sizeof(uint64_t), stream));
-  if (S.rec) HIPCHK(hipMemsetAsync(S.rec, 0, GN * sizeof(MaskRec), stream));
-  HIPCHK(hipMemsetAsync(S.cnt, 0, ((size_t)n + kLevelChunkMax + 4) * kMaxParts * sizeof(uint32_t), stream));
+  if (S.msk) HIPCHK(hipMemsetAsync(S.msk, 0, M_COUNT * GN * sizeof(uint64_t), stream));
+  HIPCHK(hipMemsetAsync(S.cnt, 0, ((size_t)n + kLevelChunkMax + 4) * kMaxLists * sizeof(uint32_t), stream));
   HIPCHK(hipMemsetAsync(S.flags, 0, 4 * sizeof(uint32_t), stream));
   HIPCHK(hipMemsetAsync(S.ctr, 0, (size_t)kCtrSlots * C_COUNT * sizeof(uint64_t), stream));
   if (weighted_ready) {
@@ -425,6 +432,11 @@ Graph::~Graph() {
   dfree(d_col);
   dfree(d_irp);
   dfree(d_icol);
+  dfree(d_prp);
+  dfree(d_pcol);
+  dfree(d_pirp);
+  dfree(d_picol);
+  dfree(d_orig);
   dfree(d_arcw);
   dfree(d_arcp);
   dfree(d_iarc);
@@ -438,15 +450,33 @@ DevGraph Graph::dev() const {
   G.col = d_col;
   G.irp = d_irp;
   G.icol = d_icol;
-  G.arcw = d_arcw;
-  G.arcp = d_arcp;
-  G.iarc = d_iarc;
+  G.arcw = G.arcp = G.iarc = nullptr;
+  G.orig = nullptr;
   return G;
 }
 
-Launch Graph::launch_parts(int P) const {
+DevGraph Graph::dev_internal() const {
+  DevGraph G;
+  G.n = n;
+  G.m = m;
+  G.rp = d_prp;
+  G.col = d_pcol;
+  G.irp = d_pirp;
+  G.icol = d_picol;
+  G.arcw = d_arcw;
+  G.arcp = d_arcp;
+  G.iarc = d_iarc;
+  G.orig = d_orig;
+  return G;
+}
+
+// Launch of a batch of `groups` column groups on P partitions: a wavefront per
+// (group, vertex) is as many as any level can use.
+Launch Graph::launch_parts(int P, int groups) const {
   Launch L = launch();
-  if (P > 1) L.grid = std::max(P, L.grid - L.grid % P);
+  const uint64_t waves = (uint64_t)groups * (uint64_t)n, per = (uint64_t)(L.block / 64);
+  L.grid = (int)std::min<uint64_t>((uint64_t)L.grid, (waves + per - 1) / per);
+  L.grid = std::max(2 * P, L.grid - L.grid % P);  // two workgroups a partition at least (ListView)
   return L;
 }
 
@@ -632,22 +662,80 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
     HIPCHK(hipMemcpy(g->d_col, col, (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(g->d_icol, icol.data(), (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice));
   }
+  // internal ids: vertices by falling total degree (a counting sort, ties by
+  // the caller's id), and both CSRs renamed to them, rows kept in arc order
+  std::vector<int32_t> orig((size_t)n);
+  g->rank.resize((size_t)n);
+  {
+    auto deg = [&](int64_t v) {
+      return row_ptr[v + 1] - row_ptr[v] + irp[(size_t)v + 1] - irp[(size_t)v];
+    };
+    int64_t top = 0;
+    for (int64_t v = 0; v < n; ++v) top = std::max(top, deg(v));
+    std::vector<int64_t> at((size_t)top + 2, 0);  // at[d]: vertices of degree > d so far placed before d
+    for (int64_t v = 0; v < n; ++v) at[(size_t)deg(v)]++;
+    int64_t before = 0;
+    for (int64_t d = top; d >= 0; --d) {
+      const int64_t c = at[(size_t)d];
+      at[(size_t)d] = before;
+      before += c;
+    }
+    for (int64_t v = 0; v < n; ++v) {
+      const int64_t i = at[(size_t)deg(v)]++;
+      orig[(size_t)i] = (int32_t)v;
+      g->rank[(size_t)v] = (int32_t)i;
+    }
+    if (!weight)
+      while (g->heavy < (uint64_t)(n / kHeavyShare) && deg(orig[g->heavy]) > kHeavyArcs) ++g->heavy;
+  }
+  std::vector<int64_t> prp((size_t)n + 1, 0), pirp((size_t)n + 1, 0);
+  for (int64_t i = 0; i < n; ++i) {
+    const size_t v = (size_t)orig[(size_t)i];
+    prp[(size_t)i + 1] = prp[(size_t)i] + row_ptr[v + 1] - row_ptr[v];
+    pirp[(size_t)i + 1] = pirp[(size_t)i] + irp[v + 1] - irp[v];
+  }
+  STCHK(dalloc(&g->d_prp, (size_t)n + 1));
+  STCHK(dalloc(&g->d_pirp, (size_t)n + 1));
+  STCHK(dalloc(&g->d_orig, (size_t)n));
+  HIPCHK(hipMemcpy(g->d_prp, prp.data(), ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(g->d_pirp, pirp.data(), ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(g->d_orig, orig.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
   if (weight) {
     STCHK(dalloc(&g->d_arcw, (size_t)m));
     STCHK(dalloc(&g->d_arcp, (size_t)m));
     STCHK(dalloc(&g->d_iarc, (size_t)m));
     if (m > 0) {
-      std::vector<uint2> arcw((size_t)m), arcp((size_t)m);
-      std::vector<uint2> iarc((size_t)m);
-      for (int64_t e = 0; e < m; ++e) {
-        arcw[(size_t)e] = make_uint2((uint32_t)col[e], weight[e]);
-        arcp[(size_t)e] = make_uint2((uint32_t)col[e], ipos[(size_t)e]);
-        iarc[(size_t)e] = make_uint2((uint32_t)icol[(size_t)e], iw[(size_t)e]);
+      std::vector<uint2> arcw((size_t)m), arcp((size_t)m), iarc((size_t)m);
+      for (int64_t i = 0; i < n; ++i) {
+        const size_t v = (size_t)orig[(size_t)i];
+        size_t p = (size_t)prp[(size_t)i];
+        for (int64_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e, ++p) {
+          const size_t w = (size_t)col[e], j = (size_t)g->rank[w];
+          arcw[p] = make_uint2((uint32_t)j, weight[e]);
+          // an in-arc keeps its place in its row of the transpose
+          arcp[p] = make_uint2((uint32_t)j, (uint32_t)(pirp[j] + ((int64_t)ipos[(size_t)e] - irp[w])));
+        }
+        p = (size_t)pirp[(size_t)i];
+        for (int64_t e = irp[v]; e < irp[v + 1]; ++e, ++p)
+          iarc[p] = make_uint2((uint32_t)g->rank[(size_t)icol[(size_t)e]], iw[(size_t)e]);
       }
       HIPCHK(hipMemcpy(g->d_arcw, arcw.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
       HIPCHK(hipMemcpy(g->d_arcp, arcp.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
       HIPCHK(hipMemcpy(g->d_iarc, iarc.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
     }
+  } else {
+    STCHK(dalloc(&g->d_pcol, (size_t)m));
+    STCHK(dalloc(&g->d_picol, (size_t)m));
+    int32_t *d_rank = nullptr;
+    STCHK(dalloc(&d_rank, (size_t)n));
+    hipError_t e = hipMemcpy(d_rank, g->rank.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+      e = launch_permute_rows(n, g->d_rp, g->d_col, g->d_prp, g->d_orig, d_rank, g->d_pcol, nullptr);
+    if (e == hipSuccess)
+      e = launch_permute_rows(n, g->d_irp, g->d_icol, g->d_pirp, g->d_orig, d_rank, g->d_picol, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    dfree(d_rank);
+    if (e != hipSuccess) return hip_fail(e, "internal vertex order");
   }
   g->cfg.engine = BCD_ENGINE_BATCHED;
   g->cfg.groups = default_groups(n, weight != nullptr);

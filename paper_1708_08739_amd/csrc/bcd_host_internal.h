@@ -51,7 +51,14 @@ inline int default_bottom_up(int64_t n) { return n >= (int64_t(1) << 19) ? 4 : 0
 // (1) instead of pulling them over in-arcs (0).
 constexpr int kDefaultPush = 0;
 constexpr int kMaxParts = 8;          // item-list partitions (one per XCD)
-constexpr int kCntStage = (kLevelChunkMax + 2) * kMaxParts;  // pinned slots for level counts
+constexpr int kCntStage = (kLevelChunkMax + 2) * kMaxLists;  // pinned slots for level counts
+// Vertices with more arcs than this (in- and out-arcs together) are taken by
+// a whole workgroup in the unweighted engine, at most one vertex in
+// kHeavyShare, so that their item lists stay small.  The limit is flat from 128
+// to 1,024 (R-MAT 16, 1,000 sources: 3.42 / 3.40 / 3.36 / 3.38 ms at 128 / 256 /
+// 512 / 1,024) and too high at 2,048 (3.82).
+constexpr int64_t kHeavyArcs = 512;
+constexpr int64_t kHeavyShare = 256;
 
 bcd_status fail(bcd_status s, const std::string &msg);
 bcd_status fail_static(bcd_status s, const char *msg);  // records the message without allocating
@@ -101,7 +108,7 @@ struct Workspace {
   uint32_t *h_items0 = nullptr;
   unsigned long long *h_masks0 = nullptr;
   uint32_t *h_dest0 = nullptr;
-  uint32_t h_cnt0[8] = {0};  // level-0 items per partition of the staged batch
+  uint32_t h_cnt0[kMaxLists] = {0};  // level-0 items per list of the staged batch
   double *h_res = nullptr;
   int last_depth = 8;
   // plain engine
@@ -145,6 +152,7 @@ struct Workspace {
   // runs source vertex src[i]; vertices must be distinct within a group.
   void stage_sources(const int32_t *src, int k);
   void stage_sources_dest(int k);
+  int lists(int P) const { return weighted_graph ? P : 2 * P; }  // item lists of a batch on P partitions
   // Partitions a batch of k staged sources uses: its groups are 0..ceil(k/64)-1
   // and group g belongs to partition g % P, so a batch of fewer groups than
   // S.P uses one partition per group and no workgroup is left without work.
@@ -174,7 +182,15 @@ struct Graph {
   int32_t *d_col = nullptr;
   int64_t *d_irp = nullptr;
   int32_t *d_icol = nullptr;
-  uint2 *d_arcw = nullptr;     // weighted: {head, length} per CSR arc
+  // the same graph in internal ids (DevGraph): rank[v] = internal id of v
+  std::vector<int32_t> rank;
+  uint32_t heavy = 0;          // internal ids below are heavy (0 on weighted graphs)
+  int64_t *d_prp = nullptr;
+  int32_t *d_pcol = nullptr;   // unweighted
+  int64_t *d_pirp = nullptr;
+  int32_t *d_picol = nullptr;  // unweighted
+  int32_t *d_orig = nullptr;
+  uint2 *d_arcw = nullptr;     // weighted, internal ids: {head, length} per CSR arc
   uint2 *d_arcp = nullptr;     // weighted: {head, transpose position} per CSR arc
   uint2 *d_iarc = nullptr;     // weighted: {tail, length} per transpose arc
   mutable std::mutex cfg_mu;
@@ -193,9 +209,10 @@ struct Graph {
   bcd_status mark_profile_origin();
 
   ~Graph();
-  DevGraph dev() const;
+  DevGraph dev() const;           // caller's vertex ids
+  DevGraph dev_internal() const;  // internal ids (batched and weighted engines)
   Launch launch() const;
-  Launch launch_parts(int P) const;  // grid a multiple of P
+  Launch launch_parts(int P, int groups) const;  // grid a multiple of P
   bcd_config config() const;
   std::unique_ptr<Workspace> acquire();
   void release(std::unique_ptr<Workspace> w);
@@ -226,6 +243,7 @@ struct SourceRun {
 
 struct TargetMap {
   Workspace *ws;
+  std::vector<int32_t> ids;  // internal ids, kept until the copy has been read
   int32_t *d_verts = nullptr;
   int k = 0;
   bool set = false;
@@ -245,7 +263,9 @@ struct TargetMap {
       d_verts = nullptr;
       return fail(BCD_ERR_OUT_OF_MEMORY, "target list allocation failed");
     }
-    HIPCHK(hipMemcpyAsync(d_verts, tgt.data(), (size_t)k * sizeof(int32_t), hipMemcpyHostToDevice, ws->stream));
+    ids = tgt;
+    for (int32_t &v : ids) v = ws->graph->rank[(size_t)v];
+    HIPCHK(hipMemcpyAsync(d_verts, ids.data(), (size_t)k * sizeof(int32_t), hipMemcpyHostToDevice, ws->stream));
     HIPCHK(launch_scatter_targets(ws->S.tgt_of, d_verts, k, 1, ws->stream));
     set = true;
     return BCD_OK;

@@ -9,22 +9,16 @@ namespace bcd {
 
 constexpr int kLanes = 64;  // sources per column group = wavefront width on gfx950
 
-// Entry of the backward pass's level-tagged mask table: which lanes of a
-// vertex sit on level `lev` of batch `epoch`.
-struct __align__(16) LevMask {
-  unsigned long long mask;
-  uint32_t lev;
-  uint32_t epoch;
-};
-
-// All level masks of one (group, vertex) of the unweighted engine in one
-// 64-byte record, so the test "is w settled for these sources" and the flag
-// for the next level touch a single cache line per arc.
-struct __align__(64) MaskRec {
-  unsigned long long vis;    // lanes settled on a level < current (lagging, see the forward kernel)
-  unsigned long long fr[4];  // rotating level masks: current, next, previous, retiring
-  unsigned long long dn;     // lanes on whose shortest-path DAG the vertex is a target or lies below one
-  unsigned long long pad[2];
+// Lane masks of the unweighted engine: one 64-bit word per (group, vertex) in
+// each of these arrays, which follow each other in BatchState::msk.  A word
+// array keeps 8 vertices to a 64-byte line, and as internal ids run by falling
+// degree, the words of the vertices most arcs lead to are neighbours.
+enum MaskArray {
+  M_SEEN = 0,  // lanes settled, or flagged for the level being discovered
+  M_FR = 1,    // 1..4: lanes of a level, by level mod 4 (current, next, previous, retiring)
+  M_DN = 5,    // lanes on whose shortest-path DAG the vertex is a target or lies below one
+  M_BW = 6,    // 6..8: lanes of a level the backward computed, by level mod 3
+  M_COUNT = 9
 };
 
 // Counters accumulated per workgroup slot (no atomics), reduced on the host.
@@ -54,35 +48,41 @@ struct BatchState {
   unsigned long long *sig;   // [G][n][64] path counts
   double *psi;               // [G][n][64] (1 + delta) / sigma
   double *dout;              // [G][n][64] delta, verification hook only (may be null)
-  MaskRec *rec;              // [G][n] level masks (unweighted engine)
+  unsigned long long *msk;   // [M_COUNT][G][n] lane masks (unweighted engine, see MaskArray)
   unsigned long long *vis;   // [G][n] reached lanes (weighted engine)
   unsigned long long *fr;    // [3][G][n] rotating round masks (weighted engine)
-  LevMask *bt;               // [2][G][n] backward level masks, by level parity
   // Item lists are split into P partitions (group g belongs to partition
   // g % P); workgroup b serves partition b % P, so with P = 8 every XCD
   // (workgroups are dealt to the 8 XCDs round-robin) walks only its own
-  // groups and their masks stay in that XCD's L2.  Partition p owns items
-  // [p * capP, (p + 1) * capP).
-  uint32_t *items;           // [cap] g * n + v, grouped by partition, then level
-  unsigned long long *imask; // [cap] lanes of the item on its level
-  uint64_t cap;              // = P * capP
-  uint64_t capP;
+  // groups and their masks stay in that XCD's L2.  The unweighted engine
+  // keeps two lists per partition and level: list p holds the vertices a
+  // wavefront takes alone, list P + p the heavy ones (internal id < H), which
+  // a workgroup takes together; the weighted engine keeps list p only.
+  uint32_t *items;           // [P * capP + P * capH] g * n + v, grouped by list, then level
+  unsigned long long *imask; // the same shape: lanes of the item on its level
+  uint64_t hbase;            // first item of the heavy lists (P * capP of the widest batch)
+  uint64_t capP;             // items of list p: [p * capP, (p + 1) * capP)
+  uint64_t capH;             // items of list P + p: [hbase + p * capH, hbase + (p + 1) * capH)
   int P;
-  uint32_t *cnt;             // [(n + 2) * 8] items per (level, partition): index level * P + p
-  uint64_t *off;             // [(n + 2) * 8] first item of each (level, partition)
+  int NL;                    // lists: 2 P (unweighted) or P (weighted)
+  uint32_t H;                // heavy vertices: internal ids 0 .. H-1 (unweighted engine)
+  uint32_t *cnt;             // [(n + 2) * 16] items per (level, list): index level * NL + l
+  uint32_t *tail;            // [4][16] lengths of the lists being filled, by level mod 4, each in a
+                             // 128-byte line of its own (see tail_at)
+  uint64_t *off;             // [(n + 2) * 16] first item of each (level, list)
   uint32_t *tmin;            // [1] smallest over all lanes
   int32_t *tgt_of;           // [n] target index of a vertex, -1 if none
   double *res;               // [ntgt][G][64] delta of lane on target
   uint64_t *ctr;             // [grid][C_COUNT] per-workgroup counters
   uint64_t *acc;             // [C_COUNT] counters of completed batches
   uint32_t *flags;           // [4]: 0 sigma overflow, 1 item capacity exceeded
-  unsigned long long *ovl;   // [G] lanes whose sigma overflowed
-  uint32_t epoch;
+  unsigned long long *ovl;   // [G] lanes whose sigma overflowed, then [G] lanes whose source is a target
   int ctr_slots;
   // per batch (unweighted engine)
   int gused;                     // column groups holding sources: 0 .. gused-1
   unsigned long long last_lanes; // lanes of group gused-1 that hold a source
   int bu_den;                    // bottom-up levels: see level_bottom_up (0 = never)
+  int top;                       // deepest level of the batch (set before the backward)
   int keep_all;                  // 1: the backward runs on every lane (exports), else only below a target
   int push;                      // 1: top-down levels push path counts along DAG arcs (k_fwd_push), 0: pull
   // weighted graphs only
@@ -113,6 +113,11 @@ struct PlainState {
   int ctr_slots;
 };
 
+// The graph as kernels see it, in the caller's vertex ids (reachability, the
+// plain and LDS engines) or in internal ids (batched and weighted engines).
+// Internal ids number the vertices by falling total degree, so that heavy
+// vertices are told by an id comparison; every row keeps its arcs in the
+// caller's order, so sums over a row run in the same order either way.
 struct DevGraph {
   int64_t n, m;
   const int64_t *rp;    // [n+1]
@@ -125,6 +130,7 @@ struct DevGraph {
   const uint2 *arcw;    // [m] CSR order: {head, length} (relaxation)
   const uint2 *arcp;    // [m] CSR order: {head, position of the arc in the transpose} (sigma, backward)
   const uint2 *iarc;    // [m] transpose order: {tail, length} (DAG in-degrees)
+  const int32_t *orig;  // [n] caller's id of an internal id (exports)
 };
 
 // Whether BFS level `level` (>= 2) of a batch is found bottom-up, from the
@@ -139,21 +145,39 @@ __host__ __device__ inline bool bottom_up_rule(int bu_den, int level, uint64_t p
 struct Launch {
   int block;      // threads per workgroup
   int grid;       // workgroups
-  int items = 1;  // frontier items per wavefront step (unweighted forward)
+  int items = 1;  // items per wavefront step (bottom-up and pushed levels)
 };
 
 // ---- launchers (bcd_kernels.hip) ----
+constexpr int kMaxLists = 16;  // two per partition
 struct PartTotals {
-  uint64_t t[8];  // items per partition over all levels of a batch
+  uint64_t t[kMaxLists];  // items per list over all levels of a batch
 };
+// Length of list l of a level while the level is being filled and read.  Every
+// workgroup reads these words at the start of a launch and appends to the next
+// level's through atomics from its own XCD, so neighbours in one line cost
+// both sides: with a level's counters packed beside the next level's, a
+// 601-vertex graph's levels took up to 156 us, with a line each up to 28.
+constexpr int kTailStride = 32;
+__host__ __device__ inline uint32_t *tail_at(const BatchState &S, int level, int l) {
+  return S.tail + ((level & 3) * kMaxLists + l) * kTailStride;
+}
+// First item of list l's region.
+__host__ __device__ inline uint64_t list_begin(const BatchState &S, int l) {
+  return l < S.P ? (uint64_t)l * S.capP : S.hbase + (uint64_t)(l - S.P) * S.capH;
+}
+__host__ __device__ inline uint64_t list_end(const BatchState &S, int l) {
+  return list_begin(S, l) + (l < S.P ? S.capP : S.capH);
+}
 hipError_t launch_batch_init(const BatchState &S, const uint32_t *items0, const unsigned long long *masks0,
                              const uint32_t *dest0, int k, hipStream_t st);
 hipError_t launch_fwd_level(const DevGraph &G, const BatchState &S, int level, Launch L, hipStream_t st);
+// cnt row of a level that is filled but whose launch has not run yet
+hipError_t launch_publish_counts(const BatchState &S, int level, hipStream_t st);
 hipError_t launch_bu_level(const DevGraph &G, const BatchState &S, int level, Launch L, hipStream_t st);
-hipError_t launch_bwd_level(const DevGraph &G, const BatchState &S, int level, int ntgt, int full,
-                            Launch L, hipStream_t st);
+hipError_t launch_bwd_level(const DevGraph &G, const BatchState &S, int level, int ntgt, Launch L, hipStream_t st);
 hipError_t launch_batch_cleanup(const BatchState &S, const PartTotals &tot, Launch L, hipStream_t st);
-hipError_t launch_batch_export(const BatchState &S, int level, uint64_t begin, uint64_t count,
+hipError_t launch_batch_export(const DevGraph &G, const BatchState &S, int level, uint64_t begin, uint64_t count,
                                const int32_t *lane_slot, uint64_t *dist, unsigned long long *sigma,
                                double *delta, int64_t k, hipStream_t st);
 
@@ -180,6 +204,10 @@ hipError_t launch_reach_bu(const int64_t *rp, const int32_t *col, const int64_t 
 hipError_t launch_scatter_targets(int32_t *tgt_of, const int32_t *verts, int k, int set, hipStream_t st);
 hipError_t launch_plain_gather(const PlainState &P, const int32_t *verts, int k, int32_t *d_out,
                                double *delta_out, hipStream_t st);
+// Rows of a CSR in internal order: row i of the new one holds the arcs of row
+// orig[i] in the same order, their ends renamed by rank.
+hipError_t launch_permute_rows(int64_t n, const int64_t *rp, const int32_t *col, const int64_t *nrp,
+                               const int32_t *orig, const int32_t *rank, int32_t *ncol, hipStream_t st);
 // weighted engine (bcd_weighted.hip)
 hipError_t launch_w_init(const BatchState &S, const uint32_t *items0, const unsigned long long *masks0,
                          const uint32_t *dest0, int k, hipStream_t st);
@@ -189,7 +217,7 @@ hipError_t launch_w_sigma(const DevGraph &G, const BatchState &S, int round, Lau
 hipError_t launch_w_bwd(const DevGraph &G, const BatchState &S, int round, int ntgt, int full, Launch L,
                         hipStream_t st);
 hipError_t launch_w_cleanup(const BatchState &S, Launch L, hipStream_t st);
-hipError_t launch_w_export(const BatchState &S, const int32_t *lane_slot, uint64_t *dist,
+hipError_t launch_w_export(const DevGraph &G, const BatchState &S, const int32_t *lane_slot, uint64_t *dist,
                            unsigned long long *sigma, double *delta, int64_t k, Launch L, hipStream_t st);
 struct ResultRoute {
   double *dst;      // device address in a query's result buffer

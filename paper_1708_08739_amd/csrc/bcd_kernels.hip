@@ -6,11 +6,9 @@
 // Batched engine layout: a column group is 64 sources, one per wavefront
 // lane.  A frontier item is (group g, vertex v) with a 64-bit mask of the
 // lanes for which v sits on the current BFS level; lane b works for source b,
-// so the 64 path counts of v are one coalesced 512-byte row.  The settled
-// lanes and the rotating level masks of (g, v) share one 64-byte record, so
-// testing "has source b already settled w" for all 64 sources reads one
-// line per arc.  A wavefront takes 1, 2 or 4 items per step (their first
-// arcs in separate slots of lanes) to keep several items' loads in flight.
+// so the 64 path counts of v are one coalesced 512-byte row, and testing "has
+// source b already settled w" for all 64 sources reads one 64-bit word per
+// arc.
 #include <algorithm>
 
 #include "bcd_device.h"
@@ -25,338 +23,461 @@ __global__ void k_batch_init(BatchState S, const uint32_t *items0, const ull *ma
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
     const uint32_t it = items0[i];
     const ull m = masks0[i];
-    S.rec[it].fr[0] = m;  // level-0 masks
+    const uint64_t GN = (uint64_t)S.G * (uint64_t)S.n;
+    S.msk[M_FR * GN + it] = m;  // level-0 masks
+    S.msk[M_SEEN * GN + it] = m;
+    const uint32_t g = it / (uint32_t)S.n;
+    if (S.tgt_of[it - g * (uint32_t)S.n] >= 0) atomicOr(&S.ovl[S.G + g], m);
     S.items[dest0[i]] = it;
     for (int b = 0; b < kLanes; ++b)
       if ((m >> b) & 1ull) S.sig[(size_t)it * kLanes + b] = 1ull;
   }
-  // level-0 item-list base of every partition of this batch
-  if (blockIdx.x == 0 && threadIdx.x < (unsigned)S.P) S.off[threadIdx.x] = (uint64_t)threadIdx.x * S.capP;
+  // level-0 base of every item list of this batch
+  if (blockIdx.x == 0 && threadIdx.x < (unsigned)S.NL) {
+    const int l = (int)threadIdx.x;
+    S.off[l] = list_begin(S, l);
+    *tail_at(S, 0, l) = S.cnt[l];
+    *tail_at(S, 1, l) = 0u;
+    *tail_at(S, 2, l) = 0u;
+  }
 }
 
-// Sum of sigma_b(u) over the in-arcs held by one chunk of lanes whose tail u
-// is on the previous level for lane b (pm = lanes of that arc).  The chunk
-// holds the arcs of up to K items, 64 / K lanes each (arc lane l belongs to
-// the item of slot l / (64 / K), whose group base is in lane l's gbase), and
-// an arc adds into its item's accumulator.  With HIT, hit[t] is also set on
-// every lane that received a count for item t (the bottom-up kernel's test
-// of which lanes reached the level).  Row loads of up to eight
-// predecessors are issued before any of them is consumed; the sums are
-// exact integers, so the order of the adds does not matter, and an
-// unsigned wrap on any add means the true sum exceeds 2^64 - 1.
-template <int K, bool HIT = false>
-static __device__ __forceinline__ void pull_slots(const BatchState &S, uint64_t gbase, uint32_t u, ull pm, int lane,
-                                                  ull (&acc)[K], bool (&lov)[K], bool (&hit)[K], uint64_t &dag_pairs) {
-  constexpr int SUB = kLanes / K;
-  ull bits = __ballot(pm != 0ull);
-  while (bits != 0ull) {
-    int j[8];
-    int c = 0;
-    for (; c < 8 && bits != 0ull; ++c) {
-      j[c] = __ffsll((long long)bits) - 1;
-      bits &= bits - 1ull;
-    }
-    // each row load writes its own register, so all eight stay in flight
-    ull x[8];
+// Predecessor rows of a chunk of arc lanes, up to eight at a time: arc lane j
+// holds the tail u and the lanes pm for which that arc is a DAG arc (bits:
+// the arc lanes not taken yet), gb is the first item of the wavefront's
+// group.  issue() starts the loads of the next eight rows; add() adds them
+// into acc (this lane's source).  The sums are exact: eight counts below 2^60
+// on top of a sum below 2^60 cannot pass 2^64, and where one is larger every
+// add is checked for a carry (the true sum then exceeds 2^64 - 1), its lanes
+// going to ov.  got collects the lanes that received a count.  bits, pm, u
+// and gb are wave-uniform or read by lane number, so all address work is
+// scalar.
+struct Rows {
+  ull x[8];
+  __device__ __forceinline__ void issue(const ull *sig, uint32_t gb, uint32_t u, ull pm, ull &bits, ull &got,
+                                        uint64_t &dag_pairs) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = 0ull;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      x[q] = 0ull;
-      if (q < c) {
-        const uint32_t uq = read_lane(u, j[q]);
-        const ull dq = read_lane64(pm, j[q]);
-        const uint64_t gq = read_lane64(gbase, j[q]);
-        dag_pairs += (uint64_t)__popcll(dq);  // wave-uniform
-        if ((dq >> lane) & 1ull) x[q] = S.sig[(gq + uq) * kLanes + lane];
+      if (bits != 0ull) {
+        const int j = __builtin_ctzll(bits);
+        bits &= bits - 1ull;
+        const ull dq = read_lane64(pm, j);
+        const ull *row = sig + (uint64_t)(gb + read_lane(u, j)) * kLanes;
+        dag_pairs += (uint64_t)__popcll(dq);
+        got |= dq;
+        if (__builtin_amdgcn_inverse_ballot_w64(dq)) x[q] = row[lane];
       }
     }
-    if (HIT) {
+  }
+  __device__ __forceinline__ void add(ull &acc, ull &ov) {
+    uint32_t hi = (uint32_t)(acc >> 32);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) hi |= (uint32_t)(x[q] >> 32);
+    if (__ballot(hi >> 28 != 0u) == 0ull) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc += x[q];
+    } else {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        if (q < c && ((read_lane64(pm, j[q]) >> lane) & 1ull)) {
-          const int slot = j[q] / SUB;
-#pragma unroll
-          for (int t = 0; t < K; ++t)
-            if (slot == t) hit[t] = true;
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const ull xq = x[q];
-      if (q < c) {
-        const int slot = j[q] / SUB;
-#pragma unroll
-        for (int t = 0; t < K; ++t) {
-          if (slot == t) {
-            const ull sum = acc[t] + xq;
-            if (sum < acc[t]) lov[t] = true;
-            acc[t] = sum;
-          }
-        }
+        const ull sum = acc + x[q];
+        ov |= __ballot(sum < acc);
+        acc = sum;
       }
     }
   }
+};
+
+static __device__ __forceinline__ void pull_rows(const ull *sig, uint32_t gb, uint32_t u, ull pm, ull &acc, ull &ov,
+                                                 ull &got, uint64_t &dag_pairs) {
+  ull bits = __ballot(pm != 0ull);
+  while (bits != 0ull) {
+    Rows r;
+    r.issue(sig, gb, u, pm, bits, got, dag_pairs);
+    r.add(acc, ov);
+  }
 }
 
-// OR of x over the lanes of each item slot (lane l in slot l / (64 / K)),
-// into wave-uniform out[]; x must be set on every lane.
-template <int K>
-static __device__ __forceinline__ void or_slots(ull x, ull (&out)[K]) {
-  constexpr int SUB = kLanes / K;
-  ull b = __ballot(x != 0ull);
+// OR of x over the wavefront (wave-uniform result).
+static __device__ __forceinline__ ull wave_or(ull x) {
+  ull out = 0ull, b = __ballot(x != 0ull);
   while (b != 0ull) {
-    const int j = __ffsll((long long)b) - 1;
-    b &= b - 1ull;
+    const int j = __builtin_ctzll(b);
     const ull v = read_lane64(x, j);
-#pragma unroll
-    for (int t = 0; t < K; ++t)
-      if (j / SUB == t) out[t] |= v;
+    out |= v;
+    b &= b - 1ull;
+    // arcs that add nothing new are skipped
+    b &= __ballot((x & ~out) != 0ull);
   }
+  return out;
 }
 
-// Discovered heads are staged in a per-wavefront LDS buffer and copied to
-// the next level's list in blocks: one counter atomic per block instead of
-// one per out-arc chunk, which keeps the partition's tail counter cold.
-constexpr int kStage = 256;
+// Discovery over one chunk of out-arc lanes: `dag` = the item's lanes not yet
+// seen at head w (0 on lanes without an arc).  One atomicOr marks them seen;
+// the lanes it was the first to set are on the next level, and the first
+// wavefront to flag (g, w) there appends it.  Returns whether this lane's
+// head is to be appended.
+static __device__ __forceinline__ bool discover(ull *seen, ull *next, uint32_t w, ull dag) {
+  bool enq = false;
+  if (dag != 0ull) {
+    const ull fresh = dag & ~atomicOr(&seen[w], dag);
+    if (fresh != 0ull) enq = atomicOr(&next[w], fresh) == 0ull;
+  }
+  return enq;
+}
 
-static __device__ __forceinline__ void flush_stage(const BatchState &S, uint32_t *stage, int &nst,
-                                                   uint32_t *next_cnt, uint64_t nbase, uint64_t rend) {
-  if (nst == 0) return;
+// Discovered heads are staged in per-wavefront LDS buffers, one for the
+// light list and one for the heavy list of the partition, and copied to the
+// next level's lists in blocks: one counter atomic per block instead of one
+// per out-arc chunk, which keeps the lists' tail counters cold.
+constexpr int kStage = 256;
+constexpr int kStageHeavy = 64;
+
+// Most items a wavefront takes as one block (level launches).
+constexpr int kBlockItems = 32;
+
+struct Stage {
+  uint32_t *buf, *hbuf;  // this wavefront's LDS buffers
+  int n, nh;             // entries staged
+};
+
+// First item of list l of the level being built: behind `level`'s items (BU:
+// of `level` itself, whose list the bottom-up kernel fills).  Read again at
+// every flush, which is rare, so that no registers hold it in between.
+template <bool BU>
+static __device__ __forceinline__ uint64_t next_base(const BatchState &S, int level, int l) {
+  return S.off[(uint64_t)level * S.NL + l] + (BU ? 0u : *tail_at(S, level, l));
+}
+
+template <bool BU>
+static __device__ __forceinline__ void flush_list(const BatchState &S, int level, int l, const uint32_t *buf, int &n) {
+  if (n == 0) return;
+  const uint64_t base = next_base<BU>(S, level, l), end = list_end(S, l);
   uint32_t p0 = 0;
-  if (lane_id() == 0) p0 = atomicAdd(next_cnt, (uint32_t)nst);
+  if (lane_id() == 0) p0 = atomicAdd(tail_at(S, level + (BU ? 0 : 1), l), (uint32_t)n);
   p0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)p0);
-  for (int j = lane_id(); j < nst; j += 64) {
-    const uint64_t p = nbase + p0 + (uint64_t)j;
-    if (p < rend) S.items[p] = stage[j];
+  for (int j = lane_id(); j < n; j += 64) {
+    const uint64_t p = base + p0 + (uint64_t)j;
+    if (p < end) S.items[p] = buf[j];
     else atomicOr(&S.flags[1], 1u);
   }
-  nst = 0;
+  n = 0;
 }
 
-static __device__ __forceinline__ void append_chunk(const BatchState &S, uint32_t *stage, int &nst,
-                                                    uint32_t *next_cnt, uint64_t nbase, uint64_t rend,
-                                                    uint64_t gbase, uint32_t w, bool enq) {
-  const ull eb = __ballot(enq);
+template <bool BU>
+static __device__ __forceinline__ void flush_stage(const BatchState &S, int level, int p, Stage &g) {
+  flush_list<BU>(S, level, p, g.buf, g.n);
+  flush_list<BU>(S, level, S.P + p, g.hbuf, g.nh);
+}
+
+// First thing of a level's top-down launch (one thread per partition): the
+// level's counts go to its cnt row, the next level's lists start behind it and
+// the tails of the level after that are cleared.
+static __device__ __forceinline__ void open_level(const BatchState &S, int level, int p, uint32_t nl, uint32_t nh,
+                                                  uint64_t nb, uint64_t nhb) {
+  const uint64_t row = (uint64_t)level * S.NL + p, next = row + S.NL;
+  S.cnt[row] = nl;
+  S.cnt[row + S.P] = nh;
+  S.off[next] = nb;
+  S.off[next + S.P] = nhb;
+  *tail_at(S, level + 2, p) = 0u;
+  *tail_at(S, level + 2, S.P + p) = 0u;
+}
+
+__global__ void k_publish_counts(BatchState S, int level) {
+  const int l = (int)threadIdx.x;
+  if (l < S.NL) S.cnt[(uint64_t)level * S.NL + l] = *tail_at(S, level, l);
+}
+
+// Append the heads w of the lanes where `enq` holds to partition p's lists.
+template <bool BU>
+static __device__ __forceinline__ void append_chunk(const BatchState &S, int level, int p, Stage &g, uint64_t gbase,
+                                                    uint32_t w, bool enq) {
+  ull eb = __ballot(enq);
   if (eb == 0ull) return;
+  const ull hb = __ballot(enq && w < S.H);
+  if (hb != 0ull) {
+    const int c = __popcll(hb);
+    if (g.nh + c > kStageHeavy) flush_list<BU>(S, level, S.P + p, g.hbuf, g.nh);
+    if (enq && w < S.H) g.hbuf[g.nh + lanes_below(hb)] = (uint32_t)(gbase + w);
+    g.nh += c;
+    eb &= ~hb;
+    if (eb == 0ull) return;
+  }
   const int c = __popcll(eb);
-  if (nst + c > kStage) flush_stage(S, stage, nst, next_cnt, nbase, rend);
-  if (enq) stage[nst + lanes_below(eb)] = (uint32_t)(gbase + w);
-  nst += c;
+  if (g.n + c > kStage) flush_list<BU>(S, level, p, g.buf, g.n);
+  if (enq && w >= S.H) g.buf[g.n + lanes_below(eb)] = (uint32_t)(gbase + w);
+  g.n += c;
 }
 
 // One BFS level of the batched forward pass (unweighted graphs).  For every
 // item (g, v, mask) on `level`:
 //   1. sigma pull: sigma_b(v) = sum of sigma_b(u) over in-arcs (u, v) with u
 //      on level-1 for lane b (the shortest-path-DAG predecessors of v), an
-//      exact uint64 sum with a carry check on every add; no atomics;
-//   2. discovery: for every out-arc (v, w), lanes b in mask for which w is
-//      not settled on a level <= `level` are DAG arcs; they are flagged on
-//      (g, w) for level+1 with one atomicOr per arc, lanes over arcs, and
-//      the first flagger appends (g, w) to the next level's item list.
-// A wavefront takes K items per step: each item's first 64 / K in-arcs and
-// out-arcs sit in its own slot of lanes, so the dependent loads of K items
-// (item -> mask and CSR bounds -> arc heads -> head masks -> flags and
-// predecessor rows) are in flight together; arcs past the first 64 / K of
-// an item are then taken 64 at a time by the whole wavefront.
-// Level masks rotate over four words of the (g, v) record: cur (level), nxt
-// (level+1, being built), prv (level-1, read by the pull) and old (level-2,
-// retired here).  vis lags: the owner of (g, v) ORs cur into vis during this
-// launch, so a reader sees vis | cur, which is the same union either way.
-// With bottom-up levels enabled, step 1 is skipped when the level was found
-// by k_bu_level (which pulled the counts), and step 2 when level+1 will be;
-// the item masks are recorded for the backward either way.
-// At least 6 waves per SIMD: with the below-target marks, asking for 7
-// (72 VGPRs) made the compiler spill 44 bytes per lane and measured 3.5 %
-// slower at R-MAT 16 (5 waves: 2 % slower).
-template <int BLOCK, int K>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_fwd_level(DevGraph G,
-                                                                                                 BatchState S,
-                                                                                                 int level) {
-  constexpr int SUB = kLanes / K;
-  const uint64_t n = (uint64_t)S.n;
-  const int P = S.P;
+//      exact uint64 sum; no atomics;
+//   2. discovery: for every out-arc (v, w), lanes b in mask not yet seen at w
+//      are DAG arcs; they are marked seen and flagged for level+1, lanes over
+//      arcs, and the first flagger appends (g, w) to the next level's list.
+// Level masks rotate over four words of (g, v): cur (level), nxt (level+1,
+// being built), prv (level-1, read by the pull) and old (level-2, retired
+// here).  With bottom-up levels enabled, step 1 is skipped when the level was
+// found by k_bu_level (which pulled the counts), and step 2 when level+1 will
+// be; the item masks are recorded for the backward either way.
+//
+// Light items: a wavefront takes a block of up to 64, loads their masks and
+// row bounds with a lane per item, then takes them one after the other in
+// steps of 32 in-arcs (lower half of the wavefront) and 32 out-arcs (upper
+// half), one gather bringing the words of all of them.  The arc ends of the
+// step after next and the words of the next one are loaded while the current
+// step's rows are added, so a step costs the latency of its rows and flags,
+// not of the whole chain item -> bounds -> arc ends -> words -> rows.
+// Heavy vertices (more than kHeavyArcs arcs, internal id < H) are on a list
+// of their own, whose items a workgroup takes one at a time: its wavefronts
+// share the item's steps and add their partial path counts in LDS.  A
+// wavefront alone walks a hub's thousands of arcs as one serial chain of
+// dependent loads, and every level waits for its largest hub.
+// Bound by the latency and rate of random accesses, not by HBM bandwidth (R-MAT
+// 16, 1,000 sources: 56 % of the cycles of resident waves wait for memory, 1
+// TB/s fetched).  A level with two items a step, 64-byte mask records and no
+// heavy list took, summed over the levels of R-MAT 16 / 20 with 1,000 sources,
+// 3.0 / 36 ms; as here 1.9 / 24.
+// At least 7 waves per SIMD (72 VGPRs): left alone the compiler takes 88
+// registers for 5 (R-MAT 16 exact 40.7 against 41.9 ms, 8 waves 42.3).
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_fwd_level(DevGraph G, BatchState S, int level) {
+  constexpr int NW = BLOCK / 64;
+  const uint32_t n = (uint32_t)S.n;
+  const uint64_t GN = (uint64_t)S.G * n;
+  const int P = S.P, NL = S.NL;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t base = S.off[(uint64_t)level * P + pv.p];
-  const uint64_t count = S.cnt[(uint64_t)level * P + pv.p];
-  const uint64_t nbase = base + count;
-  const uint64_t rend = (uint64_t)(pv.p + 1) * S.capP;
-  if (pv.thread == 0) S.off[(uint64_t)(level + 1) * P + pv.p] = nbase;
-  // capacity exceeded (the batch is redone); the test is the same for every
-  // thread of the workgroup, so no wave leaves before the counter barrier
-  if (nbase > rend) return;
+  const uint64_t lrow = (uint64_t)level * NL, nrow = lrow + NL;
+  __shared__ uint32_t stage_all[NW * kStage], hstage_all[NW * kStageHeavy];
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
+  {
+    const uint32_t nl = *tail_at(S, level, pv.p), nh = *tail_at(S, level, P + pv.p);
+    const uint64_t nb = S.off[lrow + pv.p] + nl, nhb = S.off[lrow + P + pv.p] + nh;
+    if (pv.thread == 0) open_level(S, level, pv.p, nl, nh, nb, nhb);
+    if ((nl | nh) == 0u) return;  // no lanes left in this partition's groups
+    // capacity exceeded (the batch is redone); the test is the same for every
+    // thread of the workgroup, so no wave leaves before the counter barrier
+    if (nb > list_end(S, pv.p) || nhb > list_end(S, P + pv.p)) return;
+  }
   const int lane = lane_id();
-  const int sl = lane % SUB;  // lane within its item slot
-  MaskRec *rec = S.rec;
-  const int kc = level & 3, kn = (level + 1) & 3, ko = (level + 2) & 3, kp = (level + 3) & 3;
+  ull *seen = S.msk + M_SEEN * GN;
+  const ull *cur = S.msk + (M_FR + (level & 3)) * GN;
+  ull *nxt = S.msk + (M_FR + ((level + 1) & 3)) * GN;
+  const ull *prv = S.msk + (M_FR + ((level + 3) & 3)) * GN;
 
   // retire the masks of level-2 so that word can collect level+2
   if (level >= 2) {
-    const uint64_t pb = S.off[(uint64_t)(level - 2) * P + pv.p];
-    const uint64_t pc = S.cnt[(uint64_t)(level - 2) * P + pv.p];
-    for (uint64_t i = pv.thread; i < pc; i += pv.nthreads) rec[S.items[pb + i]].fr[ko] = 0ull;
+    ull *old = S.msk + (M_FR + ((level + 2) & 3)) * GN;
+    for (int l = pv.p; l < NL; l += P) {
+      const uint64_t pb = S.off[lrow - 2 * NL + l], pc = S.cnt[lrow - 2 * NL + l];
+      for (uint64_t i = pv.thread; i < pc; i += pv.nthreads) old[S.items[pb + i]] = 0ull;
+    }
   }
-  // This launch pulls sigma for the level's items (and settles their lanes)
-  // unless the bottom-up kernel already found them with their counts, and
-  // discovers level+1 unless that level will be found bottom-up.  Both
-  // tests read complete counts, so every workgroup decides alike.
-  uint64_t prev = 0;
-  if (level >= 1)
-    for (int p = 0; p < P; ++p) prev += S.cnt[(uint64_t)(level - 1) * P + p];
-  uint64_t cur = 0;
-  for (int p = 0; p < P; ++p) cur += S.cnt[(uint64_t)level * P + p];
-  const bool pull = !bottom_up_rule(S.bu_den, level, prev, S.gused, S.n);
-  const bool disc = !bottom_up_rule(S.bu_den, level + 1, cur, S.gused, S.n);
+  // This launch pulls sigma for the level's items unless the bottom-up kernel
+  // already found them with their counts, and discovers level+1 unless that
+  // level will be found bottom-up.  Both tests read complete counts, so every
+  // workgroup decides alike.
+  bool pull = true, disc = true;
+  if (S.bu_den > 0) {
+    uint64_t prev = 0, here = 0;
+    if (level >= 1)
+      for (int l = 0; l < NL; ++l) prev += S.cnt[lrow - NL + l];
+    for (int l = 0; l < NL; ++l) here += *tail_at(S, level, l);
+    pull = !bottom_up_rule(S.bu_den, level, prev, S.gused, S.n);
+    disc = !bottom_up_rule(S.bu_den, level + 1, here, S.gused, S.n);
+  }
+  // Level 1 needs no pull: lane b's only level-0 vertex is its source and no
+  // arc is repeated, so each lane of an item has the one predecessor: sigma is
+  // 1, and v lies below a target iff the source is one (S.ovl[G + g]).  Level 1
+  // holds the hubs, whose thousands of in-arcs would be read for one tail each
+  // (R-MAT 20, 1,000 sources: the level takes 2.5 ms with the pull, 2.2 without).
+  const bool rows = level > 1 && pull;
 
   // counters, all wave-uniform: (source, vertex), (source, arc) and
   // (source, DAG arc) pairs; items and the out-degree sum over items
   uint64_t c_v = 0, c_a = 0, c_d = 0, c_it = 0, c_ia = 0;
   bool ovf = false;
-  const uint64_t step = pv.nwaves * (uint64_t)K;
-  uint32_t *next_cnt = &S.cnt[(uint64_t)(level + 1) * P + pv.p];
-  __shared__ uint32_t stage_all[(BLOCK / 64) * kStage];
-  uint32_t *stage = stage_all + (threadIdx.x >> 6) * kStage;
-  int nst = 0;
-  uint64_t ii = pv.wave * (uint64_t)K + (uint64_t)(lane / SUB);  // this lane's item
-  uint32_t it_next = ii < count ? S.items[base + ii] : 0u;
-  for (uint64_t i0 = pv.wave * (uint64_t)K; i0 < count; i0 += step, ii += step) {
-    const bool has = ii < count;
-    const uint32_t it = it_next;
-    if (ii + step < count) it_next = S.items[base + ii + step];  // prefetch the next step's items
-    const uint32_t g = (uint32_t)(it / n);
-    const uint32_t v = (uint32_t)(it - (uint64_t)g * n);
-    const uint64_t gbase = (uint64_t)g * n;
-    // independent loads of this slot's item, issued together
-    ull mask = 0ull;
-    int64_t e0 = 0, e1 = 0, f0 = 0, f1 = 0;
-    int32_t tg = -1;
-    if (has) {
-      mask = rec[it].fr[kc];
-      e0 = G.rp[v];
-      e1 = G.rp[v + 1];
-      if (level > 0 && pull) {
-        f0 = G.irp[v];
-        f1 = G.irp[v + 1];
+  const ListView lv = list_view(S);
+  const uint64_t base = S.off[lrow + (lv.heavy ? P : 0) + pv.p];
+  const uint64_t count = *tail_at(S, level, (lv.heavy ? P : 0) + pv.p);
+  // light: a block holds as many items as give every wavefront one block, at
+  // most kBlockItems, and its wavefront takes every step; heavy: a workgroup
+  // per item, wavefront wv takes every NW-th step
+  const uint64_t nwv = lv.heavy ? lv.nwg : lv.nwg * NW;
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  const uint32_t cstart = lv.heavy ? 32u * wv : 0u, cstep = lv.heavy ? 32u * NW : 32u;
+  const bool upper = lane >= 32;
+  const uint32_t k32 = (uint32_t)lane & 31u;
+  __shared__ ull red_acc[NW][kLanes], red_ov[NW], red_dn[NW];
+  for (uint64_t b0 = (lv.heavy ? lv.wg : lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
+    const int nb = (int)min((uint64_t)B, count - b0);
+    // a lane per item: its lanes, where its rows start and how long they
+    // are, and whether it is a target
+    uint32_t it = 0, gb = 0, e0 = 0, ed = 0, f0 = 0, fd = 0;
+    ull mk = 0ull, dnr = 0ull;
+    bool tgt = false;
+    if (lane < nb) {
+      it = S.items[base + b0 + lane];
+      const uint32_t g = it / n, v = it - g * n;
+      gb = it - v;
+      mk = cur[it];
+      e0 = (uint32_t)G.rp[v];
+      ed = (uint32_t)(G.rp[v + 1] - G.rp[v]);
+      if (rows) {
+        f0 = (uint32_t)G.irp[v];
+        fd = (uint32_t)(G.irp[v + 1] - G.irp[v]);
       }
-      if (pull) tg = S.tgt_of[v];
-    }
-    const int64_t d1 = disc ? e1 : e0;  // end of the out-arcs to scan
-    if (has && sl == 0 && pull) rec[it].vis = rec[it].vis | mask;
-    // first chunk of in-arcs (sigma pull) and of out-arcs (discovery) of
-    // every slot, interleaved: 1. both index chunks
-    const int64_t mi = f0 + sl, mo = e0 + sl;
-    uint32_t u = 0, w = 0;
-    if (mi < f1) u = (uint32_t)G.icol[mi];
-    if (mo < d1) w = (uint32_t)G.col[mo];
-    // 2. both mask gathers
-    ull pfr = 0ull, svis = 0ull, sfc = 0ull, sfn = 0ull;
-    if (mi < f1) pfr = rec[gbase + u].fr[kp];
-    if (mo < d1) {
-      const MaskRec &R = rec[gbase + w];
-      svis = R.vis;
-      sfc = R.fr[kc];
-      sfn = R.fr[kn];
-    }
-    const ull pm = pfr & mask;
-    // lanes already flagged for level+1 by another wavefront need no atomic
-    // (a stale read only costs a redundant atomic)
-    const ull dag = (mo < d1) ? (mask & ~(svis | sfc | sfn)) : 0ull;
-    // 3. discovery flags, then the predecessor rows; the flag results are
-    //    consumed only after the rows
-    bool enq = false;
-    if (dag != 0ull) enq = (atomicOr(&rec[gbase + w].fr[kn], dag) == 0ull);
-    ull acc[K];
-    bool lov[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-      acc[t] = 0ull;
-      lov[t] = false;
-    }
-    // a DAG tail's lanes that are a target or below one: the same record
-    // line as its level mask, loaded beside the predecessor rows
-    const ull pdn = pm != 0ull ? rec[gbase + u].dn : 0ull;
-    pull_slots<K>(S, gbase, u, pm, lane, acc, lov, lov, c_d);
-    ull dnacc[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) dnacc[t] = 0ull;
-    or_slots<K>(pm & pdn, dnacc);
-    append_chunk(S, stage, nst, next_cnt, nbase, rend, gbase, w, enq);
-    // per item: the remaining arcs with the whole wavefront, then the path
-    // counts and target levels of its lanes
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-      const int ld = t * SUB;
-      const ull mt = read_lane64(mask, ld);
-      if (mt == 0ull) {  // slot past the end of the list (or an empty item)
-        if (lane == 0 && i0 + (uint64_t)t < count) S.imask[base + i0 + t] = 0ull;
-        continue;
+      if (pull) {
+        tgt = S.tgt_of[v] >= 0;
+        dnr = tgt ? mk : (level == 1 ? mk & S.ovl[S.G + g] : 0ull);
+      } else {
+        dnr = S.msk[M_DN * GN + it] & mk;
       }
-      const uint32_t itt = read_lane(it, ld);
-      const uint32_t gt = read_lane(g, ld);
-      const uint64_t gbt = read_lane64(gbase, ld);
-      const int64_t F1 = (int64_t)read_lane64((ull)f1, ld), E1 = (int64_t)read_lane64((ull)d1, ld);
-      const int64_t F0 = (int64_t)read_lane64((ull)f0, ld), E0 = (int64_t)read_lane64((ull)e0, ld);
-      const uint64_t deg = (uint64_t)((int64_t)read_lane64((ull)e1, ld) - E0);
-      c_it += 1;
-      c_ia += deg;
+    }
+    if (!lv.heavy || wv == 0) {
+      const uint64_t pc = (uint64_t)__popcll(mk);
+      c_it += (uint64_t)nb;
+      c_ia += wave_sum(ed);
       if (pull) {  // a level found bottom-up was counted there
-        c_v += (uint64_t)__popcll(mt);
-        c_a += (uint64_t)__popcll(mt) * deg;
+        const uint64_t pairs = wave_sum(pc);
+        c_v += pairs;
+        c_a += wave_sum(pc * ed);
+        if (level == 1) c_d += pairs;
+        if (__ballot(tgt) != 0ull && lane == 0) atomicMin(S.tmin, (uint32_t)level);
       }
-      for (int64_t e = F0 + SUB; e < F1; e += kLanes) {
-        const int64_t my = e + lane;
-        uint32_t uu = 0;
-        ull pp = 0ull, pd = 0ull;
-        if (my < F1) {
-          uu = (uint32_t)G.icol[my];
-          pp = rec[gbt + uu].fr[kp] & mt;
-          if (pp != 0ull) pd = rec[gbt + uu].dn;
+    }
+    if (!disc) ed = 0;
+    // the block's steps: 32 in-arcs (lower half of the wavefront) and 32
+    // out-arcs (upper half) of an item, item after item
+    const uint32_t longest = max(ed, fd);
+    auto advance = [&](int &j, uint32_t &c) {
+      if (j >= nb) return;
+      c += cstep;
+      if (c >= read_lane(longest, j)) {
+        c = cstart;
+        ++j;
+      }
+    };
+    // loads without branches (a lane without an arc reads element 0), so
+    // that they stay in flight across the step
+    auto ends = [&](int j, uint32_t c, bool &has) -> uint32_t {
+      const int jj = j < nb ? j : 0;
+      const uint32_t at = c + k32;
+      has = j < nb && at < (upper ? read_lane(ed, jj) : read_lane(fd, jj));
+      const uint64_t i = (uint64_t)(upper ? read_lane(e0, jj) : read_lane(f0, jj)) + at;
+      return (uint32_t)(upper ? G.col : G.icol)[has ? i : 0];
+    };
+    auto words = [&](int j, uint32_t x, bool has) -> ull {
+      const uint32_t gj = read_lane(gb, j < nb ? j : 0);
+      return (upper ? seen : prv)[has ? gj + x : 0u];
+    };
+    int j0 = 0, j1 = 0, j2;
+    uint32_t c0 = cstart, c1 = cstart, c2;
+    bool h0, h1, h2;
+    uint32_t x0 = ends(j0, c0, h0);
+    advance(j1, c1);
+    uint32_t x1 = ends(j1, c1, h1);
+    ull m0 = words(j0, x0, h0);
+    ull acc = 0ull, ov = 0ull, got = 0ull, pdn = 0ull;
+    while ((rows || disc) && j0 < nb) {
+      const ull mj = read_lane64(mk, j0);
+      const uint32_t gj = read_lane(gb, j0);
+      // flags of the out-arcs; their results are used after the rows
+      const ull dag = (upper && h0) ? mj & ~m0 : 0ull;
+      const ull pm = (!upper && h0) ? mj & m0 : 0ull;
+      ull was = ~0ull;
+      if (dag != 0ull) was = atomicOr(&seen[gj + x0], dag);
+      const ull pd = S.msk[M_DN * GN + (pm != 0ull ? gj + x0 : 0u)];
+      ull bits = __ballot(pm != 0ull);
+      Rows r;
+      r.issue(S.sig, gj, x0, pm, bits, got, c_d);
+      // the next step's words and the arc ends of the one after
+      j2 = j1;
+      c2 = c1;
+      advance(j2, c2);
+      const ull m1 = words(j1, x1, h1);
+      const uint32_t x2 = ends(j2, c2, h2);
+      const ull fresh = dag & ~was;
+      ull first = ~0ull;
+      if (fresh != 0ull) first = atomicOr(&nxt[gj + x0], fresh);
+      r.add(acc, ov);
+      while (bits != 0ull) {
+        r.issue(S.sig, gj, x0, pm, bits, got, c_d);
+        r.add(acc, ov);
+      }
+      pdn |= pd & pm;
+      if (j1 != j0 && !lv.heavy) {  // the item's last step
+        if (rows) {
+          const uint32_t ij = read_lane(it, j0);
+          if (__builtin_amdgcn_inverse_ballot_w64(mj)) S.sig[(uint64_t)ij * kLanes + lane] = acc;
+          if (ov != 0ull) {
+            ovf = true;
+            if (lane == 0) atomicOr(&S.ovl[gj / n], ov);
+          }
+          const ull dn = wave_or(pdn);
+          if (lane == j0) dnr |= dn;
         }
-        ull a1[1] = {acc[t]};
-        bool l1[1] = {lov[t]};
-        pull_slots<1>(S, gbt, uu, pp, lane, a1, l1, l1, c_d);
-        acc[t] = a1[0];
-        lov[t] = l1[0];
-        ull d1[1] = {0ull};
-        or_slots<1>(pp & pd, d1);
-        dnacc[t] |= d1[0];
+        acc = ov = pdn = 0ull;
       }
-      for (int64_t e = E0 + SUB; e < E1; e += kLanes) {
-        const int64_t my = e + lane;
-        uint32_t ww = 0;
-        bool eq = false;
-        if (my < E1) {
-          ww = (uint32_t)G.col[my];
-          const MaskRec &R = rec[gbt + ww];
-          const ull dd = mt & ~(R.vis | R.fr[kc] | R.fr[kn]);
-          if (dd != 0ull) eq = (atomicOr(&rec[gbt + ww].fr[kn], dd) == 0ull);
+      append_chunk<false>(S, level, pv.p, sg, gj, x0, first == 0ull);
+      j0 = j1;
+      c0 = c1;
+      j1 = j2;
+      c1 = c2;
+      x0 = x1;
+      x1 = x2;
+      h0 = h1;
+      h1 = h2;
+      m0 = m1;
+    }
+    if (level == 1)  // every lane's one path
+      for (int j = 0; j < nb; ++j)
+        if ((!lv.heavy || wv == 0) && __builtin_amdgcn_inverse_ballot_w64(read_lane64(mk, j)))
+          S.sig[(uint64_t)read_lane(it, j) * kLanes + lane] = 1ull;
+    if (lv.heavy) {
+      if (rows) {  // the same for the whole workgroup
+        const ull dn = wave_or(pdn);
+        red_acc[wv][lane] = acc;
+        if (lane == 0) {
+          red_ov[wv] = ov;
+          red_dn[wv] = dn;
         }
-        append_chunk(S, stage, nst, next_cnt, nbase, rend, gbt, ww, eq);
-      }
-      // the item's lanes for the backward: all of them for exports, else
-      // those where v is a target or lies below one (a target's dependency
-      // reads psi nowhere else)
-      if (!pull) {  // found bottom-up: its marks are in the record already
-        if (lane == 0) S.imask[base + i0 + t] = S.keep_all ? mt : (mt & rec[itt].dn);
-        continue;
-      }
-      const bool act = (mt >> lane) & 1ull;
-      const bool is_tgt = (int32_t)read_lane((uint32_t)tg, ld) >= 0;
-      if (is_tgt && lane == 0) atomicMin(S.tmin, (uint32_t)level);
-      const ull dnt = dnacc[t] | (is_tgt ? mt : 0ull);
-      if (lane == 0) {
-        if (dnt != 0ull) rec[itt].dn = rec[itt].dn | dnt;
-        S.imask[base + i0 + t] = S.keep_all ? mt : dnt;
-      }
-      if (level > 0) {
-        if (act) S.sig[(uint64_t)itt * kLanes + lane] = acc[t];
-        if (lov[t]) {
-          ovf = true;
-          atomicOr(&S.ovl[gt], 1ull << lane);
+        __syncthreads();
+        if (wv == 0) {
+          ull dnt = dn;
+          for (int q = 1; q < NW; ++q) {
+            const ull sum = acc + red_acc[q][lane];
+            ov |= red_ov[q] | __ballot(sum < acc);
+            dnt |= red_dn[q];
+            acc = sum;
+          }
+          if (__builtin_amdgcn_inverse_ballot_w64(read_lane64(mk, 0)))
+            S.sig[(uint64_t)read_lane(it, 0) * kLanes + lane] = acc;
+          if (ov != 0ull) {
+            ovf = true;
+            if (lane == 0) atomicOr(&S.ovl[read_lane(gb, 0) / n], ov);
+          }
+          if (lane == 0) dnr |= dnt;
         }
+        __syncthreads();  // the next item overwrites the partial sums
       }
+      if (wv != 0) continue;
+    }
+    // the items' lanes for the backward: all of them for exports, else
+    // those where v is a target or lies below one (a target's dependency
+    // reads psi nowhere else)
+    if (lane < nb) {
+      if (pull && dnr != 0ull) S.msk[M_DN * GN + it] |= dnr;
+      S.imask[base + b0 + lane] = S.keep_all ? mk : dnr;
     }
   }
-  flush_stage(S, stage, nst, next_cnt, nbase, rend);
+  flush_stage<false>(S, level, pv.p, sg);
   const int ck[5] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS, C_FWD_ITEMS, C_FWD_IARCS};
   const uint64_t cv[5] = {c_v, c_a, c_d, c_it, c_ia};
   flush_wave_counters<BLOCK, 5>(S.ctr, S.ctr_slots, ck, cv, ovf, S.flags);
@@ -411,7 +532,7 @@ static __device__ __forceinline__ void push_slots(const BatchState &S, uint64_t 
         }
         // the head's lanes below a target on this arc (one atomic per arc)
         const ull dd = dnq & dq;
-        if (dd != 0ull && lane == 0) atomicOr(&S.rec[gq + wq].dn, dd);
+        if (dd != 0ull && lane == 0) atomicOr(&S.msk[(uint64_t)M_DN * S.G * S.n + gq + wq], dd);
       }
     }
 #pragma unroll
@@ -431,6 +552,9 @@ static __device__ __forceinline__ void push_slots(const BatchState &S, uint64_t 
 // not settled on a level <= `level` for lane b of mask is a DAG arc of lane
 // b: w is flagged for level+1 (one atomicOr per arc, the first flagger
 // appends it) and sigma_b(v) is added into sigma_b(w).  No in-arc is read.
+// Here seen lags by a level (the owner of (g, v) ORs its lanes in during this
+// launch, and a reader sees seen | cur, the same union either way), since a
+// lane already flagged for level+1 still takes this arc's count.
 // Path-count rows must start at zero on every lane (k_batch_cleanup resets
 // the lanes a batch settled).
 template <int BLOCK, int K>
@@ -439,41 +563,46 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
                                                                                                 int level) {
   constexpr int SUB = kLanes / K;
   const uint64_t n = (uint64_t)S.n;
-  const int P = S.P;
+  const int P = S.P, NL = S.NL;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t base = S.off[(uint64_t)level * P + pv.p];
-  const uint64_t count = S.cnt[(uint64_t)level * P + pv.p];
-  const uint64_t nbase = base + count;
-  const uint64_t rend = (uint64_t)(pv.p + 1) * S.capP;
-  if (pv.thread == 0) S.off[(uint64_t)(level + 1) * P + pv.p] = nbase;
-  if (nbase > rend) return;  // capacity exceeded (workgroup-uniform test): the batch is redone
+  const uint64_t lrow = (uint64_t)level * NL, nrow = lrow + NL;
+  __shared__ uint32_t stage_all[(BLOCK / 64) * kStage], hstage_all[(BLOCK / 64) * kStageHeavy];
+  const int wv = threadIdx.x >> 6;
+  Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
+  const uint32_t nl = *tail_at(S, level, pv.p), nh = *tail_at(S, level, P + pv.p);
+  const uint64_t nb = S.off[lrow + pv.p] + nl, nhb = S.off[lrow + P + pv.p] + nh;
+  if (pv.thread == 0) open_level(S, level, pv.p, nl, nh, nb, nhb);
+  if ((nl | nh) == 0u) return;  // no lanes left in this partition's groups
+  // capacity exceeded (workgroup-uniform test): the batch is redone
+  if (nb > list_end(S, pv.p) || nhb > list_end(S, P + pv.p)) return;
   const int lane = lane_id();
   const int sl = lane % SUB;
-  MaskRec *rec = S.rec;
-  const int kc = level & 3, kn = (level + 1) & 3, ko = (level + 2) & 3;
-  if (level >= 2) {  // retire the masks of level-2
-    const uint64_t pb = S.off[(uint64_t)(level - 2) * P + pv.p];
-    const uint64_t pc = S.cnt[(uint64_t)(level - 2) * P + pv.p];
-    for (uint64_t i = pv.thread; i < pc; i += pv.nthreads) rec[S.items[pb + i]].fr[ko] = 0ull;
-  }
-  uint64_t prev = 0;
+  const uint64_t GN = (uint64_t)S.G * n;
+  ull *seen = S.msk + M_SEEN * GN, *dnm = S.msk + M_DN * GN;
+  const ull *cur = S.msk + (M_FR + (level & 3)) * GN;
+  ull *nxt = S.msk + (M_FR + ((level + 1) & 3)) * GN, *old = S.msk + (M_FR + ((level + 2) & 3)) * GN;
+  if (level >= 2)  // retire the masks of level-2
+    for (int l = pv.p; l < NL; l += P) {
+      const uint64_t pb = S.off[lrow - 2 * NL + l], pc = S.cnt[lrow - 2 * NL + l];
+      for (uint64_t i = pv.thread; i < pc; i += pv.nthreads) old[S.items[pb + i]] = 0ull;
+    }
+  uint64_t prev = 0, here = 0;
   if (level >= 1)
-    for (int p = 0; p < P; ++p) prev += S.cnt[(uint64_t)(level - 1) * P + p];
-  uint64_t cur = 0;
-  for (int p = 0; p < P; ++p) cur += S.cnt[(uint64_t)level * P + p];
+    for (int l = 0; l < NL; ++l) prev += S.cnt[lrow - NL + l];
+  for (int l = 0; l < NL; ++l) here += *tail_at(S, level, l);
   const bool own = !bottom_up_rule(S.bu_den, level, prev, S.gused, S.n);  // found top-down
-  const bool disc = !bottom_up_rule(S.bu_den, level + 1, cur, S.gused, S.n);
+  const bool disc = !bottom_up_rule(S.bu_den, level + 1, here, S.gused, S.n);
 
   uint64_t c_v = 0, c_a = 0, c_d = 0, c_it = 0, c_ia = 0;  // wave-uniform counters
   bool ovf = false;
-  const uint64_t step = pv.nwaves * (uint64_t)K;
-  uint32_t *next_cnt = &S.cnt[(uint64_t)(level + 1) * P + pv.p];
-  __shared__ uint32_t stage_all[(BLOCK / 64) * kStage];
-  uint32_t *stage = stage_all + (threadIdx.x >> 6) * kStage;
-  int nst = 0;
-  uint64_t ii = pv.wave * (uint64_t)K + (uint64_t)(lane / SUB);  // this lane's item
+  const ListView lv = list_view(S);
+  const int l = lv.heavy ? P + pv.p : pv.p;
+  const uint64_t base = S.off[lrow + l], count = *tail_at(S, level, l);
+  const uint64_t step = lv.nwg * (uint64_t)(BLOCK / 64 * K);
+  const uint64_t first = (lv.wg * (BLOCK / 64) + (uint64_t)wv) * (uint64_t)K;
+  uint64_t ii = first + (uint64_t)(lane / SUB);  // this lane's item
   uint32_t it_next = ii < count ? S.items[base + ii] : 0u;
-  for (uint64_t i0 = pv.wave * (uint64_t)K; i0 < count; i0 += step, ii += step) {
+  for (uint64_t i0 = first; i0 < count; i0 += step, ii += step) {
     const bool has = ii < count;
     const uint32_t it = it_next;
     if (ii + step < count) it_next = S.items[base + ii + step];
@@ -484,14 +613,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
     int64_t e0 = 0, e1 = 0;
     int32_t tg = -1;
     if (has) {
-      mask = rec[it].fr[kc];
-      dnr = rec[it].dn;
+      mask = cur[it];
+      dnr = dnm[it];
       e0 = G.rp[v];
       e1 = G.rp[v + 1];
       if (own) tg = S.tgt_of[v];
     }
     const int64_t d1 = disc ? e1 : e0;  // end of the out-arcs to scan
-    if (has && sl == 0 && own) rec[it].vis = rec[it].vis | mask;
+    if (has && sl == 0 && own) seen[it] = seen[it] | mask;
     // per slot: the item's lanes, their marks, and this lane's path count
     ull mt[K], dn[K], sv[K];
 #pragma unroll
@@ -509,14 +638,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
     bool enq = false;
     if (mo < d1) {
       w = (uint32_t)G.col[mo];
-      const MaskRec &R = rec[gbase + w];
-      const ull settled = R.vis | R.fr[kc];
-      push = mask & ~settled;  // the DAG lanes of this arc
-      const ull dag = push & ~R.fr[kn];  // lanes already flagged by another wavefront need no atomic
-      if (dag != 0ull) enq = (atomicOr(&rec[gbase + w].fr[kn], dag) == 0ull);
+      push = mask & ~(seen[gbase + w] | cur[gbase + w]);  // the DAG lanes of this arc
+      const ull dag = push & ~nxt[gbase + w];  // lanes already flagged by another wavefront need no atomic
+      if (dag != 0ull) enq = (atomicOr(&nxt[gbase + w], dag) == 0ull);
     }
     push_slots<K>(S, gbase, w, push, lane, sv, dn, ovf, c_d);
-    append_chunk(S, stage, nst, next_cnt, nbase, rend, gbase, w, enq);
+    append_chunk<false>(S, level, pv.p, sg, gbase, w, enq);
 #pragma unroll
     for (int t = 0; t < K; ++t) {
       const int ld = t * SUB;
@@ -537,7 +664,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
         const bool is_tgt = (int32_t)read_lane((uint32_t)tg, ld) >= 0;
         if (is_tgt && lane == 0) {
           atomicMin(S.tmin, (uint32_t)level);
-          rec[itt].dn = rec[itt].dn | m;
+          dnm[itt] |= m;
         }
       }
       if (lane == 0) S.imask[base + i0 + t] = S.keep_all ? m : dn[t];
@@ -549,17 +676,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
         bool eq = false;
         if (my < E1) {
           ww = (uint32_t)G.col[my];
-          const MaskRec &R = rec[gbt + ww];
-          pp = m & ~(R.vis | R.fr[kc]);
-          const ull dd = pp & ~R.fr[kn];
-          if (dd != 0ull) eq = (atomicOr(&rec[gbt + ww].fr[kn], dd) == 0ull);
+          pp = m & ~(seen[gbt + ww] | cur[gbt + ww]);
+          const ull dd = pp & ~nxt[gbt + ww];
+          if (dd != 0ull) eq = (atomicOr(&nxt[gbt + ww], dd) == 0ull);
         }
         push_slots<1>(S, gbt, ww, pp, lane, s1, d1m, ovf, c_d);
-        append_chunk(S, stage, nst, next_cnt, nbase, rend, gbt, ww, eq);
+        append_chunk<false>(S, level, pv.p, sg, gbt, ww, eq);
       }
     }
   }
-  flush_stage(S, stage, nst, next_cnt, nbase, rend);
+  flush_stage<false>(S, level, pv.p, sg);
   const int ck[5] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS, C_FWD_ITEMS, C_FWD_IARCS};
   const uint64_t cv[5] = {c_v, c_a, c_d, c_it, c_ia};
   flush_wave_counters<BLOCK, 5>(S.ctr, S.ctr_slots, ck, cv, ovf, S.flags);
@@ -581,45 +707,113 @@ static __device__ __forceinline__ ull shfl64(ull x, int src) {
 // masks; (g, w) is appended to the level's list if it gained any lane.
 // Runs before the top-down kernel of the same level, and only when
 // bottom_up_rule holds for the level.  The unsettled pairs of a 64-vertex
-// block are taken K at a time, 64 / K lanes each for their first in-arcs.
+// block are taken K at a time, 64 / K lanes each for their first in-arcs;
+// a heavy vertex is taken by a workgroup, as in k_fwd_level.
 template <int BLOCK, int K>
 __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, int level) {
   constexpr int SUB = kLanes / K;
+  constexpr int NW = BLOCK / 64;
   const uint64_t n = (uint64_t)S.n;
-  const int P = S.P;
+  const int P = S.P, NL = S.NL;
+  const uint64_t lrow = (uint64_t)level * NL;
   uint64_t prev = 0;
-  for (int p = 0; p < P; ++p) prev += S.cnt[(uint64_t)(level - 1) * P + p];
+  for (int l = 0; l < NL; ++l) prev += S.cnt[lrow - NL + l];
   if (!bottom_up_rule(S.bu_den, level, prev, S.gused, S.n)) return;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t base = S.off[(uint64_t)level * P + pv.p];
-  const uint64_t rend = (uint64_t)(pv.p + 1) * S.capP;
-  if (base > rend) return;  // capacity exceeded earlier (workgroup-uniform test): the batch is redone
+  __shared__ uint32_t stage_all[NW * kStage], hstage_all[NW * kStageHeavy];
+  const int wv = threadIdx.x >> 6;
+  Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
+  // capacity exceeded earlier (workgroup-uniform test): the batch is redone
+  if (S.off[lrow + pv.p] > list_end(S, pv.p) || S.off[lrow + P + pv.p] > list_end(S, P + pv.p)) return;
   const int lane = lane_id();
   const int slot = lane / SUB, sl = lane % SUB;
-  MaskRec *rec = S.rec;
-  const int kc = level & 3, kp = (level + 3) & 3;
-  uint32_t *cnt_here = &S.cnt[(uint64_t)level * P + pv.p];
-  __shared__ uint32_t stage_all[(BLOCK / 64) * kStage];
-  uint32_t *stage = stage_all + (threadIdx.x >> 6) * kStage;
-  int nst = 0;
+  const uint64_t GN = (uint64_t)S.G * n;
+  ull *seen = S.msk + M_SEEN * GN, *dnm = S.msk + M_DN * GN, *cur = S.msk + (M_FR + (level & 3)) * GN;
+  const ull *prv = S.msk + (M_FR + ((level + 3) & 3)) * GN;
   uint64_t c_v = 0, c_a = 0, c_d = 0;
   bool ovf = false;
   // groups p, p + P, ... below gused belong to this partition
   const uint64_t ngp = S.gused > pv.p ? (uint64_t)(S.gused - pv.p + P - 1) / (uint64_t)P : 0;
-  const uint64_t nvb = (n + 63) / 64;
-  for (uint64_t b = pv.wave; b < ngp * nvb; b += pv.nwaves) {
+  // heavy vertices: a workgroup each, its wavefronts share the in-arcs
+  const ListView lv = list_view(S);
+  __shared__ ull red_acc[NW][kLanes], red_hit[NW], red_ov[NW], red_dn[NW];
+  if (lv.heavy) for (uint64_t i = lv.wg; i < ngp * S.H; i += lv.nwg) {
+    const uint64_t gl = i / S.H;
+    const uint32_t g = (uint32_t)(pv.p + gl * (uint64_t)P);
+    const uint32_t w = (uint32_t)(i - gl * S.H);
+    const uint64_t gbase = (uint64_t)g * n;
+    const ull un = ((g + 1 == (uint32_t)S.gused) ? S.last_lanes : ~0ull) & ~seen[gbase + w];
+    const int64_t f1 = G.irp[w + 1];
+    ull acc = 0ull, dnt = 0ull, ovm = 0ull, nm = 0ull;
+    if (un != 0ull)
+      for (int64_t e = G.irp[w] + 64 * wv; e < f1; e += BLOCK) {
+        const int64_t my = e + lane;
+        uint32_t u = 0;
+        ull pm = 0ull, pd = 0ull;
+        if (my < f1) {
+          u = (uint32_t)G.icol[my];
+          pm = prv[gbase + u] & un;
+          if (pm != 0ull) pd = dnm[gbase + u] & pm;
+        }
+        pull_rows(S.sig, (uint32_t)gbase, u, pm, acc, ovm, nm, c_d);
+        dnt |= wave_or(pd);
+      }
+    red_acc[wv][lane] = acc;
+    if (lane == 0) {
+      red_ov[wv] = ovm;
+      red_hit[wv] = nm;
+      red_dn[wv] = dnt;
+    }
+    __syncthreads();
+    if (wv == 0) {
+      for (int q = 1; q < NW; ++q) {
+        const ull sum = acc + red_acc[q][lane];
+        ovm |= red_ov[q] | __ballot(sum < acc);
+        dnt |= red_dn[q];
+        nm |= red_hit[q];
+        acc = sum;
+      }
+      if (nm != 0ull) {
+        const uint32_t it = (uint32_t)(gbase + w);
+        const uint64_t deg = (uint64_t)(G.rp[w + 1] - G.rp[w]);
+        const bool is_tgt = S.tgt_of[w] >= 0;
+        if ((nm >> lane) & 1ull) S.sig[(uint64_t)it * kLanes + lane] = acc;
+        if (ovm != 0ull) {
+          ovf = true;
+          if (lane == 0) atomicOr(&S.ovl[g], ovm);
+        }
+        if (is_tgt) dnt |= nm;
+        if (lane == 0) {
+          cur[it] = nm;
+          seen[it] |= nm;
+          if (dnt != 0ull) dnm[it] |= dnt;
+          if (is_tgt) atomicMin(S.tmin, (uint32_t)level);
+        }
+        c_v += (uint64_t)__popcll(nm);
+        c_a += (uint64_t)__popcll(nm) * deg;
+        append_chunk<true>(S, level, pv.p, sg, gbase, w, lane == 0);
+      }
+    }
+    __syncthreads();  // the next vertex overwrites the partial results
+  }
+  // light vertices H .. n-1, 64 to a block; the ids run by falling degree, so
+  // a block takes eight runs of eight (a line of words each) spread evenly
+  // over them, and all blocks hold about the same arcs
+  const uint64_t nlt = n - S.H, nvb = (nlt + 63) / 64;
+  const uint64_t first = lv.heavy ? ngp * nvb : lv.wg * NW + (uint64_t)wv;
+  for (uint64_t b = first; b < ngp * nvb; b += lv.nwg * NW) {
     const uint64_t gl = b / nvb;
     const uint32_t g = (uint32_t)(pv.p + gl * (uint64_t)P);
     const uint64_t gbase = (uint64_t)g * n;
-    const uint64_t w0 = (b - gl * nvb) * 64;
-    const uint64_t w = w0 + lane;
+    const uint64_t w0 = S.H + (b - gl * nvb) * 8;
+    const uint64_t w = w0 + (uint64_t)(lane >> 3) * nvb * 8 + (uint64_t)(lane & 7);
     const ull act_lanes = (g + 1 == (uint32_t)S.gused) ? S.last_lanes : ~0ull;
     int64_t f0 = 0, f1 = 0;
     ull uns = 0ull;
     if (w < n) {
       f0 = G.irp[w];
       f1 = G.irp[w + 1];
-      if (f1 > f0) uns = act_lanes & ~rec[gbase + w].vis;
+      if (f1 > f0) uns = act_lanes & ~seen[gbase + w];
     }
     ull cm = __ballot(uns != 0ull);
     while (cm != 0ull) {
@@ -649,250 +843,325 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
       ull pfr = 0ull, pdn = 0ull;
       if (mi < F1) {
         u = (uint32_t)G.icol[mi];
-        pfr = rec[gbase + u].fr[kp];
-        pdn = rec[gbase + u].dn;
+        pfr = prv[gbase + u] & un;
+        if (pfr != 0ull) pdn = dnm[gbase + u] & pfr;
       }
-      const ull pm = pfr & un;
-      ull acc[K];
-      bool lov[K], hit[K];
-#pragma unroll
-      for (int t = 0; t < K; ++t) {
-        acc[t] = 0ull;
-        lov[t] = false;
-        hit[t] = false;
-      }
-      pull_slots<K, true>(S, gbase, u, pm, lane, acc, lov, hit, c_d);
-      ull dnacc[K];
-#pragma unroll
-      for (int t = 0; t < K; ++t) dnacc[t] = 0ull;
-      or_slots<K>(pm & pdn, dnacc);
+      const ull pm = pfr;
 #pragma unroll
       for (int t = 0; t < K; ++t) {
         if (jc[t] < 0) continue;
         const ull ut = read_lane64(uns, jc[t]);
         const int64_t G0 = (int64_t)read_lane64((ull)f0, jc[t]), G1 = (int64_t)read_lane64((ull)f1, jc[t]);
+        ull acc = 0ull, ovm = 0ull, nm = 0ull;  // nm: lanes of w on this level
+        pull_rows(S.sig, (uint32_t)gbase, u, slot == t ? pm : 0ull, acc, ovm, nm, c_d);
+        ull dnt = wave_or(slot == t ? pdn : 0ull);
         for (int64_t e = G0 + SUB; e < G1; e += kLanes) {
           const int64_t my = e + lane;
           uint32_t uu = 0;
           ull pp = 0ull, pd = 0ull;
           if (my < G1) {
             uu = (uint32_t)G.icol[my];
-            pp = rec[gbase + uu].fr[kp] & ut;
-            pd = rec[gbase + uu].dn;
+            pp = prv[gbase + uu] & ut;
+            if (pp != 0ull) pd = dnm[gbase + uu] & pp;
           }
-          ull a1[1] = {acc[t]};
-          bool l1[1] = {lov[t]}, h1[1] = {hit[t]};
-          pull_slots<1, true>(S, gbase, uu, pp, lane, a1, l1, h1, c_d);
-          acc[t] = a1[0];
-          lov[t] = l1[0];
-          hit[t] = h1[0];
-          ull d1[1] = {0ull};
-          or_slots<1>(pp & pd, d1);
-          dnacc[t] |= d1[0];
+          pull_rows(S.sig, (uint32_t)gbase, uu, pp, acc, ovm, nm, c_d);
+          dnt |= wave_or(pd);
         }
-        const ull nm = __ballot(hit[t]);  // lanes of w on this level
         if (nm == 0ull) continue;
-        const uint32_t wt = (uint32_t)(w0 + (uint64_t)jc[t]);
+        const uint32_t wt = (uint32_t)(w0 + (uint64_t)(jc[t] >> 3) * nvb * 8 + (uint64_t)(jc[t] & 7));
         const uint32_t it = (uint32_t)(gbase + wt);
         const bool act = (nm >> lane) & 1ull;
         const int64_t e0 = G.rp[wt], e1 = G.rp[wt + 1];
         const int32_t tg = S.tgt_of[wt];
-        if (act) S.sig[(uint64_t)it * kLanes + lane] = acc[t];
-        if (lov[t]) {
+        if (act) S.sig[(uint64_t)it * kLanes + lane] = acc;
+        if (ovm != 0ull) {
           ovf = true;
-          atomicOr(&S.ovl[g], 1ull << lane);
+          if (lane == 0) atomicOr(&S.ovl[g], ovm);
         }
-        const ull dnt = (dnacc[t] & nm) | (tg >= 0 ? nm : 0ull);
+        if (tg >= 0) dnt |= nm;
         if (lane == 0) {
-          rec[it].fr[kc] = nm;
-          rec[it].vis = rec[it].vis | nm;
-          if (dnt != 0ull) rec[it].dn = rec[it].dn | dnt;
+          cur[it] = nm;
+          seen[it] |= nm;
+          if (dnt != 0ull) dnm[it] |= dnt;
         }
         c_v += (uint64_t)__popcll(nm);
         c_a += (uint64_t)__popcll(nm) * (uint64_t)(e1 - e0);
         if (tg >= 0 && lane == 0) atomicMin(S.tmin, (uint32_t)level);
-        append_chunk(S, stage, nst, cnt_here, base, rend, gbase, wt, lane == 0);
+        append_chunk<true>(S, level, pv.p, sg, gbase, wt, lane == 0);
       }
     }
   }
-  flush_stage(S, stage, nst, cnt_here, base, rend);
+  flush_stage<true>(S, level, pv.p, sg);
   const int ck[3] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS};
   const uint64_t cv[3] = {c_v, c_a, c_d};  // wave-uniform
   flush_wave_counters<BLOCK, 3>(S.ctr, S.ctr_slots, ck, cv, ovf, S.flags);
 }
 
-// Sum of psi_b(w) over the out-arcs held by one chunk of lanes whose head w
-// is a shortest-path-DAG successor for lane b (d = lanes of that arc); the
-// chunk holds the arcs of up to K items, 64 / K lanes each, and an arc adds
-// into its item's accumulator.  Bits are taken in lane order, which is arc
-// order within an item, so every item's sum runs in arc order whatever K is.
-// Row loads of up to eight successors are issued before any is consumed.
-template <int K>
-static __device__ __forceinline__ void push_sum_slots(const BatchState &S, uint64_t gbase, uint32_t w, ull d,
-                                                      int lane, double (&acc)[K], uint64_t &dag_pairs) {
-  constexpr int SUB = kLanes / K;
-  ull bits = __ballot(d != 0ull);
-  while (bits != 0ull) {
-    int j[8];
-    int c = 0;
-    for (; c < 8 && bits != 0ull; ++c) {
-      j[c] = __ffsll((long long)bits) - 1;
-      bits &= bits - 1ull;
-    }
-    double x[8];
+// Successor rows of a chunk of arc lanes, up to eight at a time, as Rows: arc
+// lane j holds the head w and the lanes d for which it is a shortest-path-DAG
+// successor.  add() adds psi_b(w) to acc (this lane's source) in arc lane
+// order, which is arc order; adding 0.0 for a lane off the DAG leaves its sum
+// unchanged.
+struct PsiRows {
+  double x[8];
+  __device__ __forceinline__ void issue(const double *psi, uint32_t gb, uint32_t w, ull d, ull &bits,
+                                        uint64_t &dag_pairs) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = 0.0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      x[q] = 0.0;
-      if (q < c) {
-        const uint32_t wq = read_lane(w, j[q]);
-        const ull dq = read_lane64(d, j[q]);
-        const uint64_t gq = read_lane64(gbase, j[q]);
-        dag_pairs += (uint64_t)__popcll(dq);  // wave-uniform
-        if ((dq >> lane) & 1ull) x[q] = S.psi[(gq + wq) * kLanes + lane];
-      }
-    }
-    // adding 0.0 for a lane off the DAG leaves its sum unchanged
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      if (q < c) {
-        const int slot = j[q] / SUB;
-#pragma unroll
-        for (int t = 0; t < K; ++t)
-          if (slot == t) acc[t] += x[q];
+      if (bits != 0ull) {
+        const int j = __builtin_ctzll(bits);
+        bits &= bits - 1ull;
+        const ull dq = read_lane64(d, j);
+        const double *row = psi + (uint64_t)(gb + read_lane(w, j)) * kLanes;
+        dag_pairs += (uint64_t)__popcll(dq);
+        if (__builtin_amdgcn_inverse_ballot_w64(dq)) x[q] = row[lane];
       }
     }
   }
-}
+  __device__ __forceinline__ void add(double &acc) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc += x[q];
+  }
+};
+
+// Heavy items of the backward with at most this many lanes go source by
+// source (see k_bwd_level), others arc by arc: R-MAT 20, 1,000 sources, all
+// arc by arc 51.3 ms, limits of 4 / 8 / 16 lanes 50.4 / 48.3 / 48.4, all source
+// by source 56.0; R-MAT 16, 1,000 sources 3.51 / 3.47 / 3.38 / 3.54 / 4.20.
+constexpr int kSparseLanes = 8;
 
 // One level of the backward pass, Eq.(4) read as
 //   delta(v) = sigma(v) * sum_{w: v in P(w)} psi(w),  psi(w) = (1 + delta(w)) / sigma(w),
 // so psi(v) = 1/sigma(v) + sum psi(w).  Successor w of v is on the DAG for
-// lane b iff w sits on level+1 for b, read from the level-tagged table the
-// previous (deeper) launch wrote.  Only the lanes the forward kept in the
-// item's mask are computed -- those where v is a target or lies below one
-// (no target's dependency reads psi anywhere else) -- and target vertices
-// report delta on their lanes.  No atomics: every sum runs
-// in arc order, so results are bit-reproducible.  A wavefront takes K items
-// per step, their first 64 / K out-arcs in one chunk of lanes (as in the
-// forward kernel), then longer out-arc lists 64 at a time.
-template <int BLOCK, int K>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_bwd_level(DevGraph G,
-                                                                                                 BatchState S,
-                                                                                                 int level, int ntgt,
-                                                                                                 int full) {
-  constexpr int SUB = kLanes / K;
-  const uint64_t n = (uint64_t)S.n;
+// lane b iff w sits on level+1 for b, read from the masks the previous
+// (deeper) launch wrote.  Only the lanes the forward kept in the item's mask
+// are computed -- those where v is a target or lies below one (no target's
+// dependency reads psi anywhere else) -- and target vertices report delta on
+// their lanes.  No atomics: every sum runs in arc order, so results are
+// bit-reproducible.  The masks rotate over three words: written (level), read
+// (level+1) and cleared (level+2).
+// Light items are taken in blocks of up to 64 as in the forward (a lane per
+// item loads what is needed of it; items without lanes are passed over), each
+// with the whole wavefront over its out-arcs, the next item's arc ends loaded
+// ahead.  Heavy items go to whole workgroups.
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, int level, int ntgt) {
+  constexpr int NW = BLOCK / 64;
+  const uint32_t n = (uint32_t)S.n;
   const uint64_t GN = (uint64_t)S.G * n;
-  const int P = S.P;
+  const int P = S.P, NL = S.NL;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t base = S.off[(uint64_t)level * P + pv.p];
-  const uint64_t count = S.cnt[(uint64_t)level * P + pv.p];
-  if (base + count > (uint64_t)(pv.p + 1) * S.capP) return;
+  const uint64_t lrow = (uint64_t)level * NL;
+  if (S.off[lrow + pv.p] + S.cnt[lrow + pv.p] > list_end(S, pv.p) ||
+      S.off[lrow + P + pv.p] + S.cnt[lrow + P + pv.p] > list_end(S, P + pv.p))
+    return;
   const int lane = lane_id();
-  const int sl = lane % SUB;
-  const LevMask *bt_in = S.bt + (uint64_t)((level + 1) & 1) * GN;
-  LevMask *bt_out = S.bt + (uint64_t)(level & 1) * GN;
-  const uint32_t E = S.epoch;
+  const ull *bw_in = S.msk + (M_BW + (level + 1) % 3) * GN;
+  ull *bw_out = S.msk + (M_BW + level % 3) * GN;
+  // level+2's masks make room for level-1 (its lists exist: the forward ran
+  // at least one level past the deepest one)
+  if (level + 2 <= S.top) {
+    ull *bw_old = S.msk + (M_BW + (level + 2) % 3) * GN;
+    for (int l = pv.p; l < NL; l += P) {
+      const uint64_t pb = S.off[lrow + 2 * NL + l], pc = S.cnt[lrow + 2 * NL + l];
+      for (uint64_t i = pv.thread; i < pc; i += pv.nthreads)
+        if (S.imask[pb + i] != 0ull) bw_old[S.items[pb + i]] = 0ull;
+    }
+  }
   uint64_t c_v = 0, c_a = 0, c_d = 0, c_it = 0, c_ia = 0;  // wave-uniform counters
-  const uint64_t step = pv.nwaves * (uint64_t)K;
-  uint64_t ii = pv.wave * (uint64_t)K + (uint64_t)(lane / SUB);  // this lane's item
-  // the next step's ids and masks are loaded while this one is processed
-  uint32_t it_next = ii < count ? S.items[base + ii] : 0u;
-  ull mask_next = ii < count ? S.imask[base + ii] : 0ull;
-  for (uint64_t i0 = pv.wave * (uint64_t)K; i0 < count; i0 += step, ii += step) {
-    const uint32_t it = it_next;
-    const ull mask = mask_next;
-    if (ii + step < count) {
-      it_next = S.items[base + ii + step];
-      mask_next = S.imask[base + ii + step];
-    }
-    const uint32_t g = (uint32_t)(it / n);
-    const uint32_t v = (uint32_t)(it - (uint64_t)g * n);
-    const uint64_t gbase = (uint64_t)g * n;
-    int32_t tg = -1;
-    int64_t e0 = 0, e1 = 0;
-    if (mask != 0ull) {
-      tg = S.tgt_of[v];
-      e0 = G.rp[v];
-      e1 = G.rp[v + 1];
-    }
-    // lanes of each item that need psi here, and their path counts
-    ull emv[K], my_em = 0ull;
-    ull sg[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-      const int ld = t * SUB;
-      const ull mt = read_lane64(mask, ld);
-      emv[t] = 0ull;
-      sg[t] = 1ull;
-      if (mt == 0ull) continue;
-      // the forward kept only the lanes that need psi here (all of them for
-      // exports): those where v is a target or lies below one
-      const bool need = (mt >> lane) & 1ull;
-      emv[t] = __ballot(need);
-      if (need) sg[t] = S.sig[(uint64_t)read_lane(it, ld) * kLanes + lane];
-    }
-#pragma unroll
-    for (int t = 0; t < K; ++t)
-      if (lane / SUB == t) my_em = emv[t];
-    // first chunk of every slot's out-arcs
-    const int64_t mo = e0 + sl;
-    uint32_t w = 0;
-    ull d = 0ull;
-    if (my_em != 0ull && mo < e1) {
-      w = (uint32_t)G.col[mo];
-      const LevMask tw = bt_in[gbase + w];
-      const ull mw = (tw.lev == (uint32_t)(level + 1) && tw.epoch == E) ? tw.mask : 0ull;
-      d = my_em & mw;
-    }
-    double acc[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) acc[t] = 0.0;
-    push_sum_slots<K>(S, gbase, w, d, lane, acc, c_d);
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-      const ull em = emv[t];
-      if (em == 0ull) continue;
-      const int ld = t * SUB;
-      const uint32_t itt = read_lane(it, ld);
-      const uint32_t gt = read_lane(g, ld);
-      const uint64_t gbt = read_lane64(gbase, ld);
-      const int64_t E0 = (int64_t)read_lane64((ull)e0, ld), E1 = (int64_t)read_lane64((ull)e1, ld);
-      // remaining out-arcs, 64 at a time, still in arc order
-      for (int64_t e = E0 + SUB; e < E1; e += kLanes) {
-        const int64_t my = e + lane;
-        uint32_t ww = 0;
-        ull dd = 0ull;
-        if (my < E1) {
-          ww = (uint32_t)G.col[my];
-          const LevMask tw = bt_in[gbt + ww];
-          const ull mw = (tw.lev == (uint32_t)(level + 1) && tw.epoch == E) ? tw.mask : 0ull;
-          dd = em & mw;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const ListView lv = list_view(S);
+  __shared__ ull seg_d[2][BLOCK];
+  __shared__ uint32_t seg_w[2][BLOCK];
+  if (lv.heavy) {
+    // the wavefronts of a workgroup look up the DAG lanes of BLOCK arcs at a
+    // time and leave them in LDS; then each takes every NW-th source of the
+    // item: the arcs of that source load its psi, 64 arcs to a load, and its
+    // sum takes them in arc order (few sources share a hub's DAG arc, so a row
+    // per arc would be read for two or three lanes)
+    const uint64_t base = S.off[lrow + P + pv.p], count = S.cnt[lrow + P + pv.p];
+    for (uint64_t i = lv.wg; i < count; i += lv.nwg) {
+      const ull em = first_lane64(S.imask[base + i]);
+      if (em == 0ull) continue;  // the same for the whole workgroup
+      const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.items[base + i]);
+      const uint32_t g = it / n, v = it - g * n, gb = g * n;
+      const int64_t e0 = G.rp[v], e1 = G.rp[v + 1];
+      const bool sparse = __popcll(em) <= kSparseLanes;
+      // this wavefront's sources
+      const ull my = sparse ? __ballot(((em >> lane) & 1ull) && lanes_below(em) % NW == wv) : (wv == 0 ? em : 0ull);
+      double acc = 0.0;  // lane b of the wavefront that has source b: its sum
+      int par = 0;
+      for (int64_t e = e0; e < e1; e += BLOCK, par ^= 1) {
+        const int64_t at = e + threadIdx.x;
+        uint32_t w = 0;
+        ull d = 0ull;
+        if (at < e1) {
+          w = (uint32_t)G.col[at];
+          d = em & bw_in[gb + w];
         }
-        double a1[1] = {acc[t]};
-        push_sum_slots<1>(S, gbt, ww, dd, lane, a1, c_d);
-        acc[t] = a1[0];
+        seg_w[par][threadIdx.x] = w;
+        seg_d[par][threadIdx.x] = d;
+        __syncthreads();
+        if (!sparse) {
+          if (wv == 0)
+            for (int q = 0; q < NW; ++q) {
+              d = seg_d[par][q * 64 + lane];
+              ull bits = __ballot(d != 0ull);
+              while (bits != 0ull) {
+                PsiRows r;
+                r.issue(S.psi, gb, seg_w[par][q * 64 + lane], d, bits, c_d);
+                r.add(acc);
+              }
+            }
+          continue;
+        }
+        for (int q = 0; q < NW; ++q) {
+          const double *row = S.psi + (uint64_t)(gb + seg_w[par][q * 64 + lane]) * kLanes;
+          d = seg_d[par][q * 64 + lane];
+          ull todo = my;
+          while (todo != 0ull) {
+            int bq[4];
+            ull aq[4];
+            double y[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              bq[t] = todo != 0ull ? __builtin_ctzll(todo) : 0;
+              aq[t] = todo != 0ull ? __ballot((d >> bq[t]) & 1ull) : 0ull;
+              todo &= todo - 1ull;
+              y[t] = __builtin_amdgcn_inverse_ballot_w64(aq[t]) ? row[bq[t]] : 0.0;
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              if (aq[t] == 0ull) continue;
+              c_d += (uint64_t)__popcll(aq[t]);
+              double a = __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(acc), bq[t]));
+              for (ull z = aq[t]; z != 0ull; z &= z - 1ull)
+                a += __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(y[t]), __builtin_ctzll(z)));
+              if (lane == bq[t]) acc = a;
+            }
+          }
+        }
       }
-      const int32_t tgt = (int32_t)read_lane((uint32_t)tg, ld);
-      if ((em >> lane) & 1ull) {
-        const double s = (double)sg[t];
-        const double dl = s * acc[t];
-        S.psi[(uint64_t)itt * kLanes + lane] = acc[t] + 1.0 / s;
-        if (S.dout) S.dout[(uint64_t)itt * kLanes + lane] = dl;
-        if (tgt >= 0 && tgt < ntgt)
-          S.res[((uint64_t)tgt * S.G + gt) * kLanes + lane] = (level > 0) ? dl : 0.0;
+      const int32_t tgt = S.tgt_of[v];
+      if ((my >> lane) & 1ull) {
+        const double s = (double)S.sig[(uint64_t)it * kLanes + lane];
+        const double dl = s * acc;
+        S.psi[(uint64_t)it * kLanes + lane] = acc + 1.0 / s;
+        if (S.dout) S.dout[(uint64_t)it * kLanes + lane] = dl;
+        if (tgt >= 0 && tgt < ntgt) S.res[((uint64_t)tgt * S.G + g) * kLanes + lane] = (level > 0) ? dl : 0.0;
       }
-      if (lane == 0) {
-        LevMask o;
-        o.mask = em;
-        o.lev = (uint32_t)level;
-        o.epoch = E;
-        bt_out[itt] = o;
+      if (wv == 0) {
+        if (lane == 0) bw_out[it] = em;
+        c_v += (uint64_t)__popcll(em);
+        c_a += (uint64_t)__popcll(em) * (uint64_t)(e1 - e0);
+        c_it += 1;
+        c_ia += (uint64_t)(e1 - e0);
       }
-      c_v += (uint64_t)__popcll(em);
-      c_a += (uint64_t)__popcll(em) * (uint64_t)(E1 - E0);
-      c_it += 1;
-      c_ia += (uint64_t)(E1 - E0);
+      __syncthreads();  // other wavefronts may still read the last arcs' entries
+    }
+  } else {
+    const uint64_t base = S.off[lrow + pv.p], count = S.cnt[lrow + pv.p];
+    const uint64_t nwv = lv.nwg * NW;
+    const uint32_t B = (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+    for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
+      const int nb = (int)min((uint64_t)B, count - b0);
+      uint32_t it = 0, gb = 0, e0 = 0, ed = 0;
+      int32_t tg = -1;
+      ull mk = 0ull;
+      if (lane < nb) mk = S.imask[base + b0 + lane];
+      ull todo = __ballot(mk != 0ull);
+      if (todo == 0ull) continue;
+      if (mk != 0ull) {
+        it = S.items[base + b0 + lane];
+        const uint32_t v = it % n;
+        gb = it - v;
+        e0 = (uint32_t)G.rp[v];
+        ed = (uint32_t)(G.rp[v + 1] - G.rp[v]);
+        tg = S.tgt_of[v];
+        bw_out[it] = mk;
+      }
+      {
+        const uint64_t pc = (uint64_t)__popcll(mk);
+        c_it += (uint64_t)__popcll(todo);
+        c_ia += wave_sum(ed);
+        c_v += wave_sum(pc);
+        c_a += wave_sum(pc * ed);
+      }
+      // the block's steps: 64 out-arcs of an item with lanes, item after item;
+      // words of the next step and arc ends of the one after are loaded ahead
+      auto advance = [&](ull &t, uint32_t &c) {
+        c += kLanes;
+        if (c >= read_lane(ed, __builtin_ctzll(t))) {
+          c = 0;
+          t &= t - 1ull;
+        }
+      };
+      auto ends = [&](ull t, uint32_t c, bool &has) -> uint32_t {
+        const int j = t != 0ull ? __builtin_ctzll(t) : 0;
+        const uint32_t at = c + (uint32_t)lane;
+        has = t != 0ull && at < read_lane(ed, j);
+        return (uint32_t)G.col[has ? (uint64_t)read_lane(e0, j) + at : 0];
+      };
+      auto words = [&](ull t, uint32_t x, bool has) -> ull {
+        const uint32_t gj = read_lane(gb, t != 0ull ? __builtin_ctzll(t) : 0);
+        return bw_in[has ? gj + x : 0u];
+      };
+      ull t0 = todo, t1 = todo, t2;
+      uint32_t c0 = 0, c1 = 0, c2;
+      bool h0, h1, h2;
+      uint32_t x0 = ends(t0, c0, h0);
+      advance(t1, c1);
+      uint32_t x1 = t1 != 0ull ? ends(t1, c1, h1) : (h1 = false, 0u);
+      ull m0 = words(t0, x0, h0), sg = 1ull;
+      double acc = 0.0;
+      while (t0 != 0ull) {
+        const int j = __builtin_ctzll(t0);
+        const ull em = read_lane64(mk, j);
+        const uint32_t gj = read_lane(gb, j), ij = read_lane(it, j);
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(em);
+        const ull d = h0 ? em & m0 : 0ull;
+        if (c0 == 0 && mine) sg = S.sig[(uint64_t)ij * kLanes + lane];
+        t2 = t1;
+        c2 = c1;
+        h2 = false;
+        uint32_t x2 = 0;
+        ull bits = __ballot(d != 0ull);
+        PsiRows r;
+        r.issue(S.psi, gj, x0, d, bits, c_d);
+        const ull m1 = words(t1, x1, h1);
+        if (t2 != 0ull) {
+          advance(t2, c2);
+          x2 = ends(t2, c2, h2);
+        }
+        r.add(acc);
+        while (bits != 0ull) {
+          r.issue(S.psi, gj, x0, d, bits, c_d);
+          r.add(acc);
+        }
+        if (t1 != t0) {  // the item's last step
+          const int32_t tgt = (int32_t)read_lane((uint32_t)tg, j);
+          if (mine) {
+            const double s = (double)sg;
+            const double dl = s * acc;
+            S.psi[(uint64_t)ij * kLanes + lane] = acc + 1.0 / s;
+            if (S.dout) S.dout[(uint64_t)ij * kLanes + lane] = dl;
+            if (tgt >= 0 && tgt < ntgt) S.res[((uint64_t)tgt * S.G + gj / n) * kLanes + lane] = (level > 0) ? dl : 0.0;
+          }
+          acc = 0.0;
+        }
+        t0 = t1;
+        c0 = c1;
+        t1 = t2;
+        c1 = c2;
+        x0 = x1;
+        x1 = x2;
+        h0 = h1;
+        h1 = h2;
+        m0 = m1;
+      }
     }
   }
   const int ck[5] = {C_BWD_VPAIRS, C_BWD_APAIRS, C_BWD_DPAIRS, C_BWD_ITEMS, C_BWD_IARCS};
@@ -910,38 +1179,44 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
 // settled lane is zeroed by the first wavefront that read the record.
 __global__ void k_batch_cleanup(BatchState S, PartTotals tot) {
   const int lane = lane_id();
+  const uint64_t GN = (uint64_t)S.G * (uint64_t)S.n;
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  for (int p = 0; p < S.P; ++p) {
-    uint64_t total = tot.t[p];
-    if (total > S.capP) total = S.capP;
-    const uint32_t *items = S.items + (uint64_t)p * S.capP;
+  for (int l = 0; l < S.NL; ++l) {
+    uint64_t total = tot.t[l];
+    const uint64_t cap = list_end(S, l) - list_begin(S, l);
+    if (total > cap) total = cap;
+    const uint32_t *items = S.items + list_begin(S, l);
     for (uint64_t i = wave; i < total; i += nwaves) {
       const uint32_t it = items[i];
-      MaskRec &R = S.rec[it];
       if (S.push) {
-        const ull vis = R.vis;
+        const ull vis = S.msk[M_SEEN * GN + it];
         if ((vis >> lane) & 1ull) S.sig[(uint64_t)it * kLanes + lane] = 0ull;
       }
-      if (lane < 6) {
-        if (lane == 0) R.vis = 0ull;
-        else if (lane == 1) R.dn = 0ull;
-        else R.fr[lane - 2] = 0ull;
-      }
+      if (lane < M_COUNT) S.msk[lane * GN + it] = 0ull;
     }
   }
 }
 
+// The same for a batch that touched a good part of its groups' vertices: every
+// mask word of the groups it used (pulled counts only), in whole lines.
+__global__ void k_batch_clear(BatchState S) {
+  const uint64_t GN = (uint64_t)S.G * (uint64_t)S.n, used = (uint64_t)S.gused * (uint64_t)S.n;
+  for (int a = 0; a < M_COUNT; ++a)
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < used; i += (uint64_t)gridDim.x * blockDim.x)
+      S.msk[a * GN + i] = 0ull;
+}
+
 // Verification export of one level: per lane with a slot, distance = level,
 // sigma and delta from the state rows.
-__global__ void k_batch_export(BatchState S, int level, uint64_t begin, uint64_t count,
+__global__ void k_batch_export(DevGraph G, BatchState S, int level, uint64_t begin, uint64_t count,
                                const int32_t *lane_slot, uint64_t *dist, ull *sigma, double *delta,
                                int64_t k) {
   const uint64_t n = (uint64_t)S.n;
   const int lane = lane_id();
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  if (begin + count > S.cap) return;
+  if (begin + count > list_end(S, S.NL - 1)) return;
   for (uint64_t i = wave; i < count; i += nwaves) {
     const uint32_t it = S.items[begin + i];  // begin: absolute position (partition region + level offset)
     const uint32_t g = (uint32_t)(it / n);
@@ -950,7 +1225,7 @@ __global__ void k_batch_export(BatchState S, int level, uint64_t begin, uint64_t
     if (!((mask >> lane) & 1ull)) continue;
     const int32_t slot = lane_slot[g * kLanes + lane];
     if (slot < 0 || slot >= k) continue;
-    const uint64_t o = (uint64_t)slot * n + v;
+    const uint64_t o = (uint64_t)slot * n + (uint32_t)G.orig[v];
     dist[o] = (uint64_t)level;
     sigma[o] = S.sig[(uint64_t)it * kLanes + lane];
     if (delta && S.dout) delta[o] = S.dout[(uint64_t)it * kLanes + lane];
@@ -1206,6 +1481,24 @@ __global__ __launch_bounds__(BLOCK) void k_reach_bu(const int64_t *rp, const int
   wave_add_u64(qout_a, arcs);
 }
 
+// Rows of a CSR in internal order (at load): a wavefront per new row.
+__global__ void k_permute_rows(int64_t n, const int64_t *rp, const int32_t *col, const int64_t *nrp,
+                               const int32_t *orig, const int32_t *rank, int32_t *ncol) {
+  const int lane = lane_id();
+  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n; i += nwaves) {
+    const int64_t a = rp[orig[i]], k = nrp[i + 1] - nrp[i], b = nrp[i];
+    for (int64_t j = lane; j < k; j += 64) ncol[b + j] = rank[col[a + j]];
+  }
+}
+
+hipError_t launch_permute_rows(int64_t n, const int64_t *rp, const int32_t *col, const int64_t *nrp,
+                               const int32_t *orig, const int32_t *rank, int32_t *ncol, hipStream_t st) {
+  const int grid = (int)std::min<int64_t>(8192, (n + 3) / 4);
+  hipLaunchKernelGGL(k_permute_rows, dim3(grid), dim3(256), 0, st, n, rp, col, nrp, orig, rank, ncol);
+  return hipGetLastError();
+}
+
 // Streaming probes over n16 16-byte words: every thread keeps four 16-byte
 // loads in flight (one per grid stride) before it uses them, so the probe is
 // bound by HBM and not by the latency of one load at a time.  Copy: loads and
@@ -1263,21 +1556,12 @@ hipError_t launch_batch_init(const BatchState &S, const uint32_t *items0, const 
 }
 
 template <int K>
-static void launch_fwd_k(const DevGraph &G, const BatchState &S, int level, const Launch &L, hipStream_t st) {
-  if (S.push) {
-    switch (L.block) {
-      case 64: k_fwd_push<64, K><<<dim3(L.grid), dim3(64), 0, st>>>(G, S, level); break;
-      case 128: k_fwd_push<128, K><<<dim3(L.grid), dim3(128), 0, st>>>(G, S, level); break;
-      case 512: k_fwd_push<512, K><<<dim3(L.grid), dim3(512), 0, st>>>(G, S, level); break;
-      default: k_fwd_push<256, K><<<dim3(L.grid), dim3(256), 0, st>>>(G, S, level); break;
-    }
-    return;
-  }
+static void launch_push_k(const DevGraph &G, const BatchState &S, int level, const Launch &L, hipStream_t st) {
   switch (L.block) {
-    case 64: k_fwd_level<64, K><<<dim3(L.grid), dim3(64), 0, st>>>(G, S, level); break;
-    case 128: k_fwd_level<128, K><<<dim3(L.grid), dim3(128), 0, st>>>(G, S, level); break;
-    case 512: k_fwd_level<512, K><<<dim3(L.grid), dim3(512), 0, st>>>(G, S, level); break;
-    default: k_fwd_level<256, K><<<dim3(L.grid), dim3(256), 0, st>>>(G, S, level); break;
+    case 64: k_fwd_push<64, K><<<dim3(L.grid), dim3(64), 0, st>>>(G, S, level); break;
+    case 128: k_fwd_push<128, K><<<dim3(L.grid), dim3(128), 0, st>>>(G, S, level); break;
+    case 512: k_fwd_push<512, K><<<dim3(L.grid), dim3(512), 0, st>>>(G, S, level); break;
+    default: k_fwd_push<256, K><<<dim3(L.grid), dim3(256), 0, st>>>(G, S, level); break;
   }
 }
 
@@ -1301,47 +1585,47 @@ hipError_t launch_bu_level(const DevGraph &G, const BatchState &S, int level, La
 }
 
 hipError_t launch_fwd_level(const DevGraph &G, const BatchState &S, int level, Launch L, hipStream_t st) {
-  switch (L.items) {
-    case 2: launch_fwd_k<2>(G, S, level, L, st); break;
-    case 4: launch_fwd_k<4>(G, S, level, L, st); break;
-    default: launch_fwd_k<1>(G, S, level, L, st); break;
+  if (S.push) {
+    switch (L.items) {
+      case 2: launch_push_k<2>(G, S, level, L, st); break;
+      case 4: launch_push_k<4>(G, S, level, L, st); break;
+      default: launch_push_k<1>(G, S, level, L, st); break;
+    }
+  } else {
+    DISPATCH_BLOCK(L, k_fwd_level, G, S, level);
   }
   return hipGetLastError();
 }
 
-template <int K>
-static void launch_bwd_k(const DevGraph &G, const BatchState &S, int level, int ntgt, int full, const Launch &L,
-                         hipStream_t st) {
-  switch (L.block) {
-    case 64: k_bwd_level<64, K><<<dim3(L.grid), dim3(64), 0, st>>>(G, S, level, ntgt, full); break;
-    case 128: k_bwd_level<128, K><<<dim3(L.grid), dim3(128), 0, st>>>(G, S, level, ntgt, full); break;
-    case 512: k_bwd_level<512, K><<<dim3(L.grid), dim3(512), 0, st>>>(G, S, level, ntgt, full); break;
-    default: k_bwd_level<256, K><<<dim3(L.grid), dim3(256), 0, st>>>(G, S, level, ntgt, full); break;
-  }
+hipError_t launch_publish_counts(const BatchState &S, int level, hipStream_t st) {
+  hipLaunchKernelGGL(k_publish_counts, dim3(1), dim3(64), 0, st, S, level);
+  return hipGetLastError();
 }
 
-hipError_t launch_bwd_level(const DevGraph &G, const BatchState &S, int level, int ntgt, int full, Launch L,
-                            hipStream_t st) {
-  switch (L.items) {
-    case 2: launch_bwd_k<2>(G, S, level, ntgt, full, L, st); break;
-    case 4: launch_bwd_k<4>(G, S, level, ntgt, full, L, st); break;
-    default: launch_bwd_k<1>(G, S, level, ntgt, full, L, st); break;
-  }
+hipError_t launch_bwd_level(const DevGraph &G, const BatchState &S, int level, int ntgt, Launch L, hipStream_t st) {
+  DISPATCH_BLOCK(L, k_bwd_level, G, S, level, ntgt);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_cleanup(const BatchState &S, const PartTotals &tot, Launch L, hipStream_t st) {
-  hipLaunchKernelGGL(k_batch_cleanup, dim3(L.grid), dim3(256), 0, st, S, tot);
+  // clearing every word costs M_COUNT words per (group, vertex) in whole
+  // lines, the sparse form M_COUNT lines per item
+  uint64_t items = 0;
+  for (int l = 0; l < S.NL; ++l) items += tot.t[l];
+  if (!S.push && items * 8 >= (uint64_t)S.gused * (uint64_t)S.n)
+    hipLaunchKernelGGL(k_batch_clear, dim3(L.grid), dim3(256), 0, st, S);
+  else
+    hipLaunchKernelGGL(k_batch_cleanup, dim3(L.grid), dim3(256), 0, st, S, tot);
   return hipGetLastError();
 }
 
-hipError_t launch_batch_export(const BatchState &S, int level, uint64_t begin, uint64_t count,
+hipError_t launch_batch_export(const DevGraph &G, const BatchState &S, int level, uint64_t begin, uint64_t count,
                                const int32_t *lane_slot, uint64_t *dist, ull *sigma, double *delta, int64_t k,
                                hipStream_t st) {
   if (count == 0) return hipSuccess;
   uint64_t waves = count < 65536 ? count : 65536;
   const int grid = (int)((waves * 64 + 255) / 256);
-  hipLaunchKernelGGL(k_batch_export, dim3(grid), dim3(256), 0, st, S, level, begin, count, lane_slot, dist,
+  hipLaunchKernelGGL(k_batch_export, dim3(grid), dim3(256), 0, st, G, S, level, begin, count, lane_slot, dist,
                      sigma, delta, k);
   return hipGetLastError();
 }

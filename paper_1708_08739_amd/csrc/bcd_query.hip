@@ -239,7 +239,7 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
                                 ProfAcc *prof, bool *sigma_overflow, bool copy_res = true,
                                 unsigned long long *ovl_out = nullptr) {
   hipStream_t st = ws->stream;
-  const DevGraph D = g->dev();
+  const DevGraph D = g->dev_internal();
   const bool profiling = g->profiling.load();
   const size_t G64 = (size_t)ws->G * kLanes;
   HIPCHK(hipMemcpyAsync(ws->d_items0, ws->h_items0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
@@ -252,34 +252,34 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
   }
   ws->sig_zero = false;  // until this batch has completed
   for (int attempt = 0;; ++attempt) {
-    ws->S.epoch += 1;
-    BatchState S = ws->S;  // kernel arguments: this batch's epoch and capacity
+    BatchState S = ws->S;  // kernel arguments
     if (!ex) S.dout = nullptr;
     S.P = ws->batch_parts(k);  // partitions that hold this batch's groups
+    S.NL = ws->lists(S.P);
     S.gused = (k + kLanes - 1) / kLanes;
     S.last_lanes = (k % kLanes) == 0 ? ~0ull : ((1ull << (k % kLanes)) - 1ull);
     S.bu_den = g->config().bottom_up;
     S.push = push;
     S.keep_all = full ? 1 : 0;
-    const int P = S.P;
-    const Launch L = g->launch_parts(P);
+    const int NL = S.NL;
+    const Launch L = g->launch_parts(S.P, S.gused);
     // level-0 placement depends on the partition sizes (they change when the list grows)
     ws->stage_sources_dest(k);
     HIPCHK(hipMemcpyAsync(ws->d_dest0, ws->h_dest0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     uint32_t *hc = ws->h_cnt;
     uint32_t *hc0 = hc + kCntStage;
-    for (int p = 0; p < P; ++p) hc0[p] = ws->h_cnt0[p];
-    HIPCHK(hipMemcpyAsync(&S.cnt[0], hc0, (size_t)P * sizeof(uint32_t), hipMemcpyHostToDevice, st));
+    for (int l = 0; l < NL; ++l) hc0[l] = ws->h_cnt0[l];
+    HIPCHK(hipMemcpyAsync(&S.cnt[0], hc0, (size_t)NL * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     if (ntgt > 0) HIPCHK(hipMemsetAsync(S.res, 0, (size_t)ntgt * G64 * sizeof(double), st));
     HIPCHK(hipMemsetAsync(S.tmin, 0xFF, sizeof(uint32_t), st));
     HIPCHK(hipMemsetAsync(S.flags, 0, 4 * sizeof(uint32_t), st));
-    HIPCHK(hipMemsetAsync(S.ovl, 0, (size_t)ws->G * sizeof(unsigned long long), st));
+    HIPCHK(hipMemsetAsync(S.ovl, 0, 2 * (size_t)ws->G * sizeof(unsigned long long), st));
     HIPCHK(launch_batch_init(S, ws->d_items0, ws->d_masks0, ws->d_dest0, k, st));
 
     // forward, in chunks of levels between host checks; a level found
     // bottom-up gets its own kernel, launched before the level's top-down
     // kernel (both decide on the device whether they have work)
-    std::vector<uint32_t> cntp(hc0, hc0 + P);  // cntp[l * P + p] = items of partition p on level l
+    std::vector<uint32_t> cntp(hc0, hc0 + NL);  // cntp[lv * NL + l] = items of list l on level lv
     uint64_t last_tot = (uint64_t)k;           // items of the last recorded level
     int lmax = -1;
     int level = 0;
@@ -306,9 +306,10 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
       }
       // counts of the levels not recorded yet, up to the one the last
       // launch discovered (or that the next chunk finds bottom-up)
-      const int rec_from = (int)(cntp.size() / P);
+      const int rec_from = (int)(cntp.size() / NL);
       const int nrec = level - rec_from + 1;
-      HIPCHK(hipMemcpyAsync(hc, &S.cnt[(size_t)rec_from * P], (size_t)nrec * P * sizeof(uint32_t),
+      HIPCHK(launch_publish_counts(S, level, st));
+      HIPCHK(hipMemcpyAsync(hc, &S.cnt[(size_t)rec_from * NL], (size_t)nrec * NL * sizeof(uint32_t),
                             hipMemcpyDeviceToHost, st));
       uint32_t *hm = reinterpret_cast<uint32_t *>(ws->h_misc);
       HIPCHK(hipMemcpyAsync(hm, S.flags, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
@@ -321,14 +322,14 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
       for (int i = 0; i < nrec; ++i) {
         const int l = rec_from + i;
         uint64_t tot = 0;
-        for (int p = 0; p < P; ++p) tot += hc[(size_t)i * P + p];
+        for (int j = 0; j < NL; ++j) tot += hc[(size_t)i * NL + j];
         // level `level` is only counted once its bottom-up kernel has run
         if (l == level && bottom_up_rule(S.bu_den, l, last_tot, S.gused, S.n)) break;
         if (tot == 0) {
           lmax = l;
           break;
         }
-        cntp.insert(cntp.end(), hc + (size_t)i * P, hc + (size_t)(i + 1) * P);
+        cntp.insert(cntp.end(), hc + (size_t)i * NL, hc + (size_t)(i + 1) * NL);
         last_tot = tot;
       }
       if (lmax < 0 && level > g->n) return fail(BCD_ERR_DEVICE, "forward pass did not terminate");
@@ -342,6 +343,7 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
       continue;
     }
     ws->last_depth = lmax;
+    S.top = lmax - 1;
     if (flags_h[0]) *sigma_overflow = true;
     const size_t fwd_events = ev;
 
@@ -352,26 +354,26 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
     if (stop >= 0) {
       for (int lv = lmax; lv >= stop; --lv) {
         if (profiling) HIPCHK(hipEventRecord(ws->event_pair(ev).first, st));
-        HIPCHK(launch_bwd_level(D, S, lv, ntgt, full ? 1 : 0, L, st));
+        HIPCHK(launch_bwd_level(D, S, lv, ntgt, L, st));
         if (profiling) {
           HIPCHK(hipEventRecord(ws->event_pair(ev).second, st));
           ++ev;
         }
       }
     }
-    const int levels = (int)(cntp.size() / P);
+    const int levels = (int)(cntp.size() / NL);
     PartTotals tot{};
     for (int l = 0; l < levels; ++l)
-      for (int p = 0; p < P; ++p) tot.t[p] += cntp[(size_t)l * P + p];
+      for (int j = 0; j < NL; ++j) tot.t[j] += cntp[(size_t)l * NL + j];
     if (ex) {
-      std::vector<uint64_t> pos((size_t)P);
-      for (int p = 0; p < P; ++p) pos[(size_t)p] = (uint64_t)p * S.capP;
+      std::vector<uint64_t> pos((size_t)NL);
+      for (int j = 0; j < NL; ++j) pos[(size_t)j] = list_begin(S, j);
       for (int l = 0; l < levels; ++l)
-        for (int p = 0; p < P; ++p) {
-          const uint64_t c = cntp[(size_t)l * P + p];
-          HIPCHK(launch_batch_export(S, l, pos[(size_t)p], c, ws->d_lane_slot, ex->dist, ex->sigma, ex->delta, ex->k,
-                                     st));
-          pos[(size_t)p] += c;
+        for (int j = 0; j < NL; ++j) {
+          const uint64_t c = cntp[(size_t)l * NL + j];
+          HIPCHK(launch_batch_export(D, S, l, pos[(size_t)j], c, ws->d_lane_slot, ex->dist, ex->sigma, ex->delta,
+                                     ex->k, st));
+          pos[(size_t)j] += c;
         }
     }
     if (ntgt > 0 && copy_res)
@@ -380,16 +382,15 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
       HIPCHK(hipMemcpyAsync(ovl_out, S.ovl, (size_t)ws->G * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     HIPCHK(launch_batch_cleanup(S, tot, L, st));
     HIPCHK(launch_ctr_fold(S.ctr, kCtrSlots, S.acc, st));
-    HIPCHK(hipMemsetAsync(S.cnt, 0, ((size_t)lmax + 2) * P * sizeof(uint32_t), st));
     HIPCHK(hipStreamSynchronize(st));
     if (profiling && prof) {
       for (size_t i = 0; i < ev; ++i) {
         prof->add(g, i < fwd_events ? 0 : 1, ws->events[i].first, ws->events[i].second);
       }
       for (int l = 0; l < levels; ++l)
-        for (int p = 0; p < P; ++p) {
-          prof->items[0] += cntp[(size_t)l * P + p];
-          if (stop >= 0 && l >= stop) prof->items[1] += cntp[(size_t)l * P + p];
+        for (int j = 0; j < NL; ++j) {
+          prof->items[0] += cntp[(size_t)l * NL + j];
+          if (stop >= 0 && l >= stop) prof->items[1] += cntp[(size_t)l * NL + j];
         }
     }
     ws->sig_zero = push != 0;  // the cleanup of a pushing batch zeroed the counts it set

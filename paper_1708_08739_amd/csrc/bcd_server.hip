@@ -401,6 +401,7 @@ static void worker_loop(bcd_server *S, Workspace *ws) {
     bool ovf = false;
     uint64_t ctr[C_COUNT] = {0};
     int ntgt = 0;
+    std::vector<int32_t> tgt_ids;  // internal ids of tg, kept until the copy has been read
     bool threw = false;
     try {
       // an earlier batch whose item-list growth failed left this workspace to
@@ -436,7 +437,9 @@ static void worker_loop(bcd_server *S, Workspace *ws) {
         if (rc == BCD_OK) {
           d_t = ws->d_tgt_list;
           d_routes = ws->d_routes;
-          hipError_t e = hipMemcpyAsync(d_t, tg.data(), (size_t)ntgt * sizeof(int32_t), hipMemcpyHostToDevice, ws->stream);
+          tgt_ids = tg;
+          for (int32_t &v : tgt_ids) v = g->rank[(size_t)v];
+          hipError_t e = hipMemcpyAsync(d_t, tgt_ids.data(), (size_t)ntgt * sizeof(int32_t), hipMemcpyHostToDevice, ws->stream);
           if (e == hipSuccess)
             e = hipMemcpyAsync(d_routes, routes.data(), routes.size() * sizeof(ResultRoute), hipMemcpyHostToDevice,
                                ws->stream);
@@ -529,9 +532,9 @@ namespace bcd {
 // lane masks; unweighted: level records).
 uint64_t batch_workspace_bytes(const Graph *g, int groups) {
   const uint64_t GN = (uint64_t)groups * (uint64_t)g->n;
-  uint64_t b = GN * kLanes * 16 + GN * 2 * sizeof(LevMask) + GN * 16 * 12 + (uint64_t)g->n * 24;
+  uint64_t b = GN * kLanes * 16 + GN * 16 * 12 + (uint64_t)g->n * 24;
   if (g->weighted) b += GN * kLanes * 8 + GN * 28 + GN * 5 * 8 + (uint64_t)groups * (uint64_t)g->m * 8;
-  else b += GN * sizeof(MaskRec);
+  else b += GN * M_COUNT * 8;
   return b;
 }
 

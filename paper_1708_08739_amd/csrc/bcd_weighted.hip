@@ -480,7 +480,7 @@ __global__ void k_w_cleanup(BatchState S) {
   }
 }
 
-__global__ void k_w_export(BatchState S, const int32_t *lane_slot, uint64_t *dist, ull *sigma, double *delta,
+__global__ void k_w_export(DevGraph G, BatchState S, const int32_t *lane_slot, uint64_t *dist, ull *sigma, double *delta,
                            int64_t k) {
   const uint64_t n = (uint64_t)S.n;
   const uint64_t GN = (uint64_t)S.G * n;
@@ -498,7 +498,7 @@ __global__ void k_w_export(BatchState S, const int32_t *lane_slot, uint64_t *dis
     if (d == kInf) continue;
     const int32_t slot = lane_slot[g * kLanes + lane];
     if (slot < 0 || slot >= k) continue;
-    const uint64_t o = (uint64_t)slot * n + v;
+    const uint64_t o = (uint64_t)slot * n + (uint32_t)G.orig[v];
     dist[o] = d;
     sigma[o] = S.sig[row];
     if (delta && S.dout) delta[o] = S.dout[row];
@@ -548,9 +548,9 @@ hipError_t launch_w_cleanup(const BatchState &S, Launch L, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_w_export(const BatchState &S, const int32_t *lane_slot, uint64_t *dist, ull *sigma,
+hipError_t launch_w_export(const DevGraph &G, const BatchState &S, const int32_t *lane_slot, uint64_t *dist, ull *sigma,
                            double *delta, int64_t k, Launch L, hipStream_t st) {
-  hipLaunchKernelGGL(k_w_export, dim3(L.grid), dim3(256), 0, st, S, lane_slot, dist, sigma, delta, k);
+  hipLaunchKernelGGL(k_w_export, dim3(L.grid), dim3(256), 0, st, G, S, lane_slot, dist, sigma, delta, k);
   return hipGetLastError();
 }
 
@@ -626,19 +626,19 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
                                  bool *sigma_overflow,
                                  bool copy_res = true, unsigned long long *ovl_out = nullptr) {
   hipStream_t st = ws->stream;
-  const DevGraph D = g->dev();
+  const DevGraph D = g->dev_internal();
   const bool profiling = g->profiling.load();
   const size_t G64 = (size_t)ws->G * kLanes;
   HIPCHK(hipMemcpyAsync(ws->d_items0, ws->h_items0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(ws->d_masks0, ws->h_masks0, (size_t)k * sizeof(unsigned long long), hipMemcpyHostToDevice,
                         st));
   for (int attempt = 0;; ++attempt) {
-    ws->S.epoch += 1;
     BatchState S = ws->S;
     if (!ex) S.dout = nullptr;
     S.P = ws->batch_parts(k);  // partitions that hold this batch's groups
+    S.NL = S.P;
     const int P = S.P;
-    const Launch L = g->launch_parts(P);
+    const Launch L = g->launch_parts(P, (k + kLanes - 1) / kLanes);
     ws->stage_sources_dest(k);
     HIPCHK(hipMemcpyAsync(ws->d_dest0, ws->h_dest0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     uint32_t *hc = ws->h_cnt;
@@ -649,7 +649,7 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
     if (ntgt > 0) HIPCHK(hipMemsetAsync(S.res, 0, (size_t)ntgt * G64 * sizeof(double), st));
     HIPCHK(hipMemsetAsync(S.tmin, 0xFF, sizeof(uint32_t), st));
     HIPCHK(hipMemsetAsync(S.flags, 0, 4 * sizeof(uint32_t), st));
-    HIPCHK(hipMemsetAsync(S.ovl, 0, (size_t)ws->G * sizeof(unsigned long long), st));
+    HIPCHK(hipMemsetAsync(S.ovl, 0, 2 * (size_t)ws->G * sizeof(unsigned long long), st));
     HIPCHK(launch_w_init(S, ws->d_items0, ws->d_masks0, ws->d_dest0, k, st));
     size_t ev = 0;
     auto rec0 = [&]() -> hipError_t {
@@ -733,7 +733,7 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
         HIPCHK(launch_w_bwd(D, S, lv, ntgt, full ? 1 : 0, L, st));
         HIPCHK(rec1());
       }
-    if (ex) HIPCHK(launch_w_export(S, ws->d_lane_slot, ex->dist, ex->sigma, ex->delta, ex->k, L, st));
+    if (ex) HIPCHK(launch_w_export(D, S, ws->d_lane_slot, ex->dist, ex->sigma, ex->delta, ex->k, L, st));
     if (ntgt > 0 && copy_res)
       HIPCHK(hipMemcpyAsync(ws->h_res, S.res, (size_t)ntgt * G64 * sizeof(double), hipMemcpyDeviceToHost, st));
     if (ovl_out)

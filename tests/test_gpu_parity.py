@@ -889,3 +889,47 @@ def test_rmat22_full_width_and_draws(B, oracle):
     got, st = G.bc_sampled(r, T=12, seed=7, flags=B.BCD_NO_EXACT_FALLBACK)
     want, ost = oracle.bc_sampled(g, r, 12, 7)
     assert close(got, want) and st["distinct_sources"] == ost["distinct_sources"]
+
+
+def fan_graph(sizes):
+    """For every k in sizes a hub with k in-arcs (from the first k feeders) and
+    k out-arcs (to the first k sinks); sink j leads back to feeder j, feeder j
+    on to feeder j + 1, so every vertex reaches every other on several levels."""
+    w = max(sizes)
+    feed, sink = 0, w
+    src, dst = [], []
+    for i, k in enumerate(sizes):
+        hub = 2 * w + i
+        for j in range(k):
+            src += [feed + j, hub]
+            dst += [hub, sink + j]
+    for j in range(w):
+        src += [sink + j, feed + j]
+        dst += [feed + j, feed + (j + 1) % w]
+    return gg.from_arcs(2 * w + len(sizes), src, dst, name="fans"), [2 * w + i for i in range(len(sizes))]
+
+
+@pytest.mark.parametrize("sizes", [(1, 31, 32, 33, 63, 64, 65, 127, 128, 129), (255, 256, 257, 511, 512, 513, 640, 1153)])
+def test_row_lengths_around_steps_and_heavy_vertices(B, oracle, sizes):
+    """Rows one below, at and one above the 32-arc steps of a wavefront, the
+    steps of a workgroup and the limit from which a workgroup takes a vertex,
+    in both directions, top-down, bottom-up and pushed: distances and counts
+    bit-exact, dependencies within 1e-10, and the same bits as the LDS engine."""
+    g, hubs = fan_graph(sizes)
+    src = hubs + gg.uniform_vertices(g.n, 130 - len(hubs), seed=7, exclude=hubs)
+    want = [oracle.source_pass(g, s) for s in src]
+    lds = dev(B, g, engine=B.BCD_ENGINE_LDS).multi_source_pass(src)
+    for bu, push in ((0, 0), (4096, 0), (4, 0), (0, 1)):
+        G = dev(B, g, groups=3, bottom_up=bu, push=push)
+        print("fans", sizes, "bottom_up", bu, "push", push, flush=True)
+        d, sg, dl = G.multi_source_pass(src)
+        for i in range(len(src)):
+            assert np.array_equal(d[i], want[i][0]) and np.array_equal(sg[i], want[i][1]), (bu, push, i)
+            assert close(dl[i], want[i][2]), (bu, push, i)
+        assert np.array_equal(dl, lds[2]), (bu, push)
+        # every source's dependency on a target that is itself a source
+        for r in (hubs[-1], src[-1]):
+            dep, cnt = G.dependencies(r, src, counters=True)
+            od, oc = oracle.dependencies(g, r, src)
+            assert close(dep, od) and np.array_equal(cnt, oc), (bu, push, r)
+            assert np.array_equal(G.dependencies(r, src), dep), (bu, push, r)
