@@ -121,28 +121,92 @@ static __device__ __forceinline__ void stage_flush(uint32_t *buf, int &nbuf, uin
   nbuf = 0;
 }
 
-// Append one wave-uniform value (when `pred` is true on the wavefront).
-template <int CAP>
-static __device__ __forceinline__ void stage_one(uint32_t *buf, int &nbuf, bool pred, uint32_t value, uint32_t *tail,
-                                                 uint32_t *dst, uint64_t dst_base, uint64_t dst_end,
-                                                 uint32_t *overflow_flag) {
-  if (!pred) return;
-  if (nbuf == CAP) stage_flush(buf, nbuf, tail, dst, dst_base, dst_end, overflow_flag);
-  if ((threadIdx.x & 63) == 0) buf[nbuf] = value;
-  nbuf += 1;
+// Appended items are staged in per-wavefront LDS buffers, one for the light
+// and one for the heavy list of the partition, and copied to the lists in
+// blocks: one counter atomic per block instead of one per chunk of arcs, which
+// keeps the lists' tail counters cold.
+constexpr int kStage = 256;
+constexpr int kStageHeavy = 64;
+// Most items a wavefront takes as one block (level launches).
+constexpr int kBlockItems = 32;
+
+struct Stage {
+  uint32_t *buf, *hbuf;  // this wavefront's LDS buffers
+  int n, nh;             // entries staged
+};
+
+// The item lists of the level being built: they start behind `level`'s items
+// (BU: the lists of `level` itself, which the bottom-up kernel fills).  The
+// positions are read again at every flush, which is rare, so that no
+// registers hold them in between.
+template <bool BU>
+struct LevelLists {
+  const BatchState &S;
+  int level;
+  __device__ __forceinline__ uint32_t *tail(int l) const { return tail_at(S, level + (BU ? 0 : 1), l); }
+  __device__ __forceinline__ uint64_t base(int l) const {
+    return S.off[(uint64_t)level * S.NL + l] + (BU ? 0u : *tail_at(S, level, l));
+  }
+  __device__ __forceinline__ uint64_t end(int l) const { return list_end(S, l); }
+  __device__ __forceinline__ uint32_t *dst() const { return S.items; }
+};
+
+template <class Lists>
+static __device__ __forceinline__ void flush_list(const BatchState &S, const Lists &L, int l, const uint32_t *buf,
+                                                  int &n) {
+  if (n == 0) return;
+  const uint64_t base = L.base(l), end = L.end(l);
+  uint32_t p0 = 0;
+  if (lane_id() == 0) p0 = atomicAdd(L.tail(l), (uint32_t)n);
+  p0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)p0);
+  for (int j = lane_id(); j < n; j += 64) {
+    const uint64_t p = base + p0 + (uint64_t)j;
+    if (p < end) L.dst()[p] = buf[j];
+    else atomicOr(&S.flags[1], 1u);
+  }
+  n = 0;
 }
 
-// Append the value of every lane where `pred` holds (lane order kept).
-template <int CAP>
-static __device__ __forceinline__ void stage_lanes(uint32_t *buf, int &nbuf, bool pred, uint32_t value, uint32_t *tail,
-                                                   uint32_t *dst, uint64_t dst_base, uint64_t dst_end,
-                                                   uint32_t *overflow_flag) {
-  const ull m = __ballot(pred);
-  if (m == 0ull) return;
-  const int c = __popcll(m);
-  if (nbuf + c > CAP) stage_flush(buf, nbuf, tail, dst, dst_base, dst_end, overflow_flag);
-  if (pred) buf[nbuf + lanes_below(m)] = value;
-  nbuf += c;
+template <class Lists>
+static __device__ __forceinline__ void flush_stage(const BatchState &S, const Lists &L, int p, Stage &g) {
+  flush_list(S, L, p, g.buf, g.n);
+  flush_list(S, L, S.P + p, g.hbuf, g.nh);
+}
+
+// Append the vertices w of the lanes where `enq` holds (items gbase + w) to
+// partition p's lists.
+template <class Lists>
+static __device__ __forceinline__ void append_chunk(const BatchState &S, const Lists &L, int p, Stage &g,
+                                                    uint64_t gbase, uint32_t w, bool enq) {
+  ull eb = __ballot(enq);
+  if (eb == 0ull) return;
+  const ull hb = __ballot(enq && w < S.H);
+  if (hb != 0ull) {
+    const int c = __popcll(hb);
+    if (g.nh + c > kStageHeavy) flush_list(S, L, S.P + p, g.hbuf, g.nh);
+    if (enq && w < S.H) g.hbuf[g.nh + lanes_below(hb)] = (uint32_t)(gbase + w);
+    g.nh += c;
+    eb &= ~hb;
+    if (eb == 0ull) return;
+  }
+  const int c = __popcll(eb);
+  if (g.n + c > kStage) flush_list(S, L, p, g.buf, g.n);
+  if (enq && w >= S.H) g.buf[g.n + lanes_below(eb)] = (uint32_t)(gbase + w);
+  g.n += c;
+}
+
+// First thing of a level's top-down launch (one thread per partition): the
+// level's counts go to its cnt row, the next level's lists start behind it and
+// the tails of the level after that are cleared.
+static __device__ __forceinline__ void open_level(const BatchState &S, int level, int p, uint32_t nl, uint32_t nh,
+                                                  uint64_t nb, uint64_t nhb) {
+  const uint64_t row = (uint64_t)level * S.NL + p, next = row + S.NL;
+  S.cnt[row] = nl;
+  S.cnt[row + S.P] = nh;
+  S.off[next] = nb;
+  S.off[next + S.P] = nhb;
+  *tail_at(S, level + 2, p) = 0u;
+  *tail_at(S, level + 2, S.P + p) = 0u;
 }
 
 // This workgroup's share of a partitioned item list (see BatchState).

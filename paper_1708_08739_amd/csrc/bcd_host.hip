@@ -370,9 +370,8 @@ bcd_status Workspace::reset_batch_dense() {
   if (weighted_ready) {
     HIPCHK(hipMemsetAsync(S.wd, 0xFF, GN * kLanes * sizeof(uint32_t), stream));
     HIPCHK(hipMemsetAsync(S.wc, 0, GN * kLanes * sizeof(uint32_t), stream));
-    HIPCHK(hipMemsetAsync(S.chg, 0, 2 * GN * sizeof(unsigned long long), stream));
-    HIPCHK(hipMemsetAsync(S.bqn, 0, 4 * sizeof(uint32_t), stream));
-    HIPCHK(hipMemsetAsync(S.rln, 0, sizeof(uint32_t), stream));
+    HIPCHK(hipMemsetAsync(S.chg, 0, 3 * GN * sizeof(unsigned long long), stream));
+    HIPCHK(hipMemsetAsync(S.rtail, 0, (size_t)kMaxLists * kTailStride * sizeof(uint32_t), stream));
     HIPCHK(hipMemsetAsync(S.wdn, 0, GN * sizeof(unsigned long long), stream));
   }
   HIPCHK(hipStreamSynchronize(stream));
@@ -438,8 +437,8 @@ Graph::~Graph() {
   dfree(d_picol);
   dfree(d_orig);
   dfree(d_arcw);
-  dfree(d_arcp);
   dfree(d_iarc);
+  dfree(d_iopos);
 }
 
 DevGraph Graph::dev() const {
@@ -450,7 +449,8 @@ DevGraph Graph::dev() const {
   G.col = d_col;
   G.irp = d_irp;
   G.icol = d_icol;
-  G.arcw = G.arcp = G.iarc = nullptr;
+  G.arcw = G.iarc = nullptr;
+  G.iopos = nullptr;
   G.orig = nullptr;
   return G;
 }
@@ -464,8 +464,8 @@ DevGraph Graph::dev_internal() const {
   G.irp = d_pirp;
   G.icol = d_picol;
   G.arcw = d_arcw;
-  G.arcp = d_arcp;
   G.iarc = d_iarc;
+  G.iopos = d_iopos;
   G.orig = d_orig;
   return G;
 }
@@ -685,8 +685,7 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
       orig[(size_t)i] = (int32_t)v;
       g->rank[(size_t)v] = (int32_t)i;
     }
-    if (!weight)
-      while (g->heavy < (uint64_t)(n / kHeavyShare) && deg(orig[g->heavy]) > kHeavyArcs) ++g->heavy;
+    while (g->heavy < (uint64_t)(n / kHeavyShare) && deg(orig[g->heavy]) > kHeavyArcs) ++g->heavy;
   }
   std::vector<int64_t> prp((size_t)n + 1, 0), pirp((size_t)n + 1, 0);
   for (int64_t i = 0; i < n; ++i) {
@@ -702,10 +701,11 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
   HIPCHK(hipMemcpy(g->d_orig, orig.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
   if (weight) {
     STCHK(dalloc(&g->d_arcw, (size_t)m));
-    STCHK(dalloc(&g->d_arcp, (size_t)m));
     STCHK(dalloc(&g->d_iarc, (size_t)m));
+    STCHK(dalloc(&g->d_iopos, (size_t)m));
     if (m > 0) {
-      std::vector<uint2> arcw((size_t)m), arcp((size_t)m), iarc((size_t)m);
+      std::vector<uint2> arcw((size_t)m), iarc((size_t)m);
+      std::vector<uint32_t> iopos((size_t)m);
       for (int64_t i = 0; i < n; ++i) {
         const size_t v = (size_t)orig[(size_t)i];
         size_t p = (size_t)prp[(size_t)i];
@@ -713,25 +713,26 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
           const size_t w = (size_t)col[e], j = (size_t)g->rank[w];
           arcw[p] = make_uint2((uint32_t)j, weight[e]);
           // an in-arc keeps its place in its row of the transpose
-          arcp[p] = make_uint2((uint32_t)j, (uint32_t)(pirp[j] + ((int64_t)ipos[(size_t)e] - irp[w])));
+          iopos[(size_t)(pirp[j] + ((int64_t)ipos[(size_t)e] - irp[w]))] = (uint32_t)p;
         }
         p = (size_t)pirp[(size_t)i];
         for (int64_t e = irp[v]; e < irp[v + 1]; ++e, ++p)
           iarc[p] = make_uint2((uint32_t)g->rank[(size_t)icol[(size_t)e]], iw[(size_t)e]);
       }
       HIPCHK(hipMemcpy(g->d_arcw, arcw.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
-      HIPCHK(hipMemcpy(g->d_arcp, arcp.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
       HIPCHK(hipMemcpy(g->d_iarc, iarc.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
+      HIPCHK(hipMemcpy(g->d_iopos, iopos.data(), (size_t)m * sizeof(uint32_t), hipMemcpyHostToDevice));
     }
-  } else {
+  }
+  {
     STCHK(dalloc(&g->d_pcol, (size_t)m));
-    STCHK(dalloc(&g->d_picol, (size_t)m));
+    if (!weight) STCHK(dalloc(&g->d_picol, (size_t)m));
     int32_t *d_rank = nullptr;
     STCHK(dalloc(&d_rank, (size_t)n));
     hipError_t e = hipMemcpy(d_rank, g->rank.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice);
     if (e == hipSuccess)
       e = launch_permute_rows(n, g->d_rp, g->d_col, g->d_prp, g->d_orig, d_rank, g->d_pcol, nullptr);
-    if (e == hipSuccess)
+    if (e == hipSuccess && !weight)
       e = launch_permute_rows(n, g->d_irp, g->d_icol, g->d_pirp, g->d_orig, d_rank, g->d_picol, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     dfree(d_rank);
@@ -839,7 +840,10 @@ bcd_status bcd_profile_get(const bcd_graph *gh, int32_t kind, bcd_kernel_profile
     }
   }
   if (open) u += b - a;
-  out->union_ms = u + g->prof_solo_ms[kind];
+  // the union is at most the sum; the interval ends are single-precision
+  // times after the origin, whose rounding can put it above where launches
+  // hardly overlap
+  out->union_ms = std::min(u + g->prof_solo_ms[kind], out->total_ms);
   return BCD_OK;
   BCD_GUARD_END
 }

@@ -53,10 +53,12 @@ constexpr int kDefaultPush = 0;
 constexpr int kMaxParts = 8;          // item-list partitions (one per XCD)
 constexpr int kCntStage = (kLevelChunkMax + 2) * kMaxLists;  // pinned slots for level counts
 // Vertices with more arcs than this (in- and out-arcs together) are taken by
-// a whole workgroup in the unweighted engine, at most one vertex in
-// kHeavyShare, so that their item lists stay small.  The limit is flat from 128
+// a whole workgroup in the unweighted engine and by several wavefronts in the
+// weighted one, at most one vertex in kHeavyShare, so that their item lists
+// stay small.  The limit is flat from 128
 // to 1,024 (R-MAT 16, 1,000 sources: 3.42 / 3.40 / 3.36 / 3.38 ms at 128 / 256 /
-// 512 / 1,024) and too high at 2,048 (3.82).
+// 512 / 1,024) and too high at 2,048 (3.82); weighted R-MAT 18, 2,048 draws: 130.5 /
+// 131.1 / 131.0 / 131.0 ms.
 constexpr int64_t kHeavyArcs = 512;
 constexpr int64_t kHeavyShare = 256;
 
@@ -152,7 +154,7 @@ struct Workspace {
   // runs source vertex src[i]; vertices must be distinct within a group.
   void stage_sources(const int32_t *src, int k);
   void stage_sources_dest(int k);
-  int lists(int P) const { return weighted_graph ? P : 2 * P; }  // item lists of a batch on P partitions
+  static int lists(int P) { return 2 * P; }  // item lists of a batch on P partitions: light, heavy
   // Partitions a batch of k staged sources uses: its groups are 0..ceil(k/64)-1
   // and group g belongs to partition g % P, so a batch of fewer groups than
   // S.P uses one partition per group and no workgroup is left without work.
@@ -184,15 +186,15 @@ struct Graph {
   int32_t *d_icol = nullptr;
   // the same graph in internal ids (DevGraph): rank[v] = internal id of v
   std::vector<int32_t> rank;
-  uint32_t heavy = 0;          // internal ids below are heavy (0 on weighted graphs)
+  uint32_t heavy = 0;          // internal ids below are heavy
   int64_t *d_prp = nullptr;
-  int32_t *d_pcol = nullptr;   // unweighted
+  int32_t *d_pcol = nullptr;
   int64_t *d_pirp = nullptr;
   int32_t *d_picol = nullptr;  // unweighted
   int32_t *d_orig = nullptr;
   uint2 *d_arcw = nullptr;     // weighted, internal ids: {head, length} per CSR arc
-  uint2 *d_arcp = nullptr;     // weighted: {head, transpose position} per CSR arc
   uint2 *d_iarc = nullptr;     // weighted: {tail, length} per transpose arc
+  uint32_t *d_iopos = nullptr; // weighted: CSR position per transpose arc
   mutable std::mutex cfg_mu;
   bcd_config cfg{};
   std::mutex pool_mu;

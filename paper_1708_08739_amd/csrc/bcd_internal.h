@@ -54,18 +54,18 @@ struct BatchState {
   // Item lists are split into P partitions (group g belongs to partition
   // g % P); workgroup b serves partition b % P, so with P = 8 every XCD
   // (workgroups are dealt to the 8 XCDs round-robin) walks only its own
-  // groups and their masks stay in that XCD's L2.  The unweighted engine
-  // keeps two lists per partition and level: list p holds the vertices a
-  // wavefront takes alone, list P + p the heavy ones (internal id < H), which
-  // a workgroup takes together; the weighted engine keeps list p only.
+  // groups and their masks stay in that XCD's L2.  There are two lists per
+  // partition and level: list p holds the vertices a wavefront takes alone,
+  // list P + p the heavy ones (internal id < H), which a workgroup takes
+  // together (unweighted engine) or several wavefronts in parts (weighted).
   uint32_t *items;           // [P * capP + P * capH] g * n + v, grouped by list, then level
   unsigned long long *imask; // the same shape: lanes of the item on its level
   uint64_t hbase;            // first item of the heavy lists (P * capP of the widest batch)
   uint64_t capP;             // items of list p: [p * capP, (p + 1) * capP)
   uint64_t capH;             // items of list P + p: [hbase + p * capH, hbase + (p + 1) * capH)
   int P;
-  int NL;                    // lists: 2 P (unweighted) or P (weighted)
-  uint32_t H;                // heavy vertices: internal ids 0 .. H-1 (unweighted engine)
+  int NL;                    // lists: 2 P
+  uint32_t H;                // heavy vertices: internal ids 0 .. H-1
   uint32_t *cnt;             // [(n + 2) * 16] items per (level, list): index level * NL + l
   uint32_t *tail;            // [4][16] lengths of the lists being filled, by level mod 4, each in a
                              // 128-byte line of its own (see tail_at)
@@ -88,13 +88,15 @@ struct BatchState {
   // weighted graphs only
   uint32_t *wd;              // [G][n][64] distances, 0xFFFFFFFF unreached
   uint32_t *wc;              // [G][n][64] shortest-path-DAG in-arcs not yet pushed
-  unsigned long long *chg;   // [2][G][n] lanes whose distance dropped (relaxation rounds)
-  uint32_t *bq;              // [2][G*n] relaxation round queues
-  uint32_t *bqn;             // [3] relaxation queue lengths (rotating)
-  uint32_t *rl;              // [G*n] items reached by any lane
-  uint32_t *rln;             // [1]
+  unsigned long long *chg;   // [3][G][n] lanes whose distance dropped, by relaxation round mod 3
+  uint32_t *bq;              // [3][queue] items changed in a round, by round mod 3 (lists as of `items`)
+  uint32_t *rl;              // [queue] items reached by any lane
+  uint32_t *qtail;           // [4][16] lengths of a round's queue lists, by round mod 4, a line each (qtail_at)
+  uint32_t *rtail;           // [16] lengths of the reached lists, a line each (rtail_at)
+  uint64_t capQ, capQH;      // a queue's list p: [p * capQ, (p + 1) * capQ), list P + p:
+  uint64_t qhbase, qsize;    //   [qhbase + p * capQH, ...); its size
   unsigned long long *wdn;   // [G][n] lanes on whose DAG the vertex is a target or lies below one
-  unsigned long long *dagm;  // [G][m] lanes on whose shortest-path DAG the arc lies, by transpose position
+  unsigned long long *dagm;  // [G][m] lanes on whose shortest-path DAG the arc lies, in CSR order
 };
 
 // Plain engine state (one source).
@@ -128,8 +130,8 @@ struct DevGraph {
   // a kernel reads of an arc (separate 4-byte arrays and one 16-byte record
   // of all fields both measured slower)
   const uint2 *arcw;    // [m] CSR order: {head, length} (relaxation)
-  const uint2 *arcp;    // [m] CSR order: {head, position of the arc in the transpose} (sigma, backward)
   const uint2 *iarc;    // [m] transpose order: {tail, length} (DAG in-degrees)
+  const uint32_t *iopos;  // [m] transpose order: position of the arc in the CSR
   const int32_t *orig;  // [n] caller's id of an internal id (exports)
 };
 
@@ -161,6 +163,17 @@ struct PartTotals {
 constexpr int kTailStride = 32;
 __host__ __device__ inline uint32_t *tail_at(const BatchState &S, int level, int l) {
   return S.tail + ((level & 3) * kMaxLists + l) * kTailStride;
+}
+__host__ __device__ inline uint32_t *qtail_at(const BatchState &S, int round, int l) {
+  return S.qtail + ((round & 3) * kMaxLists + l) * kTailStride;
+}
+__host__ __device__ inline uint32_t *rtail_at(const BatchState &S, int l) { return S.rtail + l * kTailStride; }
+// First item of list l in a relaxation queue (and in the reached list).
+__host__ __device__ inline uint64_t queue_begin(const BatchState &S, int l) {
+  return l < S.P ? (uint64_t)l * S.capQ : S.qhbase + (uint64_t)(l - S.P) * S.capQH;
+}
+__host__ __device__ inline uint64_t queue_end(const BatchState &S, int l) {
+  return queue_begin(S, l) + (l < S.P ? S.capQ : S.capQH);
 }
 // First item of list l's region.
 __host__ __device__ inline uint64_t list_begin(const BatchState &S, int l) {

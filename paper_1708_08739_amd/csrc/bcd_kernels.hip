@@ -128,88 +128,9 @@ static __device__ __forceinline__ bool discover(ull *seen, ull *next, uint32_t w
   return enq;
 }
 
-// Discovered heads are staged in per-wavefront LDS buffers, one for the
-// light list and one for the heavy list of the partition, and copied to the
-// next level's lists in blocks: one counter atomic per block instead of one
-// per out-arc chunk, which keeps the lists' tail counters cold.
-constexpr int kStage = 256;
-constexpr int kStageHeavy = 64;
-
-// Most items a wavefront takes as one block (level launches).
-constexpr int kBlockItems = 32;
-
-struct Stage {
-  uint32_t *buf, *hbuf;  // this wavefront's LDS buffers
-  int n, nh;             // entries staged
-};
-
-// First item of list l of the level being built: behind `level`'s items (BU:
-// of `level` itself, whose list the bottom-up kernel fills).  Read again at
-// every flush, which is rare, so that no registers hold it in between.
-template <bool BU>
-static __device__ __forceinline__ uint64_t next_base(const BatchState &S, int level, int l) {
-  return S.off[(uint64_t)level * S.NL + l] + (BU ? 0u : *tail_at(S, level, l));
-}
-
-template <bool BU>
-static __device__ __forceinline__ void flush_list(const BatchState &S, int level, int l, const uint32_t *buf, int &n) {
-  if (n == 0) return;
-  const uint64_t base = next_base<BU>(S, level, l), end = list_end(S, l);
-  uint32_t p0 = 0;
-  if (lane_id() == 0) p0 = atomicAdd(tail_at(S, level + (BU ? 0 : 1), l), (uint32_t)n);
-  p0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)p0);
-  for (int j = lane_id(); j < n; j += 64) {
-    const uint64_t p = base + p0 + (uint64_t)j;
-    if (p < end) S.items[p] = buf[j];
-    else atomicOr(&S.flags[1], 1u);
-  }
-  n = 0;
-}
-
-template <bool BU>
-static __device__ __forceinline__ void flush_stage(const BatchState &S, int level, int p, Stage &g) {
-  flush_list<BU>(S, level, p, g.buf, g.n);
-  flush_list<BU>(S, level, S.P + p, g.hbuf, g.nh);
-}
-
-// First thing of a level's top-down launch (one thread per partition): the
-// level's counts go to its cnt row, the next level's lists start behind it and
-// the tails of the level after that are cleared.
-static __device__ __forceinline__ void open_level(const BatchState &S, int level, int p, uint32_t nl, uint32_t nh,
-                                                  uint64_t nb, uint64_t nhb) {
-  const uint64_t row = (uint64_t)level * S.NL + p, next = row + S.NL;
-  S.cnt[row] = nl;
-  S.cnt[row + S.P] = nh;
-  S.off[next] = nb;
-  S.off[next + S.P] = nhb;
-  *tail_at(S, level + 2, p) = 0u;
-  *tail_at(S, level + 2, S.P + p) = 0u;
-}
-
 __global__ void k_publish_counts(BatchState S, int level) {
   const int l = (int)threadIdx.x;
   if (l < S.NL) S.cnt[(uint64_t)level * S.NL + l] = *tail_at(S, level, l);
-}
-
-// Append the heads w of the lanes where `enq` holds to partition p's lists.
-template <bool BU>
-static __device__ __forceinline__ void append_chunk(const BatchState &S, int level, int p, Stage &g, uint64_t gbase,
-                                                    uint32_t w, bool enq) {
-  ull eb = __ballot(enq);
-  if (eb == 0ull) return;
-  const ull hb = __ballot(enq && w < S.H);
-  if (hb != 0ull) {
-    const int c = __popcll(hb);
-    if (g.nh + c > kStageHeavy) flush_list<BU>(S, level, S.P + p, g.hbuf, g.nh);
-    if (enq && w < S.H) g.hbuf[g.nh + lanes_below(hb)] = (uint32_t)(gbase + w);
-    g.nh += c;
-    eb &= ~hb;
-    if (eb == 0ull) return;
-  }
-  const int c = __popcll(eb);
-  if (g.n + c > kStage) flush_list<BU>(S, level, p, g.buf, g.n);
-  if (enq && w >= S.H) g.buf[g.n + lanes_below(eb)] = (uint32_t)(gbase + w);
-  g.n += c;
 }
 
 // One BFS level of the batched forward pass (unweighted graphs).  For every
@@ -256,6 +177,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
   __shared__ uint32_t stage_all[NW * kStage], hstage_all[NW * kStageHeavy];
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
+  const LevelLists<false> lists{S, level};
   {
     const uint32_t nl = *tail_at(S, level, pv.p), nh = *tail_at(S, level, P + pv.p);
     const uint64_t nb = S.off[lrow + pv.p] + nl, nhb = S.off[lrow + P + pv.p] + nh;
@@ -425,7 +347,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
         }
         acc = ov = pdn = 0ull;
       }
-      append_chunk<false>(S, level, pv.p, sg, gj, x0, first == 0ull);
+      append_chunk(S, lists, pv.p, sg, gj, x0, first == 0ull);
       j0 = j1;
       c0 = c1;
       j1 = j2;
@@ -477,7 +399,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
       S.imask[base + b0 + lane] = S.keep_all ? mk : dnr;
     }
   }
-  flush_stage<false>(S, level, pv.p, sg);
+  flush_stage(S, lists, pv.p, sg);
   const int ck[5] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS, C_FWD_ITEMS, C_FWD_IARCS};
   const uint64_t cv[5] = {c_v, c_a, c_d, c_it, c_ia};
   flush_wave_counters<BLOCK, 5>(S.ctr, S.ctr_slots, ck, cv, ovf, S.flags);
@@ -569,6 +491,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
   __shared__ uint32_t stage_all[(BLOCK / 64) * kStage], hstage_all[(BLOCK / 64) * kStageHeavy];
   const int wv = threadIdx.x >> 6;
   Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
+  const LevelLists<false> lists{S, level};
   const uint32_t nl = *tail_at(S, level, pv.p), nh = *tail_at(S, level, P + pv.p);
   const uint64_t nb = S.off[lrow + pv.p] + nl, nhb = S.off[lrow + P + pv.p] + nh;
   if (pv.thread == 0) open_level(S, level, pv.p, nl, nh, nb, nhb);
@@ -643,7 +566,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
       if (dag != 0ull) enq = (atomicOr(&nxt[gbase + w], dag) == 0ull);
     }
     push_slots<K>(S, gbase, w, push, lane, sv, dn, ovf, c_d);
-    append_chunk<false>(S, level, pv.p, sg, gbase, w, enq);
+    append_chunk(S, lists, pv.p, sg, gbase, w, enq);
 #pragma unroll
     for (int t = 0; t < K; ++t) {
       const int ld = t * SUB;
@@ -681,11 +604,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
           if (dd != 0ull) eq = (atomicOr(&nxt[gbt + ww], dd) == 0ull);
         }
         push_slots<1>(S, gbt, ww, pp, lane, s1, d1m, ovf, c_d);
-        append_chunk<false>(S, level, pv.p, sg, gbt, ww, eq);
+        append_chunk(S, lists, pv.p, sg, gbt, ww, eq);
       }
     }
   }
-  flush_stage<false>(S, level, pv.p, sg);
+  flush_stage(S, lists, pv.p, sg);
   const int ck[5] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS, C_FWD_ITEMS, C_FWD_IARCS};
   const uint64_t cv[5] = {c_v, c_a, c_d, c_it, c_ia};
   flush_wave_counters<BLOCK, 5>(S.ctr, S.ctr_slots, ck, cv, ovf, S.flags);
@@ -723,6 +646,7 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
   __shared__ uint32_t stage_all[NW * kStage], hstage_all[NW * kStageHeavy];
   const int wv = threadIdx.x >> 6;
   Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
+  const LevelLists<true> lists{S, level};
   // capacity exceeded earlier (workgroup-uniform test): the batch is redone
   if (S.off[lrow + pv.p] > list_end(S, pv.p) || S.off[lrow + P + pv.p] > list_end(S, P + pv.p)) return;
   const int lane = lane_id();
@@ -791,7 +715,7 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
         }
         c_v += (uint64_t)__popcll(nm);
         c_a += (uint64_t)__popcll(nm) * deg;
-        append_chunk<true>(S, level, pv.p, sg, gbase, w, lane == 0);
+        append_chunk(S, lists, pv.p, sg, gbase, w, lane == 0);
       }
     }
     __syncthreads();  // the next vertex overwrites the partial results
@@ -887,11 +811,11 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
         c_v += (uint64_t)__popcll(nm);
         c_a += (uint64_t)__popcll(nm) * (uint64_t)(e1 - e0);
         if (tg >= 0 && lane == 0) atomicMin(S.tmin, (uint32_t)level);
-        append_chunk<true>(S, level, pv.p, sg, gbase, wt, lane == 0);
+        append_chunk(S, lists, pv.p, sg, gbase, wt, lane == 0);
       }
     }
   }
-  flush_stage<true>(S, level, pv.p, sg);
+  flush_stage(S, lists, pv.p, sg);
   const int ck[3] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS};
   const uint64_t cv[3] = {c_v, c_a, c_d};  // wave-uniform
   flush_wave_counters<BLOCK, 3>(S.ctr, S.ctr_slots, ck, cv, ovf, S.flags);

@@ -5,9 +5,11 @@
 //      dist_b(w) with atomicMin and flags (g, w) for the next round;
 //   2. shortest-path-DAG in-degrees: for every reached (g, w), count the
 //      in-arcs (u, w) with dist_b(u) + len(u, w) = dist_b(w) (a pull over the
-//      reverse graph, no atomics), and store each in-arc's lanes of that test
-//      as one 64-bit mask per (group, arc), so that steps 3 and 4 find the
-//      DAG lanes of an arc in one word instead of a distance per lane;
+//      reverse graph), and store each in-arc's lanes of that test as one
+//      64-bit mask per (group, arc), so that steps 3 and 4 find the DAG lanes
+//      of an arc in one word instead of a distance per lane.  The masks lie in
+//      CSR order: written once per arc at scattered places, and read by lanes
+//      over consecutive arcs in every round that holds the tail;
 //   3. path counts in topological rounds: a lane of a vertex is ready when
 //      all its DAG in-arcs have pushed; it then pushes sigma along its DAG
 //      out-arcs and counts them down (Kahn's order on each source's SPD);
@@ -16,6 +18,11 @@
 // Step 3's round of a vertex plays the role of the BFS level of the
 // unweighted engine; the backward computes psi only on lanes where the
 // vertex is a target or lies below one (marks OR'd along the sigma pushes).
+//
+// Work lists are kept per partition (XCD) and split in light and heavy items
+// as in the unweighted engine; a heavy item is taken in kParts parts of its
+// arcs by as many wavefronts (nothing but atomics joins them, except in the
+// backward, whose sums run in arc order and stay with one wavefront).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,15 +37,39 @@ namespace bcd {
 
 constexpr uint32_t kInf = 0xFFFFFFFFu;
 
+// Parts a heavy item's arcs are dealt in (R-MAT 18, 2,048 draws, on one box: 8
+// parts 130.5 ms, 16 131.0, 32 135.5; 8,191-vertex exact 19.27 / 19.17 / 19.5).
+constexpr uint32_t kParts = 16;
+
+// The lists of the relaxation queue being filled, and the reached lists.
+struct QueueLists {
+  const BatchState &S;
+  int round;  // the round the queue is for
+  __device__ __forceinline__ uint32_t *tail(int l) const { return qtail_at(S, round, l); }
+  __device__ __forceinline__ uint64_t base(int l) const { return queue_begin(S, l); }
+  __device__ __forceinline__ uint64_t end(int l) const { return queue_end(S, l); }
+  __device__ __forceinline__ uint32_t *dst() const { return S.bq + (uint64_t)(round % 3) * S.qsize; }
+};
+struct ReachLists {
+  const BatchState &S;
+  __device__ __forceinline__ uint32_t *tail(int l) const { return rtail_at(S, l); }
+  __device__ __forceinline__ uint64_t base(int l) const { return queue_begin(S, l); }
+  __device__ __forceinline__ uint64_t end(int l) const { return queue_end(S, l); }
+  __device__ __forceinline__ uint32_t *dst() const { return S.rl; }
+};
+
 __global__ void k_w_init(BatchState S, const uint32_t *items0, const ull *masks0, const uint32_t *dest0, int k) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
     const uint32_t it = items0[i];
     const ull m = masks0[i];
+    const uint32_t g = it / (uint32_t)S.n, v = it - g * (uint32_t)S.n;
+    const int l = (int)(g % (uint32_t)S.P) + (v < S.H ? S.P : 0);
+    const uint64_t q = queue_begin(S, l) + (dest0[i] - list_begin(S, l));
     S.fr[it] = m;       // topological round 0
     S.items[dest0[i]] = it;
     S.chg[it] = m;      // relaxation round 0: the sources changed
-    S.bq[i] = it;
-    S.rl[i] = it;
+    S.bq[q] = it;
+    S.rl[q] = it;
     S.vis[it] = m;      // reached lanes
     for (int b = 0; b < kLanes; ++b)
       if ((m >> b) & 1ull) {
@@ -46,13 +77,24 @@ __global__ void k_w_init(BatchState S, const uint32_t *items0, const ull *masks0
         S.wd[(size_t)it * kLanes + b] = 0u;
       }
   }
-  if (blockIdx.x == 0 && threadIdx.x < (unsigned)S.P) S.off[threadIdx.x] = (uint64_t)threadIdx.x * S.capP;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    S.bqn[0] = (uint32_t)k;
-    S.bqn[1] = 0u;
-    S.bqn[2] = 0u;
-    *S.rln = (uint32_t)k;
+  if (blockIdx.x == 0 && threadIdx.x < (unsigned)S.NL) {
+    const int l = (int)threadIdx.x;
+    const uint32_t c = S.cnt[l];
+    S.off[l] = list_begin(S, l);
+    *tail_at(S, 0, l) = c;
+    *tail_at(S, 1, l) = 0u;
+    *tail_at(S, 2, l) = 0u;
+    *qtail_at(S, 0, l) = c;
+    *qtail_at(S, 1, l) = 0u;
+    *qtail_at(S, 2, l) = 0u;
+    *rtail_at(S, l) = c;
   }
+}
+
+// Part `part` of a heavy item's `deg` arcs: first arc and number.
+static __device__ __forceinline__ void part_of(uint32_t deg, uint32_t part, uint32_t &first, uint32_t &num) {
+  first = (uint32_t)((uint64_t)deg * part / kParts);
+  num = (uint32_t)((uint64_t)deg * (part + 1) / kParts) - first;
 }
 
 // Lane compaction for one work item: the A lanes of `em` are renumbered
@@ -64,9 +106,8 @@ struct Compact {
   int A, slots, j, slot, src;
 };
 // Arcs per slot per step of the relaxation: four, so that each lane has four
-// distance reads in flight before it waits (a full-width R-MAT 18 batch of
-// 8,192 sources: 0.94-0.97 s with one, 0.90-0.92 with two, 0.855-0.88 with
-// four, 0.846-0.854 with eight, which needs 74 VGPRs instead of 64).
+// distance reads in flight before it waits (R-MAT 18, 2,048 draws: 131 ms; with
+// two 135).
 constexpr int kWU = 4;
 
 // Orders this wavefront's LDS accesses before and after the call (lanes of
@@ -97,165 +138,249 @@ static __device__ __forceinline__ Compact compact_lanes(ull em, bool mine) {
   return c;
 }
 
-// One relaxation round.  Input: queue bq[round&1] (length bqn[round%3]) with
-// changed-lane masks chg[round&1]; output: bq[(round+1)&1], chg[(round+1)&1],
-// length bqn[(round+1)%3]; bqn[(round+2)%3] is zeroed for the round after.
-// Lanes are compacted per item (compact_lanes).
+// One relaxation round.  Input: the queue of `round` with changed-lane masks
+// chg[round % 3]; output: the queue and masks of round + 1; the masks of
+// round - 1 are retired (their word is the one round + 2 collects).  A
+// wavefront takes a block of light items (their masks and row bounds loaded
+// with a lane per item) or one part of a heavy item; lanes are compacted per
+// item (compact_lanes), the next arcs are loaded while the heads' distances of
+// the current ones are compared.
+// Bound by the latency of random accesses.  With one queue for all groups and
+// XCDs, its counters in one cache line and every item walked by one wavefront
+// the rounds of R-MAT 18 with 2,048 sources took 138 ms, as here 60; sigma
+// rounds 85 and 49, in-degrees 21 and 14, the backward 18 and 8.  Held to 5 waves
+// per SIMD or more the compiler takes 79 registers, left alone 89 (131 against
+// 135 ms for the query; 8 waves 136).
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_w_relax(DevGraph G, BatchState S, int round) {
-  const uint64_t n = (uint64_t)S.n;
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_w_relax(DevGraph G, BatchState S, int round) {
+  constexpr int NW = BLOCK / 64;
+  const uint32_t n = (uint32_t)S.n;
   const uint64_t GN = (uint64_t)S.G * n;
-  const uint32_t count = S.bqn[round % 3];
-  if (blockIdx.x == 0 && threadIdx.x == 0) S.bqn[(round + 2) % 3] = 0u;
-  const uint32_t *qin = S.bq + (uint64_t)(round & 1) * GN;
-  uint32_t *qout = S.bq + (uint64_t)((round + 1) & 1) * GN;
-  uint32_t *qout_n = &S.bqn[(round + 1) % 3];
-  ull *ccur = S.chg + (uint64_t)(round & 1) * GN;
-  ull *cnxt = S.chg + (uint64_t)((round + 1) & 1) * GN;
+  const int P = S.P;
+  const PartView pv = part_view<BLOCK>(P);
+  const uint32_t nl = *qtail_at(S, round, pv.p), nh = *qtail_at(S, round, P + pv.p);
+  if (pv.thread == 0) {
+    *qtail_at(S, round + 2, pv.p) = 0u;
+    *qtail_at(S, round + 2, P + pv.p) = 0u;
+  }
+  if ((nl | nh) == 0u) return;  // this partition has converged
+  if (round > 0) {
+    ull *old = S.chg + (uint64_t)((round + 2) % 3) * GN;
+    const uint32_t *qold = S.bq + (uint64_t)((round + 2) % 3) * S.qsize;
+    for (int l = pv.p; l < S.NL; l += P) {
+      const uint64_t qb = queue_begin(S, l), qc = *qtail_at(S, round - 1, l);
+      for (uint64_t i = pv.thread; i < qc; i += pv.nthreads) old[qold[qb + i]] = 0ull;
+    }
+  }
+  const ull *ccur = S.chg + (uint64_t)(round % 3) * GN;
+  ull *cnxt = S.chg + (uint64_t)((round + 1) % 3) * GN;
   const int lane = lane_id();
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   uint64_t c_r = 0;
-  const uint64_t wave = ((uint64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6;
-  const uint64_t nwaves = ((uint64_t)gridDim.x * BLOCK) >> 6;
-  constexpr int kCap = 128;
-  __shared__ uint32_t qst_all[(BLOCK / 64) * kCap];
-  __shared__ uint32_t rst_all[(BLOCK / 64) * kCap];
-  uint32_t *qst = qst_all + (threadIdx.x >> 6) * kCap;
-  uint32_t *rst = rst_all + (threadIdx.x >> 6) * kCap;
+  __shared__ uint32_t qst_all[NW * kStage], qht_all[NW * kStageHeavy];
+  __shared__ uint32_t rst_all[NW * kStage], rht_all[NW * kStageHeavy];
+  Stage qs = {qst_all + wv * kStage, qht_all + wv * kStageHeavy, 0, 0};
+  Stage rs = {rst_all + wv * kStage, rht_all + wv * kStageHeavy, 0, 0};
+  const QueueLists qlists{S, round + 1};
+  const ReachLists rlists{S};
   // per slot: the lanes that improved the slot's head in this step, and those
   // that reached it first, combined so that the head's flags take one atomic
   // per step, not one per source
   __shared__ ull cm_all[BLOCK], cr_all[BLOCK];
-  ull *cm = cm_all + (threadIdx.x & ~63u);
-  ull *cr = cr_all + (threadIdx.x & ~63u);
+  ull *cm = cm_all + wv * 64;
+  ull *cr = cr_all + wv * 64;
   cm[lane] = 0ull;
   cr[lane] = 0ull;
   wave_lds_sync();
-  int nq = 0, nr = 0;
-  for (uint64_t i = wave; i < count; i += nwaves) {
-    const uint32_t it = qin[i];
-    const uint32_t g = (uint32_t)(it / n);
-    const uint32_t v = (uint32_t)(it - (uint64_t)g * n);
-    const uint64_t gbase = (uint64_t)g * n;
-    const ull mask = ccur[it];
-    if (lane == 0) ccur[it] = 0ull;  // the owner retires its flag; others write cnxt only
-    if (mask == 0ull) continue;
-    const Compact cp = compact_lanes(mask, (mask >> lane) & 1ull);
-    const bool on = cp.slot < cp.slots;
-    const uint32_t dv = on ? S.wd[(uint64_t)it * kLanes + (uint32_t)cp.src] : kInf;
-    const bool live = on && dv != kInf;
-    const ull bit = 1ull << cp.src;
-    const int64_t e0 = G.rp[v], e1 = G.rp[v + 1];
-    if (lane == 0) c_r += (uint64_t)cp.A * (uint64_t)(e1 - e0);
-    const int64_t stepw = (int64_t)cp.slots * kWU;
-    for (int64_t e = e0; e < e1; e += stepw) {
-      uint32_t wq[kWU], nd[kWU], dw[kWU];
-#pragma unroll
-      for (int u = 0; u < kWU; ++u) {
-        const int64_t ea = e + (int64_t)u * cp.slots + cp.slot;
-        wq[u] = 0u;
-        nd[u] = kInf;
-        if (live && ea < e1) {
-          const uint2 a = G.arcw[ea];
-          wq[u] = a.x;
-          nd[u] = dv + a.y;
-        }
+  const ListView lv = list_view(S);
+  const uint32_t *qin = S.bq + (uint64_t)(round % 3) * S.qsize + queue_begin(S, (lv.heavy ? P : 0) + pv.p);
+  const uint64_t count = lv.heavy ? (uint64_t)nh * kParts : nl;
+  const uint64_t nwv = lv.nwg * NW;
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
+    const int nb = (int)min((uint64_t)B, count - b0);
+    uint32_t it = 0, gb = 0, e0 = 0, ed = 0;
+    ull mk = 0ull;
+    if (lane < nb) {
+      it = qin[lv.heavy ? b0 / kParts : b0 + lane];
+      const uint32_t v = it % n;
+      gb = it - v;
+      mk = ccur[it];
+      const int64_t r0 = G.rp[v];
+      e0 = (uint32_t)r0;
+      ed = (uint32_t)(G.rp[v + 1] - r0);
+      if (lv.heavy) {
+        uint32_t f;
+        part_of(ed, (uint32_t)(b0 % kParts), f, ed);
+        e0 += f;
       }
-#pragma unroll
-      for (int u = 0; u < kWU; ++u) dw[u] = nd[u] != kInf ? S.wd[(gbase + wq[u]) * kLanes + (uint32_t)cp.src] : 0u;
-      // a lower tentative distance: lower it (the minimum wins whatever the
-      // order) and flag the vertex for the next round; a flag raised by a
-      // value another wavefront has already beaten only costs a re-scan
-      bool imp[kWU];
+    }
+    c_r += wave_sum((uint64_t)__popcll(mk) * ed);
+    // distances of the first item's sources; the next item's are loaded while
+    // one is relaxed
+    uint32_t dnext = S.wd[(uint64_t)read_lane(it, 0) * kLanes + lane];
+    for (int j = 0; j < nb; ++j) {
+      const uint32_t drow = dnext;
+      if (j + 1 < nb) dnext = S.wd[(uint64_t)read_lane(it, j + 1) * kLanes + lane];
+      const ull mask = read_lane64(mk, j);
+      const uint32_t dj = read_lane(ed, j), gj = read_lane(gb, j);
+      if (mask == 0ull || dj == 0u) continue;
+      const uint2 *arcs = G.arcw + read_lane(e0, j);
+      const Compact cp = compact_lanes(mask, (mask >> lane) & 1ull);
+      const bool on = cp.slot < cp.slots;
+      const uint32_t dv = (uint32_t)__shfl((int)drow, cp.src);
+      const bool live = on && dv != kInf;
+      const ull bit = 1ull << cp.src;
+      const uint32_t stepw = (uint32_t)cp.slots * kWU;
+      uint2 a[kWU];
 #pragma unroll
       for (int u = 0; u < kWU; ++u) {
-        imp[u] = nd[u] != kInf && nd[u] < dw[u];
-        if (imp[u])
-          __hip_atomic_fetch_min(&S.wd[(gbase + wq[u]) * kLanes + (uint32_t)cp.src], nd[u], __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t k = (uint32_t)(u * cp.slots + cp.slot);
+        a[u] = arcs[k < dj ? k : 0u];
       }
+      for (uint32_t k0 = 0; k0 < dj; k0 += stepw) {
+        uint32_t wq[kWU], nd[kWU], dw[kWU];
 #pragma unroll
-      for (int u = 0; u < kWU; ++u) {
-        if (__ballot(imp[u]) == 0ull) continue;  // nothing improved in this step (wave-uniform)
-        // a lane that read the head unreached: the wavefront whose lowering
-        // of a lane lands first read it unreached, so the pair's first reach
-        // is among these and the reached list needs no atomic for the others
-        const bool fst = imp[u] && dw[u] == kInf;
-        if (imp[u]) __hip_atomic_fetch_or(&cm[cp.slot], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        if (fst) __hip_atomic_fetch_or(&cr[cp.slot], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        wave_lds_sync();
-        ull m = 0ull, mr = 0ull;
-        if (cp.j == 0 && on) {
-          m = cm[cp.slot];
-          mr = cr[cp.slot];
-          cm[cp.slot] = 0ull;
-          cr[cp.slot] = 0ull;
+        for (int u = 0; u < kWU; ++u) {
+          wq[u] = a[u].x;
+          nd[u] = (live && k0 + (uint32_t)(u * cp.slots + cp.slot) < dj) ? dv + a[u].y : kInf;
         }
-        wave_lds_sync();
-        bool fq = false, fr = false;
-        if (m != 0ull) fq = atomicOr(&cnxt[gbase + wq[u]], m) == 0ull;
-        if (mr != 0ull) fr = atomicOr(&S.vis[gbase + wq[u]], mr) == 0ull;
-        stage_lanes<kCap>(qst, nq, fq, (uint32_t)(gbase + wq[u]), qout_n, qout, 0, GN, nullptr);
-        stage_lanes<kCap>(rst, nr, fr, (uint32_t)(gbase + wq[u]), S.rln, S.rl, 0, GN, nullptr);
+#pragma unroll
+        for (int u = 0; u < kWU; ++u)
+          dw[u] = nd[u] != kInf ? S.wd[(uint64_t)(gj + wq[u]) * kLanes + (uint32_t)cp.src] : 0u;
+#pragma unroll
+        for (int u = 0; u < kWU; ++u) {
+          const uint64_t k = (uint64_t)k0 + stepw + (uint32_t)(u * cp.slots + cp.slot);
+          a[u] = arcs[k < dj ? k : 0u];
+        }
+        // a lower tentative distance: lower it (the minimum wins whatever the
+        // order) and flag the vertex for the next round; a flag raised by a
+        // value another wavefront has already beaten only costs a re-scan
+        bool imp[kWU];
+#pragma unroll
+        for (int u = 0; u < kWU; ++u) {
+          imp[u] = nd[u] != kInf && nd[u] < dw[u];
+          if (imp[u])
+            __hip_atomic_fetch_min(&S.wd[(uint64_t)(gj + wq[u]) * kLanes + (uint32_t)cp.src], nd[u], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // all flags are issued before the result of any is used
+        ull oldq[kWU], oldr[kWU];
+#pragma unroll
+        for (int u = 0; u < kWU; ++u) {
+          oldq[u] = ~0ull;
+          oldr[u] = ~0ull;
+          if (__ballot(imp[u]) == 0ull) continue;  // nothing improved on this arc slot (wave-uniform)
+          // a lane that read the head unreached: the wavefront whose lowering
+          // of a lane lands first read it unreached, so the pair's first reach
+          // is among these and the reached list needs no atomic for the others
+          const bool fst = imp[u] && dw[u] == kInf;
+          if (imp[u]) __hip_atomic_fetch_or(&cm[cp.slot], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+          if (fst) __hip_atomic_fetch_or(&cr[cp.slot], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+          wave_lds_sync();
+          ull m = 0ull, mr = 0ull;
+          if (cp.j == 0 && on) {
+            m = cm[cp.slot];
+            mr = cr[cp.slot];
+            cm[cp.slot] = 0ull;
+            cr[cp.slot] = 0ull;
+          }
+          wave_lds_sync();
+          if (m != 0ull) oldq[u] = atomicOr(&cnxt[gj + wq[u]], m);
+          if (mr != 0ull) oldr[u] = atomicOr(&S.vis[gj + wq[u]], mr);
+        }
+#pragma unroll
+        for (int u = 0; u < kWU; ++u) {
+          append_chunk(S, qlists, pv.p, qs, gj, wq[u], oldq[u] == 0ull);
+          append_chunk(S, rlists, pv.p, rs, gj, wq[u], oldr[u] == 0ull);
+        }
       }
     }
   }
-  stage_flush(qst, nq, qout_n, qout, 0, GN, nullptr);
-  stage_flush(rst, nr, S.rln, S.rl, 0, GN, nullptr);
-  flush_counters<BLOCK>(S.ctr, S.ctr_slots, C_RLX_APAIRS, c_r, 0, 0, false, S.flags);
+  flush_stage(S, qlists, pv.p, qs);
+  flush_stage(S, rlists, pv.p, rs);
+  const int ck[1] = {C_RLX_APAIRS};
+  const uint64_t cv[1] = {c_r};
+  flush_wave_counters<BLOCK, 1>(S.ctr, S.ctr_slots, ck, cv, false, S.flags);
 }
 
-// DAG in-degree of every reached (g, w) on each lane, pulled over in-arcs.
+// DAG in-degree of every reached (g, w) on each lane, pulled over in-arcs, and
+// the DAG lanes of every in-arc.  A wavefront reads 64 in-arcs at a time with
+// a lane each, then the tails' distance rows eight at a time; lane q keeps the
+// DAG lanes of arc q, and the 64 masks go out as one store.  The parts of a
+// heavy vertex add their counts.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_w_count(DevGraph G, BatchState S) {
-  const uint64_t n = (uint64_t)S.n;
-  const uint64_t GN = (uint64_t)S.G * n;
-  uint32_t count = *S.rln;
-  if (count > GN) count = (uint32_t)GN;
+  constexpr int NW = BLOCK / 64;
+  const uint32_t n = (uint32_t)S.n;
+  const int P = S.P;
+  const PartView pv = part_view<BLOCK>(P);
   const int lane = lane_id();
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   uint64_t c_v = 0, c_a = 0, c_d = 0;
-  const uint64_t wave = ((uint64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6;
-  const uint64_t nwaves = ((uint64_t)gridDim.x * BLOCK) >> 6;
-  for (uint64_t i = wave; i < count; i += nwaves) {
-    const uint32_t it = S.rl[i];
-    const uint32_t g = (uint32_t)(it / n);
-    const uint32_t w = (uint32_t)(it - (uint64_t)g * n);
-    const uint64_t gbase = (uint64_t)g * n;
-    const uint32_t dw = S.wd[(uint64_t)it * kLanes + lane];
-    const bool fin = dw != kInf;
-    uint32_t c = 0;
-    const int64_t e0 = G.irp[w], e1 = G.irp[w + 1];
-    ull *dm = S.dagm + (uint64_t)g * (uint64_t)G.m;
-    for (int64_t e = e0; e < e1; e += 8) {
-      const int cc = (int)((e1 - e) < 8 ? (e1 - e) : 8);
-      uint32_t du[8], ln[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        du[q] = kInf;
-        ln[q] = 0u;
-        if (q < cc && fin) {
-          const uint2 a = G.iarc[e + q];
-          ln[q] = a.y;
-          du[q] = S.wd[(gbase + a.x) * kLanes + lane];
-        }
+  const ListView lv = list_view(S);
+  const int l = (lv.heavy ? P : 0) + pv.p;
+  const uint32_t *rl = S.rl + queue_begin(S, l);
+  const uint64_t len = *rtail_at(S, l), count = lv.heavy ? len * kParts : len;
+  const uint64_t nwv = lv.nwg * NW;
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
+    const int nb = (int)min((uint64_t)B, count - b0);
+    uint32_t it = 0, gb = 0, f0 = 0, fd = 0, od = 0;
+    if (lane < nb) {
+      it = rl[lv.heavy ? b0 / kParts : b0 + lane];
+      const uint32_t v = it % n;
+      gb = it - v;
+      const int64_t r0 = G.irp[v];
+      f0 = (uint32_t)r0;
+      fd = (uint32_t)(G.irp[v + 1] - r0);
+      od = (uint32_t)(G.rp[v + 1] - G.rp[v]);
+      if (lv.heavy) {
+        uint32_t f;
+        part_of(fd, (uint32_t)(b0 % kParts), f, fd);
+        f0 += f;
       }
-      // lane q keeps the DAG lanes of in-arc e + q; the eight masks go out as
-      // one 64-byte store
-      ull mine = 0ull;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const bool dag = du[q] != kInf && du[q] + ln[q] == dw;
-        if (dag) ++c;
-        const ull bq = __ballot(dag);
-        if (lane == q) mine = bq;
-      }
-      if (lane < cc) dm[e + lane] = mine;
     }
-    S.wc[(uint64_t)it * kLanes + lane] = c;
-    const ull fm = __ballot(fin);
-    c_d += c;
-    if (lane == 0) {
-      c_v += (uint64_t)__popcll(fm);
-      c_a += (uint64_t)__popcll(fm) * (uint64_t)(G.rp[w + 1] - G.rp[w]);
+    const bool first_part = !lv.heavy || b0 % kParts == 0;
+    for (int j = 0; j < nb; ++j) {
+      const uint32_t ij = read_lane(it, j), gj = read_lane(gb, j), dj = read_lane(fd, j);
+      const uint32_t dw = S.wd[(uint64_t)ij * kLanes + lane];
+      const bool fin = dw != kInf;
+      const uint2 *arcs = G.iarc + read_lane(f0, j);
+      const uint32_t *opos = G.iopos + read_lane(f0, j);
+      ull *dm = S.dagm + (uint64_t)(gj / n) * (uint64_t)G.m;
+      uint32_t c = 0;
+      for (uint32_t k = 0; k < dj; k += kLanes) {
+        const uint32_t at = k + (uint32_t)lane < dj ? k + (uint32_t)lane : 0u;
+        const uint2 a = arcs[at];
+        const uint32_t op = opos[at];
+        const int cc = (int)min(dj - k, (uint32_t)kLanes);
+        ull mine = 0ull;
+        for (int q0 = 0; q0 < cc; q0 += 8) {
+          uint32_t du[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            du[q] = kInf;
+            if (q0 + q < cc && fin) du[q] = S.wd[(uint64_t)(gj + read_lane(a.x, q0 + q)) * kLanes + lane];
+          }
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const bool dag = du[q] != kInf && du[q] + read_lane(a.y, (q0 + q) & 63) == dw;
+            if (dag) ++c;
+            const ull bq = __ballot(dag);
+            if (lane == q0 + q) mine = bq;
+          }
+        }
+        if (lane < cc) dm[op] = mine;
+      }
+      if (!lv.heavy) S.wc[(uint64_t)ij * kLanes + lane] = c;
+      else if (c != 0u) atomicAdd(&S.wc[(uint64_t)ij * kLanes + lane], c);
+      c_d += c;
+      const ull fm = __ballot(fin);
+      if (lane == 0 && first_part) {
+        c_v += (uint64_t)__popcll(fm);
+        c_a += (uint64_t)__popcll(fm) * read_lane(od, j);
+      }
     }
   }
   flush_counters<BLOCK>(S.ctr, S.ctr_slots, C_FWD_VPAIRS, c_v, c_a, c_d, false, S.flags);
@@ -265,243 +390,309 @@ __global__ __launch_bounds__(BLOCK) void k_w_count(DevGraph G, BatchState S) {
 // their DAG out-arcs; a lane of w whose last DAG in-arc pushed is ready next
 // round.  Level lists, rotation of the mask arrays and target bookkeeping
 // mirror the unweighted forward kernel.  A wavefront lane takes one out-arc
-// of the item and reads the arc's DAG mask word, so the DAG test costs one
-// load per arc for all 64 sources; pushes happen only on the (source, arc)
-// pairs of the DAG, and a head's ready and below-target lanes take one atomic
-// each.
+// of the item and its DAG mask word (consecutive words), so the DAG test costs
+// one coalesced load for 64 arcs and all 64 sources; pushes happen only on the
+// (source, arc) pairs of the DAG, two sources of an arc at a time, and a
+// head's ready and below-target lanes take one atomic each.  The next step's
+// arcs and words and the next item's counts are loaded ahead.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_w_sigma(DevGraph G, BatchState S, int level) {
-  const uint64_t n = (uint64_t)S.n;
+  constexpr int NW = BLOCK / 64;
+  const uint32_t n = (uint32_t)S.n;
   const uint64_t GN = (uint64_t)S.G * n;
-  const int P = S.P;
+  const int P = S.P, NL = S.NL;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t base = S.off[(uint64_t)level * P + pv.p];
-  const uint64_t count = S.cnt[(uint64_t)level * P + pv.p];
-  const uint64_t nbase = base + count;
-  const uint64_t rend = (uint64_t)(pv.p + 1) * S.capP;
-  if (pv.thread == 0) S.off[(uint64_t)(level + 1) * P + pv.p] = nbase;
-  if (nbase > rend) return;  // capacity exceeded earlier (workgroup-uniform test): batch is redone
+  const uint64_t lrow = (uint64_t)level * NL;
+  const uint32_t nl = *tail_at(S, level, pv.p), nh = *tail_at(S, level, P + pv.p);
+  {
+    const uint64_t nb = S.off[lrow + pv.p] + nl, nhb = S.off[lrow + P + pv.p] + nh;
+    if (pv.thread == 0) open_level(S, level, pv.p, nl, nh, nb, nhb);
+    if ((nl | nh) == 0u) return;  // no lanes left in this partition's groups
+    // capacity exceeded (workgroup-uniform test): the batch is redone
+    if (nb > list_end(S, pv.p) || nhb > list_end(S, P + pv.p)) return;
+  }
   const int lane = lane_id();
-  ull *cur = S.fr + (uint64_t)(level % 3) * GN;
+  const ull *cur = S.fr + (uint64_t)(level % 3) * GN;
   ull *nxt = S.fr + (uint64_t)((level + 1) % 3) * GN;
-  ull *old = S.fr + (uint64_t)((level + 2) % 3) * GN;
   if (level > 0) {
-    const uint64_t pb = S.off[(uint64_t)(level - 1) * P + pv.p];
-    const uint64_t pc = S.cnt[(uint64_t)(level - 1) * P + pv.p];
-    for (uint64_t i = pv.thread; i < pc; i += pv.nthreads) old[S.items[pb + i]] = 0ull;
+    ull *old = S.fr + (uint64_t)((level + 2) % 3) * GN;
+    for (int l = pv.p; l < NL; l += P) {
+      const uint64_t pb = S.off[lrow - NL + l], pc = S.cnt[lrow - NL + l];
+      for (uint64_t i = pv.thread; i < pc; i += pv.nthreads) old[S.items[pb + i]] = 0ull;
+    }
   }
   bool ovf = false;
-  const uint64_t wave = pv.wave;
-  const uint64_t nwaves = pv.nwaves;
-  uint32_t *next_cnt = &S.cnt[(uint64_t)(level + 1) * P + pv.p];
-  constexpr int kCap = 256;
-  __shared__ uint32_t st_all[(BLOCK / 64) * kCap];
-  uint32_t *stg = st_all + (threadIdx.x >> 6) * kCap;
-  int nst = 0;
-  for (uint64_t i = wave; i < count; i += nwaves) {
-    const uint32_t it = S.items[base + i];
-    const uint32_t g = (uint32_t)(it / n);
-    const uint32_t v = (uint32_t)(it - (uint64_t)g * n);
-    const uint64_t gbase = (uint64_t)g * n;
-    const ull mask = cur[it];
-    if (lane == 0) S.imask[base + i] = mask;
-    const bool is_tgt = S.tgt_of[v] >= 0;
-    if (is_tgt && lane == 0) atomicMin(S.tmin, (uint32_t)level);
-    if (mask == 0ull) continue;
-    // lanes on which v is a target or lies below one: final now (every DAG
-    // in-arc of a ready lane has pushed); the backward reads only these
-    // (an atomic: waves pushing to v's other, not yet ready lanes may add
-    // their bits in this round)
-    ull dnv = S.wdn[it];
-    if (is_tgt) {
-      dnv |= mask;
-      if (lane == 0) atomicOr(&S.wdn[it], mask);
-    }
-    const ull *dm = S.dagm + (uint64_t)g * (uint64_t)G.m;
-    const uint64_t vrow = (uint64_t)it * kLanes;
-    // lane b holds sigma_b(v) of the ready lanes (a per-pair read of the row
-    // instead measured 5 % slower on a full-width R-MAT 18 batch)
-    const ull svl = ((mask >> lane) & 1ull) ? S.sig[vrow + lane] : 0ull;
-    const int64_t e0 = G.rp[v], e1 = G.rp[v + 1];
-    // lane j takes arc e + j; its DAG lanes among the ready ones come from
-    // the arc's mask word, and only those (source, arc) pairs push
-    for (int64_t e = e0; e < e1; e += kLanes) {
-      const int64_t ea = e + lane;
-      uint32_t x = 0u;
-      ull d = 0ull;
-      if (ea < e1) {
-        const uint2 a = G.arcp[ea];
-        x = a.x;
-        d = dm[a.y] & mask;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  __shared__ uint32_t stage_all[NW * kStage], hstage_all[NW * kStageHeavy];
+  Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
+  const LevelLists<false> lists{S, level};
+  const ListView lv = list_view(S);
+  const uint64_t base = S.off[lrow + (lv.heavy ? P : 0) + pv.p];
+  const uint64_t count = lv.heavy ? (uint64_t)nh * kParts : nl;
+  const uint64_t nwv = lv.nwg * NW;
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
+    const int nb = (int)min((uint64_t)B, count - b0);
+    uint32_t it = 0, gb = 0, e0 = 0, ed = 0;
+    ull mk = 0ull, dnv = 0ull;
+    if (lane < nb) {
+      const uint64_t pos = base + (lv.heavy ? b0 / kParts : b0 + lane);
+      const bool owner = !lv.heavy || b0 % kParts == 0;
+      it = S.items[pos];
+      const uint32_t v = it % n;
+      gb = it - v;
+      mk = cur[it];
+      // lanes on which v is a target or lies below one: final now (every DAG
+      // in-arc of a ready lane has pushed); the backward reads only these
+      // (an atomic: waves pushing to v's other, not yet ready lanes may add
+      // their bits in this round)
+      dnv = S.wdn[it];
+      const int64_t r0 = G.rp[v];
+      e0 = (uint32_t)r0;
+      ed = (uint32_t)(G.rp[v + 1] - r0);
+      if (lv.heavy) {
+        uint32_t f;
+        part_of(ed, (uint32_t)(b0 % kParts), f, ed);
+        e0 += f;
       }
-      const uint64_t xrow = (gbase + x) * kLanes;
-      ull rdy = 0ull, mdn = 0ull;
-      // one source of each arc per pass, lowest first; the passes are few
-      // (DAG lanes are a small share of an item's lanes)
-      while (__ballot(d != 0ull) != 0ull) {
-        const int b = d != 0ull ? __builtin_ctzll(d) : 0;
-        const ull sb = shfl64_w(svl, b);  // every lane takes part in the shuffle
-        if (d != 0ull) {
-          d &= d - 1ull;
-          const ull bit = 1ull << b;
-          const ull so = atomicAdd(&S.sig[xrow + (uint32_t)b], sb);
-          const uint32_t co = atomicSub(&S.wc[xrow + (uint32_t)b], 1u);
-          if (so + sb < so) {
-            ovf = true;
-            atomicOr(&S.ovl[g], bit);
-          }
-          // the push that completes the head's DAG in-arcs makes the lane ready
-          if (co == 1u) rdy |= bit;
-          if ((dnv >> b) & 1ull) mdn |= bit;
+      if (S.tgt_of[v] >= 0) {
+        dnv |= mk;
+        if (owner) {
+          atomicOr(&S.wdn[it], mk);
+          atomicMin(S.tmin, (uint32_t)level);
         }
       }
-      if (mdn != 0ull) atomicOr(&S.wdn[gbase + x], mdn);
+      if (owner) S.imask[pos] = mk;
+    }
+    // steps of 64 out-arcs, item after item
+    auto advance = [&](int &j, uint32_t &c) {
+      if (j >= nb) return;
+      c += kLanes;
+      if (c >= read_lane(ed, j)) {
+        c = 0;
+        ++j;
+      }
+    };
+    auto load = [&](int j, uint32_t c, uint32_t &x, ull &d) {
+      const int jj = j < nb ? j : 0;
+      const bool has = j < nb && c + (uint32_t)lane < read_lane(ed, jj);
+      const uint64_t e = has ? (uint64_t)read_lane(e0, jj) + c + (uint32_t)lane : 0u;
+      const uint64_t row = (uint64_t)(read_lane(gb, jj) / n) * (uint64_t)G.m;
+      x = (uint32_t)G.col[e];
+      d = S.dagm[row + e];
+      if (!has) d = 0ull;
+    };
+    int j0 = 0, j1;
+    uint32_t c0 = 0, c1, x0, x1;
+    ull d0, d1;
+    load(j0, c0, x0, d0);
+    ull srow = S.sig[(uint64_t)read_lane(it, 0) * kLanes + lane];
+    while (j0 < nb) {
+      const ull mask = read_lane64(mk, j0), dn = read_lane64(dnv, j0);
+      const uint32_t gj = read_lane(gb, j0);
+      j1 = j0;
+      c1 = c0;
+      advance(j1, c1);
+      load(j1, c1, x1, d1);
+      // lane b holds sigma_b(v) (a per-pair read of the row instead measured
+      // 5 % slower on a full-width R-MAT 18 batch)
+      const ull svl = srow;
+      if (j1 != j0 && j1 < nb) srow = S.sig[(uint64_t)read_lane(it, j1) * kLanes + lane];
+      ull d = d0 & mask;
+      const uint64_t xrow = (uint64_t)(gj + x0) * kLanes;
+      ull rdy = 0ull, mdn = d & dn;
+      // the sources of each arc, lowest first, two per pass
+      while (__ballot(d != 0ull) != 0ull) {
+        const bool p0 = d != 0ull;
+        const int q0 = p0 ? __builtin_ctzll(d) : 0;
+        d &= d - 1ull;
+        const bool p1 = p0 && d != 0ull;
+        const int q1 = p1 ? __builtin_ctzll(d) : 0;
+        if (p1) d &= d - 1ull;
+        if (!p0) d = 0ull;
+        const ull s0 = shfl64_w(svl, q0), s1 = shfl64_w(svl, q1);  // every lane takes part in the shuffles
+        ull o0 = 0ull, o1 = 0ull;
+        uint32_t k0 = 0u, k1 = 0u;
+        if (p0) {
+          o0 = atomicAdd(&S.sig[xrow + (uint32_t)q0], s0);
+          k0 = atomicSub(&S.wc[xrow + (uint32_t)q0], 1u);
+        }
+        if (p1) {
+          o1 = atomicAdd(&S.sig[xrow + (uint32_t)q1], s1);
+          k1 = atomicSub(&S.wc[xrow + (uint32_t)q1], 1u);
+        }
+        // the push that completes the head's DAG in-arcs makes the lane ready
+        if (k0 == 1u) rdy |= 1ull << q0;
+        if (k1 == 1u) rdy |= 1ull << q1;
+        const bool w0 = p0 && o0 + s0 < o0, w1 = p1 && o1 + s1 < o1;
+        if (w0 || w1) {
+          ovf = true;
+          atomicOr(&S.ovl[gj / n], (w0 ? 1ull << q0 : 0ull) | (w1 ? 1ull << q1 : 0ull));
+        }
+      }
+      if (mdn != 0ull) atomicOr(&S.wdn[gj + x0], mdn);
       bool first = false;
-      if (rdy != 0ull) first = atomicOr(&nxt[gbase + x], rdy) == 0ull;
+      if (rdy != 0ull) first = atomicOr(&nxt[gj + x0], rdy) == 0ull;
       // the first mark of the head appends it to the next round
-      stage_lanes<kCap>(stg, nst, first, (uint32_t)(gbase + x), next_cnt, S.items, nbase, rend, &S.flags[1]);
+      append_chunk(S, lists, pv.p, sg, gj, x0, first);
+      j0 = j1;
+      c0 = c1;
+      x0 = x1;
+      d0 = d1;
     }
   }
-  stage_flush(stg, nst, next_cnt, S.items, nbase, rend, &S.flags[1]);
+  flush_stage(S, lists, pv.p, sg);
   flush_counters<BLOCK>(S.ctr, S.ctr_slots, C_SCRATCH, 0, 0, 0, ovf, S.flags);
 }
 
 // Backward over topological round `level`: psi(v) = 1/sigma(v) + sum of
 // psi(w) over DAG out-arcs (v, w) of the lane; lanes pruned as in the
-// unweighted kernel.  A wavefront lane takes one out-arc and its DAG mask
-// word, psi is read only on the DAG (source, arc) pairs, and every source's
-// sum runs in arc order, so the result does not depend on the item's lanes.
+// unweighted kernel (blocks of items, a lane each; items without lanes are
+// passed over).  A wavefront lane takes one out-arc and its DAG mask word, psi
+// is read only on the DAG (source, arc) pairs, and every source's sum runs in
+// arc order, so the result does not depend on the item's lanes.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_w_bwd(DevGraph G, BatchState S, int level, int ntgt, int full) {
-  const uint64_t n = (uint64_t)S.n;
-  const int P = S.P;
+  constexpr int NW = BLOCK / 64;
+  const uint32_t n = (uint32_t)S.n;
+  const int P = S.P, NL = S.NL;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t base = S.off[(uint64_t)level * P + pv.p];
-  const uint64_t count = S.cnt[(uint64_t)level * P + pv.p];
-  if (base + count > (uint64_t)(pv.p + 1) * S.capP) return;
+  const uint64_t lrow = (uint64_t)level * NL;
   const int lane = lane_id();
-  uint64_t c_v = 0, c_a = 0, c_d = 0;
-  const uint64_t wave = pv.wave;
-  const uint64_t nwaves = pv.nwaves;
-  for (uint64_t i = wave; i < count; i += nwaves) {
-    const uint32_t it = S.items[base + i];
-    const uint32_t g = (uint32_t)(it / n);
-    const uint32_t v = (uint32_t)(it - (uint64_t)g * n);
-    const uint64_t gbase = (uint64_t)g * n;
-    const ull mask = S.imask[base + i];
-    const int32_t tg = S.tgt_of[v];
-    // a target's dependency reads psi only on lanes where v is a target or
-    // lies below one
-    const ull dnv = S.wdn[it];
-    const bool need = ((mask >> lane) & 1ull) && (full || ((dnv >> lane) & 1ull) || tg >= 0);
-    const ull em = __ballot(need);
-    if (em == 0ull) continue;
-    const ull *dm = S.dagm + (uint64_t)g * (uint64_t)G.m;
-    const int64_t e0 = G.rp[v], e1 = G.rp[v + 1];
-    double acc = 0.0;  // lane b: the sum of source b, over its DAG arcs in arc order
-    uint64_t pairs = 0;
-    for (int64_t e = e0; e < e1; e += kLanes) {
-      // lane j takes arc e + j and its DAG lanes among the needed ones
-      const int64_t ea = e + lane;
-      uint32_t x = 0u;
-      ull d = 0ull;
-      if (ea < e1) {
-        const uint2 a = G.arcp[ea];
-        x = a.x;
-        d = dm[a.y] & em;
-      }
-      const uint64_t xrow = (gbase + x) * kLanes;
-      // eight sources at a time: the lanes of each source's DAG arcs load its
-      // psi (all eight loads in flight together), then the source's sum takes
-      // them in arc order, so every sum runs in the same order whatever the
-      // lanes and batch
-      ull rem = em;
-      while (rem != 0ull) {
-        int bq[8];
-        ull aq[8];
-        double y[8];
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  uint64_t c_v = 0, c_a = 0, c_d = 0;  // wave-uniform
+  const ListView lv = list_view(S);
+  const int l = (lv.heavy ? P : 0) + pv.p;
+  const uint64_t base = S.off[lrow + l], count = S.cnt[lrow + l];
+  const uint64_t nwv = lv.nwg * NW;
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
+    const int nb = (int)min((uint64_t)B, count - b0);
+    uint32_t it = 0, gb = 0, e0 = 0, ed = 0;
+    int32_t tg = -1;
+    ull mk = 0ull;
+    if (lane < nb) {
+      it = S.items[base + b0 + lane];
+      mk = S.imask[base + b0 + lane];
+      const uint32_t v = it % n;
+      gb = it - v;
+      tg = S.tgt_of[v];
+      // a target's dependency reads psi only on lanes where v is a target or
+      // lies below one
+      if (!full && tg < 0) mk &= S.wdn[it];
+      const int64_t r0 = G.rp[v];
+      e0 = (uint32_t)r0;
+      ed = (uint32_t)(G.rp[v + 1] - r0);
+    }
+    ull todo = __ballot(mk != 0ull);
+    c_v += wave_sum((uint64_t)__popcll(mk));
+    c_a += wave_sum((uint64_t)__popcll(mk) * ed);
+    for (; todo != 0ull; todo &= todo - 1ull) {
+      const int j = __builtin_ctzll(todo);
+      const ull em = read_lane64(mk, j);
+      const uint32_t ij = read_lane(it, j), gj = read_lane(gb, j), dj = read_lane(ed, j);
+      const uint64_t row = (uint64_t)ij * kLanes + (uint32_t)lane;
+      const ull sv = ((em >> lane) & 1ull) ? S.sig[row] : 1ull;
+      const uint32_t a0 = read_lane(e0, j);
+      const int32_t *dst = G.col + a0;
+      const ull *dm = S.dagm + (uint64_t)(gj / n) * (uint64_t)G.m + a0;
+      double acc = 0.0;  // lane b: the sum of source b, over its DAG arcs in arc order
+      for (uint32_t k = 0; k < dj; k += kLanes) {
+        // lane q takes arc k + q and its DAG lanes among the needed ones
+        const bool has = k + (uint32_t)lane < dj;
+        const uint32_t x = (uint32_t)dst[has ? k + (uint32_t)lane : 0u];
+        const ull d = has ? dm[k + (uint32_t)lane] & em : 0ull;
+        const uint64_t xrow = (uint64_t)(gj + x) * kLanes;
+        // eight sources at a time: the lanes of each source's DAG arcs load its
+        // psi (all eight loads in flight together), then the source's sum takes
+        // them in arc order, so every sum runs in the same order whatever the
+        // lanes and batch
+        ull rem = em;
+        while (rem != 0ull) {
+          int bq[8];
+          ull aq[8];
+          double y[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const bool live = rem != 0ull;
-          bq[q] = live ? __builtin_ctzll(rem) : 0;
-          aq[q] = __ballot(live && ((d >> bq[q]) & 1ull));
-          if (live) rem &= rem - 1ull;
-          y[q] = ((aq[q] >> lane) & 1ull) ? S.psi[xrow + (uint32_t)bq[q]] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          ull t = aq[q];
-          if (t == 0ull) continue;
-          pairs += (uint64_t)__popcll(t);
-          double a = __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(acc), bq[q]));
-          while (t != 0ull) {
-            const int j = __builtin_ctzll(t);
-            t &= t - 1ull;
-            a += __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(y[q]), j));
+          for (int q = 0; q < 8; ++q) {
+            const bool live = rem != 0ull;
+            bq[q] = live ? __builtin_ctzll(rem) : 0;
+            aq[q] = __ballot(live && ((d >> bq[q]) & 1ull));
+            if (live) rem &= rem - 1ull;
+            y[q] = ((aq[q] >> lane) & 1ull) ? S.psi[xrow + (uint32_t)bq[q]] : 0.0;
           }
-          if (lane == bq[q]) acc = a;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            ull t = aq[q];
+            if (t == 0ull) continue;
+            c_d += (uint64_t)__popcll(t);
+            double a = __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(acc), bq[q]));
+            while (t != 0ull) {
+              const int z = __builtin_ctzll(t);
+              t &= t - 1ull;
+              a += __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(y[q]), z));
+            }
+            if (lane == bq[q]) acc = a;
+          }
         }
       }
-    }
-    if ((em >> lane) & 1ull) {
-      const uint64_t row = (uint64_t)it * kLanes + (uint32_t)lane;
-      const double s = (double)S.sig[row];
-      const double dl = s * acc;
-      S.psi[row] = acc + 1.0 / s;
-      if (S.dout) S.dout[row] = dl;
-      if (tg >= 0 && tg < ntgt) S.res[((uint64_t)tg * S.G + g) * kLanes + (uint32_t)lane] = (level > 0) ? dl : 0.0;
-    }
-    if (lane == 0) {
-      c_v += (uint64_t)__popcll(em);
-      c_a += (uint64_t)__popcll(em) * (uint64_t)(e1 - e0);
-      c_d += pairs;
+      if ((em >> lane) & 1ull) {
+        const double s = (double)sv;
+        const double dl = s * acc;
+        const int32_t t = (int32_t)read_lane((uint32_t)tg, j);
+        S.psi[row] = acc + 1.0 / s;
+        if (S.dout) S.dout[row] = dl;
+        if (t >= 0 && t < ntgt) S.res[((uint64_t)t * S.G + gj / n) * kLanes + (uint32_t)lane] = (level > 0) ? dl : 0.0;
+      }
     }
   }
-  flush_counters<BLOCK>(S.ctr, S.ctr_slots, C_BWD_VPAIRS, c_v, c_a, c_d, false, S.flags);
+  const int ck[3] = {C_BWD_VPAIRS, C_BWD_APAIRS, C_BWD_DPAIRS};
+  const uint64_t cv[3] = {c_v, c_a, c_d};
+  flush_wave_counters<BLOCK, 3>(S.ctr, S.ctr_slots, ck, cv, false, S.flags);
 }
 
 __global__ void k_w_cleanup(BatchState S) {
   const uint64_t GN = (uint64_t)S.G * (uint64_t)S.n;
-  uint64_t count = *S.rln;
-  if (count > GN) count = GN;
   const int lane = lane_id();
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  for (uint64_t i = wave; i < count; i += nwaves) {
-    const uint32_t it = S.rl[i];
-    const uint64_t row = (uint64_t)it * kLanes + lane;
-    S.wd[row] = kInf;
-    S.wc[row] = 0u;
-    S.sig[row] = 0ull;
-    if (lane == 0) S.vis[it] = 0ull;
-    if (lane == 5) S.wdn[it] = 0ull;
-    if (lane < 3) S.fr[(uint64_t)lane * GN + it] = 0ull;
-    if (lane >= 3 && lane < 5) S.chg[(uint64_t)(lane - 3) * GN + it] = 0ull;
+  for (int l = 0; l < S.NL; ++l) {
+    const uint32_t *rl = S.rl + queue_begin(S, l);
+    for (uint64_t i = wave; i < *rtail_at(S, l); i += nwaves) {
+      const uint32_t it = rl[i];
+      const uint64_t row = (uint64_t)it * kLanes + lane;
+      S.wd[row] = kInf;
+      S.wc[row] = 0u;
+      S.sig[row] = 0ull;
+      if (lane == 0) S.vis[it] = 0ull;
+      if (lane == 1) S.wdn[it] = 0ull;
+      if (lane >= 2 && lane < 5) S.fr[(uint64_t)(lane - 2) * GN + it] = 0ull;
+      if (lane >= 5 && lane < 8) S.chg[(uint64_t)(lane - 5) * GN + it] = 0ull;
+    }
   }
 }
 
-__global__ void k_w_export(DevGraph G, BatchState S, const int32_t *lane_slot, uint64_t *dist, ull *sigma, double *delta,
-                           int64_t k) {
+__global__ void k_w_export(DevGraph G, BatchState S, const int32_t *lane_slot, uint64_t *dist, ull *sigma,
+                           double *delta, int64_t k) {
   const uint64_t n = (uint64_t)S.n;
-  const uint64_t GN = (uint64_t)S.G * n;
-  uint64_t count = *S.rln;
-  if (count > GN) count = GN;
   const int lane = lane_id();
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  for (uint64_t i = wave; i < count; i += nwaves) {
-    const uint32_t it = S.rl[i];
-    const uint32_t g = (uint32_t)(it / n);
-    const uint32_t v = (uint32_t)(it - (uint64_t)g * n);
-    const uint64_t row = (uint64_t)it * kLanes + lane;
-    const uint32_t d = S.wd[row];
-    if (d == kInf) continue;
-    const int32_t slot = lane_slot[g * kLanes + lane];
-    if (slot < 0 || slot >= k) continue;
-    const uint64_t o = (uint64_t)slot * n + (uint32_t)G.orig[v];
-    dist[o] = d;
-    sigma[o] = S.sig[row];
-    if (delta && S.dout) delta[o] = S.dout[row];
+  for (int l = 0; l < S.NL; ++l) {
+    const uint32_t *rl = S.rl + queue_begin(S, l);
+    for (uint64_t i = wave; i < *rtail_at(S, l); i += nwaves) {
+      const uint32_t it = rl[i];
+      const uint32_t g = (uint32_t)(it / n);
+      const uint32_t v = (uint32_t)(it - (uint64_t)g * n);
+      const uint64_t row = (uint64_t)it * kLanes + lane;
+      const uint32_t d = S.wd[row];
+      if (d == kInf) continue;
+      const int32_t slot = lane_slot[g * kLanes + lane];
+      if (slot < 0 || slot >= k) continue;
+      const uint64_t o = (uint64_t)slot * n + (uint32_t)G.orig[v];
+      dist[o] = d;
+      sigma[o] = S.sig[row];
+      if (delta && S.dout) delta[o] = S.dout[row];
+    }
   }
 }
 
@@ -576,21 +767,25 @@ bcd_status Workspace::ensure_weighted() {
   if (weighted_ready && weighted_G == G) return BCD_OK;
   release_weighted();
   const size_t GN = (size_t)G * (size_t)n;
+  const size_t per = (size_t)((G + S.P - 1) / S.P);  // groups of a partition
+  S.capQ = per * (size_t)n;
+  S.capQH = per * S.H;
+  S.qhbase = S.capQ * S.P;
+  S.qsize = S.qhbase + S.capQH * S.P;
   STCHK(walloc(&S.wd, GN * kLanes));
   STCHK(walloc(&S.wc, GN * kLanes));
-  STCHK(walloc(&S.chg, 2 * GN));
-  STCHK(walloc(&S.bq, 2 * GN));
-  STCHK(walloc(&S.bqn, 4));
-  STCHK(walloc(&S.rl, GN));
-  STCHK(walloc(&S.rln, 1));
+  STCHK(walloc(&S.chg, 3 * GN));
+  STCHK(walloc(&S.bq, 3 * S.qsize));
+  STCHK(walloc(&S.rl, S.qsize));
+  STCHK(walloc(&S.qtail, (size_t)4 * kMaxLists * kTailStride));
+  STCHK(walloc(&S.rtail, (size_t)kMaxLists * kTailStride));
   STCHK(walloc(&S.wdn, GN));
   STCHK(walloc(&S.dagm, (size_t)G * (size_t)graph->m));
   HIPCHK(hipMemsetAsync(S.wd, 0xFF, GN * kLanes * sizeof(uint32_t), stream));
   HIPCHK(hipMemsetAsync(S.wdn, 0, GN * sizeof(unsigned long long), stream));
   HIPCHK(hipMemsetAsync(S.wc, 0, GN * kLanes * sizeof(uint32_t), stream));
-  HIPCHK(hipMemsetAsync(S.chg, 0, 2 * GN * sizeof(unsigned long long), stream));
-  HIPCHK(hipMemsetAsync(S.bqn, 0, 4 * sizeof(uint32_t), stream));
-  HIPCHK(hipMemsetAsync(S.rln, 0, sizeof(uint32_t), stream));
+  HIPCHK(hipMemsetAsync(S.chg, 0, 3 * GN * sizeof(unsigned long long), stream));
+  HIPCHK(hipMemsetAsync(S.rtail, 0, (size_t)kMaxLists * kTailStride * sizeof(uint32_t), stream));
   HIPCHK(hipStreamSynchronize(stream));
   weighted_ready = true;
   weighted_G = G;
@@ -606,9 +801,9 @@ void Workspace::release_weighted() {
   f(S.wc);
   f(S.chg);
   f(S.bq);
-  f(S.bqn);
   f(S.rl);
-  f(S.rln);
+  f(S.qtail);
+  f(S.rtail);
   f(S.wdn);
   f(S.dagm);
   weighted_ready = false;
@@ -636,16 +831,16 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
     BatchState S = ws->S;
     if (!ex) S.dout = nullptr;
     S.P = ws->batch_parts(k);  // partitions that hold this batch's groups
-    S.NL = S.P;
-    const int P = S.P;
-    const Launch L = g->launch_parts(P, (k + kLanes - 1) / kLanes);
+    S.NL = ws->lists(S.P);
+    const int NL = S.NL;
+    const Launch L = g->launch_parts(S.P, (k + kLanes - 1) / kLanes);
     ws->stage_sources_dest(k);
     HIPCHK(hipMemcpyAsync(ws->d_dest0, ws->h_dest0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     uint32_t *hc = ws->h_cnt;
     uint32_t *hc0 = hc + kCntStage;
     uint32_t *hm = reinterpret_cast<uint32_t *>(ws->h_misc);
-    for (int p = 0; p < P; ++p) hc0[p] = ws->h_cnt0[p];
-    HIPCHK(hipMemcpyAsync(&S.cnt[0], hc0, (size_t)P * sizeof(uint32_t), hipMemcpyHostToDevice, st));
+    for (int l = 0; l < NL; ++l) hc0[l] = ws->h_cnt0[l];
+    HIPCHK(hipMemcpyAsync(&S.cnt[0], hc0, (size_t)NL * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     if (ntgt > 0) HIPCHK(hipMemsetAsync(S.res, 0, (size_t)ntgt * G64 * sizeof(double), st));
     HIPCHK(hipMemsetAsync(S.tmin, 0xFF, sizeof(uint32_t), st));
     HIPCHK(hipMemsetAsync(S.flags, 0, 4 * sizeof(uint32_t), st));
@@ -670,9 +865,12 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
         HIPCHK(launch_w_relax(D, S, round, L, st));
         HIPCHK(rec1());
       }
-      HIPCHK(hipMemcpyAsync(hm, &S.bqn[round % 3], sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipMemcpyAsync(hc, qtail_at(S, round, 0), (size_t)kMaxLists * kTailStride * sizeof(uint32_t),
+                            hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
-      if (hm[0] == 0) break;
+      uint64_t left = 0;
+      for (int l = 0; l < NL; ++l) left += hc[l * kTailStride];
+      if (left == 0) break;
       if (round > g->n + 16) return fail(BCD_ERR_DEVICE, "relaxation rounds did not converge");
     }
     // 2. DAG in-degrees
@@ -680,7 +878,7 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
     HIPCHK(launch_w_count(D, S, L, st));
     HIPCHK(rec1());
     // 3. path counts in topological rounds
-    std::vector<uint32_t> cntp(hc0, hc0 + P);
+    std::vector<uint32_t> cntp(hc0, hc0 + NL);
     int lmax = -1, level = 0;
     int chunk = std::min(kLevelChunkMax, std::max(4, ws->last_depth + 2));
     uint32_t flags_h[2] = {0, 0}, tmin_h = 0xFFFFFFFFu;
@@ -692,7 +890,8 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
         HIPCHK(launch_w_sigma(D, S, level, L, st));
         HIPCHK(rec1());
       }
-      HIPCHK(hipMemcpyAsync(hc, &S.cnt[(size_t)(first + 1) * P], (size_t)launched * P * sizeof(uint32_t),
+      HIPCHK(launch_publish_counts(S, level, st));
+      HIPCHK(hipMemcpyAsync(hc, &S.cnt[(size_t)(first + 1) * NL], (size_t)launched * NL * sizeof(uint32_t),
                             hipMemcpyDeviceToHost, st));
       HIPCHK(hipMemcpyAsync(hm, S.flags, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
       HIPCHK(hipMemcpyAsync(hm + 2, S.tmin, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
@@ -703,12 +902,12 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
       if (flags_h[1]) break;
       for (int i = 0; i < launched; ++i) {
         uint64_t tot = 0;
-        for (int p = 0; p < P; ++p) tot += hc[(size_t)i * P + p];
+        for (int l = 0; l < NL; ++l) tot += hc[(size_t)i * NL + l];
         if (tot == 0) {
           lmax = first + i;
           break;
         }
-        cntp.insert(cntp.end(), hc + (size_t)i * P, hc + (size_t)(i + 1) * P);
+        cntp.insert(cntp.end(), hc + (size_t)i * NL, hc + (size_t)(i + 1) * NL);
       }
       if (lmax < 0 && level > g->n) return fail(BCD_ERR_DEVICE, "topological rounds did not terminate");
       chunk = kLevelChunkMax;
@@ -740,15 +939,14 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
       HIPCHK(hipMemcpyAsync(ovl_out, S.ovl, (size_t)ws->G * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     HIPCHK(launch_w_cleanup(S, L, st));
     HIPCHK(launch_ctr_fold(S.ctr, kCtrSlots, S.acc, st));
-    HIPCHK(hipMemsetAsync(S.cnt, 0, ((size_t)lmax + 2) * P * sizeof(uint32_t), st));
     HIPCHK(hipStreamSynchronize(st));
     if (profiling && prof) {
       for (size_t i = 0; i < ev; ++i) prof->add(g, i < fwd_events ? 0 : 1, ws->events[i].first, ws->events[i].second);
       // work items: one per (group, vertex, topological round) with ready lanes
-      for (size_t l = 0; l * P < cntp.size(); ++l)
-        for (int p = 0; p < P; ++p) {
-          prof->items[0] += cntp[l * P + p];
-          if (stop >= 0 && (int)l >= stop) prof->items[1] += cntp[l * P + p];
+      for (size_t lv = 0; lv * NL < cntp.size(); ++lv)
+        for (int l = 0; l < NL; ++l) {
+          prof->items[0] += cntp[lv * NL + l];
+          if (stop >= 0 && (int)lv >= stop) prof->items[1] += cntp[lv * NL + l];
         }
     }
     return BCD_OK;

@@ -933,3 +933,23 @@ def test_row_lengths_around_steps_and_heavy_vertices(B, oracle, sizes):
             od, oc = oracle.dependencies(g, r, src)
             assert close(dep, od) and np.array_equal(cnt, oc), (bu, push, r)
             assert np.array_equal(G.dependencies(r, src), dep), (bu, push, r)
+
+
+@pytest.mark.parametrize("wmax", [1, 3])
+def test_weighted_row_lengths_around_steps_and_parts(B, oracle, wmax):
+    """Weighted rows around the 64-arc steps and the parts a heavy vertex's
+    arcs are dealt in, with ties (all lengths 1, or 1..3)."""
+    g, hubs = fan_graph((1, 63, 64, 65, 129, 256, 257, 260, 513, 1153))
+    g = gg.with_weights(g, seed=3, max_weight=wmax)
+    src = hubs + gg.uniform_vertices(g.n, 130 - len(hubs), seed=9, exclude=hubs)
+    G = dev(B, g, groups=3)
+    d, sg, dl = G.multi_source_pass(src)
+    for i, s in enumerate(src):
+        od, osg, odl, ovf, _ = oracle.source_pass(g, s)
+        assert np.array_equal(d[i], od) and np.array_equal(sg[i], osg), (wmax, i, s)
+        assert close(dl[i], odl), (wmax, i, s)
+    for r in (hubs[-1], src[-1]):
+        dep, cnt = G.dependencies(r, src, counters=True)
+        od, oc = oracle.dependencies(g, r, src)
+        assert close(dep, od) and np.array_equal(cnt, oc), (wmax, r)
+        assert np.array_equal(G.dependencies(r, src), dep), (wmax, r)
