@@ -275,10 +275,10 @@ class Graph:
     # -- queries
     def rv(self, r: int) -> np.ndarray:
         cnt = C.c_int64()
-        check(load().bcd_rv(self.h, r, None, 0, C.byref(cnt)), "bcd_rv")
-        out = np.empty(max(cnt.value, 1), dtype=np.int32)
+        out = np.empty(self.n, dtype=np.int32)  # one call: RV(r) has fewer than n vertices
         check(load().bcd_rv(self.h, r, _ptr(out), out.size, C.byref(cnt)), "bcd_rv")
-        return out[: cnt.value].copy()
+        out.resize(cnt.value, refcheck=False)  # gives the rest back without a copy
+        return out
 
     def bc_exact(self, r: int):
         bc = C.c_double()

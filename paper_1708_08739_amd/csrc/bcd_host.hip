@@ -160,6 +160,8 @@ void Workspace::release() {
   dfree(rq[0]);
   dfree(rq[1]);
   dfree(rqn);
+  dfree(d_roots);
+  roots_cap = 0;
   hfree(h_items0);
   hfree(h_masks0);
   hfree(h_cnt);
@@ -193,7 +195,7 @@ bcd_status Workspace::ensure_reach() {
   STCHK(dalloc(&bitmap, words));
   STCHK(dalloc(&rq[0], (size_t)n));
   STCHK(dalloc(&rq[1], (size_t)n));
-  STCHK(dalloc(&rqn, 8));  // two queues: length, pad, arcs (uint64)
+  STCHK(dalloc(&rqn, 4 * kTailStride));
   STCHK(halloc(&h_bitmap, words));
   if (!h_misc) STCHK(halloc(&h_misc, 64));  // shared with the plain engine
   reach_ready = true;

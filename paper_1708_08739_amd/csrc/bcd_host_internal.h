@@ -1,6 +1,7 @@
 // Host-side objects of libbcd: the resident graph and per-call workspaces.
 #pragma once
 
+#include <algorithm>
 #include <atomic>
 #include <functional>
 #include <memory>
@@ -120,7 +121,10 @@ struct Workspace {
   bool reach_ready = false;
   uint32_t *bitmap = nullptr;
   int32_t *rq[2] = {nullptr, nullptr};
-  uint32_t *rqn = nullptr;  // [8]: per queue c, length at 4c, arcs of its vertices (uint64) at 4c + 2
+  uint32_t *rqn = nullptr;  // frontier counters (ReachCtr), a line per level mod 4
+  int32_t *d_roots = nullptr;  // several roots of one traversal
+  size_t roots_cap = 0;
+  int reach_depth = 6;      // levels of the last traversal
   uint32_t *h_bitmap = nullptr;
   // host staging
   uint32_t *h_cnt = nullptr;
@@ -306,6 +310,11 @@ bcd_status run_pipelined(Graph *g, Workspace *ws, size_t nbatches, const std::fu
 // Query layer (bcd_query.hip).
 bcd_status reach_set(Graph *g, Workspace *ws, int32_t root, bool reverse, std::vector<uint32_t> &bits,
                      int64_t *count, uint8_t *d_lev);
+// D of the set form: the union of RV(r) over the targets (ascending, distinct)
+// with out-arcs, as a bitmap.
+bcd_status reach_union(Graph *g, Workspace *ws, const std::vector<int32_t> &targets, std::vector<uint32_t> &uni);
+// Frontier arcs from which a reachability level goes bottom-up.
+inline uint64_t reach_bu_arcs(const Graph *g) { return (uint64_t)std::max<int64_t>(64, g->m / 64); }
 bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src,
                         const std::vector<int32_t> &tgt, bool want_counters, SourceRun &out);
 bcd_status multi_source_pass_weighted(Graph *g, const int32_t *sources, int64_t k, uint64_t *dist,
@@ -317,8 +326,8 @@ size_t lds_bytes_for(int64_t n);
 bool lds_fits(const Graph *g);
 // Single-workgroup reachability (n < 2^16, visited bits and queue in LDS).
 bool lds_reach_fits(const Graph *g);
-hipError_t launch_lds_reach(const Graph *g, const int64_t *rp, const int32_t *col, int32_t root, uint32_t *bitmap,
-                            hipStream_t st);
+hipError_t launch_lds_reach(const Graph *g, const int64_t *rp, const int32_t *col, int32_t root,
+                            const int32_t *roots, int k, uint32_t *bitmap, hipStream_t st);
 bcd_status run_lds(Graph *g, Workspace *ws, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt,
                    bool want_counters, SourceRun &out);
 bcd_status multi_source_pass_lds(Graph *g, Workspace *ws, const int32_t *sources, int64_t k, uint64_t *dist,

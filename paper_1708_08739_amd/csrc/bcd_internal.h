@@ -203,17 +203,26 @@ hipError_t launch_plain_export(const PlainState &P, uint64_t total, uint64_t *di
                                unsigned long long *sigma, double *delta, hipStream_t st);
 
 // Reachability BFS over one CSR (reverse graph for RV, forward for FR).
-hipError_t launch_reach_init(uint32_t *bitmap, int32_t *q, uint32_t *qn, int32_t root, hipStream_t st);
-// Reachability levels: queue lengths *_n and the arcs their vertices have
-// in the traversed CSR *_a; a level goes bottom-up (launch_reach_bu, over the
-// other CSR) when its frontier has at least bu_arcs arcs, else top-down.
-hipError_t launch_reach_level(const int64_t *rp, const int32_t *col, uint32_t *bitmap, const int32_t *qin,
-                              const uint32_t *qin_n, const uint64_t *qin_a, int32_t *qout, uint32_t *qout_n,
-                              uint64_t *qout_a, uint8_t *lev, int level, uint64_t bu_arcs, Launch L,
-                              hipStream_t st);
-hipError_t launch_reach_bu(const int64_t *rp, const int32_t *col, const int64_t *rp_td, uint32_t *bitmap,
-                           const uint64_t *qin_a, int32_t *qout, uint32_t *qout_n, uint64_t *qout_a, int64_t n,
-                           uint64_t bu_arcs, Launch L, hipStream_t st);
+// Counters of the frontiers, by level mod 4: the queue's length and the arcs
+// its vertices have in the traversed CSR, `stride` words apart; word 1 holds the
+// deepest level that had vertices.
+struct ReachCtr {
+  uint32_t *c;
+  int stride;
+  __host__ __device__ uint32_t *len(int level) const { return c + (level & 3) * stride; }
+  __host__ __device__ uint64_t *arcs(int level) const {
+    return reinterpret_cast<uint64_t *>(c + (level & 3) * stride + 2);
+  }
+};
+// Clears the bitmap and the counters, then enters the roots (root, or
+// roots[0 .. k-1] on the device when roots is not null).
+hipError_t launch_reach_init(uint32_t *bitmap, int64_t words, int32_t *q, ReachCtr ctr, int32_t root,
+                             const int32_t *roots, int k, hipStream_t st);
+// One level: rp / col is the CSR traversed, rpo / colo the other direction; a
+// level whose frontier has at least bu_arcs arcs goes bottom-up.
+hipError_t launch_reach_level(const int64_t *rp, const int32_t *col, const int64_t *rpo, const int32_t *colo,
+                              uint32_t *bitmap, int32_t *q0, int32_t *q1, ReachCtr ctr, uint8_t *lev, int level,
+                              int64_t n, uint64_t bu_arcs, Launch L, hipStream_t st);
 hipError_t launch_scatter_targets(int32_t *tgt_of, const int32_t *verts, int k, int set, hipStream_t st);
 hipError_t launch_plain_gather(const PlainState &P, const int32_t *verts, int k, int32_t *d_out,
                                double *delta_out, hipStream_t st);

@@ -205,46 +205,96 @@ __global__ __launch_bounds__(BLOCK) void k_lds_pass(DevGraph G, LdsArgs A) {
   }
 }
 
-// Reachability of Def.3 from `root` (on the transpose for RV(r), on the graph
-// for the forward reach of r) in one workgroup: visited bits and the BFS
-// queue live in LDS, levels are separated by barriers, and the visited
-// bitmap is written out at the end.  For n < 2^16.
+// Reachability of Def.3 from the roots (on the transpose for RV(r), on the
+// graph for the forward reach of r) in one workgroup: visited bits and the
+// BFS queue live in LDS, levels are separated by barriers, and the visited
+// bitmap is written out at the end.  For n < 2^16.  A lane per frontier vertex
+// takes its first kAlone arcs, kAtOnce at a time; the rest of a longer row is
+// taken by the whole wavefront: a hub's row walked by one thread made up most of
+// the time (R-MAT of 4,096 vertices, RV(r) 200 us, as here 60).
 constexpr int kReachBlock = 1024;
+constexpr int kAlone = 32;
+constexpr int kAtOnce = 8;
 
 size_t lds_reach_bytes(int64_t n) { return (size_t)4 * (((size_t)n + 31) / 32) + (size_t)2 * (size_t)n + 64; }
 
 __global__ __launch_bounds__(kReachBlock) void k_lds_reach(const int64_t *rp, const int32_t *col, int32_t n,
-                                                          int32_t root, uint32_t *bitmap_out) {
+                                                          int32_t root, const int32_t *roots, int k,
+                                                          uint32_t *bitmap_out) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t words = ((uint32_t)n + 31) / 32;
   uint32_t *vis = reinterpret_cast<uint32_t *>(smem);
   uint16_t *queue = reinterpret_cast<uint16_t *>(smem + 4 * (size_t)words);
   __shared__ uint32_t s_tail;
   const uint32_t tid = threadIdx.x;
+  const int lane = lane_id();
   for (uint32_t w = tid; w < words; w += kReachBlock) vis[w] = 0u;
   __syncthreads();
-  if (tid == 0) {
-    vis[(uint32_t)root >> 5] = 1u << ((uint32_t)root & 31);
-    queue[0] = (uint16_t)root;
-    s_tail = 1u;
+  for (int i = (int)tid; i < k; i += kReachBlock) {
+    const uint32_t r = (uint32_t)(roots ? roots[i] : root);
+    atomicOr(&vis[r >> 5], 1u << (r & 31));
+    queue[i] = (uint16_t)r;
   }
+  if (tid == 0) s_tail = (uint32_t)k;
   __syncthreads();
-  uint32_t qb = 0, qe = 1;
+  // marks the vertices w[j] (where has[j]) and queues those whose first mark
+  // this is: the marks are issued together, then one atomic on the queue's end
+  auto visit = [&](const uint32_t (&w)[kAtOnce], const bool (&has)[kAtOnce]) {
+    ull fb[kAtOnce];
+    uint32_t old[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      old[j] = ~0u;
+      if (has[j]) old[j] = atomicOr(&vis[w[j] >> 5], 1u << (w[j] & 31));
+    }
+    uint32_t total = 0;
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      fb[j] = __ballot(((old[j] >> (w[j] & 31)) & 1u) == 0u);
+      total += (uint32_t)__popcll(fb[j]);
+    }
+    if (total == 0u) return;
+    uint32_t p = 0;
+    if (lane == 0) p = atomicAdd(&s_tail, total);
+    p = read_lane(p, 0);
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      if ((fb[j] >> lane) & 1ull) queue[p + lanes_below(fb[j])] = (uint16_t)w[j];
+      p += (uint32_t)__popcll(fb[j]);
+    }
+  };
+  uint32_t qb = 0, qe = (uint32_t)k;
   while (qb < qe) {
-    for (uint32_t q = qb + tid; q < qe; q += kReachBlock) {
-      const uint32_t v = queue[q];
-      const int64_t e0 = rp[v], e1 = rp[v + 1];
-      for (int64_t e = e0; e < e1; e += 4) {
-        uint32_t wq[4];
+    for (uint32_t b = qb + (tid & ~63u); b < qe; b += kReachBlock) {  // the same for a wavefront
+      int64_t e0 = 0;
+      uint32_t deg = 0;
+      if (b + lane < qe) {
+        const uint32_t v = queue[b + lane];
+        e0 = rp[v];
+        deg = (uint32_t)(rp[v + 1] - e0);
+      }
+      uint32_t w[kAtOnce];
+      bool has[kAtOnce];
+      for (uint32_t c = 0; c < kAlone && __ballot(c < deg) != 0ull; c += kAtOnce) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) wq[j] = (e + j < e1) ? (uint32_t)col[e + j] : kUnseen;
+        for (int j = 0; j < kAtOnce; ++j) {
+          has[j] = c + j < deg;
+          w[j] = has[j] ? (uint32_t)col[e0 + c + j] : 0u;
+        }
+        visit(w, has);
+      }
+      for (ull rest = __ballot(deg > kAlone); rest != 0ull; rest &= rest - 1ull) {
+        const int i = __builtin_ctzll(rest);
+        const int32_t *row = col + (int64_t)read_lane64((ull)e0, i);
+        const uint32_t d = read_lane(deg, i);
+        for (uint32_t c = kAlone; c < d; c += 64 * kAtOnce) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const uint32_t w = wq[j];
-          if (w == kUnseen) break;
-          const uint32_t bit = 1u << (w & 31);
-          if ((vis[w >> 5] & bit) == 0u && (atomicOr(&vis[w >> 5], bit) & bit) == 0u)
-            queue[atomicAdd(&s_tail, 1u)] = (uint16_t)w;
+          for (int j = 0; j < kAtOnce; ++j) {
+            const uint32_t at = c + (uint32_t)(64 * j + lane);
+            has[j] = at < d;
+            w[j] = has[j] ? (uint32_t)row[at] : 0u;
+          }
+          visit(w, has);
         }
       }
     }
@@ -256,15 +306,24 @@ __global__ __launch_bounds__(kReachBlock) void k_lds_reach(const int64_t *rp, co
   for (uint32_t w = tid; w < words; w += kReachBlock) bitmap_out[w] = vis[w];
 }
 
-bool lds_reach_fits(const Graph *g) { return g->n >= 1 && g->n < 65536 && lds_reach_bytes(g->n) <= g->lds_block_bytes; }
+// One compute unit scans the arcs alone, so graphs of more than kLdsReachArcs
+// go to the launch-per-level form even where their bits would fit.  RV(r), whole
+// call, one workgroup against a launch per level: 3,005 arcs 27 / 82 us, 10,000
+// 33 / 82, 32,000 (uniform) 48 / 95, 28,672 (R-MAT) 60 / 65, 58,778 74 / 65,
+// 110,551 110 / 68.
+constexpr int64_t kLdsReachArcs = 1 << 15;
+bool lds_reach_fits(const Graph *g) {
+  return g->n >= 1 && g->n < 65536 && g->m <= kLdsReachArcs && lds_reach_bytes(g->n) <= g->lds_block_bytes;
+}
 
-hipError_t launch_lds_reach(const Graph *g, const int64_t *rp, const int32_t *col, int32_t root, uint32_t *bitmap,
-                            hipStream_t st) {
+hipError_t launch_lds_reach(const Graph *g, const int64_t *rp, const int32_t *col, int32_t root,
+                            const int32_t *roots, int k, uint32_t *bitmap, hipStream_t st) {
   const size_t shm = lds_reach_bytes(g->n);
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_lds_reach), hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)shm) != hipSuccess)
     (void)hipGetLastError();
-  hipLaunchKernelGGL(k_lds_reach, dim3(1), dim3(kReachBlock), shm, st, rp, col, (int32_t)g->n, root, bitmap);
+  hipLaunchKernelGGL(k_lds_reach, dim3(1), dim3(kReachBlock), shm, st, rp, col, (int32_t)g->n, root, roots, k,
+                     bitmap);
   return hipGetLastError();
 }
 

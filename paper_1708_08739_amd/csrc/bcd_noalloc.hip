@@ -12,7 +12,7 @@
 // device address of each GPU's copy is looked up once per device with
 // hipGetSymbolAddress and kept.  Calls are serialized by a process-wide lock,
 // so calls from several host threads do not overlap on the array; every call
-// clears the bitmap and counters it uses with a fill kernel before the
+// clears the bitmap and counters it uses with a kernel before the
 // traversal, so nothing of an earlier call survives into its result.
 #include <hip/hip_runtime.h>
 
@@ -25,7 +25,8 @@ namespace bcd {
 
 // Largest graph the scratch holds: 2^22 vertices (R-MAT scale 22).
 constexpr int64_t kNoAllocMaxN = int64_t(1) << 22;
-constexpr size_t kCtrBytes = 256;  // counters: queue sizes [2], list size, queue arc counts (uint64) at words 4-7
+constexpr size_t kCtrBytes = 256;  // counters: four frontiers (ReachCtr) from word 0, list size at word kListWord
+constexpr int kListWord = 32;
 constexpr size_t kBitmapBytes = (size_t)(kNoAllocMaxN / 32) * 4;  // visited bits
 constexpr size_t kQueueBytes = (size_t)kNoAllocMaxN * 4;          // one frontier queue (int32 ids)
 constexpr size_t kScratchBytes = kCtrBytes + kBitmapBytes + 2 * kQueueBytes;  // 34,079,000 bytes
@@ -37,11 +38,6 @@ namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_noalloc_mu;                         // one call at a time in this process
 unsigned char *g_scratch_dev[kMaxDevices] = {};  // device address of `scratch` per device
-
-__global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
 
 // One workgroup: the ids of the set bits of bitmap[0 .. words) below n,
 // except `skip`, in ascending order into out[]; their number into *count.
@@ -135,57 +131,42 @@ extern "C" bcd_status bcd_rv_noalloc(const bcd_graph *gh, bcd_vid r, bcd_vid *ou
   unsigned char *base = nullptr;
   bcd_status st0 = scratch_address(&base);
   if (st0 != BCD_OK) return st0;
-  uint32_t *ctr = reinterpret_cast<uint32_t *>(base);            // [0], [1]: queue sizes; [2]: list size
+  uint32_t *ctr = reinterpret_cast<uint32_t *>(base);
   uint32_t *bitmap = reinterpret_cast<uint32_t *>(base + kCtrBytes);
   int32_t *q0 = reinterpret_cast<int32_t *>(base + kCtrBytes + kBitmapBytes);
   int32_t *q1 = reinterpret_cast<int32_t *>(base + kCtrBytes + kBitmapBytes + kQueueBytes);
   const int64_t words = (n + 31) / 32;
   hipStream_t st = nullptr;  // the null stream: every step below is ordered after the one before
-  // clear what this call reads before writing it: the bitmap and the counters
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 1024)), dim3(256), 0, st,
-                     bitmap, words, 0u);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, ctr, (int64_t)(kCtrBytes / 4), 0u);
-  NA_HIPCHK(hipGetLastError(), "fill launch failed");
   const int64_t *rp = g->d_irp;
   const int32_t *col = g->d_icol;
   if (lds_reach_fits(g)) {
     // small graph: the whole traversal in one workgroup (visited bits and
     // queue in LDS), bitmap written out at the end
-    NA_HIPCHK(launch_lds_reach(g, rp, col, r, bitmap, st), "reachability launch failed");
+    NA_HIPCHK(launch_lds_reach(g, rp, col, r, nullptr, 1, bitmap, st), "reachability launch failed");
   } else {
-    NA_HIPCHK(launch_reach_init(bitmap, q0, &ctr[0], r, st), "reachability launch failed");
+    // clears what this call reads before writing it, the bitmap and the counters
+    const ReachCtr rc{ctr, 4};
+    NA_HIPCHK(launch_reach_init(bitmap, words, q0, rc, r, nullptr, 1, st), "reachability launch failed");
     const Launch L = g->launch();
-    int32_t *q[2] = {q0, q1};
-    int cur = 0;
-    // large levels bottom-up over the out-arcs, as the allocating call does;
-    // the arcs of queue c's vertices (uint64) at ctr[4 + 2c]
-    const uint64_t bu_arcs = (uint64_t)std::max<int64_t>(64, g->m / 64);
-    uint64_t *arcs = reinterpret_cast<uint64_t *>(ctr + 4);
+    const uint64_t bu_arcs = reach_bu_arcs(g);
     for (int64_t level = 0; level <= n;) {
       // levels 8 at a time between host checks of the frontier size
-      for (int i = 0; i < 8; ++i, ++level) {
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctr[1 - cur], (int64_t)1, 0u);
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, ctr + 4 + 2 * (1 - cur), (int64_t)2, 0u);
-        NA_HIPCHK(hipGetLastError(), "fill launch failed");
-        NA_HIPCHK(launch_reach_level(rp, col, bitmap, q[cur], &ctr[cur], &arcs[cur], q[1 - cur], &ctr[1 - cur],
-                                     &arcs[1 - cur], nullptr, (int)level, bu_arcs, L, st),
+      for (int i = 0; i < 8; ++i, ++level)
+        NA_HIPCHK(launch_reach_level(rp, col, g->d_rp, g->d_col, bitmap, q0, q1, rc, nullptr, (int)level, n, bu_arcs, L,
+                                     st),
                   "reachability launch failed");
-        NA_HIPCHK(launch_reach_bu(g->d_rp, g->d_col, rp, bitmap, &arcs[cur], q[1 - cur], &ctr[1 - cur], &arcs[1 - cur],
-                                  n, bu_arcs, L, st),
-                  "reachability launch failed");
-        cur = 1 - cur;
-      }
       uint32_t left = 0;
-      NA_HIPCHK(hipMemcpy(&left, &ctr[cur], sizeof(uint32_t), hipMemcpyDeviceToHost), "frontier size copy failed");
+      NA_HIPCHK(hipMemcpy(&left, rc.len((int)level), sizeof(uint32_t), hipMemcpyDeviceToHost),
+                "frontier size copy failed");
       if (left == 0) break;
     }
   }
-  // RV(r) ascending into the first queue (free again), its size into ctr[2]
+  // RV(r) ascending into the first queue (free again), its size into ctr[kListWord]
   hipLaunchKernelGGL(k_bitmap_compact, dim3(1), dim3(kCompactBlock), 0, st, bitmap, words, n, (int32_t)r, q0,
-                     &ctr[2]);
+                     &ctr[kListWord]);
   NA_HIPCHK(hipGetLastError(), "compaction launch failed");
   uint32_t k = 0;
-  NA_HIPCHK(hipMemcpy(&k, &ctr[2], sizeof(uint32_t), hipMemcpyDeviceToHost), "count copy failed");
+  NA_HIPCHK(hipMemcpy(&k, &ctr[kListWord], sizeof(uint32_t), hipMemcpyDeviceToHost), "count copy failed");
   *count = (int64_t)k;
   if (!out) return BCD_OK;
   if ((int64_t)k > cap) return fail_static(BCD_ERR_BUFFER_TOO_SMALL, "out holds fewer than |RV(r)| ids");

@@ -51,11 +51,17 @@ uint64_t index_below(uint64_t x, uint64_t k) {
 
 // ------------------------------------------------------- reachability
 
-// Vertices reachable from `root` over the reverse graph (reverse = true,
-// Def.3: the vertices that reach root) or the graph itself.  Bit v of
-// `bits` is set for every vertex met, root included; *count excludes root.
-bcd_status reach_set(Graph *g, Workspace *ws, int32_t root, bool reverse, std::vector<uint32_t> &bits,
-                     int64_t *count, uint8_t *d_lev) {
+// Set bits of a word (the host build targets no popcount instruction).
+static inline int popcount32(uint32_t x) {
+  x -= (x >> 1) & 0x55555555u;
+  x = (x & 0x33333333u) + ((x >> 2) & 0x33333333u);
+  return (int)((((x + (x >> 4)) & 0x0F0F0F0Fu) * 0x01010101u) >> 24);
+}
+
+// Vertices reachable from any of the `k` roots over the reverse graph
+// (reverse = true, Def.3: the vertices that reach one) or the graph itself.
+// Bit v of ws->h_bitmap is set for every vertex met, roots included.
+static bcd_status reach_bitmap(Graph *g, Workspace *ws, const int32_t *roots, int k, bool reverse, uint8_t *d_lev) {
   STCHK(ws->ensure_reach());
   const int64_t n = g->n;
   const size_t words = (size_t)(n + 31) / 32;
@@ -65,68 +71,154 @@ bcd_status reach_set(Graph *g, Workspace *ws, int32_t root, bool reverse, std::v
   // the other direction, for levels found bottom-up
   const int64_t *rpo = reverse ? g->d_rp : g->d_irp;
   const int32_t *colo = reverse ? g->d_col : g->d_icol;
-  Launch L = g->launch();
+  const int32_t *d_roots = nullptr;
+  if (k > 1) {
+    if ((size_t)k > ws->roots_cap) {
+      if (ws->d_roots) (void)hipFree(ws->d_roots);
+      ws->d_roots = nullptr;
+      ws->roots_cap = 0;
+      if (hipMalloc((void **)&ws->d_roots, (size_t)k * sizeof(int32_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        ws->d_roots = nullptr;
+        return fail(BCD_ERR_OUT_OF_MEMORY, "root list");
+      }
+      ws->roots_cap = (size_t)k;
+    }
+    HIPCHK(hipMemcpyAsync(ws->d_roots, roots, (size_t)k * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    d_roots = ws->d_roots;
+  }
   if (!d_lev && lds_reach_fits(g)) {
     // small graph: the whole traversal in one workgroup, one launch
-    HIPCHK(launch_lds_reach(g, rp, col, root, ws->bitmap, st));
+    HIPCHK(launch_lds_reach(g, rp, col, roots[0], d_roots, k, ws->bitmap, st));
     HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    bits.assign(ws->h_bitmap, ws->h_bitmap + words);
-    int64_t c = 0;
-    for (size_t i = 0; i < words; ++i) c += __builtin_popcount(bits[i]);
-    *count = c - 1;
     return BCD_OK;
   }
-  HIPCHK(hipMemsetAsync(ws->bitmap, 0, words * sizeof(uint32_t), st));
-  // per queue c: its length at rqn[4c], the arcs of its vertices (uint64) at rqn[4c + 2]
-  HIPCHK(hipMemsetAsync(ws->rqn, 0, 8 * sizeof(uint32_t), st));
-  auto qlen = [&](int c) { return ws->rqn + 4 * c; };
-  auto qarcs = [&](int c) { return reinterpret_cast<uint64_t *>(ws->rqn + 4 * c + 2); };
-  HIPCHK(launch_reach_init(ws->bitmap, ws->rq[0], qlen(0), root, st));
-  int cur = 0;
-  const int chunk = 8;
+  const ReachCtr ctr{ws->rqn, kTailStride};
+  HIPCHK(launch_reach_init(ws->bitmap, (int64_t)words, ws->rq[0], ctr, roots[0], d_roots, k, st));
   // a level whose frontier has at least m/64 arcs to scan is found bottom-up
   // (Beamer's direction switch), unless levels are wanted: at R-MAT 22 the
   // two largest levels of RV(r) take about 60 M in-arc checks top-down and
   // far fewer out-arc checks bottom-up.  The rule counts arcs, not vertices:
   // the second level's frontier is a few ten thousand vertices of large
   // in-degree (40 M in-arcs)
-  const uint64_t bu_arcs = d_lev ? ~0ull : (uint64_t)std::max<int64_t>(64, g->m / 64);
+  const uint64_t bu_arcs = d_lev ? ~0ull : reach_bu_arcs(g);
+  const Launch L = g->launch();
+  int chunk = std::min(kLevelChunkMax, std::max(4, ws->reach_depth + 2));
   for (int64_t level = 0; level <= n;) {
-    for (int i = 0; i < chunk; ++i, ++level) {
-      HIPCHK(hipMemsetAsync(qlen(1 - cur), 0, 4 * sizeof(uint32_t), st));
-      HIPCHK(launch_reach_level(rp, col, ws->bitmap, ws->rq[cur], qlen(cur), qarcs(cur), ws->rq[1 - cur],
-                                qlen(1 - cur), qarcs(1 - cur), d_lev, (int)level, bu_arcs, L, st));
-      if (!d_lev)
-        HIPCHK(launch_reach_bu(rpo, colo, rp, ws->bitmap, qarcs(cur), ws->rq[1 - cur], qlen(1 - cur),
-                               qarcs(1 - cur), n, bu_arcs, L, st));
-      cur = 1 - cur;
-    }
+    for (int i = 0; i < chunk; ++i, ++level)
+      HIPCHK(launch_reach_level(rp, col, rpo, colo, ws->bitmap, ws->rq[0], ws->rq[1], ctr, d_lev, (int)level, n, bu_arcs,
+                                L, st));
     uint32_t *h = reinterpret_cast<uint32_t *>(ws->h_misc);
-    HIPCHK(hipMemcpyAsync(h, qlen(cur), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(h, ctr.c, (size_t)4 * kTailStride * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (h[0] == 0) break;
+    if (*ReachCtr{h, kTailStride}.len((int)level) == 0) {
+      ws->reach_depth = (int)std::min<uint32_t>(h[1], kLevelChunkMax);
+      break;
+    }
+    chunk = 8;
   }
-  HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  bits.assign(ws->h_bitmap, ws->h_bitmap + words);
+  return BCD_OK;
+}
+
+// The same for one root into `bits`; *count excludes the root.
+bcd_status reach_set(Graph *g, Workspace *ws, int32_t root, bool reverse, std::vector<uint32_t> &bits,
+                     int64_t *count, uint8_t *d_lev) {
+  STCHK(reach_bitmap(g, ws, &root, 1, reverse, d_lev));
+  bits.assign(ws->h_bitmap, ws->h_bitmap + (size_t)(g->n + 31) / 32);
   int64_t c = 0;
-  for (size_t i = 0; i < words; ++i) c += __builtin_popcount(bits[i]);
+  for (const uint32_t x : bits) c += popcount32(x);
   *count = c - 1;
   return BCD_OK;
 }
 
-void bits_to_list(const std::vector<uint32_t> &bits, int64_t n, int32_t skip, std::vector<int32_t> &out) {
-  out.clear();
-  for (size_t wi = 0; wi < bits.size(); ++wi) {
-    uint32_t x = bits[wi];
-    while (x) {
-      const int b = __builtin_ctz(x);
-      x &= x - 1;
-      const int64_t v = (int64_t)wi * 32 + b;
-      if (v < n && v != skip) out.push_back((int32_t)v);
+// The vertices other than roots are in D iff a traversal from all roots meets
+// them.  Root i is in D iff it reaches another root j: i and j differ in some
+// bit b of their positions, so iff for some b a traversal from the roots whose
+// bit b is not i's meets it.  That takes two traversals per bit instead of one
+// per target; with few targets it is one each.
+bcd_status reach_union(Graph *g, Workspace *ws, const std::vector<int32_t> &targets, std::vector<uint32_t> &uni) {
+  const size_t words = (size_t)(g->n + 31) / 32;
+  uni.assign(words, 0u);
+  std::vector<int32_t> t;
+  for (int32_t r : targets)
+    if (g->outdeg(r) != 0) t.push_back(r);
+  int nbits = 0;
+  while ((size_t(1) << nbits) < t.size()) ++nbits;
+  auto has = [](const uint32_t *bits, int32_t v) { return (bits[(size_t)v >> 5] >> (v & 31)) & 1u; };
+  if (t.size() <= (size_t)(2 * nbits) || t.size() == 1) {
+    for (int32_t r : t) {
+      STCHK(reach_bitmap(g, ws, &r, 1, true, nullptr));
+      ws->h_bitmap[(size_t)r >> 5] &= ~(1u << (r & 31));
+      for (size_t i = 0; i < words; ++i) uni[i] |= ws->h_bitmap[i];
+    }
+    return BCD_OK;
+  }
+  std::vector<uint8_t> in(t.size(), 0);
+  for (int b = 0; b < nbits; ++b)
+    for (size_t side = 0; side < 2; ++side) {
+      std::vector<int32_t> roots;
+      for (size_t i = 0; i < t.size(); ++i)
+        if (((i >> b) & 1) == side) roots.push_back(t[i]);
+      STCHK(reach_bitmap(g, ws, roots.data(), (int)roots.size(), true, nullptr));
+      for (size_t i = 0; i < t.size(); ++i)
+        if (((i >> b) & 1) != side && has(ws->h_bitmap, t[i])) in[i] = 1;
+      if (b == 0)
+        for (size_t i = 0; i < words; ++i) uni[i] |= ws->h_bitmap[i];
+    }
+  for (size_t i = 0; i < t.size(); ++i)
+    if (!in[i]) uni[(size_t)t[i] >> 5] &= ~(1u << (t[i] & 31));
+  return BCD_OK;
+}
+
+// Positions of the set bits of every byte, in order, and their number.
+struct ByteBits {
+  uint8_t pos[256][8];
+  uint8_t num[256];
+  ByteBits() {
+    for (int x = 0; x < 256; ++x) {
+      int c = 0;
+      for (int b = 0; b < 8; ++b) {
+        pos[x][b] = 0;
+        if ((x >> b) & 1) pos[x][c++] = (uint8_t)b;
+      }
+      num[x] = (uint8_t)c;
     }
   }
+};
+
+// Ascending ids of the set bits except `skip`, into out[0 .. room-1] (room for
+// all).  A byte's ids are written eight at a time, past their number where
+// there is room (no branch per bit), else one by one.
+static int64_t list_bits(const std::vector<uint32_t> &bits, int64_t n, int32_t skip, int32_t *out, int64_t room) {
+  static const ByteBits tab;
+  int32_t *p = out, *const end = out + room;
+  for (size_t wi = 0; wi < bits.size(); ++wi) {
+    uint32_t x = bits[wi];
+    if (skip >= 0 && (size_t)(skip >> 5) == wi) x &= ~(1u << (skip & 31));
+    const int64_t v0 = (int64_t)wi * 32;
+    if (n - v0 < 32) x &= (1u << (n - v0)) - 1u;
+    if (x == 0) continue;
+    if (end - p >= 32) {
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t byte = (x >> (8 * q)) & 255u;
+        const int32_t base = (int32_t)v0 + 8 * q;
+        for (int j = 0; j < 8; ++j) p[j] = base + tab.pos[byte][j];
+        p += tab.num[byte];
+      }
+    } else {
+      for (; x != 0; x &= x - 1) *p++ = (int32_t)v0 + __builtin_ctz(x);
+    }
+  }
+  return p - out;
+}
+
+void bits_to_list(const std::vector<uint32_t> &bits, int64_t n, int32_t skip, std::vector<int32_t> &out) {
+  int64_t c = 0;
+  for (const uint32_t x : bits) c += popcount32(x);
+  out.resize((size_t)c);
+  out.resize((size_t)list_bits(bits, n, skip, out.data(), c));
 }
 
 // ------------------------------------------------------ source order
@@ -956,11 +1048,7 @@ bcd_status bcd_rv(const bcd_graph *gh, bcd_vid r, bcd_vid *out, int64_t cap, int
     *count = k;
     return fail(BCD_ERR_BUFFER_TOO_SMALL, "RV(r) has " + std::to_string(k) + " vertices");
   }
-  if (out) {
-    std::vector<int32_t> list;
-    bits_to_list(bits, g->n, r, list);
-    std::copy(list.begin(), list.end(), out);
-  }
+  if (out) (void)list_bits(bits, g->n, r, out, k);
   *count = k;
   return BCD_OK;
   BCD_GUARD_END
@@ -1020,14 +1108,8 @@ bcd_status bcd_bc_set(const bcd_graph *gh, const bcd_vid *rs, int64_t l, double 
   std::vector<int32_t> tg(rs, rs + l);
   std::sort(tg.begin(), tg.end());
   tg.erase(std::unique(tg.begin(), tg.end()), tg.end());
-  std::vector<uint32_t> uni((size_t)(g->n + 31) / 32, 0u), bits;
-  for (int32_t r : tg) {
-    if (g->outdeg(r) == 0) continue;
-    int64_t k = 0;
-    STCHK(reach_set(g, ls.w.get(), r, true, bits, &k, nullptr));
-    bits[(size_t)r >> 5] &= ~(1u << (r & 31));
-    for (size_t i = 0; i < uni.size(); ++i) uni[i] |= bits[i];
-  }
+  std::vector<uint32_t> uni;
+  STCHK(reach_union(g, ls.w.get(), tg, uni));
   std::vector<int32_t> D;
   bits_to_list(uni, g->n, -1, D);
   const double t1 = now_s();

@@ -144,13 +144,8 @@ static bcd_status plan_query(bcd_server *S, Workspace *ws, SQuery &q) {
     q.targets = q.rs;
     std::sort(q.targets.begin(), q.targets.end());
     q.targets.erase(std::unique(q.targets.begin(), q.targets.end()), q.targets.end());
-    std::vector<uint32_t> uni((size_t)(g->n + 31) / 32, 0u);
-    for (int32_t r : q.targets) {
-      if (g->outdeg(r) == 0) continue;
-      STCHK(reach_set(g, ws, r, true, bits, &k, nullptr));
-      bits[(size_t)r >> 5] &= ~(1u << (r & 31));
-      for (size_t i = 0; i < uni.size(); ++i) uni[i] |= bits[i];
-    }
+    std::vector<uint32_t> uni;
+    STCHK(reach_union(g, ws, q.targets, uni));
     bits_to_list(uni, g->n, -1, q.sources);
     st.rv_size = (int64_t)q.sources.size();
     st.distinct_sources = st.rv_size;

@@ -953,3 +953,40 @@ def test_weighted_row_lengths_around_steps_and_parts(B, oracle, wmax):
         od, oc = oracle.dependencies(g, r, src)
         assert close(dep, od) and np.array_equal(cnt, oc), (wmax, r)
         assert np.array_equal(G.dependencies(r, src), dep), (wmax, r)
+
+
+@pytest.mark.parametrize("l", [1, 2, 3, 5, 7, 9, 16, 17, 33])
+def test_set_union_of_reaching_vertices(B, oracle, l):
+    """D of the set form from grouped traversals: targets that reach each other
+    or not, with and without out-arcs, on graphs with many components, one
+    strong component and none."""
+    for g in (gg.random_small(60, 0.03, seed=8), gg.random_small(60, 0.12, seed=9), gg.transitive_tournament(40),
+              gg.headed_random(30, 12, seed=4)):
+        rs = gg.uniform_vertices(g.n, min(l, g.n), seed=l)
+        D = set()
+        for r in rs:
+            if g.row_ptr[r + 1] > g.row_ptr[r]:
+                D |= set(oracle.rv(g, r).tolist())
+        G = dev(B, g)
+        got, st = G.bc_set(rs)
+        assert st["rv_size"] == len(D), (g.name, l)
+        assert close(got, oracle.bc_set(g, rs)[0]), (g.name, l)
+
+
+@pytest.mark.parametrize("sizes", [(7, 8, 9, 31, 32, 33, 63, 65, 1025), (15, 16, 17, 4097, 20000)])
+def test_rv_row_lengths(B, oracle, sizes):
+    """RV(r) and the forward reach around the row lengths at which a row goes
+    from one thread to a wavefront and from one wavefront to several, in the
+    one-workgroup form and the launch per level."""
+    g, hubs = fan_graph(sizes)
+    G = dev(B, g)
+    for r in hubs + [0, max(sizes)]:
+        assert np.array_equal(G.rv(r), oracle.rv(g, r)), r
+    # the same rows met from a part of the graph only: no way back
+    k = max(sizes)
+    src = [i for s in range(len(sizes)) for i in range(sizes[s])]
+    dst = [k + s for s in range(len(sizes)) for _ in range(sizes[s])]
+    one = gg.from_arcs(k + len(sizes) + 1, src + dst[-1:], dst + [k + len(sizes)], name="in_stars")
+    H = dev(B, one)
+    for r in range(k, k + len(sizes) + 1):
+        assert np.array_equal(H.rv(r), oracle.rv(one, r)), r
