@@ -147,7 +147,7 @@ __host__ __device__ inline bool bottom_up_rule(int bu_den, int level, uint64_t p
 struct Launch {
   int block;      // threads per workgroup
   int grid;       // workgroups
-  int items = 1;  // items per wavefront step (bottom-up and pushed levels)
+  int items = 1;  // items per wavefront step (pushed levels)
 };
 
 // ---- launchers (bcd_kernels.hip) ----

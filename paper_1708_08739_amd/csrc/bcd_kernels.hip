@@ -614,13 +614,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
   flush_wave_counters<BLOCK, 5>(S.ctr, S.ctr_slots, ck, cv, ovf, S.flags);
 }
 
-// 64-bit lane shuffle (ds_bpermute on both halves).
-static __device__ __forceinline__ ull shfl64(ull x, int src) {
-  const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)x, src);
-  const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(x >> 32), src);
-  return ((ull)hi << 32) | lo;
-}
-
 // One BFS level found bottom-up (direction-optimizing BFS, here over 64
 // sources at once): every (g, w) of the batch with in-arcs and with lanes
 // not yet settled scans its in-arcs (u, w); lanes b of u's previous-level
@@ -630,11 +623,13 @@ static __device__ __forceinline__ ull shfl64(ull x, int src) {
 // masks; (g, w) is appended to the level's list if it gained any lane.
 // Runs before the top-down kernel of the same level, and only when
 // bottom_up_rule holds for the level.  The unsettled pairs of a 64-vertex
-// block are taken K at a time, 64 / K lanes each for their first in-arcs;
-// a heavy vertex is taken by a workgroup, as in k_fwd_level.
-template <int BLOCK, int K>
+// block are taken two at a time in steps of 32 in-arcs each; a heavy vertex is
+// taken by a workgroup, as in k_fwd_level.  Bound as that kernel is (R-MAT 20,
+// 1,000 sources: 19 ms of two levels with one chain of loads per pair, 12.6
+// with rows of words and a chunk at a time, 8.8 as here: 6.4 + 2.4; 5, 6 or 7
+// waves per SIMD alike).
+template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, int level) {
-  constexpr int SUB = kLanes / K;
   constexpr int NW = BLOCK / 64;
   const uint64_t n = (uint64_t)S.n;
   const int P = S.P, NL = S.NL;
@@ -650,7 +645,6 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
   // capacity exceeded earlier (workgroup-uniform test): the batch is redone
   if (S.off[lrow + pv.p] > list_end(S, pv.p) || S.off[lrow + P + pv.p] > list_end(S, P + pv.p)) return;
   const int lane = lane_id();
-  const int slot = lane / SUB, sl = lane % SUB;
   const uint64_t GN = (uint64_t)S.G * n;
   ull *seen = S.msk + M_SEEN * GN, *dnm = S.msk + M_DN * GN, *cur = S.msk + (M_FR + (level & 3)) * GN;
   const ull *prv = S.msk + (M_FR + ((level + 3) & 3)) * GN;
@@ -725,95 +719,138 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
   // over them, and all blocks hold about the same arcs
   const uint64_t nlt = n - S.H, nvb = (nlt + 63) / 64;
   const uint64_t first = lv.heavy ? ngp * nvb : lv.wg * NW + (uint64_t)wv;
+  const bool upper = lane >= 32;
+  const uint32_t k32 = (uint32_t)lane & 31u;
   for (uint64_t b = first; b < ngp * nvb; b += lv.nwg * NW) {
     const uint64_t gl = b / nvb;
     const uint32_t g = (uint32_t)(pv.p + gl * (uint64_t)P);
-    const uint64_t gbase = (uint64_t)g * n;
-    const uint64_t w0 = S.H + (b - gl * nvb) * 8;
-    const uint64_t w = w0 + (uint64_t)(lane >> 3) * nvb * 8 + (uint64_t)(lane & 7);
+    const uint32_t gb = g * (uint32_t)n;
+    const uint64_t wl = S.H + (b - gl * nvb) * 8 + (uint64_t)(lane >> 3) * nvb * 8 + (uint64_t)(lane & 7);
     const ull act_lanes = (g + 1 == (uint32_t)S.gused) ? S.last_lanes : ~0ull;
-    int64_t f0 = 0, f1 = 0;
-    ull uns = 0ull;
-    if (w < n) {
-      f0 = G.irp[w];
-      f1 = G.irp[w + 1];
-      if (f1 > f0) uns = act_lanes & ~seen[gbase + w];
+    uint32_t w = 0, f0 = 0, fd = 0;
+    ull un = 0ull;
+    if (wl < n) {
+      w = (uint32_t)wl;
+      const int64_t r0 = G.irp[w];
+      f0 = (uint32_t)r0;
+      fd = (uint32_t)(G.irp[w + 1] - r0);
+      if (fd != 0u) un = act_lanes & ~seen[gb + w];
+      if (un == 0ull) fd = 0u;
     }
-    ull cm = __ballot(uns != 0ull);
-    while (cm != 0ull) {
-      // the next K candidates of the block, one per slot
-      int jc[K];
-#pragma unroll
-      for (int t = 0; t < K; ++t) {
-        jc[t] = cm != 0ull ? __ffsll((long long)cm) - 1 : -1;
-        if (cm != 0ull) cm &= cm - 1ull;
+    const ull cm = __ballot(un != 0ull);
+    const int nc = __popcll(cm);
+    if (nc == 0) continue;
+    // the candidates move to lanes 0 .. nc-1 (every lane takes part)
+    {
+      const int to = 4 * (un != 0ull ? lanes_below(cm) : nc + lanes_below(~cm));
+      w = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)w);
+      f0 = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)f0);
+      fd = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)fd);
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)un);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)(un >> 32));
+      un = ((ull)hi << 32) | lo;
+    }
+    // steps of 32 in-arcs of candidate j (lower half of the wavefront) and 32
+    // of j + 1 (upper half), loaded ahead as in the forward
+    const uint32_t longest = max(fd, (uint32_t)__shfl_xor((int)fd, 1));
+    auto advance = [&](int &j, uint32_t &c) {
+      if (j >= nc) return;
+      c += 32;
+      if (c >= read_lane(longest, j)) {
+        c = 0;
+        j += 2;
       }
-      int js = jc[0];
-#pragma unroll
-      for (int t = 1; t < K; ++t)
-        if (slot == t) js = jc[t];
-      // the shuffles run on every lane: a permute reads nothing from a lane
-      // that is switched off, and the candidate's own lane may sit in a slot
-      // that has no candidate this step
-      const int src = js < 0 ? 0 : js;
-      const ull un_src = shfl64(uns, src);
-      const int64_t F0 = (int64_t)shfl64((ull)f0, src);
-      const int64_t F1_src = (int64_t)shfl64((ull)f1, src);
-      const ull un = js < 0 ? 0ull : un_src;
-      const int64_t F1 = js < 0 ? F0 : F1_src;
-      // first chunk of every slot's in-arcs
-      const int64_t mi = F0 + sl;
-      uint32_t u = 0;
-      ull pfr = 0ull, pdn = 0ull;
-      if (mi < F1) {
-        u = (uint32_t)G.icol[mi];
-        pfr = prv[gbase + u] & un;
-        if (pfr != 0ull) pdn = dnm[gbase + u] & pfr;
+    };
+    auto ends = [&](int j, uint32_t c, bool &has) -> uint32_t {
+      const int jj = j < nc ? j : 0;
+      const uint32_t at = c + k32;
+      has = j < nc && at < (upper ? read_lane(fd, jj + 1) : read_lane(fd, jj));
+      const uint64_t i = (uint64_t)(upper ? read_lane(f0, jj + 1) : read_lane(f0, jj)) + at;
+      return (uint32_t)G.icol[has ? i : 0];
+    };
+    auto words = [&](uint32_t x, bool has) -> ull { return prv[has ? gb + x : 0u]; };
+    int j0 = 0, j1 = 0, j2;
+    uint32_t c0 = 0, c1 = 0, c2;
+    bool h0, h1, h2;
+    uint32_t x0 = ends(j0, c0, h0);
+    advance(j1, c1);
+    uint32_t x1 = ends(j1, c1, h1);
+    ull m0 = words(x0, h0);
+    ull acc[2] = {0ull, 0ull}, ov[2] = {0ull, 0ull}, got[2] = {0ull, 0ull}, pdn = 0ull;
+    ull nm = 0ull, dnr = 0ull;  // lane j: candidate j's lanes on this level, and those below a target
+    while (j0 < nc) {
+      const ull u0 = read_lane64(un, j0), u1 = read_lane64(un, j0 + 1);
+      const ull pm = h0 ? m0 & (upper ? u1 : u0) : 0ull;
+      const ull pd = dnm[pm != 0ull ? gb + x0 : 0u];
+      const ull all = __ballot(pm != 0ull);
+      ull bits = all & 0xFFFFFFFFull;
+      Rows r;
+      r.issue(S.sig, gb, x0, pm, bits, got[0], c_d);
+      j2 = j1;
+      c2 = c1;
+      advance(j2, c2);
+      const ull m1 = words(x1, h1);
+      const uint32_t x2 = ends(j2, c2, h2);
+      r.add(acc[0], ov[0]);
+      while (bits != 0ull) {
+        r.issue(S.sig, gb, x0, pm, bits, got[0], c_d);
+        r.add(acc[0], ov[0]);
       }
-      const ull pm = pfr;
+      bits = all & ~0xFFFFFFFFull;
+      while (bits != 0ull) {
+        r.issue(S.sig, gb, x0, pm, bits, got[1], c_d);
+        r.add(acc[1], ov[1]);
+      }
+      pdn |= pd & pm;
+      if (j1 != j0) {  // the pair's last step
 #pragma unroll
-      for (int t = 0; t < K; ++t) {
-        if (jc[t] < 0) continue;
-        const ull ut = read_lane64(uns, jc[t]);
-        const int64_t G0 = (int64_t)read_lane64((ull)f0, jc[t]), G1 = (int64_t)read_lane64((ull)f1, jc[t]);
-        ull acc = 0ull, ovm = 0ull, nm = 0ull;  // nm: lanes of w on this level
-        pull_rows(S.sig, (uint32_t)gbase, u, slot == t ? pm : 0ull, acc, ovm, nm, c_d);
-        ull dnt = wave_or(slot == t ? pdn : 0ull);
-        for (int64_t e = G0 + SUB; e < G1; e += kLanes) {
-          const int64_t my = e + lane;
-          uint32_t uu = 0;
-          ull pp = 0ull, pd = 0ull;
-          if (my < G1) {
-            uu = (uint32_t)G.icol[my];
-            pp = prv[gbase + uu] & ut;
-            if (pp != 0ull) pd = dnm[gbase + uu] & pp;
+        for (int t = 0; t < 2; ++t) {
+          if (got[t] != 0ull) {
+            const uint64_t it = (uint64_t)(gb + read_lane(w, j0 + t));
+            if (__builtin_amdgcn_inverse_ballot_w64(got[t])) S.sig[it * kLanes + lane] = acc[t];
+            if (ov[t] != 0ull) {
+              ovf = true;
+              if (lane == 0) atomicOr(&S.ovl[g], ov[t]);
+            }
+            const ull dn = wave_or((t == 1) == upper ? pdn : 0ull);
+            if (lane == j0 + t) {
+              nm = got[t];
+              dnr = dn;
+            }
           }
-          pull_rows(S.sig, (uint32_t)gbase, uu, pp, acc, ovm, nm, c_d);
-          dnt |= wave_or(pd);
+          acc[t] = ov[t] = got[t] = 0ull;
         }
-        if (nm == 0ull) continue;
-        const uint32_t wt = (uint32_t)(w0 + (uint64_t)(jc[t] >> 3) * nvb * 8 + (uint64_t)(jc[t] & 7));
-        const uint32_t it = (uint32_t)(gbase + wt);
-        const bool act = (nm >> lane) & 1ull;
-        const int64_t e0 = G.rp[wt], e1 = G.rp[wt + 1];
-        const int32_t tg = S.tgt_of[wt];
-        if (act) S.sig[(uint64_t)it * kLanes + lane] = acc;
-        if (ovm != 0ull) {
-          ovf = true;
-          if (lane == 0) atomicOr(&S.ovl[g], ovm);
-        }
-        if (tg >= 0) dnt |= nm;
-        if (lane == 0) {
-          cur[it] = nm;
-          seen[it] |= nm;
-          if (dnt != 0ull) dnm[it] |= dnt;
-        }
-        c_v += (uint64_t)__popcll(nm);
-        c_a += (uint64_t)__popcll(nm) * (uint64_t)(e1 - e0);
-        if (tg >= 0 && lane == 0) atomicMin(S.tmin, (uint32_t)level);
-        append_chunk(S, lists, pv.p, sg, gbase, wt, lane == 0);
+        pdn = 0ull;
       }
+      j0 = j1;
+      c0 = c1;
+      j1 = j2;
+      c1 = c2;
+      x0 = x1;
+      x1 = x2;
+      h0 = h1;
+      h1 = h2;
+      m0 = m1;
     }
+    // a lane per candidate: its masks, marks and counters
+    if (__ballot(nm != 0ull) == 0ull) continue;
+    uint64_t pairs = 0, arcs = 0;
+    if (nm != 0ull) {
+      const uint32_t it = gb + w;
+      const bool is_tgt = S.tgt_of[w] >= 0;
+      if (is_tgt) {
+        dnr |= nm;
+        atomicMin(S.tmin, (uint32_t)level);
+      }
+      cur[it] = nm;
+      seen[it] |= nm;
+      if (dnr != 0ull) dnm[it] |= dnr;
+      pairs = (uint64_t)__popcll(nm);
+      arcs = pairs * (uint64_t)(G.rp[w + 1] - G.rp[w]);
+    }
+    c_v += wave_sum(pairs);
+    c_a += wave_sum(arcs);
+    append_chunk(S, lists, pv.p, sg, gb, w, nm != 0ull);
   }
   flush_stage_wg<BLOCK / 64>(S, lists, pv.p, sg);
   const int ck[3] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS};
@@ -1532,22 +1569,8 @@ static void launch_push_k(const DevGraph &G, const BatchState &S, int level, con
   }
 }
 
-template <int K>
-static void launch_bu_k(const DevGraph &G, const BatchState &S, int level, const Launch &L, hipStream_t st) {
-  switch (L.block) {
-    case 64: k_bu_level<64, K><<<dim3(L.grid), dim3(64), 0, st>>>(G, S, level); break;
-    case 128: k_bu_level<128, K><<<dim3(L.grid), dim3(128), 0, st>>>(G, S, level); break;
-    case 512: k_bu_level<512, K><<<dim3(L.grid), dim3(512), 0, st>>>(G, S, level); break;
-    default: k_bu_level<256, K><<<dim3(L.grid), dim3(256), 0, st>>>(G, S, level); break;
-  }
-}
-
 hipError_t launch_bu_level(const DevGraph &G, const BatchState &S, int level, Launch L, hipStream_t st) {
-  switch (L.items) {
-    case 2: launch_bu_k<2>(G, S, level, L, st); break;
-    case 4: launch_bu_k<4>(G, S, level, L, st); break;
-    default: launch_bu_k<1>(G, S, level, L, st); break;
-  }
+  DISPATCH_BLOCK(L, k_bu_level, G, S, level);
   return hipGetLastError();
 }
 
