@@ -204,6 +204,8 @@ struct Graph {
   std::mutex pool_mu;
   std::vector<std::unique_ptr<Workspace>> pool;
   std::atomic<bool> profiling{false};
+  // a batch met a path count above 2^32 - 1: batches store 64-bit counts from then on
+  std::atomic<bool> wide_counts{false};
   std::mutex lm_mu;                // landmark distance signatures (source ordering)
   bool lm_ready = false;
   std::vector<uint8_t> lm_sig;     // [n][16] BFS distance to each hub, 255 = unreachable

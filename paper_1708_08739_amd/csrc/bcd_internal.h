@@ -45,7 +45,7 @@ enum Ctr {
 struct BatchState {
   int64_t n;
   int G;
-  unsigned long long *sig;   // [G][n][64] path counts
+  unsigned long long *sig;   // [G][n][64] path counts (rows of 64 uint32 when narrow)
   double *psi;               // [G][n][64] (1 + delta) / sigma
   double *dout;              // [G][n][64] delta, verification hook only (may be null)
   unsigned long long *msk;   // [M_COUNT][G][n] lane masks (unweighted engine, see MaskArray)
@@ -75,7 +75,7 @@ struct BatchState {
   double *res;               // [ntgt][G][64] delta of lane on target
   uint64_t *ctr;             // [grid][C_COUNT] per-workgroup counters
   uint64_t *acc;             // [C_COUNT] counters of completed batches
-  uint32_t *flags;           // [4]: 0 sigma overflow, 1 item capacity exceeded
+  uint32_t *flags;           // [4]: 0 sigma overflow, 1 item capacity exceeded, 2 a count too wide for a narrow row
   unsigned long long *ovl;   // [G] lanes whose sigma overflowed, then [G] lanes whose source is a target
   int ctr_slots;
   // per batch (unweighted engine)
@@ -85,6 +85,7 @@ struct BatchState {
   int top;                       // deepest level of the batch (set before the backward)
   int keep_all;                  // 1: the backward runs on every lane (exports), else only below a target
   int push;                      // 1: top-down levels push path counts along DAG arcs (k_fwd_push), 0: pull
+  int narrow;                // 1: path counts stored in 32 bits (pulled counts only)
   // weighted graphs only
   uint32_t *wd;              // [G][n][64] distances, 0xFFFFFFFF unreached
   uint32_t *wc;              // [G][n][64] shortest-path-DAG in-arcs not yet pushed

@@ -17,6 +17,24 @@ namespace bcd {
 
 // ------------------------------------------------------------ batched
 
+// The path counts as rows of 64 T, T = uint32_t when S.narrow.  Sums are
+// 64-bit either way; a sum that does not fit the stored type raises flags[2]
+// and the batch is redone with 64-bit rows, so a narrow count is exact too.  The
+// rows are what the large forward levels fetch, and half of a row is half of
+// its cache lines (R-MAT 16 exact 40.7 -> 36.0 ms, R-MAT 20 with 1,000 sources
+// 44.2 -> 39.6).
+template <class T>
+static __device__ __forceinline__ T *counts(const BatchState &S) {
+  return reinterpret_cast<T *>(S.sig);
+}
+
+// Stores this lane's count, wide = a count that T cannot hold was met.
+template <class T>
+static __device__ __forceinline__ void store_count(T *row, ull c, bool &wide) {
+  if (sizeof(T) == 4) wide |= (c >> 32) != 0ull;
+  *row = (T)c;
+}
+
 // Level 0: each item is (g, source vertex) with the lanes it is the source
 // of; sigma = 1 on those lanes.
 __global__ void k_batch_init(BatchState S, const uint32_t *items0, const ull *masks0, const uint32_t *dest0, int k) {
@@ -30,7 +48,10 @@ __global__ void k_batch_init(BatchState S, const uint32_t *items0, const ull *ma
     if (S.tgt_of[it - g * (uint32_t)S.n] >= 0) atomicOr(&S.ovl[S.G + g], m);
     S.items[dest0[i]] = it;
     for (int b = 0; b < kLanes; ++b)
-      if ((m >> b) & 1ull) S.sig[(size_t)it * kLanes + b] = 1ull;
+      if ((m >> b) & 1ull) {
+        if (S.narrow) counts<uint32_t>(S)[(size_t)it * kLanes + b] = 1u;
+        else S.sig[(size_t)it * kLanes + b] = 1ull;
+      }
   }
   // level-0 base of every item list of this batch
   if (blockIdx.x == 0 && threadIdx.x < (unsigned)S.NL) {
@@ -52,20 +73,21 @@ __global__ void k_batch_init(BatchState S, const uint32_t *items0, const ull *ma
 // going to ov.  got collects the lanes that received a count.  bits, pm, u
 // and gb are wave-uniform or read by lane number, so all address work is
 // scalar.
+template <class T>
 struct Rows {
-  ull x[8];
-  __device__ __forceinline__ void issue(const ull *sig, uint32_t gb, uint32_t u, ull pm, ull &bits, ull &got,
+  T x[8];
+  __device__ __forceinline__ void issue(const T *sig, uint32_t gb, uint32_t u, ull pm, ull &bits, ull &got,
                                         uint64_t &dag_pairs) {
     const int lane = lane_id();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) x[q] = 0ull;
+    for (int q = 0; q < 8; ++q) x[q] = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       if (bits != 0ull) {
         const int j = __builtin_ctzll(bits);
         bits &= bits - 1ull;
         const ull dq = read_lane64(pm, j);
-        const ull *row = sig + (uint64_t)(gb + read_lane(u, j)) * kLanes;
+        const T *row = sig + (uint64_t)(gb + read_lane(u, j)) * kLanes;
         dag_pairs += (uint64_t)__popcll(dq);
         got |= dq;
         if (__builtin_amdgcn_inverse_ballot_w64(dq)) x[q] = row[lane];
@@ -73,9 +95,19 @@ struct Rows {
     }
   }
   __device__ __forceinline__ void add(ull &acc, ull &ov) {
+    if (sizeof(T) == 4) {  // fewer than 2^32 arcs: no carry
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        // keeps the widening out of issue()'s branches, where every load
+        // would be waited for on its own
+        asm volatile("" : "+v"(x[q]));
+        acc += x[q];
+      }
+      return;
+    }
     uint32_t hi = (uint32_t)(acc >> 32);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) hi |= (uint32_t)(x[q] >> 32);
+    for (int q = 0; q < 8; ++q) hi |= (uint32_t)((ull)x[q] >> 32);
     if (__ballot(hi >> 28 != 0u) == 0ull) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) acc += x[q];
@@ -90,11 +122,12 @@ struct Rows {
   }
 };
 
-static __device__ __forceinline__ void pull_rows(const ull *sig, uint32_t gb, uint32_t u, ull pm, ull &acc, ull &ov,
+template <class T>
+static __device__ __forceinline__ void pull_rows(const T *sig, uint32_t gb, uint32_t u, ull pm, ull &acc, ull &ov,
                                                  ull &got, uint64_t &dag_pairs) {
   ull bits = __ballot(pm != 0ull);
   while (bits != 0ull) {
-    Rows r;
+    Rows<T> r;
     r.issue(sig, gb, u, pm, bits, got, dag_pairs);
     r.add(acc, ov);
   }
@@ -164,10 +197,11 @@ __global__ void k_publish_counts(BatchState S, int level) {
 // TB/s fetched).  A level with two items a step, 64-byte mask records and no
 // heavy list took, summed over the levels of R-MAT 16 / 20 with 1,000 sources,
 // 3.0 / 36 ms; as here 1.9 / 24.
-// At least 7 waves per SIMD (72 VGPRs): left alone the compiler takes 88
-// registers for 5 (R-MAT 16 exact 40.7 against 41.9 ms, 8 waves 42.3).
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_fwd_level(DevGraph G, BatchState S, int level) {
+// 8 waves per SIMD (64 VGPRs): left alone the compiler takes 88 registers for 5
+// (R-MAT 16 exact with narrow rows, 5 / 6 / 7 / 8 waves: 38.7 / 36.6 / 35.9 /
+// 35.4 ms; four or six rows at a time instead of eight 35.5 / 35.9).
+template <int BLOCK, class T>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fwd_level(DevGraph G, BatchState S, int level) {
   constexpr int NW = BLOCK / 64;
   const uint32_t n = (uint32_t)S.n;
   const uint64_t GN = (uint64_t)S.G * n;
@@ -224,7 +258,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
   // counters, all wave-uniform: (source, vertex), (source, arc) and
   // (source, DAG arc) pairs; items and the out-degree sum over items
   uint64_t c_v = 0, c_a = 0, c_d = 0, c_it = 0, c_ia = 0;
-  bool ovf = false;
+  bool ovf = false, wide = false;
+  T *sig = counts<T>(S);
   const ListView lv = list_view(S);
   const uint64_t base = S.off[lrow + (lv.heavy ? P : 0) + pv.p];
   const uint64_t count = *tail_at(S, level, (lv.heavy ? P : 0) + pv.p);
@@ -317,8 +352,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
       if (dag != 0ull) was = atomicOr(&seen[gj + x0], dag);
       const ull pd = S.msk[M_DN * GN + (pm != 0ull ? gj + x0 : 0u)];
       ull bits = __ballot(pm != 0ull);
-      Rows r;
-      r.issue(S.sig, gj, x0, pm, bits, got, c_d);
+      Rows<T> r;
+      r.issue(sig, gj, x0, pm, bits, got, c_d);
       // the next step's words and the arc ends of the one after
       j2 = j1;
       c2 = c1;
@@ -330,14 +365,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
       if (fresh != 0ull) first = atomicOr(&nxt[gj + x0], fresh);
       r.add(acc, ov);
       while (bits != 0ull) {
-        r.issue(S.sig, gj, x0, pm, bits, got, c_d);
+        r.issue(sig, gj, x0, pm, bits, got, c_d);
         r.add(acc, ov);
       }
       pdn |= pd & pm;
       if (j1 != j0 && !lv.heavy) {  // the item's last step
         if (rows) {
           const uint32_t ij = read_lane(it, j0);
-          if (__builtin_amdgcn_inverse_ballot_w64(mj)) S.sig[(uint64_t)ij * kLanes + lane] = acc;
+          if (__builtin_amdgcn_inverse_ballot_w64(mj)) store_count(&sig[(uint64_t)ij * kLanes + lane], acc, wide);
           if (ov != 0ull) {
             ovf = true;
             if (lane == 0) atomicOr(&S.ovl[gj / n], ov);
@@ -361,7 +396,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
     if (level == 1)  // every lane's one path
       for (int j = 0; j < nb; ++j)
         if ((!lv.heavy || wv == 0) && __builtin_amdgcn_inverse_ballot_w64(read_lane64(mk, j)))
-          S.sig[(uint64_t)read_lane(it, j) * kLanes + lane] = 1ull;
+          sig[(uint64_t)read_lane(it, j) * kLanes + lane] = 1;
     if (lv.heavy) {
       if (rows) {  // the same for the whole workgroup
         const ull dn = wave_or(pdn);
@@ -380,7 +415,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
             acc = sum;
           }
           if (__builtin_amdgcn_inverse_ballot_w64(read_lane64(mk, 0)))
-            S.sig[(uint64_t)read_lane(it, 0) * kLanes + lane] = acc;
+            store_count(&sig[(uint64_t)read_lane(it, 0) * kLanes + lane], acc, wide);
           if (ov != 0ull) {
             ovf = true;
             if (lane == 0) atomicOr(&S.ovl[read_lane(gb, 0) / n], ov);
@@ -399,6 +434,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7, 8))) v
       S.imask[base + b0 + lane] = S.keep_all ? mk : dnr;
     }
   }
+  if (sizeof(T) == 4 && __ballot(wide) != 0ull && lane == 0) atomicOr(&S.flags[2], 1u);
   flush_stage_wg<BLOCK / 64>(S, lists, pv.p, sg);
   const int ck[5] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS, C_FWD_ITEMS, C_FWD_IARCS};
   const uint64_t cv[5] = {c_v, c_a, c_d, c_it, c_ia};
@@ -628,7 +664,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
 // 1,000 sources: 19 ms of two levels with one chain of loads per pair, 12.6
 // with rows of words and a chunk at a time, 8.8 as here: 6.4 + 2.4; 5, 6 or 7
 // waves per SIMD alike).
-template <int BLOCK>
+template <int BLOCK, class T>
 __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, int level) {
   constexpr int NW = BLOCK / 64;
   const uint64_t n = (uint64_t)S.n;
@@ -649,7 +685,8 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
   ull *seen = S.msk + M_SEEN * GN, *dnm = S.msk + M_DN * GN, *cur = S.msk + (M_FR + (level & 3)) * GN;
   const ull *prv = S.msk + (M_FR + ((level + 3) & 3)) * GN;
   uint64_t c_v = 0, c_a = 0, c_d = 0;
-  bool ovf = false;
+  bool ovf = false, wide = false;
+  T *sig = counts<T>(S);
   // groups p, p + P, ... below gused belong to this partition
   const uint64_t ngp = S.gused > pv.p ? (uint64_t)(S.gused - pv.p + P - 1) / (uint64_t)P : 0;
   // heavy vertices: a workgroup each, its wavefronts share the in-arcs
@@ -673,7 +710,7 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
           pm = prv[gbase + u] & un;
           if (pm != 0ull) pd = dnm[gbase + u] & pm;
         }
-        pull_rows(S.sig, (uint32_t)gbase, u, pm, acc, ovm, nm, c_d);
+        pull_rows(sig, (uint32_t)gbase, u, pm, acc, ovm, nm, c_d);
         dnt |= wave_or(pd);
       }
     red_acc[wv][lane] = acc;
@@ -695,7 +732,7 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
         const uint32_t it = (uint32_t)(gbase + w);
         const uint64_t deg = (uint64_t)(G.rp[w + 1] - G.rp[w]);
         const bool is_tgt = S.tgt_of[w] >= 0;
-        if ((nm >> lane) & 1ull) S.sig[(uint64_t)it * kLanes + lane] = acc;
+        if ((nm >> lane) & 1ull) store_count(&sig[(uint64_t)it * kLanes + lane], acc, wide);
         if (ovm != 0ull) {
           ovf = true;
           if (lane == 0) atomicOr(&S.ovl[g], ovm);
@@ -784,8 +821,8 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
       const ull pd = dnm[pm != 0ull ? gb + x0 : 0u];
       const ull all = __ballot(pm != 0ull);
       ull bits = all & 0xFFFFFFFFull;
-      Rows r;
-      r.issue(S.sig, gb, x0, pm, bits, got[0], c_d);
+      Rows<T> r;
+      r.issue(sig, gb, x0, pm, bits, got[0], c_d);
       j2 = j1;
       c2 = c1;
       advance(j2, c2);
@@ -793,12 +830,12 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
       const uint32_t x2 = ends(j2, c2, h2);
       r.add(acc[0], ov[0]);
       while (bits != 0ull) {
-        r.issue(S.sig, gb, x0, pm, bits, got[0], c_d);
+        r.issue(sig, gb, x0, pm, bits, got[0], c_d);
         r.add(acc[0], ov[0]);
       }
       bits = all & ~0xFFFFFFFFull;
       while (bits != 0ull) {
-        r.issue(S.sig, gb, x0, pm, bits, got[1], c_d);
+        r.issue(sig, gb, x0, pm, bits, got[1], c_d);
         r.add(acc[1], ov[1]);
       }
       pdn |= pd & pm;
@@ -807,7 +844,7 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
         for (int t = 0; t < 2; ++t) {
           if (got[t] != 0ull) {
             const uint64_t it = (uint64_t)(gb + read_lane(w, j0 + t));
-            if (__builtin_amdgcn_inverse_ballot_w64(got[t])) S.sig[it * kLanes + lane] = acc[t];
+            if (__builtin_amdgcn_inverse_ballot_w64(got[t])) store_count(&sig[it * kLanes + lane], acc[t], wide);
             if (ov[t] != 0ull) {
               ovf = true;
               if (lane == 0) atomicOr(&S.ovl[g], ov[t]);
@@ -852,6 +889,7 @@ __global__ __launch_bounds__(BLOCK) void k_bu_level(DevGraph G, BatchState S, in
     c_a += wave_sum(arcs);
     append_chunk(S, lists, pv.p, sg, gb, w, nm != 0ull);
   }
+  if (sizeof(T) == 4 && __ballot(wide) != 0ull && lane == 0) atomicOr(&S.flags[2], 1u);
   flush_stage_wg<BLOCK / 64>(S, lists, pv.p, sg);
   const int ck[3] = {C_FWD_VPAIRS, C_FWD_APAIRS, C_FWD_DPAIRS};
   const uint64_t cv[3] = {c_v, c_a, c_d};  // wave-uniform
@@ -908,7 +946,7 @@ constexpr int kSparseLanes = 8;
 // item loads what is needed of it; items without lanes are passed over), each
 // with the whole wavefront over its out-arcs, the next item's arc ends loaded
 // ahead.  Heavy items go to whole workgroups.
-template <int BLOCK>
+template <int BLOCK, class T>
 __global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, int level, int ntgt) {
   constexpr int NW = BLOCK / 64;
   const uint32_t n = (uint32_t)S.n;
@@ -1008,7 +1046,7 @@ __global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, i
       }
       const int32_t tgt = S.tgt_of[v];
       if ((my >> lane) & 1ull) {
-        const double s = (double)S.sig[(uint64_t)it * kLanes + lane];
+        const double s = (double)counts<T>(S)[(uint64_t)it * kLanes + lane];
         const double dl = s * acc;
         S.psi[(uint64_t)it * kLanes + lane] = acc + 1.0 / s;
         if (S.dout) S.dout[(uint64_t)it * kLanes + lane] = dl;
@@ -1076,7 +1114,7 @@ __global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, i
       uint32_t x0 = ends(t0, c0, h0);
       advance(t1, c1);
       uint32_t x1 = t1 != 0ull ? ends(t1, c1, h1) : (h1 = false, 0u);
-      ull m0 = words(t0, x0, h0), sg = 1ull;
+      ull m0 = words(t0, x0, h0), sg = 1;
       double acc = 0.0;
       while (t0 != 0ull) {
         const int j = __builtin_ctzll(t0);
@@ -1084,7 +1122,7 @@ __global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, i
         const uint32_t gj = read_lane(gb, j), ij = read_lane(it, j);
         const bool mine = __builtin_amdgcn_inverse_ballot_w64(em);
         const ull d = h0 ? em & m0 : 0ull;
-        if (c0 == 0 && mine) sg = S.sig[(uint64_t)ij * kLanes + lane];
+        if (c0 == 0 && mine) sg = counts<T>(S)[(uint64_t)ij * kLanes + lane];
         t2 = t1;
         c2 = c1;
         h2 = false;
@@ -1188,7 +1226,7 @@ __global__ void k_batch_export(DevGraph G, BatchState S, int level, uint64_t beg
     if (slot < 0 || slot >= k) continue;
     const uint64_t o = (uint64_t)slot * n + (uint32_t)G.orig[v];
     dist[o] = (uint64_t)level;
-    sigma[o] = S.sig[(uint64_t)it * kLanes + lane];
+    sigma[o] = S.narrow ? counts<uint32_t>(S)[(uint64_t)it * kLanes + lane] : S.sig[(uint64_t)it * kLanes + lane];
     if (delta && S.dout) delta[o] = S.dout[(uint64_t)it * kLanes + lane];
   }
 }
@@ -1551,6 +1589,17 @@ __global__ __launch_bounds__(256) void k_read(const v4u *__restrict__ src, int64
     }                                                                                      \
   } while (0)
 
+// the same for the kernels that read or write the path counts
+#define DISPATCH_COUNTS(T, L, KERNEL, ...)                                                 \
+  do {                                                                                     \
+    switch ((L).block) {                                                                   \
+      case 64: KERNEL<64, T><<<dim3((L).grid), dim3(64), 0, st>>>(__VA_ARGS__); break;     \
+      case 128: KERNEL<128, T><<<dim3((L).grid), dim3(128), 0, st>>>(__VA_ARGS__); break;  \
+      case 512: KERNEL<512, T><<<dim3((L).grid), dim3(512), 0, st>>>(__VA_ARGS__); break;  \
+      default: KERNEL<256, T><<<dim3((L).grid), dim3(256), 0, st>>>(__VA_ARGS__); break;   \
+    }                                                                                      \
+  } while (0)
+
 hipError_t launch_batch_init(const BatchState &S, const uint32_t *items0, const ull *masks0, const uint32_t *dest0,
                              int k, hipStream_t st) {
   if (k <= 0) return hipSuccess;
@@ -1570,7 +1619,8 @@ static void launch_push_k(const DevGraph &G, const BatchState &S, int level, con
 }
 
 hipError_t launch_bu_level(const DevGraph &G, const BatchState &S, int level, Launch L, hipStream_t st) {
-  DISPATCH_BLOCK(L, k_bu_level, G, S, level);
+  if (S.narrow) DISPATCH_COUNTS(uint32_t, L, k_bu_level, G, S, level);
+  else DISPATCH_COUNTS(ull, L, k_bu_level, G, S, level);
   return hipGetLastError();
 }
 
@@ -1582,7 +1632,8 @@ hipError_t launch_fwd_level(const DevGraph &G, const BatchState &S, int level, L
       default: launch_push_k<1>(G, S, level, L, st); break;
     }
   } else {
-    DISPATCH_BLOCK(L, k_fwd_level, G, S, level);
+    if (S.narrow) DISPATCH_COUNTS(uint32_t, L, k_fwd_level, G, S, level);
+    else DISPATCH_COUNTS(ull, L, k_fwd_level, G, S, level);
   }
   return hipGetLastError();
 }
@@ -1593,7 +1644,8 @@ hipError_t launch_publish_counts(const BatchState &S, int level, hipStream_t st)
 }
 
 hipError_t launch_bwd_level(const DevGraph &G, const BatchState &S, int level, int ntgt, Launch L, hipStream_t st) {
-  DISPATCH_BLOCK(L, k_bwd_level, G, S, level, ntgt);
+  if (S.narrow) DISPATCH_COUNTS(uint32_t, L, k_bwd_level, G, S, level, ntgt);
+  else DISPATCH_COUNTS(ull, L, k_bwd_level, G, S, level, ntgt);
   return hipGetLastError();
 }
 

@@ -352,6 +352,8 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
     S.last_lanes = (k % kLanes) == 0 ? ~0ull : ((1ull << (k % kLanes)) - 1ull);
     S.bu_den = g->config().bottom_up;
     S.push = push;
+    // 32-bit rows until a batch of this graph has met a larger count
+    S.narrow = !push && !g->wide_counts.load(std::memory_order_relaxed);
     S.keep_all = full ? 1 : 0;
     const int NL = S.NL;
     const Launch L = g->launch_parts(S.P, S.gused);
@@ -376,7 +378,7 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
     int lmax = -1;
     int level = 0;
     int chunk = std::min(kLevelChunkMax, std::max(4, ws->last_depth + 2));
-    uint32_t flags_h[2] = {0, 0}, tmin_h = 0xFFFFFFFFu;
+    uint32_t flags_h[3] = {0, 0, 0}, tmin_h = 0xFFFFFFFFu;
     size_t ev = 0;
     while (lmax < 0) {
       int launched = 0;
@@ -404,13 +406,14 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
       HIPCHK(hipMemcpyAsync(hc, &S.cnt[(size_t)rec_from * NL], (size_t)nrec * NL * sizeof(uint32_t),
                             hipMemcpyDeviceToHost, st));
       uint32_t *hm = reinterpret_cast<uint32_t *>(ws->h_misc);
-      HIPCHK(hipMemcpyAsync(hm, S.flags, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-      HIPCHK(hipMemcpyAsync(hm + 2, S.tmin, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipMemcpyAsync(hm, S.flags, 3 * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipMemcpyAsync(hm + 3, S.tmin, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
       flags_h[0] = hm[0];
       flags_h[1] = hm[1];
-      tmin_h = hm[2];
-      if (flags_h[1]) break;
+      flags_h[2] = hm[2];
+      tmin_h = hm[3];
+      if (flags_h[1] | flags_h[2]) break;
       for (int i = 0; i < nrec; ++i) {
         const int l = rec_from + i;
         uint64_t tot = 0;
@@ -426,6 +429,13 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
       }
       if (lmax < 0 && level > g->n) return fail(BCD_ERR_DEVICE, "forward pass did not terminate");
       chunk = kLevelChunkMax;
+    }
+    if (flags_h[2]) {
+      // a count above 2^32 - 1: 64-bit rows for this batch and the next ones
+      g->wide_counts.store(true, std::memory_order_relaxed);
+      STCHK(ws->reset_batch_dense());
+      if (flags_h[1]) STCHK(ws->grow_items());
+      continue;
     }
     if (flags_h[1]) {
       // item list overflow: grow and redo this batch from a clean state

@@ -935,6 +935,73 @@ def test_row_lengths_around_steps_and_heavy_vertices(B, oracle, sizes):
             assert np.array_equal(G.dependencies(r, src), dep), (bu, push, r)
 
 
+def counted_sink(count, fans):
+    """A graph whose last vertex has `count` shortest paths from vertex 0:
+    one for each of `fans` arcs of one hub's sinks, the rest from the joints of
+    a chain of diamonds (joint i has 2**i paths), every branch padded to one
+    length.  One vertex lies beyond the sink, a tail leads back to vertex 0."""
+    arcs, n = [], [1]
+
+    def new():
+        n[0] += 1
+        return n[0] - 1
+
+    rest = count - fans
+    joints = [0]
+    while len(joints) <= rest.bit_length() - 1:
+        a, b, x = new(), new(), new()
+        arcs += [(joints[-1], a), (joints[-1], b), (a, x), (b, x)]
+        joints.append(x)
+    depth = 2 * len(joints) + 2
+    ends = []
+    for i, x in enumerate(joints):
+        if (rest >> i) & 1:
+            for _ in range(depth - 2 * i):
+                y = new()
+                arcs.append((x, y))
+                x = y
+            ends.append(x)
+    if fans:
+        x = 0
+        for _ in range(depth - 1):
+            y = new()
+            arcs.append((x, y))
+            x = y
+        for _ in range(fans):
+            y = new()
+            arcs.append((x, y))
+            ends.append(y)
+    sink = new()
+    arcs += [(x, sink) for x in ends]
+    last = new()
+    arcs += [(sink, last), (last, 0)]
+    src, dst = zip(*arcs)
+    return gg.from_arcs(n[0], list(src), list(dst), name="counted"), sink
+
+
+@pytest.mark.parametrize("fans", [0, 3, 700])
+@pytest.mark.parametrize("count", [(1 << 32) - 1, 1 << 32, (1 << 32) + 1, (1 << 33) + 12345])
+def test_counts_around_32_bits(B, oracle, count, fans):
+    """Path counts at and above the largest that 32 bits hold, summed by a
+    wavefront and by a workgroup, top-down and bottom-up: bit-exact on the first call
+    and on a later one of the same graph, counters included."""
+    g, sink = counted_sink(count, fans)
+    src = [0, 1, sink, g.n - 1]
+    want = [oracle.source_pass(g, s) for s in src]
+    assert int(want[0][1][sink]) == count
+    for bu in (0, 4096):
+        G = dev(B, g, bottom_up=bu)
+        print("counted", count, fans, "bottom_up", bu, flush=True)
+        od, oc = oracle.dependencies(g, sink, src)
+        for _ in range(2):
+            dep, cnt = G.dependencies(sink, src, counters=True)
+            assert close(dep, od) and np.array_equal(cnt, oc)
+            d, sg, dl = G.multi_source_pass(src)
+            for i in range(len(src)):
+                assert np.array_equal(d[i], want[i][0]) and np.array_equal(sg[i], want[i][1]), i
+                assert close(dl[i], want[i][2]), i
+
+
 @pytest.mark.parametrize("wmax", [1, 3])
 def test_weighted_row_lengths_around_steps_and_parts(B, oracle, wmax):
     """Weighted rows around the 64-arc steps and the parts a heavy vertex's
