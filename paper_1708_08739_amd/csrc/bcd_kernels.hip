@@ -926,12 +926,6 @@ struct PsiRows {
   }
 };
 
-// Heavy items of the backward with at most this many lanes go source by
-// source (see k_bwd_level), others arc by arc: R-MAT 20, 1,000 sources, all
-// arc by arc 51.3 ms, limits of 4 / 8 / 16 lanes 50.4 / 48.3 / 48.4, all source
-// by source 56.0; R-MAT 16, 1,000 sources 3.51 / 3.47 / 3.38 / 3.54 / 4.20.
-constexpr int kSparseLanes = 8;
-
 // One level of the backward pass, Eq.(4) read as
 //   delta(v) = sigma(v) * sum_{w: v in P(w)} psi(w),  psi(w) = (1 + delta(w)) / sigma(w),
 // so psi(v) = 1/sigma(v) + sum psi(w).  Successor w of v is on the DAG for
@@ -945,7 +939,12 @@ constexpr int kSparseLanes = 8;
 // Light items are taken in blocks of up to 64 as in the forward (a lane per
 // item loads what is needed of it; items without lanes are passed over), each
 // with the whole wavefront over its out-arcs, the next item's arc ends loaded
-// ahead.  Heavy items go to whole workgroups.
+// ahead.  Heavy items are dealt to wavefronts by eight sources, lanes over
+// eight of the part's DAG arcs by its eight sources, 64 arcs in flight: a hub
+// summed by one wavefront a few rows at a time kept the level waiting with 2
+// to 30 % of the wavefront slots used (R-MAT 20, 1,000 sources: the two
+// shallowest levels 4.0 + 1.4 ms, as here 1.8 + 0.65; R-MAT 16 2.99 -> 2.60 ms a
+// call).
 template <int BLOCK, class T>
 __global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, int level, int ntgt) {
   constexpr int NW = BLOCK / 64;
@@ -973,94 +972,96 @@ __global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, i
   uint64_t c_v = 0, c_a = 0, c_d = 0, c_it = 0, c_ia = 0;  // wave-uniform counters
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const ListView lv = list_view(S);
-  __shared__ ull seg_d[2][BLOCK];
-  __shared__ uint32_t seg_w[2][BLOCK];
+  __shared__ uint32_t part_w[NW][128], part_d[NW][128];
+  __shared__ double part_x[NW][64 * 8];
   if (lv.heavy) {
-    // the wavefronts of a workgroup look up the DAG lanes of BLOCK arcs at a
-    // time and leave them in LDS; then each takes every NW-th source of the
-    // item: the arcs of that source load its psi, 64 arcs to a load, and its
-    // sum takes them in arc order (few sources share a hub's DAG arc, so a row
-    // per arc would be read for two or three lanes)
+    // a wavefront per (item, eight sources): psi's 64 bytes of those sources
+    // are one access, so the parts share no line of it
     const uint64_t base = S.off[lrow + P + pv.p], count = S.cnt[lrow + P + pv.p];
-    for (uint64_t i = lv.wg; i < count; i += lv.nwg) {
-      const ull em = first_lane64(S.imask[base + i]);
-      if (em == 0ull) continue;  // the same for the whole workgroup
-      const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.items[base + i]);
+    uint32_t *qw = part_w[wv], *qd = part_d[wv];  // arcs of the part's DAG lanes, a ring of 128
+    double *xs = part_x[wv];
+    const uint32_t a8 = (uint32_t)lane >> 3, b8 = (uint32_t)lane & 7u;
+    uint32_t dl_pairs = 0;  // this lane's
+    for (uint64_t t = lv.wg * NW + (uint64_t)wv; t < count * 8; t += lv.nwg * NW) {
+      const uint32_t p = (uint32_t)(t & 7u);
+      const ull em = first_lane64(S.imask[base + (t >> 3)]);
+      if (em == 0ull) continue;
+      const uint32_t eb = (uint32_t)(em >> (8 * p)) & 0xFFu;
+      if (eb == 0u && p != 0u) continue;
+      const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.items[base + (t >> 3)]);
       const uint32_t g = it / n, v = it - g * n, gb = g * n;
-      const int64_t e0 = G.rp[v], e1 = G.rp[v + 1];
-      const bool sparse = __popcll(em) <= kSparseLanes;
-      // this wavefront's sources
-      const ull my = sparse ? __ballot(((em >> lane) & 1ull) && lanes_below(em) % NW == wv) : (wv == 0 ? em : 0ull);
-      double acc = 0.0;  // lane b of the wavefront that has source b: its sum
-      int par = 0;
-      for (int64_t e = e0; e < e1; e += BLOCK, par ^= 1) {
-        const int64_t at = e + threadIdx.x;
-        uint32_t w = 0;
-        ull d = 0ull;
-        if (at < e1) {
-          w = (uint32_t)G.col[at];
-          d = em & bw_in[gb + w];
-        }
-        seg_w[par][threadIdx.x] = w;
-        seg_d[par][threadIdx.x] = d;
-        __syncthreads();
-        if (!sparse) {
-          if (wv == 0)
-            for (int q = 0; q < NW; ++q) {
-              d = seg_d[par][q * 64 + lane];
-              ull bits = __ballot(d != 0ull);
-              while (bits != 0ull) {
-                PsiRows r;
-                r.issue(S.psi, gb, seg_w[par][q * 64 + lane], d, bits, c_d);
-                r.add(acc);
-              }
-            }
-          continue;
-        }
-        for (int q = 0; q < NW; ++q) {
-          const double *row = S.psi + (uint64_t)(gb + seg_w[par][q * 64 + lane]) * kLanes;
-          d = seg_d[par][q * 64 + lane];
-          ull todo = my;
-          while (todo != 0ull) {
-            int bq[4];
-            ull aq[4];
-            double y[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              bq[t] = todo != 0ull ? __builtin_ctzll(todo) : 0;
-              aq[t] = todo != 0ull ? __ballot((d >> bq[t]) & 1ull) : 0ull;
-              todo &= todo - 1ull;
-              y[t] = __builtin_amdgcn_inverse_ballot_w64(aq[t]) ? row[bq[t]] : 0.0;
-            }
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              if (aq[t] == 0ull) continue;
-              c_d += (uint64_t)__popcll(aq[t]);
-              double a = __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(acc), bq[t]));
-              for (ull z = aq[t]; z != 0ull; z &= z - 1ull)
-                a += __longlong_as_double((long long)read_lane64((ull)__double_as_longlong(y[t]), __builtin_ctzll(z)));
-              if (lane == bq[t]) acc = a;
-            }
-          }
-        }
-      }
-      const int32_t tgt = S.tgt_of[v];
-      if ((my >> lane) & 1ull) {
-        const double s = (double)counts<T>(S)[(uint64_t)it * kLanes + lane];
-        const double dl = s * acc;
-        S.psi[(uint64_t)it * kLanes + lane] = acc + 1.0 / s;
-        if (S.dout) S.dout[(uint64_t)it * kLanes + lane] = dl;
-        if (tgt >= 0 && tgt < ntgt) S.res[((uint64_t)tgt * S.G + g) * kLanes + lane] = (level > 0) ? dl : 0.0;
-      }
-      if (wv == 0) {
+      const uint64_t e0 = (uint64_t)G.rp[v];
+      const uint32_t ed = (uint32_t)((uint64_t)G.rp[v + 1] - e0);
+      if (p == 0u) {
         if (lane == 0) bw_out[it] = em;
         c_v += (uint64_t)__popcll(em);
-        c_a += (uint64_t)__popcll(em) * (uint64_t)(e1 - e0);
+        c_a += (uint64_t)__popcll(em) * (uint64_t)ed;
         c_it += 1;
-        c_ia += (uint64_t)(e1 - e0);
+        c_ia += (uint64_t)ed;
+        if (eb == 0u) continue;
       }
-      __syncthreads();  // other wavefronts may still read the last arcs' entries
+      const uint8_t *bytes = reinterpret_cast<const uint8_t *>(bw_in + gb) + p;
+      const double *psi = S.psi + (uint64_t)gb * kLanes + 8 * p + b8;
+      auto ends = [&](uint32_t c) -> uint32_t {
+        const uint32_t at = c + (uint32_t)lane;
+        return (uint32_t)G.col[at < ed ? e0 + at : 0];
+      };
+      auto byte_of = [&](uint32_t c, uint32_t x) -> uint32_t { return bytes[c + (uint32_t)lane < ed ? (uint64_t)x * 8 : 0]; };
+      uint32_t c = 0, head = 0, queued = 0, flying = 0;
+      uint32_t x0 = ends(0), x1 = ends(64), m0 = byte_of(0, x0);
+      double acc = 0.0, x[8];  // acc: the sum of source 8 p + b8, the same in all eight lanes
+      for (;;) {
+        // the next 64 DAG arcs, in arc order; the words of the next step and
+        // the arc ends of the one after are loaded ahead
+        while (queued < 64u && c < ed) {
+          const uint32_t d = c + (uint32_t)lane < ed ? m0 & eb : 0u;
+          const uint32_t m1 = byte_of(c + 64, x1), x2 = ends(c + 128);
+          const ull on = __ballot(d != 0u);
+          if (d != 0u) {
+            const uint32_t at = (head + queued + (uint32_t)lanes_below(on)) & 127u;
+            qw[at] = x0;
+            qd[at] = d;
+          }
+          dl_pairs += (uint32_t)__popc(d);
+          queued += (uint32_t)__popcll(on);
+          c += 64;
+          x0 = x1;
+          x1 = x2;
+          m0 = m1;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // the arcs in flight are added in their order
+        if (flying != 0u) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) xs[q * 64 + lane] = x[q];
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          for (uint32_t r = 0; r < flying; r += 8)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc += xs[(r + q) * 8 + b8];
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        flying = min(queued, 64u);
+        if (flying == 0u) break;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const uint32_t k = 8u * q + a8, at = (head + k) & 127u;
+          x[q] = 0.0;
+          if (k < flying && ((qd[at] >> b8) & 1u)) x[q] = psi[(uint64_t)qw[at] * kLanes];
+        }
+        head += flying;
+        queued -= flying;
+      }
+      if (lane < 8 && ((eb >> b8) & 1u)) {
+        const int32_t tgt = S.tgt_of[v];
+        const uint64_t o = (uint64_t)it * kLanes + 8 * p + b8;
+        const double s = (double)counts<T>(S)[o];
+        const double dl = s * acc;
+        S.psi[o] = acc + 1.0 / s;
+        if (S.dout) S.dout[o] = dl;
+        if (tgt >= 0 && tgt < ntgt) S.res[((uint64_t)tgt * S.G + g) * kLanes + 8 * p + b8] = (level > 0) ? dl : 0.0;
+      }
     }
+    c_d += wave_sum(dl_pairs);
   } else {
     const uint64_t base = S.off[lrow + pv.p], count = S.cnt[lrow + pv.p];
     const uint64_t nwv = lv.nwg * NW;
