@@ -306,6 +306,7 @@ using StripeFn = std::function<bcd_status(Workspace *ws, size_t first, size_t st
 // second workspace can be had (`prepare` readies it), every other batch goes
 // to that workspace on a helper thread.  The second workspace's counters are
 // added to `tot`.
+size_t pipelined_batch(const Graph *g, size_t ns, size_t width);
 bcd_status run_pipelined(Graph *g, Workspace *ws, size_t nbatches, const std::function<bcd_status(Workspace *)> &prepare,
                          const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot);
 

@@ -541,15 +541,16 @@ static void add_profile(Graph *g, const ProfAcc &p, const uint64_t *ctr) {
 // write the same element.
 static bcd_status run_batch_stripe(Graph *g, Workspace *ws, const std::vector<int32_t> &src,
                                    const std::vector<uint32_t> &ord, const std::vector<int32_t> &tgt, size_t first,
-                                   size_t stride, std::vector<double> &dep, ProfAcc &prof, bool &ovf) {
+                                   size_t stride, size_t per, std::vector<double> &dep, ProfAcc &prof, bool &ovf) {
   const int ntgt = (int)tgt.size();
   const size_t G64 = (size_t)ws->G * kLanes;
   const size_t ns = src.size();
   TargetMap tm;
   STCHK(tm.install(ws, tgt));
-  std::vector<int32_t> bsrc(G64);
-  for (size_t b0 = first * G64; b0 < ns; b0 += stride * G64) {
-    const int k = (int)std::min(G64, ns - b0);
+  if (stride == 1) per = G64;  // alone: whole batches
+  std::vector<int32_t> bsrc(per);
+  for (size_t b0 = first * per; b0 < ns; b0 += stride * per) {
+    const int k = (int)std::min(per, ns - b0);
     for (int i = 0; i < k; ++i) bsrc[(size_t)i] = src[ord[b0 + i]];
     ws->stage_sources(bsrc.data(), k);
     STCHK(run_one_batch(g, ws, k, ntgt, false, nullptr, &prof, &ovf));
@@ -580,6 +581,21 @@ void ProfAcc::add(const Graph *g, int kind, hipEvent_t a, hipEvent_t b) {
     iv[kind].emplace_back((double)t0, (double)t1);
   else
     (void)hipGetLastError();
+}
+
+// Sources per batch of a run that run_pipelined deals to two workspaces: where
+// the search is long enough, an even number of equal batches.  A level waits for
+// its longest chain of loads, and the other workspace's levels fill the slots
+// that are idle meanwhile.  ms on one workspace / on two: R-MAT 20 with 1,000
+// sources (2^34 source-arc pairs) 30.4 / 26.4, an (eps, delta) draw on 200,003
+// vertices (2^33) 7.2 / 6.3, R-MAT 16 with 1,000 (2^29) 2.32 / 2.31; weighted
+// R-MAT 18 with 2,048 draws (2^33) 127 / 98, R-MAT 13 exact (2^30) 19.0 / 16.0.
+size_t pipelined_batch(const Graph *g, size_t ns, size_t width) {
+  const size_t groups = (ns + kLanes - 1) / kLanes;
+  size_t nb = (ns + width - 1) / width;
+  if (groups < 2 || (uint64_t)ns * (uint64_t)g->m < (1ull << (g->weighted ? 29 : 31))) return width;
+  nb += nb & 1;
+  return (groups + nb - 1) / nb * kLanes;
 }
 
 bcd_status run_pipelined(Graph *g, Workspace *ws, size_t nbatches, const std::function<bcd_status(Workspace *)> &prepare,
@@ -661,14 +677,15 @@ static bcd_status run_batched(Graph *g, Workspace *ws, const std::vector<int32_t
   std::vector<uint32_t> ord;
   STCHK(source_order(g, ws, src, ord));
   if (!want_counters) {
+    const size_t per = pipelined_batch(g, ns, G64);
     auto prepare = [&](Workspace *w) -> bcd_status {
       STCHK(w->ensure_batch(cfg.groups));
       return w->ensure_res((size_t)std::max(ntgt, 1) * G64);
     };
     auto stripe = [&](Workspace *w, size_t first, size_t stride, ProfAcc &p, bool &o) -> bcd_status {
-      return run_batch_stripe(g, w, src, ord, tgt, first, stride, out.dep, p, o);
+      return run_batch_stripe(g, w, src, ord, tgt, first, stride, per, out.dep, p, o);
     };
-    STCHK(run_pipelined(g, ws, (ns + G64 - 1) / G64, prepare, stripe, prof, ovf, tot));
+    STCHK(run_pipelined(g, ws, (ns + per - 1) / per, prepare, stripe, prof, ovf, tot));
   }
   // counters per source need one source per batch
   TargetMap tm;

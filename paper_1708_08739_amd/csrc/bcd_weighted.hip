@@ -19,7 +19,7 @@
 // unweighted engine; the backward computes psi only on lanes where the
 // vertex is a target or lies below one (marks OR'd along the sigma pushes).
 //
-// Work lists are kept per partition (XCD) and split in light and heavy items
+// Work lists are kept per partition and split in light and heavy items
 // as in the unweighted engine; a heavy item is taken in kParts parts of its
 // arcs by as many wavefronts (nothing but atomics joins them, except in the
 // backward, whose sums run in arc order and stay with one wavefront).
@@ -987,8 +987,8 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
   if (want_counters) out.counters.assign(ns * 3, 0);
   // the plain engine on a weighted graph runs one source per batch
   const bool one = want_counters || cfg.engine == BCD_ENGINE_PLAIN;
-  const size_t per = one ? 1 : G64;
-  out.width = (int32_t)per;
+  const size_t two = one ? 1 : pipelined_batch(g, ns, G64);
+  out.width = (int32_t)(one ? 1 : G64);
   std::vector<uint32_t> ord;
   STCHK(source_order(g, ws, src, ord));
   ProfAcc prof;
@@ -999,6 +999,7 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
   auto stripe = [&](Workspace *w, size_t first, size_t stride, ProfAcc &p, bool &o) -> bcd_status {
     TargetMap tm;
     STCHK(tm.install(w, tgt));
+    const size_t per = one ? 1 : (stride == 1 ? G64 : two);  // alone: whole batches
     std::vector<int32_t> bsrc(per);
     for (size_t b0 = first * per; b0 < ns; b0 += stride * per) {
       const int k = (int)std::min(per, ns - b0);
@@ -1026,7 +1027,7 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
       STCHK(w->ensure_weighted());
       return w->ensure_res((size_t)std::max(ntgt, 1) * G64);
     };
-    STCHK(run_pipelined(g, ws, (ns + per - 1) / per, prepare, stripe, prof, ovf, tot));
+    STCHK(run_pipelined(g, ws, (ns + two - 1) / two, prepare, stripe, prof, ovf, tot));
     uint64_t t1[C_COUNT];
     STCHK(wcounters(ws, t1));
     for (int j = 0; j < C_COUNT; ++j) tot[j] += t1[j];

@@ -1057,3 +1057,20 @@ def test_rv_row_lengths(B, oracle, sizes):
     H = dev(B, one)
     for r in range(k, k + len(sizes) + 1):
         assert np.array_equal(H.rv(r), oracle.rv(one, r)), r
+
+
+@pytest.mark.parametrize("weighted,scale,ns,groups", [(False, 16, 4480, 0), (False, 16, 4501, 24), (True, 13, 5001, 0),
+                                                       (True, 13, 5056, 33)])
+def test_long_runs_split_over_two_workspaces(B, weighted, scale, ns, groups):
+    """A run of one batch or an odd number of batches, long enough to be dealt
+    to two workspaces in equal parts: every source's dependency has the bits it has
+    in short runs of its own, with whole groups and a ragged last one."""
+    g = gg.rmat(scale, 8 if scale == 16 else 16, seed=5, weighted=weighted, max_weight=100)
+    r = gg.top_out_degree(g, 1)[0]
+    src = gg.uniform_vertices(g.n, ns, seed=3, exclude=[r])
+    print("split run", weighted, scale, ns, groups, flush=True)
+    G = dev(B, g, **({"groups": groups} if groups else {}))
+    got = G.dependencies(r, src)
+    assert np.any(got > 0)
+    short = np.concatenate([G.dependencies(r, src[i:i + 500]) for i in range(0, ns, 500)])
+    assert np.array_equal(got, short)
