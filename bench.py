@@ -690,9 +690,8 @@ def oracle_timing(args):
 def serving_width(workspace_bytes, start: int, budget: int) -> int:
     """Largest group count <= start whose workspaces (workspace_bytes(groups),
     all workers) fit in 85 % of the budget (the rest holds the queries'
-    result buffers) and that splits evenly over the 8 XCD partitions (at most
-    8 groups, or a multiple of 8): group g goes to partition g % 8, so 9
-    groups would leave one partition twice the work.  At least 1."""
+    result buffers) and that is at most 8 or a multiple of 8 (widths that
+    split evenly over a batch's partitions).  At least 1."""
     groups = max(1, start)
     while groups > 1 and (workspace_bytes(groups) > budget * 85 // 100 or (groups > 8 and groups % 8 != 0)):
         groups -= 1

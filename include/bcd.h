@@ -86,8 +86,8 @@ typedef struct bcd_config {
   int32_t engine;     /* BCD_ENGINE_* */
   int32_t groups;     /* batched engine: 64-source column groups per batch, >= 1
                          (default: the path-count rows near 64 GiB, at most 96,
-                         128 on weighted graphs, a multiple of 8 above 8 since
-                         group j runs in partition j % 8 of the 8 XCDs) */
+                         128 on weighted graphs, a multiple of 8 above 8; an
+                         even width splits evenly over the two partitions) */
   int32_t block;      /* threads per workgroup for traversal kernels: 64, 128, 256, 512
                          (default 256, 64 on weighted graphs) */
   int32_t grid_mult;  /* workgroups per compute unit for traversal kernels, >= 1 */
@@ -309,7 +309,7 @@ typedef struct bcd_server_config {
   uint64_t hbm_budget_bytes; /* device bytes for workspaces + per-query buffers; 0 = 64 GiB */
   int32_t workers;           /* concurrent batches (one stream each), >= 1; 0 = 2 */
   int32_t groups;            /* 64-source column groups per batch; 0 = graph's configured value.
-                                Above 8, a multiple of 8 keeps the 8 XCD partitions even */
+                                An even width splits evenly over the two partitions */
   int32_t queue_capacity;    /* max queries submitted and not yet polled; 0 = 4096 */
   int32_t reserved;
 } bcd_server_config;

@@ -229,7 +229,7 @@ bcd_status Workspace::ensure_batch(int G_) {
   } else {
     STCHK(dalloc(&S.msk, M_COUNT * GN));
   }
-  S.P = std::min(kMaxParts, G);
+  S.P = default_parts(G);
   S.NL = lists(S.P);
   S.H = graph->heavy;
   S.capP = ((uint64_t)GN * 16 + (uint64_t)S.P - 1) / (uint64_t)S.P;

@@ -51,7 +51,17 @@ inline int default_bottom_up(int64_t n) { return n >= (int64_t(1) << 19) ? 4 : 0
 // Top-down levels of the unweighted forward add path counts along DAG arcs
 // (1) instead of pulling them over in-arcs (0).
 constexpr int kDefaultPush = 0;
-constexpr int kMaxParts = 8;          // item-list partitions (one per XCD)
+// Item-list partitions of a workspace of G groups: two where they split
+// evenly (nearly so above 8), else one.  More partitions keep a group's masks
+// in fewer L2s, but groups are unlike (a batch's neighbouring sources are
+// alike, so one group's wide levels fall on others' empty ones), and the
+// workgroups of a partition without work wait for the launch's end.  8 / 4 / 2 /
+// 1 partitions, ms: R-MAT 20 with 1,000 sources 33.8 / 29.6 / 26.5 / 27.0, R-MAT
+// 16 with 1,000 2.65 / 2.45 / 2.35 / 2.28, exact (96 groups a batch: one list's
+// counters are contended) 35.6 / 35.2 / 35.5 / 37.2; R-MAT 20 serving in batches
+// of 3 groups: 3 / 2 / 1 partitions 272 / 325 / 270.
+constexpr int kMaxParts = 2;
+inline int default_parts(int G) { return G % 2 == 0 || G > 8 ? kMaxParts : 1; }
 constexpr int kCntStage = (kLevelChunkMax + 2) * kMaxLists;  // pinned slots for level counts
 // Vertices with more arcs than this (in- and out-arcs together) are taken by
 // a whole workgroup in the unweighted engine and by several wavefronts in the
@@ -80,10 +90,8 @@ inline int default_groups(int64_t n, bool weighted) {
   const int64_t cap = weighted ? 128 : 96;
   if (g > cap) g = cap;
   while (g > 1 && (uint64_t)g * (uint64_t)n >= (1ull << 32)) --g;
-  // group j runs in XCD partition j % 8: above 8 groups, a width that is not
-  // a multiple of 8 gives some partitions one group more than the others and
-  // every level waits for them (R-MAT 22 serving: 9-group batches 252 GTEPS,
-  // 8-group batches 301)
+  // an even width splits evenly over the partitions (default_parts), here a
+  // multiple of 8
   if (g > 8) g -= g % 8;
   return (int)g;
 }

@@ -52,9 +52,9 @@ struct BatchState {
   unsigned long long *vis;   // [G][n] reached lanes (weighted engine)
   unsigned long long *fr;    // [3][G][n] rotating round masks (weighted engine)
   // Item lists are split into P partitions (group g belongs to partition
-  // g % P); workgroup b serves partition b % P, so with P = 8 every XCD
-  // (workgroups are dealt to the 8 XCDs round-robin) walks only its own
-  // groups and their masks stay in that XCD's L2.  There are two lists per
+  // g % P); workgroup b serves partition b % P, so with P = 2 (workgroups
+  // are dealt to the 8 XCDs round-robin) four XCDs walk each half of the
+  // groups.  There are two lists per
   // partition and level: list p holds the vertices a wavefront takes alone,
   // list P + p the heavy ones (internal id < H), which a workgroup takes
   // together (unweighted engine) or several wavefronts in parts (weighted).
@@ -66,10 +66,10 @@ struct BatchState {
   int P;
   int NL;                    // lists: 2 P
   uint32_t H;                // heavy vertices: internal ids 0 .. H-1
-  uint32_t *cnt;             // [(n + 2) * 16] items per (level, list): index level * NL + l
-  uint32_t *tail;            // [4][16] lengths of the lists being filled, by level mod 4, each in a
+  uint32_t *cnt;             // [(n + 2) * kMaxLists] items per (level, list): index level * NL + l
+  uint32_t *tail;            // [4][kMaxLists] lengths of the lists being filled, by level mod 4, each in a
                              // 128-byte line of its own (see tail_at)
-  uint64_t *off;             // [(n + 2) * 16] first item of each (level, list)
+  uint64_t *off;             // [(n + 2) * kMaxLists] first item of each (level, list)
   uint32_t *tmin;            // [1] smallest over all lanes
   int32_t *tgt_of;           // [n] target index of a vertex, -1 if none
   double *res;               // [ntgt][G][64] delta of lane on target
@@ -92,8 +92,8 @@ struct BatchState {
   unsigned long long *chg;   // [3][G][n] lanes whose distance dropped, by relaxation round mod 3
   uint32_t *bq;              // [3][queue] items changed in a round, by round mod 3 (lists as of `items`)
   uint32_t *rl;              // [queue] items reached by any lane
-  uint32_t *qtail;           // [4][16] lengths of a round's queue lists, by round mod 4, a line each (qtail_at)
-  uint32_t *rtail;           // [16] lengths of the reached lists, a line each (rtail_at)
+  uint32_t *qtail;           // [4][kMaxLists] lengths of a round's queue lists, by round mod 4, a line each (qtail_at)
+  uint32_t *rtail;           // [kMaxLists] lengths of the reached lists, a line each (rtail_at)
   uint64_t capQ, capQH;      // a queue's list p: [p * capQ, (p + 1) * capQ), list P + p:
   uint64_t qhbase, qsize;    //   [qhbase + p * capQH, ...); its size
   unsigned long long *wdn;   // [G][n] lanes on whose DAG the vertex is a target or lies below one
@@ -152,7 +152,7 @@ struct Launch {
 };
 
 // ---- launchers (bcd_kernels.hip) ----
-constexpr int kMaxLists = 16;  // two per partition
+constexpr int kMaxLists = 4;  // two per partition (kMaxParts)
 struct PartTotals {
   uint64_t t[kMaxLists];  // items per list over all levels of a batch
 };
