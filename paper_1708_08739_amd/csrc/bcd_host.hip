@@ -438,6 +438,8 @@ Graph::~Graph() {
   dfree(d_pirp);
   dfree(d_picol);
   dfree(d_orig);
+  dfree(d_lrp);
+  dfree(d_lcol);
   dfree(d_arcw);
   dfree(d_iarc);
   dfree(d_iopos);
@@ -663,6 +665,14 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
   if (m > 0) {
     HIPCHK(hipMemcpy(g->d_col, col, (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(g->d_icol, icol.data(), (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice));
+  }
+  if (lds_fits(g.get())) {
+    std::vector<uint32_t> lrp(row_ptr, row_ptr + n + 1);
+    std::vector<uint16_t> lcol(col, col + m);
+    STCHK(dalloc(&g->d_lrp, (size_t)n + 1));
+    STCHK(dalloc(&g->d_lcol, (size_t)std::max<int64_t>(m, 1)));
+    HIPCHK(hipMemcpy(g->d_lrp, lrp.data(), ((size_t)n + 1) * sizeof(uint32_t), hipMemcpyHostToDevice));
+    if (m > 0) HIPCHK(hipMemcpy(g->d_lcol, lcol.data(), (size_t)m * sizeof(uint16_t), hipMemcpyHostToDevice));
   }
   // internal ids: vertices by falling total degree (a counting sort, ties by
   // the caller's id), and both CSRs renamed to them, rows kept in arc order

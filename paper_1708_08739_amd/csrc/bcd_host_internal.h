@@ -204,6 +204,8 @@ struct Graph {
   int64_t *d_pirp = nullptr;
   int32_t *d_picol = nullptr;  // unweighted
   int32_t *d_orig = nullptr;
+  uint32_t *d_lrp = nullptr;   // the CSR in 32- and 16-bit words, where lds_fits
+  uint16_t *d_lcol = nullptr;
   uint2 *d_arcw = nullptr;     // weighted, internal ids: {head, length} per CSR arc
   uint2 *d_iarc = nullptr;     // weighted: {tail, length} per transpose arc
   uint32_t *d_iopos = nullptr; // weighted: CSR position per transpose arc
