@@ -91,9 +91,10 @@ typedef struct bcd_config {
   int32_t block;      /* threads per workgroup for traversal kernels: 64, 128, 256, 512
                          (default 256, 64 on weighted graphs) */
   int32_t grid_mult;  /* workgroups per compute unit for traversal kernels, >= 1 */
-  int32_t items;      /* batched engine, unweighted forward: frontier items a
-                         wavefront takes per step, 1, 2 or 4 (64 / items lanes
-                         per item for its first arcs); 0 = default */
+  int32_t items;      /* batched engine, unweighted levels with pushed path
+                         counts: frontier items a wavefront takes per step, 1, 2
+                         or 4 (64 / items lanes per item for its first arcs);
+                         0 = default.  Pulled levels do not read it */
   int32_t bottom_up;  /* batched engine, unweighted forward: a BFS level is
                          found bottom-up (in-arcs of the unsettled (group,
                          vertex) pairs) when the level before it holds at

@@ -43,7 +43,7 @@ namespace bcd {
 
 constexpr int kCtrSlots = 8192;       // max workgroups of a traversal launch
 constexpr int kLevelChunkMax = 64;    // level launches enqueued between host checks
-constexpr int kDefaultItems = 2;      // frontier items per wavefront step, unweighted forward
+constexpr int kDefaultItems = 2;      // frontier items per wavefront step, pushed levels
 // Bottom-up threshold denominator of the unweighted forward (0: top-down
 // only).  Bottom-up levels pay on large graphs (R-MAT 20 and 22, acyclic
 // R-MAT 20: +4 to +14 %) and cost a little on small ones (R-MAT 16: -4 %).
