@@ -40,6 +40,11 @@ constexpr uint32_t kInf = 0xFFFFFFFFu;
 // Parts a heavy item's arcs are dealt in (R-MAT 18, 2,048 draws, on one box: 8
 // parts 130.5 ms, 16 131.0, 32 135.5; 8,191-vertex exact 19.27 / 19.17 / 19.5).
 constexpr uint32_t kParts = 16;
+// Light items a wavefront takes at a time, at most.  Rows are uneven, and on a
+// small graph a round waits for the block with the longest: weighted R-MAT 13
+// exact / R-MAT 18 with 2,048 draws, ms, at 4 / 8 / 16 / 32 items: 13.3 / 13.6 / 14.5 /
+// 16.1 and 101.3 / 98.6 / 98.0 / 98.5.
+constexpr int kWBlockItems = 8;
 
 // The lists of the relaxation queue being filled, and the reached lists.
 struct QueueLists {
@@ -196,7 +201,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5, 8))) v
   const uint32_t *qin = S.bq + (uint64_t)(round % 3) * S.qsize + queue_begin(S, (lv.heavy ? P : 0) + pv.p);
   const uint64_t count = lv.heavy ? (uint64_t)nh * kParts : nl;
   const uint64_t nwv = lv.nwg * NW;
-  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kWBlockItems, (count + nwv - 1) / nwv);
   for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
     const int nb = (int)min((uint64_t)B, count - b0);
     uint32_t it = 0, gb = 0, e0 = 0, ed = 0;
@@ -323,7 +328,7 @@ __global__ __launch_bounds__(BLOCK) void k_w_count(DevGraph G, BatchState S) {
   const uint32_t *rl = S.rl + queue_begin(S, l);
   const uint64_t len = *rtail_at(S, l), count = lv.heavy ? len * kParts : len;
   const uint64_t nwv = lv.nwg * NW;
-  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kWBlockItems, (count + nwv - 1) / nwv);
   for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
     const int nb = (int)min((uint64_t)B, count - b0);
     uint32_t it = 0, gb = 0, f0 = 0, fd = 0, od = 0;
@@ -430,7 +435,7 @@ __global__ __launch_bounds__(BLOCK) void k_w_sigma(DevGraph G, BatchState S, int
   const uint64_t base = S.off[lrow + (lv.heavy ? P : 0) + pv.p];
   const uint64_t count = lv.heavy ? (uint64_t)nh * kParts : nl;
   const uint64_t nwv = lv.nwg * NW;
-  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kWBlockItems, (count + nwv - 1) / nwv);
   for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
     const int nb = (int)min((uint64_t)B, count - b0);
     uint32_t it = 0, gb = 0, e0 = 0, ed = 0;
@@ -565,7 +570,7 @@ __global__ __launch_bounds__(BLOCK) void k_w_bwd(DevGraph G, BatchState S, int l
   const int l = (lv.heavy ? P : 0) + pv.p;
   const uint64_t base = S.off[lrow + l], count = S.cnt[lrow + l];
   const uint64_t nwv = lv.nwg * NW;
-  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kWBlockItems, (count + nwv - 1) / nwv);
   for (uint64_t b0 = (lv.wg * NW + (uint64_t)wv) * B; b0 < count; b0 += nwv * B) {
     const int nb = (int)min((uint64_t)B, count - b0);
     uint32_t it = 0, gb = 0, e0 = 0, ed = 0;
