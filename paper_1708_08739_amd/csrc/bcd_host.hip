@@ -286,20 +286,14 @@ void Workspace::stage_sources(const int32_t *src, int k) {
     h_masks0[i] = 1ull << (i % kLanes);
   }
   staged = k;
-  stage_sources_dest(k);
-}
-
-// Level-0 slot of every staged item in its list of its group's partition.
-void Workspace::stage_sources_dest(int k) {
+  // the place of every staged item in its list (level0_slot)
   uint32_t fill[kMaxLists] = {0};
   BatchState T = S;
   T.P = batch_parts(k);
   T.NL = lists(T.P);
   for (int i = 0; i < k; ++i) {
-    const int p = (i / kLanes) % T.P;
-    const uint64_t v = h_items0[i] - (uint64_t)(i / kLanes) * (uint64_t)n;
-    const int l = v < T.H ? T.P + p : p;
-    h_dest0[i] = (uint32_t)(list_begin(T, l) + fill[l]++);
+    const uint32_t g = (uint32_t)(i / kLanes);
+    h_dest0[i] = fill[list_of(T, g, h_items0[i] - g * (uint32_t)n)]++;
   }
   for (int l = 0; l < kMaxLists; ++l) h_cnt0[l] = fill[l];
 }

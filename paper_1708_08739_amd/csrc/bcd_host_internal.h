@@ -165,7 +165,6 @@ struct Workspace {
   // Stage a batch: lane i of the batch (column group i / 64, lane i % 64)
   // runs source vertex src[i]; vertices must be distinct within a group.
   void stage_sources(const int32_t *src, int k);
-  void stage_sources_dest(int k);
   static int lists(int P) { return 2 * P; }  // item lists of a batch on P partitions: light, heavy
   // Partitions a batch of k staged sources uses: its groups are 0..ceil(k/64)-1
   // and group g belongs to partition g % P, so a batch of fewer groups than

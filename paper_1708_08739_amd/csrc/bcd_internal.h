@@ -183,6 +183,16 @@ __host__ __device__ inline uint64_t list_begin(const BatchState &S, int l) {
 __host__ __device__ inline uint64_t list_end(const BatchState &S, int l) {
   return list_begin(S, l) + (l < S.P ? S.capP : S.capH);
 }
+// List of vertex v (internal id) of group g, and the level-0 slot of a staged
+// item that is the at-th of its list.  The slot is 64-bit: a heavy list begins
+// behind all light ones, which grow to 64 items a (group, vertex), past 2^32.
+__host__ __device__ inline int list_of(const BatchState &S, uint32_t g, uint32_t v) {
+  return (int)(g % (uint32_t)S.P) + (v < S.H ? S.P : 0);
+}
+__host__ __device__ inline uint64_t level0_slot(const BatchState &S, uint32_t item, uint32_t at) {
+  const uint32_t g = item / (uint32_t)S.n;
+  return list_begin(S, list_of(S, g, item - g * (uint32_t)S.n)) + at;
+}
 hipError_t launch_batch_init(const BatchState &S, const uint32_t *items0, const unsigned long long *masks0,
                              const uint32_t *dest0, int k, hipStream_t st);
 hipError_t launch_fwd_level(const DevGraph &G, const BatchState &S, int level, Launch L, hipStream_t st);

@@ -46,7 +46,7 @@ __global__ void k_batch_init(BatchState S, const uint32_t *items0, const ull *ma
     S.msk[M_SEEN * GN + it] = m;
     const uint32_t g = it / (uint32_t)S.n;
     if (S.tgt_of[it - g * (uint32_t)S.n] >= 0) atomicOr(&S.ovl[S.G + g], m);
-    S.items[dest0[i]] = it;
+    S.items[level0_slot(S, it, dest0[i])] = it;
     for (int b = 0; b < kLanes; ++b)
       if ((m >> b) & 1ull) {
         if (S.narrow) counts<uint32_t>(S)[(size_t)it * kLanes + b] = 1u;

@@ -337,6 +337,7 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
   HIPCHK(hipMemcpyAsync(ws->d_items0, ws->h_items0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(ws->d_masks0, ws->h_masks0, (size_t)k * sizeof(unsigned long long), hipMemcpyHostToDevice,
                         st));
+  HIPCHK(hipMemcpyAsync(ws->d_dest0, ws->h_dest0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
   const int push = g->config().push;
   if (push && !ws->sig_zero) {
     // counts pulled by an earlier batch on this workspace: clear them all once
@@ -357,9 +358,6 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
     S.keep_all = full ? 1 : 0;
     const int NL = S.NL;
     const Launch L = g->launch_parts(S.P, S.gused);
-    // level-0 placement depends on the partition sizes (they change when the list grows)
-    ws->stage_sources_dest(k);
-    HIPCHK(hipMemcpyAsync(ws->d_dest0, ws->h_dest0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     uint32_t *hc = ws->h_cnt;
     uint32_t *hc0 = hc + kCntStage;
     for (int l = 0; l < NL; ++l) hc0[l] = ws->h_cnt0[l];

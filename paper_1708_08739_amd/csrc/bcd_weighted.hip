@@ -68,10 +68,9 @@ __global__ void k_w_init(BatchState S, const uint32_t *items0, const ull *masks0
     const uint32_t it = items0[i];
     const ull m = masks0[i];
     const uint32_t g = it / (uint32_t)S.n, v = it - g * (uint32_t)S.n;
-    const int l = (int)(g % (uint32_t)S.P) + (v < S.H ? S.P : 0);
-    const uint64_t q = queue_begin(S, l) + (dest0[i] - list_begin(S, l));
+    const uint64_t q = queue_begin(S, list_of(S, g, v)) + dest0[i];
     S.fr[it] = m;       // topological round 0
-    S.items[dest0[i]] = it;
+    S.items[level0_slot(S, it, dest0[i])] = it;
     S.chg[it] = m;      // relaxation round 0: the sources changed
     S.bq[q] = it;
     S.rl[q] = it;
@@ -832,6 +831,7 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
   HIPCHK(hipMemcpyAsync(ws->d_items0, ws->h_items0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(ws->d_masks0, ws->h_masks0, (size_t)k * sizeof(unsigned long long), hipMemcpyHostToDevice,
                         st));
+  HIPCHK(hipMemcpyAsync(ws->d_dest0, ws->h_dest0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
   for (int attempt = 0;; ++attempt) {
     BatchState S = ws->S;
     if (!ex) S.dout = nullptr;
@@ -839,8 +839,6 @@ static bcd_status run_one_wbatch(Graph *g, Workspace *ws, int k, int ntgt, bool 
     S.NL = ws->lists(S.P);
     const int NL = S.NL;
     const Launch L = g->launch_parts(S.P, (k + kLanes - 1) / kLanes);
-    ws->stage_sources_dest(k);
-    HIPCHK(hipMemcpyAsync(ws->d_dest0, ws->h_dest0, (size_t)k * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     uint32_t *hc = ws->h_cnt;
     uint32_t *hc0 = hc + kCntStage;
     uint32_t *hm = reinterpret_cast<uint32_t *>(ws->h_misc);

@@ -1,0 +1,54 @@
+// C entries to host rules of libbcd that need no GPU, for test_host_rules.py.
+#include <cstring>
+
+#include "../paper_1708_08739_amd/csrc/bcd_host_internal.h"
+
+using namespace bcd;
+
+extern "C" {
+
+// Level-0 slots of sources 0 .. k-1 (internal ids = vertex ids) staged on a
+// workspace of G groups and P partitions whose light lists hold capP items
+// each; bounds[2 i], bounds[2 i + 1]: the region of source i's list.
+void staged_slots(int64_t n, int G, int P, uint64_t capP, uint32_t H, int k, uint64_t *slot, uint64_t *bounds) {
+  Graph g;
+  g.n = n;
+  g.rank.resize((size_t)n);
+  for (int64_t v = 0; v < n; ++v) g.rank[(size_t)v] = (int32_t)v;
+  Workspace ws;
+  ws.graph = &g;
+  ws.n = n;
+  ws.G = G;
+  std::memset(&ws.S, 0, sizeof(ws.S));
+  BatchState &S = ws.S;
+  S.n = n;
+  S.G = G;
+  S.P = P;
+  S.NL = Workspace::lists(P);
+  S.H = H;
+  S.capP = capP;
+  S.hbase = capP * (uint64_t)P;
+  S.capH = (uint64_t)((G + P - 1) / P) * H * kLanes;
+  std::vector<uint32_t> items((size_t)k), dest((size_t)k);
+  std::vector<unsigned long long> masks((size_t)k);
+  std::vector<int32_t> src((size_t)k);
+  for (int i = 0; i < k; ++i) src[(size_t)i] = i;
+  ws.h_items0 = items.data();
+  ws.h_masks0 = masks.data();
+  ws.h_dest0 = dest.data();
+  ws.stage_sources(src.data(), k);
+  BatchState T = S;
+  T.P = ws.batch_parts(k);
+  T.NL = Workspace::lists(T.P);
+  for (int i = 0; i < k; ++i) {
+    const int l = list_of(T, (uint32_t)(i / kLanes), (uint32_t)i);
+    slot[i] = level0_slot(T, items[(size_t)i], dest[(size_t)i]);
+    bounds[2 * i] = list_begin(T, l);
+    bounds[2 * i + 1] = list_end(T, l);
+  }
+  ws.h_items0 = nullptr;
+  ws.h_masks0 = nullptr;
+  ws.h_dest0 = nullptr;
+}
+
+}  // extern "C"

@@ -1,0 +1,44 @@
+"""Host rules of the library that need no GPU: sizes, placements and launch
+shapes, through small C entries compiled against its internal headers."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1708_08739_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if not os.path.exists(build.LIB):
+        build.build()
+    out = str(tmp_path_factory.mktemp("rules") / "librules.so")
+    libdir = os.path.dirname(build.LIB)
+    subprocess.run([build.HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared",
+                    "-x", "hip", os.path.join(HERE, "host_rules.cpp"), "-o", out, "-L", libdir, "-l:libbcd.so",
+                    "-Wl,-rpath," + libdir], check=True)
+    return C.CDLL(out)
+
+
+def _arr(a):
+    return C.c_void_p(a.ctypes.data)
+
+
+@pytest.mark.parametrize("n,G,P,cap", [(1 << 20, 64, 2, (1 << 31) + 64 * 64), (1000, 3, 1, 48000), (1000, 4, 2, 32000),
+                                       (1 << 20, 63, 1, 1 << 32)])
+@pytest.mark.parametrize("k", [1, 64, 65, 192])
+def test_level0_slots_stay_in_their_lists(rules, n, G, P, cap, k):
+    """Staged sources, heavy ones among them, get distinct slots of their own
+    list's region, also where a heavy list begins past 2^32 items."""
+    slot = np.zeros(k, dtype=np.uint64)
+    bounds = np.zeros((k, 2), dtype=np.uint64)
+    rules.staged_slots(C.c_int64(n), G, P, C.c_uint64(cap), C.c_uint32(3), k, _arr(slot), _arr(bounds))
+    assert np.all(slot >= bounds[:, 0]) and np.all(slot < bounds[:, 1])
+    assert np.unique(slot).size == k
+    for b in np.unique(bounds[:, 0]):  # packed from the list's beginning
+        mine = np.sort(slot[bounds[:, 0] == b])
+        assert np.array_equal(mine, b + np.arange(mine.size, dtype=np.uint64))
