@@ -71,7 +71,8 @@ typedef struct bcd_stats {
   uint64_t dag_arcs;        /* sum over passes of a_s = shortest-path-DAG arcs */
   double t_rv_s;            /* seconds spent finding RV(r) (device BFS + transfer) */
   double t_bc_s;            /* seconds from the first pass enqueued to the result on the host */
-  int32_t batch_width;      /* sources per batch (64 * groups), 1 for the plain engine */
+  int32_t batch_width;      /* sources per batch: 64 * groups, less where a long run is dealt in
+                               equal batches to two workspaces, 1 for the plain engine */
   int32_t ran_exact;        /* sampled calls: 1 if T >= |RV| made it run the exact sum */
 } bcd_stats;
 

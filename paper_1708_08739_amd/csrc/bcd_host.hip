@@ -501,12 +501,21 @@ void Graph::trim_pool() {
   // destroyed here, outside the lock
 }
 
-std::unique_ptr<Workspace> Graph::acquire() {
+std::unique_ptr<Workspace> Graph::acquire(int lo, int hi) {
   {
     std::lock_guard<std::mutex> lk(pool_mu);
+    auto groups = [](const std::unique_ptr<Workspace> &w) { return w->batch_ready ? w->G : 0; };
+    auto better = [&](int a, int b) {
+      if (lo == 0) return a > b;
+      const int ra = a > hi ? 0 : a >= lo ? 2 : 1, rb = b > hi ? 0 : b >= lo ? 2 : 1;
+      return ra != rb ? ra > rb : ra == 1 ? a > b : a < b;
+    };
     if (!pool.empty()) {
-      std::unique_ptr<Workspace> w = std::move(pool.back());
-      pool.pop_back();
+      size_t best = pool.size() - 1;
+      for (size_t i = best; i-- > 0;)
+        if (better(groups(pool[i]), groups(pool[best]))) best = i;
+      std::unique_ptr<Workspace> w = std::move(pool[best]);
+      pool.erase(pool.begin() + (std::ptrdiff_t)best);
       return w;
     }
   }

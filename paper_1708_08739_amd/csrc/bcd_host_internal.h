@@ -231,7 +231,10 @@ struct Graph {
   Launch launch() const;
   Launch launch_parts(int P, int groups) const;  // grid a multiple of P
   bcd_config config() const;
-  std::unique_ptr<Workspace> acquire();
+  // A pooled workspace, else a new one: the widest (a call's own), or, for the
+  // second of a run, the narrowest of lo .. hi groups, else the widest below lo,
+  // else the narrowest above hi (to be rebuilt).
+  std::unique_ptr<Workspace> acquire(int lo = 0, int hi = INT32_MAX);
   void release(std::unique_ptr<Workspace> w);
   void trim_pool();  // free the device memory of idle pooled workspaces
   void add_profile(int kind, int64_t launches, double ms, const uint64_t *c3, double alg_bytes,
@@ -245,6 +248,7 @@ struct Lease {
   Graph *g;
   std::unique_ptr<Workspace> w;
   explicit Lease(Graph *g_) : g(g_), w(g_->acquire()) {}
+  Lease(Graph *g_, int lo, int hi) : g(g_), w(g_->acquire(lo, hi)) {}
   ~Lease() { g->release(std::move(w)); }
   Workspace *operator->() { return w.get(); }
   bool ok() const { return (bool)w; }
@@ -311,13 +315,16 @@ struct ProfAcc {
 // Batches b = first, first + stride, ... of one run on workspace `ws`
 // (ws's own stream; results to their own positions).
 using StripeFn = std::function<bcd_status(Workspace *ws, size_t first, size_t stride, ProfAcc &prof, bool &ovf)>;
-// Runs `stripe` over all batches; when the run has more than one batch and a
-// second workspace can be had (`prepare` readies it), every other batch goes
-// to that workspace on a helper thread.  The second workspace's counters are
-// added to `tot`.
+// Readies a workspace for batches of `groups` column groups.
+using PrepareFn = std::function<bcd_status(Workspace *ws, int groups)>;
 size_t pipelined_batch(const Graph *g, size_t ns, size_t width);
-bcd_status run_pipelined(Graph *g, Workspace *ws, size_t nbatches, const std::function<bcd_status(Workspace *)> &prepare,
-                         const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot);
+// Runs `stripe` over the batches of `per` sources each; when the run has more
+// than one and a second workspace can be had (`prepare` readies it, as wide as
+// such a batch), every other batch goes to that workspace on a helper thread,
+// else whole batches run on ws.  The second workspace's counters are added to
+// `tot`; *width receives the sources per batch that ran.
+bcd_status run_pipelined(Graph *g, Workspace *ws, size_t ns, size_t per, const PrepareFn &prepare,
+                         const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot, int32_t *width);
 
 // Query layer (bcd_query.hip).
 bcd_status reach_set(Graph *g, Workspace *ws, int32_t root, bool reverse, std::vector<uint32_t> &bits,

@@ -560,8 +560,10 @@ static bcd_status run_batch_stripe(Graph *g, Workspace *ws, const std::vector<in
 
 // A second workspace runs every other batch on its own stream from a helper
 // thread, so one batch's host steps (result copy, staging, the level-count
-// checks) and its small tail levels overlap the other's kernels.  It is taken
-// from the graph's pool if one is there with the same width, else allocated
+// checks) and its small tail levels overlap the other's kernels.  It holds the
+// groups of the batches it is dealt, not the configured width (an (eps, delta)
+// estimate on R-MAT 18, about ten of 96 groups: 37 GB held in all, 65 with two full
+// ones, 33 with one).  It is taken from the graph's pool if one of at least that width is there, else allocated
 // only when HBM keeps kPipelineHeadroom free beside it (the pair then stays
 // pooled with the graph; a server releases idle pooled workspaces).
 constexpr uint64_t kPipelineHeadroom = 16ull << 30;
@@ -596,20 +598,24 @@ size_t pipelined_batch(const Graph *g, size_t ns, size_t width) {
   return (groups + nb - 1) / nb * kLanes;
 }
 
-bcd_status run_pipelined(Graph *g, Workspace *ws, size_t nbatches, const std::function<bcd_status(Workspace *)> &prepare,
-                         const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot) {
+bcd_status run_pipelined(Graph *g, Workspace *ws, size_t ns, size_t per, const PrepareFn &prepare,
+                         const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot, int32_t *width) {
   std::unique_ptr<Lease> ls2;
   Workspace *ws2 = nullptr;
-  if (nbatches > 1) {
-    ls2.reset(new (std::nothrow) Lease(g));
-    bool room = ls2 && ls2->ok() && (*ls2)->batch_ready && (*ls2)->G == ws->G &&
+  *width = (int32_t)((size_t)ws->G * kLanes);
+  if (ns > per) {
+    int share = (int)((per + kLanes - 1) / kLanes);
+    ls2.reset(new (std::nothrow) Lease(g, share, ws->G));
+    bool room = ls2 && ls2->ok() && (*ls2)->batch_ready && (*ls2)->G >= share && (*ls2)->G <= ws->G &&
                 (!g->weighted || (*ls2)->weighted_ready);
-    if (!room && ls2 && ls2->ok()) {
+    if (room) {
+      share = (*ls2)->G;
+    } else if (ls2 && ls2->ok()) {
       size_t free_b = 0, total_b = 0;
       room = hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
-             (uint64_t)free_b >= batch_workspace_bytes(g, ws->G) + kPipelineHeadroom;
+             (uint64_t)free_b >= batch_workspace_bytes(g, share) + kPipelineHeadroom;
     }
-    if (room && (*ls2)->init_common(g) == BCD_OK && prepare(ls2->w.get()) == BCD_OK && (*ls2)->G == ws->G)
+    if (room && (*ls2)->init_common(g) == BCD_OK && prepare(ls2->w.get(), share) == BCD_OK && (*ls2)->G == share)
       ws2 = ls2->w.get();
     else
       (void)hipGetLastError();  // run on one workspace
@@ -652,6 +658,7 @@ bcd_status run_pipelined(Graph *g, Workspace *ws, size_t nbatches, const std::fu
       uint64_t t2[C_COUNT] = {0};
       STCHK(collect_counters(ws2, t2, ws2->S.acc));
       for (int j = 0; j < C_COUNT; ++j) tot[j] += t2[j];
+      *width = (int32_t)per;
       return BCD_OK;
     }
   }
@@ -668,7 +675,7 @@ static bcd_status run_batched(Graph *g, Workspace *ws, const std::vector<int32_t
   const size_t ns = src.size();
   out.dep.assign(ns * (size_t)std::max(ntgt, 0), 0.0);
   if (want_counters) out.counters.assign(ns * 3, 0);
-  out.width = want_counters ? 1 : (int32_t)G64;
+  out.width = 1;
   ProfAcc prof;
   bool ovf = false;
   uint64_t tot[C_COUNT] = {0};
@@ -676,14 +683,14 @@ static bcd_status run_batched(Graph *g, Workspace *ws, const std::vector<int32_t
   STCHK(source_order(g, ws, src, ord));
   if (!want_counters) {
     const size_t per = pipelined_batch(g, ns, G64);
-    auto prepare = [&](Workspace *w) -> bcd_status {
-      STCHK(w->ensure_batch(cfg.groups));
-      return w->ensure_res((size_t)std::max(ntgt, 1) * G64);
+    auto prepare = [&](Workspace *w, int groups) -> bcd_status {
+      STCHK(w->ensure_batch(groups));
+      return w->ensure_res((size_t)std::max(ntgt, 1) * (size_t)groups * kLanes);
     };
     auto stripe = [&](Workspace *w, size_t first, size_t stride, ProfAcc &p, bool &o) -> bcd_status {
       return run_batch_stripe(g, w, src, ord, tgt, first, stride, per, out.dep, p, o);
     };
-    STCHK(run_pipelined(g, ws, (ns + per - 1) / per, prepare, stripe, prof, ovf, tot));
+    STCHK(run_pipelined(g, ws, ns, per, prepare, stripe, prof, ovf, tot, &out.width));
   }
   // counters per source need one source per batch
   TargetMap tm;

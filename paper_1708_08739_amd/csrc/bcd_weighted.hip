@@ -991,7 +991,7 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
   // the plain engine on a weighted graph runs one source per batch
   const bool one = want_counters || cfg.engine == BCD_ENGINE_PLAIN;
   const size_t two = one ? 1 : pipelined_batch(g, ns, G64);
-  out.width = (int32_t)(one ? 1 : G64);
+  out.width = 1;
   std::vector<uint32_t> ord;
   STCHK(source_order(g, ws, src, ord));
   ProfAcc prof;
@@ -1002,7 +1002,8 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
   auto stripe = [&](Workspace *w, size_t first, size_t stride, ProfAcc &p, bool &o) -> bcd_status {
     TargetMap tm;
     STCHK(tm.install(w, tgt));
-    const size_t per = one ? 1 : (stride == 1 ? G64 : two);  // alone: whole batches
+    const size_t w64 = (size_t)w->G * kLanes;
+    const size_t per = one ? 1 : (stride == 1 ? w64 : two);  // alone: whole batches
     std::vector<int32_t> bsrc(per);
     for (size_t b0 = first * per; b0 < ns; b0 += stride * per) {
       const int k = (int)std::min(per, ns - b0);
@@ -1010,7 +1011,7 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
       w->stage_sources(bsrc.data(), k);
       STCHK(run_one_wbatch(g, w, k, ntgt, false, nullptr, &p, &o));
       for (int i = 0; i < k; ++i)
-        for (int t = 0; t < ntgt; ++t) out.dep[(size_t)ord[b0 + i] * ntgt + t] = w->h_res[(size_t)t * G64 + i];
+        for (int t = 0; t < ntgt; ++t) out.dep[(size_t)ord[b0 + i] * ntgt + t] = w->h_res[(size_t)t * w64 + i];
       if (want_counters) {
         uint64_t c[C_COUNT];
         STCHK(wcounters(w, c));
@@ -1025,12 +1026,12 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
   if (one) {
     STCHK(stripe(ws, 0, 1, prof, ovf));
   } else {
-    auto prepare = [&](Workspace *w) -> bcd_status {
-      STCHK(w->ensure_batch(cfg.groups));
+    auto prepare = [&](Workspace *w, int groups) -> bcd_status {
+      STCHK(w->ensure_batch(groups));
       STCHK(w->ensure_weighted());
-      return w->ensure_res((size_t)std::max(ntgt, 1) * G64);
+      return w->ensure_res((size_t)std::max(ntgt, 1) * (size_t)groups * kLanes);
     };
-    STCHK(run_pipelined(g, ws, (ns + two - 1) / two, prepare, stripe, prof, ovf, tot));
+    STCHK(run_pipelined(g, ws, ns, two, prepare, stripe, prof, ovf, tot, &out.width));
     uint64_t t1[C_COUNT];
     STCHK(wcounters(ws, t1));
     for (int j = 0; j < C_COUNT; ++j) tot[j] += t1[j];

@@ -51,4 +51,26 @@ void staged_slots(int64_t n, int G, int P, uint64_t capP, uint32_t H, int k, uin
   ws.h_dest0 = nullptr;
 }
 
+// Sources per batch of a run of ns sources (pipelined_batch).
+uint64_t sources_per_batch(int64_t m, int weighted, uint64_t ns, uint64_t width) {
+  Graph g;
+  g.m = m;
+  g.weighted = weighted != 0;
+  return pipelined_batch(&g, ns, width);
+}
+
+// Width of the pooled workspace a lease takes: pool[0 .. k-1] are the widths of
+// the idle ones; 0 = a new one.  lo = 0: a call's own, else a run's second.
+int leased_width(const int *pool, int k, int lo, int hi) {
+  Graph g;
+  for (int i = 0; i < k; ++i) {
+    std::unique_ptr<Workspace> w(new Workspace());
+    w->batch_ready = true;
+    w->G = pool[i];
+    g.release(std::move(w));
+  }
+  std::unique_ptr<Workspace> w = lo == 0 ? g.acquire() : g.acquire(lo, hi);
+  return w->batch_ready ? w->G : 0;
+}
+
 }  // extern "C"

@@ -1074,3 +1074,45 @@ def test_long_runs_split_over_two_workspaces(B, weighted, scale, ns, groups):
     assert np.any(got > 0)
     short = np.concatenate([G.dependencies(r, src[i:i + 500]) for i in range(0, ns, 500)])
     assert np.array_equal(got, short)
+
+
+def free_bytes():
+    """Free device memory, from the HIP runtime the library itself loaded."""
+    import ctypes as C
+    hip = C.CDLL(next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln))
+    free_b, total_b = C.c_size_t(), C.c_size_t()
+    assert hip.hipMemGetInfo(C.byref(free_b), C.byref(total_b)) == 0
+    return free_b.value
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_second_workspace_is_as_wide_as_its_batches(B, weighted):
+    """A run of a few groups dealt to two workspaces holds a second one of its
+    share of them, not of the configured width, says so in batch_width, and
+    gives the bits of short runs; a longer run on the same handle widens it."""
+    scale = 14 if weighted else 17
+    g = gg.rmat(scale, 16, seed=6, weighted=weighted, max_weight=100)
+    r = gg.top_out_degree(g, 1)[0]
+    src = gg.uniform_vertices(g.n, 4000, seed=4, exclude=[r])
+    one = dev(B, g)
+    ns = 3000 if weighted else 1800  # times arcs: 1.3 x 2^29 weighted, 1.6 x 2^31
+
+    def held(G, k):
+        before = free_bytes()
+        dep = G.dependencies(r, src[:k])
+        return dep, before - free_bytes()
+    _, alone = held(one, 64)
+    G = dev(B, g)
+    dep, both = held(G, ns)
+    width = 64 * G.config().groups
+    share = -(-ns // 64) / 2 / G.config().groups
+    print("held", weighted, alone, both, share, flush=True)
+    assert both < alone * (1.1 + share)
+    assert np.array_equal(dep, np.concatenate([one.dependencies(r, src[i:i + 600]) for i in range(0, ns, 600)]))
+    bc, st = G.bc_sampled(r, T=ns, seed=2, flags=B.BCD_NO_EXACT_FALLBACK)
+    groups = -(-st["distinct_sources"] // 64)
+    assert st["batch_width"] == 64 * -(-groups // 2) < width
+    assert one.bc_sampled(r, T=64, seed=2, flags=B.BCD_NO_EXACT_FALLBACK)[1]["batch_width"] == width
+    dep = G.dependencies(r, src)
+    assert np.array_equal(dep[:ns], G.dependencies(r, src[:ns]))
+    assert np.array_equal(dep, np.concatenate([one.dependencies(r, src[i:i + 600]) for i in range(0, 4000, 600)]))

@@ -42,3 +42,38 @@ def test_level0_slots_stay_in_their_lists(rules, n, G, P, cap, k):
     for b in np.unique(bounds[:, 0]):  # packed from the list's beginning
         mine = np.sort(slot[bounds[:, 0] == b])
         assert np.array_equal(mine, b + np.arange(mine.size, dtype=np.uint64))
+
+
+def test_long_runs_split_from_their_threshold_on(rules):
+    """Runs whose sources times arcs reach 2^31 (2^29 weighted) are dealt in an
+    even number of equal batches of whole groups; shorter ones, and runs of one
+    group, keep the configured width."""
+    per = rules.sources_per_batch
+    per.argtypes, per.restype = [C.c_int64, C.c_int, C.c_uint64, C.c_uint64], C.c_uint64
+    for weighted, bit in ((0, 31), (1, 29)):
+        m = 1 << 19
+        ns = 1 << (bit - 19)
+        width = 64 * 96
+        assert per(m, weighted, ns - 1, width) == width
+        assert per(m - 1, weighted, ns, width) == width
+        groups = ns // 64
+        assert per(m, weighted, ns, width) == 64 * -(-groups // 2)
+        assert per(1 << 40, weighted, 64, width) == width
+        for n in (65, 200, 6145, 20000, 33358):
+            p = per(1 << 26, weighted, n, width)
+            batches = -(-n // p)
+            assert p % 64 == 0 and p <= width
+            assert n <= p or batches % 2 == 0 or -(-n // 64) % 2 == 1, (n, p)
+
+
+def test_workspace_of_a_lease(rules):
+    """A call takes the widest idle workspace, a run's second one the narrowest
+    that holds its share, else one to be rebuilt."""
+    def take(pool, lo=0, hi=0):
+        return rules.leased_width(_arr(np.array(pool, dtype=np.int32)), len(pool), lo, hi)
+    assert take([]) == 0
+    assert take([96, 9]) == 96 and take([9, 96]) == 96
+    assert take([96, 9, 12], 9, 96) == 9 and take([96, 9, 12], 10, 96) == 12
+    assert take([96, 9, 12], 13, 96) == 96
+    assert take([4, 9], 13, 96) == 9
+    assert take([128, 100], 13, 96) == 100 and take([128, 4], 13, 96) == 4
