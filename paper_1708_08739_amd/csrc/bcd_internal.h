@@ -229,6 +229,13 @@ struct ReachCtr {
 // roots[0 .. k-1] on the device when roots is not null).
 hipError_t launch_reach_init(uint32_t *bitmap, int64_t words, int32_t *q, ReachCtr ctr, int32_t root,
                              const int32_t *roots, int k, hipStream_t st);
+// Launch of a reachability level: workgroups of 256 threads for as many
+// wavefronts as the configured shape L has, at most 1,024 workgroups.
+constexpr int kReachLevelBlock = 256;
+inline int reach_level_grid(const Launch &L) {
+  const int64_t wg = (int64_t)L.grid * L.block / kReachLevelBlock;
+  return (int)(wg < 1 ? 1 : wg > 1024 ? 1024 : wg);
+}
 // One level: rp / col is the CSR traversed, rpo / colo the other direction; a
 // level whose frontier has at least bu_arcs arcs goes bottom-up.
 hipError_t launch_reach_level(const int64_t *rp, const int32_t *col, const int64_t *rpo, const int32_t *colo,

@@ -1418,11 +1418,12 @@ static __device__ __forceinline__ void queue_append(uint32_t *stg, int &nst, uin
 // (about 10 ns each) made 390 and 320 us of the two large levels of R-MAT 20;
 // with 1,024 workgroups adding once each they take 61 and 55.
 constexpr int kReachAlone = 16;
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_reach_level(const int64_t *rp, const int32_t *col, const int64_t *rpo,
-                                                       const int32_t *colo, uint32_t *bitmap, int32_t *q0, int32_t *q1,
-                                                       ReachCtr ctr, uint8_t *lev, int level, int64_t n,
-                                                       uint64_t bu_arcs) {
+__global__ __launch_bounds__(kReachLevelBlock) void k_reach_level(const int64_t *rp, const int32_t *col,
+                                                                  const int64_t *rpo, const int32_t *colo,
+                                                                  uint32_t *bitmap, int32_t *q0, int32_t *q1,
+                                                                  ReachCtr ctr, uint8_t *lev, int level, int64_t n,
+                                                                  uint64_t bu_arcs) {
+  constexpr int BLOCK = kReachLevelBlock;
   const uint64_t tid = (uint64_t)blockIdx.x * BLOCK + threadIdx.x;
   const uint32_t count = *ctr.len(level);
   if (tid == 0) {
@@ -1724,9 +1725,11 @@ hipError_t launch_reach_level(const int64_t *rp, const int32_t *col, const int64
                               int64_t n, uint64_t bu_arcs, Launch L, hipStream_t st) {
   // a part of the resident workgroups: each adds to the same two counters at
   // its end, one after the other (RV(r) of R-MAT 20, whole call: 512 workgroups
-  // 0.76 ms, 1,024 0.74, 2,048 0.78, 4,096 0.87)
-  L.grid = std::min(L.grid, 1024);
-  DISPATCH_BLOCK(L, k_reach_level, rp, col, rpo, colo, bitmap, q0, q1, ctr, lev, level, n, bu_arcs);
+  // 0.76 ms, 1,024 0.74, 2,048 0.78, 4,096 0.87).  Not the configured workgroup:
+  // 1,024 of 64 threads (the weighted default) are a wavefront per SIMD
+  // (R-MAT 20, edge factor 8, 64-thread workgroups configured: 0.51 ms, 0.43 as here)
+  hipLaunchKernelGGL(k_reach_level, dim3(reach_level_grid(L)), dim3(kReachLevelBlock), 0, st, rp, col, rpo, colo, bitmap,
+                     q0, q1, ctr, lev, level, n, bu_arcs);
   return hipGetLastError();
 }
 

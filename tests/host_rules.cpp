@@ -73,4 +73,12 @@ int leased_width(const int *pool, int k, int lo, int hi) {
   return w->batch_ready ? w->G : 0;
 }
 
+// Workgroups of 256 threads of a reachability level on a configured shape.
+int reach_grid(int block, int grid) {
+  Launch L;
+  L.block = block;
+  L.grid = grid;
+  return reach_level_grid(L);
+}
+
 }  // extern "C"

@@ -77,3 +77,14 @@ def test_workspace_of_a_lease(rules):
     assert take([96, 9, 12], 13, 96) == 96
     assert take([4, 9], 13, 96) == 9
     assert take([128, 100], 13, 96) == 100 and take([128, 4], 13, 96) == 4
+
+
+@pytest.mark.parametrize("block", [64, 128, 256, 512])
+def test_reach_levels_keep_their_wavefronts_at_every_block_size(rules, block):
+    """A reachability level runs the configured shape's wavefronts, 4,096 at
+    most, whatever the workgroup size of the other kernels."""
+    for mult in (1, 8, 32):
+        grid = min(8192, 256 * mult)
+        waves = rules.reach_grid(block, grid) * 4
+        assert waves == min(4096, grid * block // 64), (block, mult)
+    assert rules.reach_grid(64, 1) == 1
