@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/bcd.h"
@@ -231,9 +232,13 @@ __global__ __launch_bounds__(BLOCK) void k_lds_pass(uint32_t n, const uint32_t *
 // graph for the forward reach of r) in one workgroup: visited bits and the
 // BFS queue live in LDS, levels are separated by barriers, and the visited
 // bitmap is written out at the end.  For n < 2^16.  A lane per frontier vertex
-// takes its first kAlone arcs, kAtOnce at a time; the rest of a longer row is
+// takes its first arcs, kAtOnce at a time; the rest of a few longer rows is
 // taken by the whole wavefront: a hub's row walked by one thread made up most of
-// the time (R-MAT of 4,096 vertices, RV(r) 200 us, as here 60).
+// the time (R-MAT of 4,096 vertices, RV(r) 200 us, as here 58).  A level of a deep
+// graph is narrow and bound by its instructions, so short rows take short steps,
+// and a level ends in one barrier (a cycle, us a level: 1.04 with steps of eight
+// and two barriers, 0.57 as here; a 180 x 180 grid both ways 434 / 377 us; many rows
+// of 64 arcs, 41 us a level row by row, 7.6 as here).
 constexpr int kReachBlock = 1024;
 constexpr int kAlone = 32;
 constexpr int kAtOnce = 8;
@@ -247,7 +252,7 @@ __global__ __launch_bounds__(kReachBlock) void k_lds_reach(const int64_t *rp, co
   const uint32_t words = ((uint32_t)n + 31) / 32;
   uint32_t *vis = reinterpret_cast<uint32_t *>(smem);
   uint16_t *queue = reinterpret_cast<uint16_t *>(smem + 4 * (size_t)words);
-  __shared__ uint32_t s_tail;
+  __shared__ uint32_t s_add[3];  // vertices appended for level l, by l mod 3
   const uint32_t tid = threadIdx.x;
   const int lane = lane_id();
   for (uint32_t w = tid; w < words; w += kReachBlock) vis[w] = 0u;
@@ -257,36 +262,46 @@ __global__ __launch_bounds__(kReachBlock) void k_lds_reach(const int64_t *rp, co
     atomicOr(&vis[r >> 5], 1u << (r & 31));
     queue[i] = (uint16_t)r;
   }
-  if (tid == 0) s_tail = (uint32_t)k;
+  if (tid < 3) s_add[tid] = 0u;
   __syncthreads();
-  // marks the vertices w[j] (where has[j]) and queues those whose first mark
-  // this is: the marks are issued together, then one atomic on the queue's end
-  auto visit = [&](const uint32_t (&w)[kAtOnce], const bool (&has)[kAtOnce]) {
-    ull fb[kAtOnce];
-    uint32_t old[kAtOnce];
+  uint32_t qb = 0, qe = (uint32_t)k, next = 2;
+  uint32_t *add = &s_add[1];
+  // marks the vertices at the ends of W arcs a lane (where has[j]) and queues
+  // those whose first mark this is: the marks are issued together, then one
+  // atomic on the queue's end
+  auto visit = [&](auto steps, auto end_of, auto has_arc) {
+    constexpr int W = decltype(steps)::value;
+    uint32_t w[W], old[W];
+    bool has[W];
+    ull fb[W];
 #pragma unroll
-    for (int j = 0; j < kAtOnce; ++j) {
+    for (int j = 0; j < W; ++j) {
+      has[j] = has_arc(j);
+      w[j] = has[j] ? (uint32_t)end_of(j) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
       old[j] = ~0u;
       if (has[j]) old[j] = atomicOr(&vis[w[j] >> 5], 1u << (w[j] & 31));
     }
     uint32_t total = 0;
 #pragma unroll
-    for (int j = 0; j < kAtOnce; ++j) {
+    for (int j = 0; j < W; ++j) {
       fb[j] = __ballot(((old[j] >> (w[j] & 31)) & 1u) == 0u);
       total += (uint32_t)__popcll(fb[j]);
     }
     if (total == 0u) return;
     uint32_t p = 0;
-    if (lane == 0) p = atomicAdd(&s_tail, total);
-    p = read_lane(p, 0);
+    if (lane == 0) p = atomicAdd(add, total);
+    p = qe + read_lane(p, 0);
 #pragma unroll
-    for (int j = 0; j < kAtOnce; ++j) {
+    for (int j = 0; j < W; ++j) {
       if ((fb[j] >> lane) & 1ull) queue[p + lanes_below(fb[j])] = (uint16_t)w[j];
       p += (uint32_t)__popcll(fb[j]);
     }
   };
-  uint32_t qb = 0, qe = (uint32_t)k;
   while (qb < qe) {
+    if (tid == 0) s_add[next] = 0u;  // read by all before the last barrier, appended to after the next
     for (uint32_t b = qb + (tid & ~63u); b < qe; b += kReachBlock) {  // the same for a wavefront
       int64_t e0 = 0;
       uint32_t deg = 0;
@@ -295,35 +310,37 @@ __global__ __launch_bounds__(kReachBlock) void k_lds_reach(const int64_t *rp, co
         e0 = rp[v];
         deg = (uint32_t)(rp[v + 1] - e0);
       }
-      uint32_t w[kAtOnce];
-      bool has[kAtOnce];
-      for (uint32_t c = 0; c < kAlone && __ballot(c < deg) != 0ull; c += kAtOnce) {
-#pragma unroll
-        for (int j = 0; j < kAtOnce; ++j) {
-          has[j] = c + j < deg;
-          w[j] = has[j] ? (uint32_t)col[e0 + c + j] : 0u;
-        }
-        visit(w, has);
+      // a narrow level is bound by its instructions: short rows take short steps
+      const ull over1 = __ballot(deg > 1u), over2 = __ballot(deg > 2u), over4 = __ballot(deg > 4u);
+      auto alone = [&](auto steps, uint32_t c) {
+        visit(steps, [&](int j) { return col[e0 + c + j]; }, [&](int j) { return c + j < deg; });
+      };
+      if (over1 == 0ull) alone(std::integral_constant<int, 1>(), 0u);
+      else if (over2 == 0ull) alone(std::integral_constant<int, 2>(), 0u);
+      else if (over4 == 0ull) alone(std::integral_constant<int, 4>(), 0u);
+      if (over4 == 0ull) continue;
+      // the wavefront takes the rest of long rows one row after the other, once
+      // its lanes have made as many steps past kAlone as there are such rows
+      uint32_t done = 0;
+      ull rest;
+      while ((rest = __ballot(done < deg)) != 0ull && done < kAlone + kAtOnce * (uint32_t)__popcll(rest)) {
+        alone(std::integral_constant<int, kAtOnce>(), done);
+        done += kAtOnce;
       }
-      for (ull rest = __ballot(deg > kAlone); rest != 0ull; rest &= rest - 1ull) {
+      for (; rest != 0ull; rest &= rest - 1ull) {
         const int i = __builtin_ctzll(rest);
-        const int32_t *row = col + (int64_t)read_lane64((ull)e0, i);
+        const int32_t *row = col + (int64_t)read_lane64((ull)e0, i) + lane;
         const uint32_t d = read_lane(deg, i);
-        for (uint32_t c = kAlone; c < d; c += 64 * kAtOnce) {
-#pragma unroll
-          for (int j = 0; j < kAtOnce; ++j) {
-            const uint32_t at = c + (uint32_t)(64 * j + lane);
-            has[j] = at < d;
-            w[j] = has[j] ? (uint32_t)row[at] : 0u;
-          }
-          visit(w, has);
-        }
+        for (uint32_t c = done; c < d; c += 64 * kAtOnce)
+          visit(std::integral_constant<int, kAtOnce>(), [&](int j) { return row[c + 64 * j]; },
+                [&](int j) { return c + 64 * j + lane < d; });
       }
     }
     __syncthreads();
     qb = qe;
-    qe = s_tail;
-    __syncthreads();
+    qe += *add;
+    add = &s_add[next];
+    next = next == 2u ? 0u : next + 1u;
   }
   for (uint32_t w = tid; w < words; w += kReachBlock) bitmap_out[w] = vis[w];
 }

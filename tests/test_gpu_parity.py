@@ -1116,3 +1116,17 @@ def test_second_workspace_is_as_wide_as_its_batches(B, weighted):
     dep = G.dependencies(r, src)
     assert np.array_equal(dep[:ns], G.dependencies(r, src[:ns]))
     assert np.array_equal(dep, np.concatenate([one.dependencies(r, src[i:i + 600]) for i in range(0, 4000, 600)]))
+
+
+@pytest.mark.parametrize("width", [1, 2, 3, 4, 5, 8, 9, 32, 33, 40, 64, 100, 600])
+def test_rv_narrow_levels(B, width):
+    """RV(r) of the one-workgroup form on graphs of many narrow levels: vertex
+    i leads to the next `width` ones, so a level holds `width` vertices with
+    rows of that many arcs, and the last vertex is reached by all."""
+    n = min(4000, 32000 // width)
+    s = np.repeat(np.arange(n), width)
+    d = s + np.tile(np.arange(1, width + 1), n)
+    g = gg.from_arcs(n, s[d < n], d[d < n], name="band")
+    G = dev(B, g)
+    for r in (n - 1, n // 2, 1, 0):
+        assert np.array_equal(G.rv(r), np.arange(r)), r
