@@ -132,7 +132,6 @@ struct Workspace {
   uint32_t *rqn = nullptr;  // frontier counters (ReachCtr), a line per level mod 4
   int32_t *d_roots = nullptr;  // several roots of one traversal
   size_t roots_cap = 0;
-  int reach_depth = 6;      // levels of the last traversal
   uint32_t *h_bitmap = nullptr;
   // host staging
   uint32_t *h_cnt = nullptr;
@@ -213,6 +212,9 @@ struct Graph {
   std::mutex pool_mu;
   std::vector<std::unique_ptr<Workspace>> pool;
   std::atomic<bool> profiling{false};
+  // levels of the last traversal that took a launch per level (a hint: it
+  // decides how a traversal runs, not what it finds)
+  mutable std::atomic<int64_t> reach_depth{6};
   // a batch met a path count above 2^32 - 1: batches store 64-bit counts from then on
   std::atomic<bool> wide_counts{false};
   std::mutex lm_mu;                // landmark distance signatures (source ordering)
@@ -343,8 +345,9 @@ uint64_t batch_workspace_bytes(const Graph *g, int groups);
 // LDS engine (bcd_lds.hip): one workgroup per source at a time, state in LDS.
 size_t lds_bytes_for(int64_t n);
 bool lds_fits(const Graph *g);
-// Single-workgroup reachability (n < 2^16, visited bits and queue in LDS).
-bool lds_reach_fits(const Graph *g);
+// Whether a traversal of at least `levels` levels goes to one workgroup (n < 2^16,
+// visited bits and queue in LDS) instead of a launch per level.
+bool reach_one_workgroup(const Graph *g, int64_t levels);
 hipError_t launch_lds_reach(const Graph *g, const int64_t *rp, const int32_t *col, int32_t root,
                             const int32_t *roots, int k, uint32_t *bitmap, hipStream_t st);
 bcd_status run_lds(Graph *g, Workspace *ws, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt,

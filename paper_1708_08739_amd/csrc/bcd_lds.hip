@@ -345,14 +345,19 @@ __global__ __launch_bounds__(kReachBlock) void k_lds_reach(const int64_t *rp, co
   for (uint32_t w = tid; w < words; w += kReachBlock) bitmap_out[w] = vis[w];
 }
 
-// One compute unit scans the arcs alone, so graphs of more than kLdsReachArcs
-// go to the launch-per-level form even where their bits would fit.  RV(r), whole
-// call, one workgroup against a launch per level: 3,005 arcs 27 / 82 us, 10,000
-// 33 / 82, 32,000 (uniform) 48 / 95, 28,672 (R-MAT) 60 / 65, 58,778 74 / 65,
-// 110,551 110 / 68.
+// One compute unit scans the arcs alone, at about 0.4 us a thousand, and a launch
+// per level costs about 8 us a level: one workgroup takes a traversal of at
+// least `levels` levels on a graph of up to 32,768 arcs, and for every two levels
+// past 8 on as many more.  RV(r), whole call, one workgroup against a
+// launch per level: 3,005 arcs 27 / 82 us, 10,000 33 / 82, 28,665 (R-MAT) 59 / 72,
+// 58,828 80 / 58, 120,110 109 / 65, 599,942 (uniform) 281 / 125; of more levels:
+// 119,997 arcs (uniform, 2 a vertex) 138 / 327, 180 x 180 grid (128,880, 359 levels)
+// 377 / 3,081, 255 x 255 549 / 4,649, a cycle of 20,000 11,330 / 167,840, bands
+// of 10,000 vertices by 16 (159,864, 625 levels) 1,220 / 5,181.
 constexpr int64_t kLdsReachArcs = 1 << 15;
-bool lds_reach_fits(const Graph *g) {
-  return g->n >= 1 && g->n < 65536 && g->m <= kLdsReachArcs && lds_reach_bytes(g->n) <= g->lds_block_bytes;
+bool reach_one_workgroup(const Graph *g, int64_t levels) {
+  return g->n >= 1 && g->n < 65536 && g->m <= kLdsReachArcs * std::max<int64_t>(1, (levels - 8) / 2) &&
+         lds_reach_bytes(g->n) <= g->lds_block_bytes;
 }
 
 hipError_t launch_lds_reach(const Graph *g, const int64_t *rp, const int32_t *col, int32_t root,

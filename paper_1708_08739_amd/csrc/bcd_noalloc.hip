@@ -26,7 +26,7 @@ namespace bcd {
 // Largest graph the scratch holds: 2^22 vertices (R-MAT scale 22).
 constexpr int64_t kNoAllocMaxN = int64_t(1) << 22;
 constexpr size_t kCtrBytes = 256;  // counters: four frontiers (ReachCtr) from word 0, list size at word kListWord
-constexpr int kListWord = 32;
+constexpr int kCtrStride = 4, kListWord = 32;
 constexpr size_t kBitmapBytes = (size_t)(kNoAllocMaxN / 32) * 4;  // visited bits
 constexpr size_t kQueueBytes = (size_t)kNoAllocMaxN * 4;          // one frontier queue (int32 ids)
 constexpr size_t kScratchBytes = kCtrBytes + kBitmapBytes + 2 * kQueueBytes;  // 34,079,000 bytes
@@ -139,13 +139,12 @@ extern "C" bcd_status bcd_rv_noalloc(const bcd_graph *gh, bcd_vid r, bcd_vid *ou
   hipStream_t st = nullptr;  // the null stream: every step below is ordered after the one before
   const int64_t *rp = g->d_irp;
   const int32_t *col = g->d_icol;
-  if (lds_reach_fits(g)) {
-    // small graph: the whole traversal in one workgroup (visited bits and
-    // queue in LDS), bitmap written out at the end
-    NA_HIPCHK(launch_lds_reach(g, rp, col, r, nullptr, 1, bitmap, st), "reachability launch failed");
-  } else {
+  // small graph: the whole traversal in one workgroup (visited bits and queue
+  // in LDS), bitmap written out at the end
+  bool one = reach_one_workgroup(g, g->reach_depth.load(std::memory_order_relaxed));
+  if (!one) {
     // clears what this call reads before writing it, the bitmap and the counters
-    const ReachCtr rc{ctr, 4};
+    const ReachCtr rc{ctr, kCtrStride};
     NA_HIPCHK(launch_reach_init(bitmap, words, q0, rc, r, nullptr, 1, st), "reachability launch failed");
     const Launch L = g->launch();
     const uint64_t bu_arcs = reach_bu_arcs(g);
@@ -155,12 +154,16 @@ extern "C" bcd_status bcd_rv_noalloc(const bcd_graph *gh, bcd_vid r, bcd_vid *ou
         NA_HIPCHK(launch_reach_level(rp, col, g->d_rp, g->d_col, bitmap, q0, q1, rc, nullptr, (int)level, n, bu_arcs, L,
                                      st),
                   "reachability launch failed");
-      uint32_t left = 0;
-      NA_HIPCHK(hipMemcpy(&left, rc.len((int)level), sizeof(uint32_t), hipMemcpyDeviceToHost),
-                "frontier size copy failed");
-      if (left == 0) break;
+      alignas(8) uint32_t h[4 * kCtrStride];
+      NA_HIPCHK(hipMemcpy(h, ctr, sizeof(h), hipMemcpyDeviceToHost), "frontier size copy failed");
+      const uint32_t left = *ReachCtr{h, kCtrStride}.len((int)level);
+      one = left != 0 && reach_one_workgroup(g, level);  // deeper than it looked: from the start
+      if (left != 0 && !one) continue;
+      g->reach_depth.store(left != 0 ? level : (int64_t)h[1], std::memory_order_relaxed);
+      break;
     }
   }
+  if (one) NA_HIPCHK(launch_lds_reach(g, rp, col, r, nullptr, 1, bitmap, st), "reachability launch failed");
   // RV(r) ascending into the first queue (free again), its size into ctr[kListWord]
   hipLaunchKernelGGL(k_bitmap_compact, dim3(1), dim3(kCompactBlock), 0, st, bitmap, words, n, (int32_t)r, q0,
                      &ctr[kListWord]);

@@ -87,13 +87,15 @@ static bcd_status reach_bitmap(Graph *g, Workspace *ws, const int32_t *roots, in
     HIPCHK(hipMemcpyAsync(ws->d_roots, roots, (size_t)k * sizeof(int32_t), hipMemcpyHostToDevice, st));
     d_roots = ws->d_roots;
   }
-  if (!d_lev && lds_reach_fits(g)) {
-    // small graph: the whole traversal in one workgroup, one launch
+  // small graph: the whole traversal in one workgroup, one launch
+  auto one_workgroup = [&]() -> bcd_status {
     HIPCHK(launch_lds_reach(g, rp, col, roots[0], d_roots, k, ws->bitmap, st));
     HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     return BCD_OK;
-  }
+  };
+  const int64_t depth = g->reach_depth.load(std::memory_order_relaxed);
+  if (!d_lev && reach_one_workgroup(g, depth)) return one_workgroup();
   const ReachCtr ctr{ws->rqn, kTailStride};
   HIPCHK(launch_reach_init(ws->bitmap, (int64_t)words, ws->rq[0], ctr, roots[0], d_roots, k, st));
   // a level whose frontier has at least m/64 arcs to scan is found bottom-up
@@ -104,7 +106,7 @@ static bcd_status reach_bitmap(Graph *g, Workspace *ws, const int32_t *roots, in
   // in-degree (40 M in-arcs)
   const uint64_t bu_arcs = d_lev ? ~0ull : reach_bu_arcs(g);
   const Launch L = g->launch();
-  int chunk = std::min(kLevelChunkMax, std::max(4, ws->reach_depth + 2));
+  int chunk = (int)std::min<int64_t>(kLevelChunkMax, std::max<int64_t>(4, depth + 2));
   for (int64_t level = 0; level <= n;) {
     for (int i = 0; i < chunk; ++i, ++level)
       HIPCHK(launch_reach_level(rp, col, rpo, colo, ws->bitmap, ws->rq[0], ws->rq[1], ctr, d_lev, (int)level, n, bu_arcs,
@@ -114,8 +116,12 @@ static bcd_status reach_bitmap(Graph *g, Workspace *ws, const int32_t *roots, in
     HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (*ReachCtr{h, kTailStride}.len((int)level) == 0) {
-      ws->reach_depth = (int)std::min<uint32_t>(h[1], kLevelChunkMax);
+      g->reach_depth.store((int64_t)h[1], std::memory_order_relaxed);
       break;
+    }
+    if (!d_lev && reach_one_workgroup(g, level)) {  // deeper than it looked: from the start
+      g->reach_depth.store(level, std::memory_order_relaxed);
+      return one_workgroup();
     }
     chunk = 8;
   }

@@ -81,4 +81,13 @@ int reach_grid(int block, int grid) {
   return reach_level_grid(L);
 }
 
+// Whether a traversal of at least `levels` levels goes to one workgroup.
+int one_workgroup(int64_t n, int64_t m, int64_t levels) {
+  Graph g;
+  g.n = n;
+  g.m = m;
+  g.lds_block_bytes = 160 * 1024;
+  return reach_one_workgroup(&g, levels);
+}
+
 }  // extern "C"

@@ -1130,3 +1130,33 @@ def test_rv_narrow_levels(B, width):
     G = dev(B, g)
     for r in (n - 1, n // 2, 1, 0):
         assert np.array_equal(G.rv(r), np.arange(r)), r
+
+
+def test_rv_deep_graphs_change_form(B, oracle):
+    """Deep graphs whose arcs are too many for one workgroup at first: the first
+    traversal starts with a launch per level and ends in one workgroup, later
+    ones begin there, and the no-alloc call does alike; the sets are the oracle's
+    throughout, shallow answers in between included."""
+    import ctypes as C
+    n = 181 * 181
+    i = np.arange(n).reshape(181, 181)
+    s = np.concatenate([i[:, :-1].ravel(), i[:-1].ravel(), i[:, 1:].ravel(), i[1:].ravel()[:-300]])
+    d = np.concatenate([i[:, 1:].ravel(), i[1:].ravel(), i[:, :-1].ravel(), i[:-1].ravel()[:-300]])
+    grid = gg.from_arcs(n, s, d, name="grid")
+    hub = gg.from_arcs(n + 1, np.append(s, [n, 5]), np.append(d, [7, n]), name="grid_hub")
+    cyc = gg.from_arcs(40000, np.arange(40000), (np.arange(40000) + 1) % 40000, name="cycle")
+    lib = B.load()
+
+    def noalloc(G, r):
+        out = np.empty(G.n, dtype=np.int32)
+        k = C.c_int64()
+        B.check(lib.bcd_rv_noalloc(G.h, r, C.c_void_p(out.ctypes.data), G.n, C.byref(k)), "bcd_rv_noalloc")
+        return out[:k.value]
+    for g, rs in ((grid, (0, n - 1, n // 2)), (hub, (n, 3)), (cyc, (0, 39999))):
+        want = [oracle.rv(g, r) for r in rs]
+        for first in (noalloc, B.Graph.rv):
+            G = dev(B, g)
+            for _ in range(2):
+                for r, w in zip(rs, want):
+                    assert np.array_equal(first(G, r), w), (g.name, r)
+            assert np.array_equal(G.rv(rs[0]), want[0]) and np.array_equal(noalloc(G, rs[0]), want[0])

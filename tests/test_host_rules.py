@@ -88,3 +88,14 @@ def test_reach_levels_keep_their_wavefronts_at_every_block_size(rules, block):
         waves = rules.reach_grid(block, grid) * 4
         assert waves == min(4096, grid * block // 64), (block, mult)
     assert rules.reach_grid(64, 1) == 1
+
+
+def test_reachability_in_one_workgroup(rules):
+    """Graphs of few arcs, and of more on deep traversals, are searched by one
+    workgroup; large ones and shallow ones of many arcs by a launch per level."""
+    def one(n, m, levels):
+        return bool(rules.one_workgroup(C.c_int64(n), C.c_int64(m), C.c_int64(levels)))
+    assert one(2000, 1 << 15, 0) and one(2000, 1 << 15, 6) and not one(2000, (1 << 15) + 1, 9)
+    assert one(180 * 180, 4 * 180 * 179, 16) and not one(180 * 180, 4 * 180 * 179, 8)
+    assert one(60000, 60000, 12) and one(65535, 15_000_000, 1000)
+    assert not one(65535, 60_000_000, 59) and not one(65536, 100, 6) and not one(1 << 20, 100, 1 << 20)
