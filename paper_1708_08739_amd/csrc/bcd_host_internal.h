@@ -334,6 +334,11 @@ bcd_status reach_set(Graph *g, Workspace *ws, int32_t root, bool reverse, std::v
 // D of the set form: the union of RV(r) over the targets (ascending, distinct)
 // with out-arcs, as a bitmap.
 bcd_status reach_union(Graph *g, Workspace *ws, const std::vector<int32_t> &targets, std::vector<uint32_t> &uni);
+// Whether the host check behind `level` levels, the last `chunk` of them just
+// launched, brings the whole bitmap.
+inline bool reach_copies_bitmap(int64_t level, int chunk, size_t bytes) {
+  return level == chunk && bytes <= (size_t(1) << 20);
+}
 // Frontier arcs from which a reachability level goes bottom-up.
 inline uint64_t reach_bu_arcs(const Graph *g) { return (uint64_t)std::max<int64_t>(64, g->m / 64); }
 bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src,

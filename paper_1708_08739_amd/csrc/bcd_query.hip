@@ -107,13 +107,18 @@ static bcd_status reach_bitmap(Graph *g, Workspace *ws, const int32_t *roots, in
   const uint64_t bu_arcs = d_lev ? ~0ull : reach_bu_arcs(g);
   const Launch L = g->launch();
   int chunk = (int)std::min<int64_t>(kLevelChunkMax, std::max<int64_t>(4, depth + 2));
+  // The bitmap comes with the first check, which ends most traversals: a copy
+  // of up to 1 MiB (about 20 us) costs less than the wait it saves.  Later checks
+  // bring the counters alone, and the bitmap follows once.
+  bool have = false;
   for (int64_t level = 0; level <= n;) {
     for (int i = 0; i < chunk; ++i, ++level)
       HIPCHK(launch_reach_level(rp, col, rpo, colo, ws->bitmap, ws->rq[0], ws->rq[1], ctr, d_lev, (int)level, n, bu_arcs,
                                 L, st));
     uint32_t *h = reinterpret_cast<uint32_t *>(ws->h_misc);
     HIPCHK(hipMemcpyAsync(h, ctr.c, (size_t)4 * kTailStride * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    have = reach_copies_bitmap(level, chunk, words * sizeof(uint32_t));
+    if (have) HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (*ReachCtr{h, kTailStride}.len((int)level) == 0) {
       g->reach_depth.store((int64_t)h[1], std::memory_order_relaxed);
@@ -124,6 +129,10 @@ static bcd_status reach_bitmap(Graph *g, Workspace *ws, const int32_t *roots, in
       return one_workgroup();
     }
     chunk = 8;
+  }
+  if (!have) {
+    HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
   }
   return BCD_OK;
 }

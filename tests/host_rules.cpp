@@ -90,4 +90,20 @@ int one_workgroup(int64_t n, int64_t m, int64_t levels) {
   return reach_one_workgroup(&g, levels);
 }
 
+// Bytes of bitmap a traversal of `levels` levels brings to the host, checked
+// first after `first` levels, then every eight.
+uint64_t bitmap_bytes_copied(int64_t n, int64_t levels, int first) {
+  const size_t bytes = ((size_t)n + 31) / 32 * 4;
+  uint64_t total = 0;
+  bool have = false;
+  int chunk = first;
+  for (int64_t level = chunk;; level += chunk) {
+    have = reach_copies_bitmap(level, chunk, bytes);
+    if (have) total += bytes;
+    if (level > levels) break;
+    chunk = 8;
+  }
+  return have ? total : total + bytes;
+}
+
 }  // extern "C"

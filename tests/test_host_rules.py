@@ -99,3 +99,16 @@ def test_reachability_in_one_workgroup(rules):
     assert one(180 * 180, 4 * 180 * 179, 16) and not one(180 * 180, 4 * 180 * 179, 8)
     assert one(60000, 60000, 12) and one(65535, 15_000_000, 1000)
     assert not one(65535, 60_000_000, 59) and not one(65536, 100, 6) and not one(1 << 20, 100, 1 << 20)
+
+
+@pytest.mark.parametrize("n", [100, 1 << 20, 1 << 23, (1 << 23) + 1, 1 << 30])
+def test_traversals_copy_the_bitmap_once_or_twice(rules, n):
+    """The visited bitmap comes to the host with the first check or once at the
+    end: at most twice whatever the depth, once where it is large."""
+    f = rules.bitmap_bytes_copied
+    f.argtypes, f.restype = [C.c_int64, C.c_int64, C.c_int], C.c_uint64
+    size = (n + 31) // 32 * 4
+    for levels in (0, 3, 7, 8, 9, 63, 64, 1000):
+        for first in (4, 8, 64):
+            once = levels < first or size > 1 << 20
+            assert f(n, levels, first) == size * (1 if once else 2), (levels, first)
