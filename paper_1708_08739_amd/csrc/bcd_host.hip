@@ -1,7 +1,7 @@
 // libbcd host layer: the C ABI of include/bcd.h.
 //
-// Graph: the out-CSR and its transpose (the reverse graph of Def.2) are
-// uploaded once and stay resident.  Queries: RV(r) by a device BFS on the
+// Graph: the out-CSR and its transpose (the reverse graph of Def.2), in the
+// caller's ids and in internal ones, are uploaded once and stay resident.  Queries: RV(r) by a device BFS on the
 // transpose (Def.3, Prop.2), then batches of sources through the batched
 // forward / backward kernels, then a compensated sum on the host in a fixed
 // order (ascending source for Alg.1, draw order for Alg.2).
@@ -17,6 +17,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/bcd.h"
@@ -423,20 +424,7 @@ std::pair<hipEvent_t, hipEvent_t> Workspace::event_pair(size_t i) {
 Graph::~Graph() {
   pool.clear();
   if (prof_ref) (void)hipEventDestroy(prof_ref);
-  dfree(d_rp);
-  dfree(d_col);
-  dfree(d_irp);
-  dfree(d_icol);
-  dfree(d_prp);
-  dfree(d_pcol);
-  dfree(d_pirp);
-  dfree(d_picol);
-  dfree(d_orig);
-  dfree(d_lrp);
-  dfree(d_lcol);
-  dfree(d_arcw);
-  dfree(d_iarc);
-  dfree(d_iopos);
+  dfree(d_arrays);
 }
 
 DevGraph Graph::dev() const {
@@ -601,17 +589,8 @@ bcd_status bcd_sample_count(double eps_abs, double delta, double K, int64_t rv_s
   BCD_GUARD_END
 }
 
-bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t *col,
-                              const uint32_t *weight, bcd_graph **out) {
-  BCD_GUARD_BEGIN
-  if (!out) return fail(BCD_ERR_INVALID_ARG, "out is NULL");
-  if (n <= 0 || n >= (1ll << 31)) return fail(BCD_ERR_INVALID_ARG, "n must be in [1, 2^31)");
-  if (m < 0 || m >= (1ll << 32)) return fail(BCD_ERR_INVALID_ARG, "m must be in [0, 2^32)");
-  if (!row_ptr || (m > 0 && !col)) return fail(BCD_ERR_INVALID_ARG, "row_ptr/col is NULL");
-  // Section 2 graph model: validate fully on the host before touching the GPU.
-  if (row_ptr[0] != 0) return fail(BCD_ERR_BAD_GRAPH, "row_ptr[0] != 0");
-  if (row_ptr[n] != m) return fail(BCD_ERR_BAD_GRAPH, "row_ptr[n] != m");
-  uint64_t max_w = 1;
+// What is wrong with a CSR that is not of Section 2's graph model.
+static bcd_status bad_csr(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t *col, const uint32_t *weight) {
   for (int64_t v = 0; v < n; ++v) {
     const int64_t a = row_ptr[v], b = row_ptr[v + 1];
     if (b < a) return fail(BCD_ERR_BAD_GRAPH, "row_ptr decreases at vertex " + std::to_string(v));
@@ -622,73 +601,112 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
       if (w == v) return fail(BCD_ERR_BAD_GRAPH, "self-loop at vertex " + std::to_string(v));
       if (e > a && w <= col[e - 1])
         return fail(BCD_ERR_BAD_GRAPH, "row " + std::to_string(v) + " not strictly increasing (repeated arc?)");
-      if (weight) {
-        if (weight[e] == 0) return fail(BCD_ERR_BAD_GRAPH, "zero weight at arc " + std::to_string(e));
-        max_w = std::max<uint64_t>(max_w, weight[e]);
-      }
+      if (weight && weight[e] == 0) return fail(BCD_ERR_BAD_GRAPH, "zero weight at arc " + std::to_string(e));
     }
   }
-  int cus = 0;
-  size_t lds_block = 0;
-  STCHK(device_check(&cus, &lds_block));
+  return fail(BCD_ERR_BAD_GRAPH, "malformed CSR");
+}
+
+bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t *col,
+                              const uint32_t *weight, bcd_graph **out) {
+  BCD_GUARD_BEGIN
+  if (!out) return fail(BCD_ERR_INVALID_ARG, "out is NULL");
+  if (n <= 0 || n >= (1ll << 31)) return fail(BCD_ERR_INVALID_ARG, "n must be in [1, 2^31)");
+  if (m < 0 || m >= (1ll << 32)) return fail(BCD_ERR_INVALID_ARG, "m must be in [0, 2^32)");
+  if (!row_ptr || (m > 0 && !col)) return fail(BCD_ERR_INVALID_ARG, "row_ptr/col is NULL");
+  // Section 2 graph model: validate fully on the host before touching the GPU.
+  if (row_ptr[0] != 0) return fail(BCD_ERR_BAD_GRAPH, "row_ptr[0] != 0");
+  if (row_ptr[n] != m) return fail(BCD_ERR_BAD_GRAPH, "row_ptr[n] != m");
+  // In flat passes without branches first (R-MAT 16, 65,536 rows: row by row
+  // 0.61 ms, mostly mispredicted row ends, 0.31 as here); where something is wrong,
+  // arc by arc for the message.  Rows are increasing iff no arc but a row's first
+  // is at or below the one before; self-loops are met in the transposition.
+  bool bad = false;
+  for (int64_t v = 0; v < n; ++v) bad |= row_ptr[v + 1] < row_ptr[v];
+  if (bad) return bad_csr(n, m, row_ptr, col, weight);
+  int64_t falls = m > 0 ? 1 : 0, row_falls = 0;  // arc 0 counts as a fall
+  for (int64_t e = 0; e < m; ++e) bad |= (uint32_t)col[e] >= (uint32_t)n;
+  for (int64_t e = 1; e < m; ++e) falls += col[e] <= col[e - 1];
+  for (int64_t v = 0; v < n; ++v) {
+    const int64_t e = row_ptr[v];
+    row_falls += e < row_ptr[v + 1] && (e == 0 || col[e] <= col[e - 1]);
+  }
+  uint32_t max_w = 1;
+  if (weight)
+    for (int64_t e = 0; e < m; ++e) {
+      bad |= weight[e] == 0;
+      max_w = std::max(max_w, weight[e]);
+    }
+  if (bad || falls != row_falls) return bad_csr(n, m, row_ptr, col, weight);
   std::unique_ptr<Graph> g(new (std::nothrow) Graph());
   if (!g) return fail(BCD_ERR_OUT_OF_MEMORY, "host allocation failed");
   g->n = n;
   g->m = m;
   g->weighted = weight != nullptr;
-  g->max_w = (uint32_t)max_w;
-  g->cus = cus;
-  g->lds_block_bytes = lds_block;
+  g->max_w = max_w;
   g->h_rp.assign(row_ptr, row_ptr + n + 1);
-  // transpose by counting sort: rows of R(G) come out sorted
-  std::vector<int64_t> irp((size_t)n + 1, 0);
-  for (int64_t e = 0; e < m; ++e) irp[(size_t)col[e] + 1]++;
-  for (int64_t v = 0; v < n; ++v) irp[(size_t)v + 1] += irp[(size_t)v];
-  std::vector<int32_t> icol((size_t)std::max<int64_t>(m, 1));
-  std::vector<uint32_t> iw(weight ? (size_t)std::max<int64_t>(m, 1) : 0);
-  std::vector<uint32_t> ipos(weight ? (size_t)std::max<int64_t>(m, 1) : 0);
-  {
-    std::vector<int64_t> fill(irp.begin(), irp.end() - 1);
+  // Host image of what the device gets: the transpose (the reverse graph R(G)),
+  // both row offsets in internal order and the two renamings, and, where they
+  // are small, the caller's arrays, so that a small graph is one copy.  On
+  // weighted graphs the transpose's ends come from {tail, CSR position} pairs.
+  const size_t N = (size_t)n, M = (size_t)std::max<int64_t>(m, 1);
+  const bool staged = (N + 1) * 8 + M * 4 <= (size_t(1) << 20);
+  size_t bytes = 0;
+  auto take = [&](size_t b) {
+    const size_t at = bytes;
+    bytes += (b + 255) & ~(size_t)255;
+    return at;
+  };
+  const size_t o_irp = take((N + 1) * 8), o_prp = take((N + 1) * 8), o_pirp = take((N + 1) * 8), o_orig = take(N * 4),
+               o_rank = take(N * 4), o_icol = weight ? 0 : take(M * 4), o_rp0 = staged ? take((N + 1) * 8) : 0,
+               o_col0 = staged ? take(M * 4) : 0;
+  const size_t image_bytes = bytes;
+  std::unique_ptr<unsigned char[]> image(new unsigned char[image_bytes]);
+  std::unique_ptr<uint2[]> pairs(weight ? new uint2[M] : nullptr);
+  auto at64 = [&](size_t o) { return reinterpret_cast<int64_t *>(image.get() + o); };
+  auto at32 = [&](size_t o) { return reinterpret_cast<int32_t *>(image.get() + o); };
+  int64_t *irp = at64(o_irp), *prp = at64(o_prp), *pirp = at64(o_pirp);
+  int32_t *orig = at32(o_orig), *rank = at32(o_rank), *icol = at32(o_icol);
+  // transpose by counting sort: rows of R(G) come out sorted.  32-bit counts and
+  // positions, and the lines to be written fetched ahead: R-MAT 20 (edge factor
+  // 8), 6 + 34 ms with 64-bit ones and no fetch, 5 + 27 as here
+  std::vector<uint32_t> next(N, 0u);
+  for (int64_t e = 0; e < m; ++e) ++next[(size_t)col[e]];
+  irp[0] = 0;
+  for (int64_t v = 0; v < n; ++v) {
+    irp[v + 1] = irp[v] + next[(size_t)v];
+    next[(size_t)v] = (uint32_t)irp[v];
+  }
+  auto transpose = [&](auto *out, auto entry) {
+    uint32_t *at = next.data();
+    const int64_t ahead = m > (int64_t(1) << 22) ? m - 32 : 0;  // smaller arrays stay in the caches
     for (int64_t u = 0; u < n; ++u)
       for (int64_t e = row_ptr[u]; e < row_ptr[u + 1]; ++e) {
-        const int64_t p = fill[(size_t)col[e]]++;
-        icol[(size_t)p] = (int32_t)u;
-        if (weight) {
-          iw[(size_t)p] = weight[e];
-          ipos[(size_t)e] = (uint32_t)p;
+        if (e < ahead) {
+          __builtin_prefetch(&at[col[e + 32]], 1);
+          __builtin_prefetch(&out[at[col[e + 16]]], 1);
         }
+        bad |= col[e] == u;
+        out[at[col[e]]++] = entry(u, e);
       }
-  }
-  STCHK(dalloc(&g->d_rp, (size_t)n + 1));
-  STCHK(dalloc(&g->d_col, (size_t)m));
-  STCHK(dalloc(&g->d_irp, (size_t)n + 1));
-  STCHK(dalloc(&g->d_icol, (size_t)m));
-  HIPCHK(hipMemcpy(g->d_rp, row_ptr, ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(g->d_irp, irp.data(), ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  if (m > 0) {
-    HIPCHK(hipMemcpy(g->d_col, col, (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(g->d_icol, icol.data(), (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice));
-  }
-  if (lds_fits(g.get())) {
-    std::vector<uint32_t> lrp(row_ptr, row_ptr + n + 1);
-    std::vector<uint16_t> lcol(col, col + m);
-    STCHK(dalloc(&g->d_lrp, (size_t)n + 1));
-    STCHK(dalloc(&g->d_lcol, (size_t)std::max<int64_t>(m, 1)));
-    HIPCHK(hipMemcpy(g->d_lrp, lrp.data(), ((size_t)n + 1) * sizeof(uint32_t), hipMemcpyHostToDevice));
-    if (m > 0) HIPCHK(hipMemcpy(g->d_lcol, lcol.data(), (size_t)m * sizeof(uint16_t), hipMemcpyHostToDevice));
-  }
+  };
+  if (weight) transpose(pairs.get(), [](int64_t u, int64_t e) { return make_uint2((uint32_t)u, (uint32_t)e); });
+  else transpose(icol, [](int64_t u, int64_t) { return (int32_t)u; });
+  if (bad) return bad_csr(n, m, row_ptr, col, weight);
+  // the host is done with the caller's graph: now the GPU
+  STCHK(device_check(&g->cus, &g->lds_block_bytes));
   // internal ids: vertices by falling total degree (a counting sort, ties by
-  // the caller's id), and both CSRs renamed to them, rows kept in arc order
-  std::vector<int32_t> orig((size_t)n);
-  g->rank.resize((size_t)n);
+  // the caller's id); both CSRs are renamed to them on the device, rows kept in
+  // arc order
   {
-    auto deg = [&](int64_t v) {
-      return row_ptr[v + 1] - row_ptr[v] + irp[(size_t)v + 1] - irp[(size_t)v];
-    };
-    int64_t top = 0;
-    for (int64_t v = 0; v < n; ++v) top = std::max(top, deg(v));
-    std::vector<int64_t> at((size_t)top + 2, 0);  // at[d]: vertices of degree > d so far placed before d
-    for (int64_t v = 0; v < n; ++v) at[(size_t)deg(v)]++;
+    std::vector<uint32_t> deg(N);
+    uint32_t top = 0;
+    for (int64_t v = 0; v < n; ++v) {
+      deg[(size_t)v] = (uint32_t)(row_ptr[v + 1] - row_ptr[v] + irp[v + 1] - irp[v]);
+      top = std::max(top, deg[(size_t)v]);
+    }
+    std::vector<int64_t> at((size_t)top + 1, 0);  // at[d]: vertices of degree > d, and those of d placed so far
+    for (int64_t v = 0; v < n; ++v) at[deg[(size_t)v]]++;
     int64_t before = 0;
     for (int64_t d = top; d >= 0; --d) {
       const int64_t c = at[(size_t)d];
@@ -696,63 +714,76 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
       before += c;
     }
     for (int64_t v = 0; v < n; ++v) {
-      const int64_t i = at[(size_t)deg(v)]++;
-      orig[(size_t)i] = (int32_t)v;
-      g->rank[(size_t)v] = (int32_t)i;
+      const int64_t i = at[deg[(size_t)v]]++;
+      orig[i] = (int32_t)v;
+      rank[v] = (int32_t)i;
+      prp[i + 1] = row_ptr[v + 1] - row_ptr[v];
+      pirp[i + 1] = irp[v + 1] - irp[v];
     }
-    while (g->heavy < (uint64_t)(n / kHeavyShare) && deg(orig[g->heavy]) > kHeavyArcs) ++g->heavy;
+    g->rank.assign(rank, rank + n);
+    while (g->heavy < (uint64_t)(n / kHeavyShare) && deg[(size_t)orig[g->heavy]] > kHeavyArcs) ++g->heavy;
   }
-  std::vector<int64_t> prp((size_t)n + 1, 0), pirp((size_t)n + 1, 0);
+  prp[0] = pirp[0] = 0;
   for (int64_t i = 0; i < n; ++i) {
-    const size_t v = (size_t)orig[(size_t)i];
-    prp[(size_t)i + 1] = prp[(size_t)i] + row_ptr[v + 1] - row_ptr[v];
-    pirp[(size_t)i + 1] = pirp[(size_t)i] + irp[v + 1] - irp[v];
+    prp[i + 1] += prp[i];
+    pirp[i + 1] += pirp[i];
   }
-  STCHK(dalloc(&g->d_prp, (size_t)n + 1));
-  STCHK(dalloc(&g->d_pirp, (size_t)n + 1));
-  STCHK(dalloc(&g->d_orig, (size_t)n));
-  HIPCHK(hipMemcpy(g->d_prp, prp.data(), ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(g->d_pirp, pirp.data(), ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(g->d_orig, orig.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
+  if (staged) {
+    std::memcpy(image.get() + o_rp0, row_ptr, (N + 1) * 8);
+    if (m > 0) std::memcpy(image.get() + o_col0, col, (size_t)m * 4);
+  }
+  // one allocation: the image's arrays, then what the device fills
+  const bool narrow = lds_fits(g.get());
+  const size_t o_rp = staged ? o_rp0 : take((N + 1) * 8), o_col = staged ? o_col0 : take(M * 4), o_pcol = take(M * 4),
+               o_in = weight ? take(M * 4) : o_icol, o_picol = weight ? 0 : take(M * 4),
+               o_arcw = weight ? take(M * 8) : 0, o_iarc = weight ? take(M * 8) : 0, o_iopos = weight ? take(M * 4) : 0,
+               o_lrp = narrow ? take((N + 1) * 4) : 0, o_lcol = narrow ? take(M * 2) : 0;
+  STCHK(dalloc(&g->d_arrays, bytes));
+  auto dev = [&](auto *&p, size_t o) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(g->d_arrays + o); };
+  dev(g->d_rp, o_rp);
+  dev(g->d_col, o_col);
+  dev(g->d_irp, o_irp);
+  dev(g->d_icol, o_in);
+  dev(g->d_prp, o_prp);
+  dev(g->d_pirp, o_pirp);
+  dev(g->d_orig, o_orig);
+  dev(g->d_pcol, o_pcol);
+  if (!weight) dev(g->d_picol, o_picol);
   if (weight) {
-    STCHK(dalloc(&g->d_arcw, (size_t)m));
-    STCHK(dalloc(&g->d_iarc, (size_t)m));
-    STCHK(dalloc(&g->d_iopos, (size_t)m));
-    if (m > 0) {
-      std::vector<uint2> arcw((size_t)m), iarc((size_t)m);
-      std::vector<uint32_t> iopos((size_t)m);
-      for (int64_t i = 0; i < n; ++i) {
-        const size_t v = (size_t)orig[(size_t)i];
-        size_t p = (size_t)prp[(size_t)i];
-        for (int64_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e, ++p) {
-          const size_t w = (size_t)col[e], j = (size_t)g->rank[w];
-          arcw[p] = make_uint2((uint32_t)j, weight[e]);
-          // an in-arc keeps its place in its row of the transpose
-          iopos[(size_t)(pirp[j] + ((int64_t)ipos[(size_t)e] - irp[w]))] = (uint32_t)p;
-        }
-        p = (size_t)pirp[(size_t)i];
-        for (int64_t e = irp[v]; e < irp[v + 1]; ++e, ++p)
-          iarc[p] = make_uint2((uint32_t)g->rank[(size_t)icol[(size_t)e]], iw[(size_t)e]);
-      }
-      HIPCHK(hipMemcpy(g->d_arcw, arcw.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
-      HIPCHK(hipMemcpy(g->d_iarc, iarc.data(), (size_t)m * sizeof(uint2), hipMemcpyHostToDevice));
-      HIPCHK(hipMemcpy(g->d_iopos, iopos.data(), (size_t)m * sizeof(uint32_t), hipMemcpyHostToDevice));
-    }
+    dev(g->d_arcw, o_arcw);
+    dev(g->d_iarc, o_iarc);
+    dev(g->d_iopos, o_iopos);
   }
-  {
-    STCHK(dalloc(&g->d_pcol, (size_t)m));
-    if (!weight) STCHK(dalloc(&g->d_picol, (size_t)m));
-    int32_t *d_rank = nullptr;
-    STCHK(dalloc(&d_rank, (size_t)n));
-    hipError_t e = hipMemcpy(d_rank, g->rank.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-      e = launch_permute_rows(n, g->d_rp, g->d_col, g->d_prp, g->d_orig, d_rank, g->d_pcol, nullptr);
-    if (e == hipSuccess && !weight)
-      e = launch_permute_rows(n, g->d_irp, g->d_icol, g->d_pirp, g->d_orig, d_rank, g->d_picol, nullptr);
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    dfree(d_rank);
-    if (e != hipSuccess) return hip_fail(e, "internal vertex order");
+  if (narrow) {
+    dev(g->d_lrp, o_lrp);
+    dev(g->d_lcol, o_lcol);
   }
+  LoadArgs A{};
+  A.n = n;
+  A.m = m;
+  A.rank = reinterpret_cast<const int32_t *>(g->d_arrays + o_rank);
+  A.lrp = g->d_lrp;
+  A.lcol = g->d_lcol;
+  unsigned char *tmp = nullptr;  // weighted: the pairs, then the lengths
+  hipError_t e = hipSuccess;
+  if (weight) {
+    STCHK(dalloc(&tmp, M * 12));
+    A.pairs = reinterpret_cast<const uint2 *>(tmp);
+    A.weight = reinterpret_cast<const uint32_t *>(tmp + M * 8);
+    A.icol = g->d_icol;
+    A.iopos = g->d_iopos;
+    A.arcw = g->d_arcw;
+    A.iarc = g->d_iarc;
+    if (m > 0) e = hipMemcpy(tmp, pairs.get(), (size_t)m * 8, hipMemcpyHostToDevice);
+    if (e == hipSuccess && m > 0) e = hipMemcpy(tmp + M * 8, weight, (size_t)m * 4, hipMemcpyHostToDevice);
+  }
+  if (e == hipSuccess) e = hipMemcpy(g->d_arrays, image.get(), image_bytes, hipMemcpyHostToDevice);
+  if (e == hipSuccess && !staged) e = hipMemcpy(g->d_rp, row_ptr, (N + 1) * 8, hipMemcpyHostToDevice);
+  if (e == hipSuccess && !staged && m > 0) e = hipMemcpy(g->d_col, col, (size_t)m * 4, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = launch_internal_rows(g->dev(), g->dev_internal(), g->d_pcol, g->d_picol, A, nullptr);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  dfree(tmp);
+  if (e != hipSuccess) return hip_fail(e, "graph upload");
   g->cfg.engine = BCD_ENGINE_BATCHED;
   g->cfg.groups = default_groups(n, weight != nullptr);
   // weighted kernels: one-wavefront workgroups, one resident grid (8 waves

@@ -190,6 +190,7 @@ struct Graph {
   std::mutex gate_mu;
   bool gates_ready = false;
   std::vector<int32_t> gate;
+  unsigned char *d_arrays = nullptr;  // the one allocation that holds the arrays below
   int64_t *d_rp = nullptr;
   int32_t *d_col = nullptr;
   int64_t *d_irp = nullptr;

@@ -244,10 +244,25 @@ hipError_t launch_reach_level(const int64_t *rp, const int32_t *col, const int64
 hipError_t launch_scatter_targets(int32_t *tgt_of, const int32_t *verts, int k, int set, hipStream_t st);
 hipError_t launch_plain_gather(const PlainState &P, const int32_t *verts, int k, int32_t *d_out,
                                double *delta_out, hipStream_t st);
-// Rows of a CSR in internal order: row i of the new one holds the arcs of row
-// orig[i] in the same order, their ends renamed by rank.
-hipError_t launch_permute_rows(int64_t n, const int64_t *rp, const int32_t *col, const int64_t *nrp,
-                               const int32_t *orig, const int32_t *rank, int32_t *ncol, hipStream_t st);
+// What the load derives on the device.
+struct LoadArgs {
+  int64_t n, m;
+  const int32_t *rank;     // [n] internal id of a caller's id
+  // weighted graphs: the transpose as {tail, CSR position} and the lengths in CSR
+  // order (inputs), the arrays of DevGraph made of them and the transpose's tails
+  const uint2 *pairs;
+  const uint32_t *weight;
+  int32_t *icol;
+  uint32_t *iopos;
+  uint2 *arcw, *iarc;
+  uint32_t *lrp;           // LDS engine's rows, or null
+  uint16_t *lcol;
+};
+// Rows of both CSRs in internal order: row i of a new one holds the arcs of row
+// orig[i] in the same order, their ends renamed by rank (weighted: with the
+// arcs' lengths and positions).
+hipError_t launch_internal_rows(const DevGraph &from, const DevGraph &to, int32_t *pcol, int32_t *picol,
+                                const LoadArgs &A, hipStream_t st);
 // weighted engine (bcd_weighted.hip)
 hipError_t launch_w_init(const BatchState &S, const uint32_t *items0, const unsigned long long *masks0,
                          const uint32_t *dest0, int k, hipStream_t st);

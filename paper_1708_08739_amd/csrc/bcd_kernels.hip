@@ -1525,21 +1525,42 @@ __global__ __launch_bounds__(kReachLevelBlock) void k_reach_level(const int64_t 
   for (int j = lane; j < nst; j += 64) qout[p0 + (uint32_t)j] = (int32_t)stg[j];
 }
 
-// Rows of a CSR in internal order (at load): a wavefront per new row.
-__global__ void k_permute_rows(int64_t n, const int64_t *rp, const int32_t *col, const int64_t *nrp,
-                               const int32_t *orig, const int32_t *rank, int32_t *ncol) {
+// At load: a wavefront per new row of either CSR, then the narrow copies.
+// On weighted graphs arc e = pairs[q].y of the CSR is arc q of the transpose,
+// and lies at the same place of its row in internal order.
+__global__ void k_internal_rows(DevGraph F, DevGraph T, int32_t *pcol, int32_t *picol, LoadArgs A) {
   const int lane = lane_id();
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n; i += nwaves) {
-    const int64_t a = rp[orig[i]], k = nrp[i + 1] - nrp[i], b = nrp[i];
-    for (int64_t j = lane; j < k; j += 64) ncol[b + j] = rank[col[a + j]];
+  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nth = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t r = tid >> 6; r < 2 * A.n; r += nth >> 6) {
+    const bool in = r >= A.n;
+    const int64_t i = in ? r - A.n : r, *nrp = in ? T.irp : T.rp;
+    const int64_t a = (in ? F.irp : F.rp)[T.orig[i]], b = nrp[i], k = nrp[i + 1] - b;
+    for (int64_t j = lane; j < k; j += 64) {
+      if (!in) {
+        const int32_t w = A.rank[F.col[a + j]];
+        pcol[b + j] = w;
+        if (A.weight) A.arcw[b + j] = make_uint2((uint32_t)w, A.weight[a + j]);
+      } else if (!A.weight) {
+        picol[b + j] = A.rank[F.icol[a + j]];
+      } else {
+        const uint2 p = A.pairs[a + j];
+        const int32_t u = A.rank[p.x];
+        A.icol[a + j] = (int32_t)p.x;
+        A.iarc[b + j] = make_uint2((uint32_t)u, A.weight[p.y]);
+        A.iopos[b + j] = (uint32_t)(T.rp[u] + ((int64_t)p.y - F.rp[p.x]));
+      }
+    }
+  }
+  if (A.lrp) {
+    for (int64_t i = tid; i <= A.n; i += nth) A.lrp[i] = (uint32_t)F.rp[i];
+    for (int64_t e = tid; e < A.m; e += nth) A.lcol[e] = (uint16_t)F.col[e];
   }
 }
 
-hipError_t launch_permute_rows(int64_t n, const int64_t *rp, const int32_t *col, const int64_t *nrp,
-                               const int32_t *orig, const int32_t *rank, int32_t *ncol, hipStream_t st) {
-  const int grid = (int)std::min<int64_t>(8192, (n + 3) / 4);
-  hipLaunchKernelGGL(k_permute_rows, dim3(grid), dim3(256), 0, st, n, rp, col, nrp, orig, rank, ncol);
+hipError_t launch_internal_rows(const DevGraph &from, const DevGraph &to, int32_t *pcol, int32_t *picol,
+                                const LoadArgs &A, hipStream_t st) {
+  const int grid = (int)std::min<int64_t>(8192, (A.n + 1) / 2);
+  hipLaunchKernelGGL(k_internal_rows, dim3(grid), dim3(256), 0, st, from, to, pcol, picol, A);
   return hipGetLastError();
 }
 

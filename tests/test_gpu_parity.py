@@ -1160,3 +1160,35 @@ def test_rv_deep_graphs_change_form(B, oracle):
                 for r, w in zip(rs, want):
                     assert np.array_equal(first(G, r), w), (g.name, r)
             assert np.array_equal(G.rv(rs[0]), want[0]) and np.array_equal(noalloc(G, rs[0]), want[0])
+
+
+@pytest.mark.parametrize("n,m", [(1, 0), (2, 1), (700, 0), (2000, 257_000), (2000, 258_200), (60_000, 140_000), (60_000, 143_000)])
+@pytest.mark.parametrize("wmax", [0, 40])
+def test_loaded_arrays_of_every_engine(B, oracle, n, m, wmax):
+    """Graphs below and above the size that is loaded in one copy, without
+    arcs, with vertices in and out of the heavy ones: RV(r) (both directions as
+    loaded), and passes of every engine (both as renamed, narrow rows, lengths)."""
+    g = gg.erdos_renyi(n, m, seed=n + m) if m else gg.from_arcs(n, [], [], name="no_arcs")
+    if m > n:  # two hubs above the heavy limit
+        s, d = g.arcs()
+        k = min(900, n - 3)
+        pairs = np.unique(np.stack([np.concatenate([s, np.full(k, 1), np.arange(2, k + 2)]),
+                                    np.concatenate([d, np.arange(2, k + 2), np.full(k, 0)])], 1), axis=0)
+        pairs = pairs[pairs[:, 0] != pairs[:, 1]]
+        g = gg.from_arcs(n, pairs[:, 0], pairs[:, 1], name="hubs")
+    if wmax:
+        g = gg.with_weights(g, seed=5, max_weight=wmax)
+    G = dev(B, g, groups=2)
+    assert G.info() == (g.n, g.m, bool(wmax))
+    src = sorted({0, min(1, n - 1), n // 2, n - 1})
+    for r in src:
+        assert np.array_equal(G.rv(r), oracle.rv(g, r)), r
+    want = [oracle.source_pass(g, s) for s in src]
+    engines = [B.BCD_ENGINE_BATCHED, B.BCD_ENGINE_PLAIN]
+    if not wmax and n <= 2000:
+        engines.append(B.BCD_ENGINE_LDS)
+    for engine in engines:
+        G.set_config(engine=engine)
+        for s, w in zip(src, want):
+            d, sg, dl = G.source_pass(s)
+            assert np.array_equal(d, w[0]) and np.array_equal(sg, w[1]) and close(dl, w[2]), (engine, s)
