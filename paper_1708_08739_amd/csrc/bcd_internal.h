@@ -199,6 +199,26 @@ hipError_t launch_fwd_level(const DevGraph &G, const BatchState &S, int level, L
 // cnt row of a level that is filled but whose launch has not run yet
 hipError_t launch_publish_counts(const BatchState &S, int level, hipStream_t st);
 hipError_t launch_bu_level(const DevGraph &G, const BatchState &S, int level, Launch L, hipStream_t st);
+// Workgroups of a backward level of cnt[l] items on list l that also clears the
+// masks of cleared[l] items (null: none): a wavefront per light item and per
+// eighth of a heavy one (ListView deals a third of a partition's workgroups to
+// those), a thread per mask, at most L's.  Deep graphs have thousands of levels
+// of few items, and a workgroup without work still takes its LDS and adds its
+// counters: a cycle of 1,500 vertices, every source (1,500 items a level), 15.6 us
+// a level on 8,192 workgroups, 5.5 as here.
+inline int bwd_level_grid(const BatchState &S, const Launch &L, const uint32_t *cnt, const uint32_t *cleared) {
+  const uint64_t nw = (uint64_t)(L.block / 64);
+  uint64_t nwg = 2;
+  for (int p = 0; p < S.P; ++p) {
+    const uint64_t light = (cnt[p] + nw - 1) / nw, heavy = ((uint64_t)cnt[S.P + p] * 8 + nw - 1) / nw;
+    const uint64_t masks = cleared ? ((uint64_t)cleared[p] + cleared[S.P + p]) / (uint64_t)L.block + 1 : 0;
+    nwg = nwg > masks ? nwg : masks;
+    const uint64_t items = S.H == 0 ? light : light + light / 2 + 2;
+    nwg = nwg > items ? nwg : items;
+    nwg = heavy == 0 || nwg > 3 * heavy + 3 ? nwg : 3 * heavy + 3;
+  }
+  return nwg * (uint64_t)S.P < (uint64_t)L.grid ? (int)(nwg * (uint64_t)S.P) : L.grid;
+}
 hipError_t launch_bwd_level(const DevGraph &G, const BatchState &S, int level, int ntgt, Launch L, hipStream_t st);
 hipError_t launch_batch_cleanup(const BatchState &S, const PartTotals &tot, Launch L, hipStream_t st);
 hipError_t launch_batch_export(const DevGraph &G, const BatchState &S, int level, uint64_t begin, uint64_t count,

@@ -467,9 +467,12 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
     if (full) stop = 0;
     else if (ntgt > 0 && tmin_h != 0xFFFFFFFFu) stop = (int)tmin_h;
     if (stop >= 0) {
-      for (int lv = lmax; lv >= stop; --lv) {
+      for (int lv = lmax - 1; lv >= stop; --lv) {  // level lmax is empty
         if (profiling) HIPCHK(hipEventRecord(ws->event_pair(ev).first, st));
-        HIPCHK(launch_bwd_level(D, S, lv, ntgt, L, st));
+        Launch Lb = L;
+        Lb.grid = bwd_level_grid(S, L, cntp.data() + (size_t)lv * NL,
+                                 lv + 2 < lmax ? cntp.data() + (size_t)(lv + 2) * NL : nullptr);
+        HIPCHK(launch_bwd_level(D, S, lv, ntgt, Lb, st));
         if (profiling) {
           HIPCHK(hipEventRecord(ws->event_pair(ev).second, st));
           ++ev;

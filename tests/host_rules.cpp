@@ -106,4 +106,20 @@ uint64_t bitmap_bytes_copied(int64_t n, int64_t levels, int first) {
   return have ? total : total + bytes;
 }
 
+// Workgroups of a backward level; *light and *heavy receive those a partition
+// deals to either side (list_view of the kernels).
+int bwd_grid(int P, uint32_t H, int block, int grid, const uint32_t *cnt, const uint32_t *cleared, int *light, int *heavy) {
+  BatchState S;
+  std::memset(&S, 0, sizeof(S));
+  S.P = P;
+  S.H = H;
+  Launch L;
+  L.block = block;
+  L.grid = grid;
+  const int g = bwd_level_grid(S, L, cnt, cleared), nwg = g / P;
+  *heavy = H == 0 ? 0 : (nwg < 6 ? 1 : nwg / 3);
+  *light = nwg - *heavy;
+  return g;
+}
+
 }  // extern "C"

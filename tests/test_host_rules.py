@@ -112,3 +112,27 @@ def test_traversals_copy_the_bitmap_once_or_twice(rules, n):
         for first in (4, 8, 64):
             once = levels < first or size > 1 << 20
             assert f(n, levels, first) == size * (1 if once else 2), (levels, first)
+
+
+@pytest.mark.parametrize("P,H,block", [(1, 0, 256), (2, 0, 64), (2, 7, 256), (2, 500, 512), (1, 3, 128)])
+def test_backward_levels_launch_what_their_items_need(rules, P, H, block):
+    """A backward level launches no more than a wavefront per light item and
+    part of a heavy one and a thread per mask to clear need, with workgroups for
+    both lists, and never more than the configured ones."""
+    nw = block // 64
+    most = 8192 - 8192 % P
+    for light in (0, 1, 5, 64, 1000, 10**6):
+        for heavy in ((0, 1, 40, 10**5) if H else (0,)):
+            for clear in (0, 1, 3000, 10**7):
+                cnt = np.zeros(2 * P, dtype=np.uint32)
+                cl = np.zeros(2 * P, dtype=np.uint32)
+                cnt[P - 1], cnt[2 * P - 1], cl[0] = light, heavy, clear
+                a, b = C.c_int(), C.c_int()
+                g = rules.bwd_grid(P, C.c_uint32(H), block, most, _arr(cnt), _arr(cl) if clear else None,
+                                   C.byref(a), C.byref(b))
+                assert g % P == 0 and 2 * P <= g <= most
+                if g < most:
+                    assert a.value * nw >= light and (heavy == 0 or b.value * nw >= 8 * heavy)
+                    assert g // P * block >= clear
+                    need = max(2, 1.5 * (light / nw + 1) + 2, 3 * (8 * heavy / nw + 1) + 3 if heavy else 0, clear / block + 1)
+                    assert g // P <= need, (light, heavy, clear)
