@@ -268,6 +268,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
   // per item, wavefront wv takes every NW-th step
   const uint64_t nwv = lv.heavy ? lv.nwg : lv.nwg * NW;
   const uint32_t B = lv.heavy ? 1u : (uint32_t)min((uint64_t)kBlockItems, (count + nwv - 1) / nwv);
+  // a workgroup without items has no appends and counts to flush (a grid of
+  // 3 x 5,000 vertices, 768 items a level: 19.8 us a level with them, 16 without)
+  if (lv.wg * (lv.heavy ? 1u : NW * B) >= count) return;
   const uint32_t cstart = lv.heavy ? 32u * wv : 0u, cstep = lv.heavy ? 32u * NW : 32u;
   const bool upper = lane >= 32;
   const uint32_t k32 = (uint32_t)lane & 31u;
