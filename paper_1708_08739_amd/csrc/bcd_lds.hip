@@ -310,23 +310,25 @@ __global__ __launch_bounds__(kReachBlock) void k_lds_reach(const int64_t *rp, co
         e0 = rp[v];
         deg = (uint32_t)(rp[v + 1] - e0);
       }
-      // a narrow level is bound by its instructions: short rows take short steps
-      const ull over1 = __ballot(deg > 1u), over2 = __ballot(deg > 2u), over4 = __ballot(deg > 4u);
       auto alone = [&](auto steps, uint32_t c) {
         visit(steps, [&](int j) { return col[e0 + c + j]; }, [&](int j) { return c + j < deg; });
       };
-      if (over1 == 0ull) alone(std::integral_constant<int, 1>(), 0u);
-      else if (over2 == 0ull) alone(std::integral_constant<int, 2>(), 0u);
-      else if (over4 == 0ull) alone(std::integral_constant<int, 4>(), 0u);
-      if (over4 == 0ull) continue;
+      // a narrow level is bound by its instructions: short rows take short steps
+      ull rest = __ballot(deg > 4u);
+      if (rest == 0ull) {
+        if (__ballot(deg > 2u) != 0ull) alone(std::integral_constant<int, 4>(), 0u);
+        else if (__ballot(deg > 1u) != 0ull) alone(std::integral_constant<int, 2>(), 0u);
+        else alone(std::integral_constant<int, 1>(), 0u);
+        continue;
+      }
       // the wavefront takes the rest of long rows one row after the other, once
       // its lanes have made as many steps past kAlone as there are such rows
       uint32_t done = 0;
-      ull rest;
-      while ((rest = __ballot(done < deg)) != 0ull && done < kAlone + kAtOnce * (uint32_t)__popcll(rest)) {
+      do {
         alone(std::integral_constant<int, kAtOnce>(), done);
         done += kAtOnce;
-      }
+        rest = __ballot(done < deg);
+      } while (rest != 0ull && (done < kAlone || done < kAlone + kAtOnce * (uint32_t)__popcll(rest)));
       for (; rest != 0ull; rest &= rest - 1ull) {
         const int i = __builtin_ctzll(rest);
         const int32_t *row = col + (int64_t)read_lane64((ull)e0, i) + lane;
