@@ -172,10 +172,10 @@ bcd_status bcd_get_config(const bcd_graph *g, bcd_config *cfg);
  * the highest traversed arcs per second: first the batched engine with
  * groups in the powers of two from the largest one <= max_groups / 8 (at
  * least 1) to max_groups, x grid_mult in {8,16,32} (block 256, or 64 on
- * weighted graphs; 2 items per step, top-down), then around the best block
- * 512 (weighted: 128 and 256) and, on unweighted graphs, items 1 and 4,
- * bottom-up levels (16, 4) and the other path-count form (push), then the
- * LDS engine when the graph fits it.  Installs the choice on the graph and
+ * weighted graphs; top-down), then around the best block 512 (weighted: 128
+ * and 256) and, on unweighted graphs, bottom-up levels (16, 4) and the other
+ * path-count form (push; pushed with items 1, 2 and 4), then the LDS engine
+ * when the graph fits it.  Installs the choice on the graph and
  * returns it in *best (and its rate in *gteps, may be NULL).  Results of
  * later calls do not depend on the choice (every engine and setting gives
  * the same per-source values).  Errors: INVALID_ARG (r out of range, RV(r)

@@ -329,6 +329,8 @@ size_t pipelined_batch(const Graph *g, size_t ns, size_t width);
 bcd_status run_pipelined(Graph *g, Workspace *ws, size_t ns, size_t per, const PrepareFn &prepare,
                          const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot, int32_t *width);
 
+// Configurations the autotuner times around `base` (bcd_tune.hip).
+std::vector<bcd_config> tune_around(const bcd_config &base, bool weighted);
 // Query layer (bcd_query.hip).
 bcd_status reach_set(Graph *g, Workspace *ws, int32_t root, bool reverse, std::vector<uint32_t> &bits,
                      int64_t *count, uint8_t *d_lev);

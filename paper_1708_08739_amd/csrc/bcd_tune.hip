@@ -1,5 +1,5 @@
 // Autotuner: measured choice of engine, batch width (column groups), launch
-// shape, items per wavefront step and forward direction per graph.
+// shape, forward direction and form of the path counts per graph.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -8,6 +8,40 @@
 
 #include "../../include/bcd.h"
 #include "bcd_host_internal.h"
+
+namespace bcd {
+
+// Settings tried around the best width and launch shape: block size; for
+// unweighted graphs bottom-up levels, and the other form of the path counts,
+// with its items per step where they are pushed (pulled levels do not read them).
+std::vector<bcd_config> tune_around(const bcd_config &base, bool weighted) {
+  std::vector<bcd_config> around;
+  bcd_config c = base;
+  for (int b : weighted ? std::vector<int>{128, 256} : std::vector<int>{512}) {
+    c.block = b;
+    around.push_back(c);
+  }
+  if (weighted) return around;
+  for (int bu : {16, 4}) {
+    c = base;
+    c.bottom_up = bu;
+    around.push_back(c);
+  }
+  c = base;
+  c.push = 1;
+  for (int it : {1, 2, 4}) {
+    c.items = it;
+    if (!base.push || it != base.items) around.push_back(c);
+  }
+  if (base.push) {
+    c = base;
+    c.push = 0;
+    around.push_back(c);
+  }
+  return around;
+}
+
+}  // namespace bcd
 
 using namespace bcd;
 
@@ -65,8 +99,7 @@ extern "C" bcd_status bcd_autotune(bcd_graph *gh, bcd_vid r, int32_t max_groups,
     return BCD_OK;
   };
   bcd_status rc = BCD_OK;
-  // 1. batch width x grid multiplier (block 256, 64 weighted; 2 items per
-  //    step, top-down)
+  // 1. batch width x grid multiplier (block 256, 64 weighted; top-down)
   bcd_config cand = saved;
   cand.engine = BCD_ENGINE_BATCHED;
   cand.block = g->weighted ? 64 : 256;
@@ -89,31 +122,9 @@ extern "C" bcd_status bcd_autotune(bcd_graph *gh, bcd_vid r, int32_t max_groups,
     }
     if (rc == BCD_OK && widest < 0 && G > 1) break;  // too wide for this device: stop widening
   }
-  // 2. around the best: block size; for unweighted graphs also items per
-  //    step, bottom-up levels and pushed against pulled path counts
+  // 2. around the best
   if (rc == BCD_OK && best_rate >= 0) {
-    const bcd_config base = best_cfg;
-    std::vector<bcd_config> around;
-    bcd_config c = base;
-    for (int b : g->weighted ? std::vector<int>{128, 256} : std::vector<int>{512}) {
-      c.block = b;
-      around.push_back(c);
-    }
-    if (!g->weighted) {
-      for (int it : {1, 4}) {
-        c = base;
-        c.items = it;
-        around.push_back(c);
-      }
-      for (int bu : {16, 4}) {
-        c = base;
-        c.bottom_up = bu;
-        around.push_back(c);
-      }
-      c = base;
-      c.push = 1 - base.push;
-      around.push_back(c);
-    }
+    const std::vector<bcd_config> around = tune_around(best_cfg, g->weighted);
     for (const bcd_config &x : around) {
       double rate = -1.0;
       rc = time_config(x, &rate);

@@ -122,4 +122,11 @@ int bwd_grid(int P, uint32_t H, int block, int grid, const uint32_t *cnt, const 
   return g;
 }
 
+// The autotuner's candidates around base, at most `cap`; returns their number.
+int tune_candidates(const bcd_config *base, int weighted, bcd_config *out, int cap) {
+  const std::vector<bcd_config> v = tune_around(*base, weighted != 0);
+  for (int i = 0; i < (int)v.size() && i < cap; ++i) out[i] = v[(size_t)i];
+  return (int)v.size();
+}
+
 }  // extern "C"

@@ -136,3 +136,24 @@ def test_backward_levels_launch_what_their_items_need(rules, P, H, block):
                     assert g // P * block >= clear
                     need = max(2, 1.5 * (light / nw + 1) + 2, 3 * (8 * heavy / nw + 1) + 3 if heavy else 0, clear / block + 1)
                     assert g // P <= need, (light, heavy, clear)
+
+
+@pytest.mark.parametrize("weighted", [0, 1])
+@pytest.mark.parametrize("push,items", [(0, 1), (0, 2), (1, 2), (1, 4)])
+def test_autotuner_times_no_setting_twice(rules, weighted, push, items):
+    """The candidates around the best one differ from it and from each other in
+    something the kernels read; the pushed form is tried at each items value."""
+    from paper_1708_08739_amd import bcd
+    base = bcd.Config(engine=0, groups=8, block=64 if weighted else 256, grid_mult=32, items=items, bottom_up=0, compress=0,
+                      push=0 if weighted else push)
+    out = (bcd.Config * 32)()
+    k = rules.tune_candidates(C.byref(base), weighted, out, 32)
+
+    def read(c):
+        what = (c.engine, c.groups, c.block, c.grid_mult)
+        return what if weighted else what + (c.bottom_up, c.push, c.items if c.push else 0)
+    seen = [read(c) for c in list(out)[:k]] + [read(base)]
+    assert len(set(seen)) == k + 1
+    if not weighted:
+        assert {s[-1] for s in seen if s[-2] == 1 and s[4] == 0 and s[2] == 256} == {1, 2, 4}
+        assert any(s[-2] == 0 for s in seen) and {s[4] for s in seen} == {0, 4, 16}
