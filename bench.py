@@ -96,9 +96,9 @@ def roofline_from_profile(G, fwd: dict, bwd: dict, ename: str, wname: str, batch
                           probe_copy_gbs: float | None = None):
     """HBM roofline of the dominant pass from the library's kernel profile.
 
-    Bytes: the per-source model (32 per (source, vertex) + 8 per (source,
-    arc) + 8 per (source, DAG arc) in each pass), and the schedule-aware
-    model that counts the graph structure once per work item (64 sources of
+    Bytes: the per-source model (24 and a path count per (source, vertex) + 8
+    per (source, arc) + a count (backward: 8) per (source, DAG arc); a count has
+    4 bytes where it is stored in 4), and the schedule-aware model that counts the graph structure once per work item (64 sources of
     a column group at one vertex and level).  Time: launches of concurrent
     batches overlap on their streams, so `achieved` and `frac` divide by the
     union of the launch intervals (each instant counted once); the

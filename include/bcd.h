@@ -265,7 +265,9 @@ const char *bcd_last_error(void);
 typedef struct bcd_kernel_profile {
   int64_t launches;
   double total_ms;     /* sum of per-launch event durations */
-  double alg_bytes;    /* algorithmic bytes moved by those launches */
+  double alg_bytes;    /* algorithmic bytes moved by those launches, path counts as
+                          stored (4 bytes each in the batched unweighted engine until
+                          one does not fit, else 8) */
   uint64_t vertex_pairs; /* (source, vertex) pairs processed */
   uint64_t arc_pairs;    /* (source, arc) pairs scanned */
   uint64_t dag_pairs;    /* (source, shortest-path-DAG arc) pairs used */
@@ -279,9 +281,9 @@ typedef struct bcd_kernel_profile {
                             (batched unweighted engine; else 0) */
   double sched_bytes;    /* algorithmic bytes with the graph structure counted once
                             per work item instead of once per source: 16 per item
-                            (row offsets) + 4 per item arc (column index) + 16 per
-                            (source, vertex) + 4 per (source, arc) + 8 per (source,
-                            DAG arc); equal to alg_bytes for engines that share
+                            (row offsets) + 4 per item arc (column index) + 8 and a
+                            count per (source, vertex) + 4 per (source, arc) + a count
+                            (backward: 8) per (source, DAG arc); equal to alg_bytes for engines that share
                             nothing across sources; 0 where not counted (weighted) */
 } bcd_kernel_profile;
 

@@ -303,7 +303,9 @@ struct ProfAcc {
   double ms[2] = {0, 0};
   uint64_t items[2] = {0, 0};
   std::vector<std::pair<double, double>> iv[2];  // launch intervals after the graph's profile origin
+  int count_bytes = 0;  // widest stored path count of the batched unweighted engine's batches
   void merge(const ProfAcc &o) {
+    count_bytes = std::max(count_bytes, o.count_bytes);
     for (int k = 0; k < 2; ++k) {
       launches[k] += o.launches[k];
       ms[k] += o.ms[k];

@@ -502,6 +502,7 @@ static bcd_status run_one_batch(Graph *g, Workspace *ws, int k, int ntgt, bool f
     HIPCHK(launch_ctr_fold(S.ctr, kCtrSlots, S.acc, st));
     HIPCHK(hipStreamSynchronize(st));
     if (profiling && prof) {
+      prof->count_bytes = std::max(prof->count_bytes, S.narrow ? 4 : 8);
       for (size_t i = 0; i < ev; ++i) {
         prof->add(g, i < fwd_events ? 0 : 1, ws->events[i].first, ws->events[i].second);
       }
@@ -529,20 +530,21 @@ bcd_status collect_counters(Workspace *ws, uint64_t *ctr /*[C_COUNT]*/, uint64_t
 
 static void add_profile(Graph *g, const ProfAcc &p, const uint64_t *ctr) {
   // Algorithmic bytes (per (source, element) pair, independent of how the
-  // kernels share reads across sources):
-  //   forward : 32 per (source, vertex) + 8 per (source, arc) + 8 per (source, DAG arc)
-  //   backward: 32 per (source, vertex) + 8 per (source, arc) + 8 per (source, DAG arc)
+  // kernels share reads across sources), c the bytes of a stored path count:
+  //   forward : 24 + c per (source, vertex) + 8 per (source, arc) + c per (source, DAG arc)
+  //   backward: 24 + c per (source, vertex) + 8 per (source, arc) + 8 per (source, DAG arc)
   // of which the graph structure is 16 per vertex (its two row offsets) and
   // 4 per arc (its column index).  Counted once per work item (64 sources of
   // a column group at one vertex and level) instead of once per source, the
   // structure gives the schedule-aware figure.
-  const double fb = 32.0 * ctr[C_FWD_VPAIRS] + 8.0 * ctr[C_FWD_APAIRS] + 8.0 * ctr[C_FWD_DPAIRS];
-  const double bb = 32.0 * ctr[C_BWD_VPAIRS] + 8.0 * ctr[C_BWD_APAIRS] + 8.0 * ctr[C_BWD_DPAIRS];
+  const double c = p.count_bytes == 4 ? 4.0 : 8.0;
+  const double fb = (24.0 + c) * ctr[C_FWD_VPAIRS] + 8.0 * ctr[C_FWD_APAIRS] + c * ctr[C_FWD_DPAIRS];
+  const double bb = (24.0 + c) * ctr[C_BWD_VPAIRS] + 8.0 * ctr[C_BWD_APAIRS] + 8.0 * ctr[C_BWD_DPAIRS];
   const bool per_item = ctr[C_FWD_ITEMS] > 0;  // the batched kernels count items on the device
-  const double fs = per_item ? 16.0 * ctr[C_FWD_ITEMS] + 4.0 * ctr[C_FWD_IARCS] + 16.0 * ctr[C_FWD_VPAIRS] +
-                                   4.0 * ctr[C_FWD_APAIRS] + 8.0 * ctr[C_FWD_DPAIRS]
+  const double fs = per_item ? 16.0 * ctr[C_FWD_ITEMS] + 4.0 * ctr[C_FWD_IARCS] + (8.0 + c) * ctr[C_FWD_VPAIRS] +
+                                   4.0 * ctr[C_FWD_APAIRS] + c * ctr[C_FWD_DPAIRS]
                              : fb;
-  const double bs = per_item ? 16.0 * ctr[C_BWD_ITEMS] + 4.0 * ctr[C_BWD_IARCS] + 16.0 * ctr[C_BWD_VPAIRS] +
+  const double bs = per_item ? 16.0 * ctr[C_BWD_ITEMS] + 4.0 * ctr[C_BWD_IARCS] + (8.0 + c) * ctr[C_BWD_VPAIRS] +
                                    4.0 * ctr[C_BWD_APAIRS] + 8.0 * ctr[C_BWD_DPAIRS]
                              : bb;
   g->add_profile(0, p.launches[0], p.ms[0], ctr + C_FWD_VPAIRS, fb, per_item ? ctr[C_FWD_ITEMS] : p.items[0],

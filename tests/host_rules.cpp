@@ -129,4 +129,18 @@ int tune_candidates(const bcd_config *base, int weighted, bcd_config *out, int c
   return (int)v.size();
 }
 
+// Algorithmic and schedule-aware bytes (forward, backward) recorded for a run of
+// the batched unweighted engine whose path counts are stored in `count_bytes`.
+void profile_bytes(int count_bytes, const uint64_t *ctr, double *alg, double *sched) {
+  Graph g;
+  ProfAcc p, other;
+  p.count_bytes = count_bytes;
+  p.merge(other);
+  record_profile(&g, p, ctr);
+  for (int k = 0; k < 2; ++k) {
+    alg[k] = g.prof[k].alg_bytes;
+    sched[k] = g.prof[k].sched_bytes;
+  }
+}
+
 }  // extern "C"

@@ -157,3 +157,18 @@ def test_autotuner_times_no_setting_twice(rules, weighted, push, items):
     if not weighted:
         assert {s[-1] for s in seen if s[-2] == 1 and s[4] == 0 and s[2] == 256} == {1, 2, 4}
         assert any(s[-2] == 0 for s in seen) and {s[4] for s in seen} == {0, 4, 16}
+
+
+@pytest.mark.parametrize("stored,c", [(4, 4), (8, 8), (0, 8)])
+def test_profile_charges_path_counts_as_stored(rules, stored, c):
+    """Bytes of the kernel profile: 4 per path count where rows hold 32 bits,
+    8 where they hold 64 (and in the engines that have no narrow rows)."""
+    ctr = np.zeros(16, dtype=np.uint64)
+    fv, fa, fd, bv, ba, bd = 1000, 20000, 3000, 700, 11000, 900
+    ctr[:6] = fv, fa, fd, bv, ba, bd
+    ctr[12:] = 50, 800, 40, 600  # items and their arcs, forward and backward
+    alg, sched = np.zeros(2), np.zeros(2)
+    rules.profile_bytes(stored, _arr(ctr), _arr(alg), _arr(sched))
+    assert alg.tolist() == [(24 + c) * fv + 8 * fa + c * fd, (24 + c) * bv + 8 * ba + 8 * bd]
+    assert sched.tolist() == [16 * 50 + 4 * 800 + (8 + c) * fv + 4 * fa + c * fd,
+                              16 * 40 + 4 * 600 + (8 + c) * bv + 4 * ba + 8 * bd]
