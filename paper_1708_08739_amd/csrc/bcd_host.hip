@@ -230,17 +230,16 @@ bcd_status Workspace::ensure_batch(int G_) {
   } else {
     STCHK(dalloc(&S.msk, M_COUNT * GN));
   }
-  S.P = default_parts(G);
+  const BatchSizes B(n, G, graph->heavy);
+  S.P = B.P;
   S.NL = lists(S.P);
   S.H = graph->heavy;
-  S.capP = ((uint64_t)GN * 16 + (uint64_t)S.P - 1) / (uint64_t)S.P;
-  // a (group, vertex) is an item at most once per level and on at most 64
-  // levels, so the heavy lists cannot overflow
-  S.capH = (uint64_t)((G + S.P - 1) / S.P) * S.H * kLanes;
-  S.hbase = S.capP * (uint64_t)S.P;
-  STCHK(dalloc(&S.items, S.hbase + S.capH * S.P));
-  STCHK(dalloc(&S.imask, S.hbase + S.capH * S.P));
-  const size_t levels = ((size_t)n + kLevelChunkMax + 4) * kMaxLists;
+  S.capP = B.capP;
+  S.capH = B.capH;
+  S.hbase = B.hbase;
+  STCHK(dalloc(&S.items, B.items));
+  STCHK(dalloc(&S.imask, B.items));
+  const size_t levels = B.levels;
   STCHK(dalloc(&S.cnt, levels));
   STCHK(dalloc(&S.off, levels));
   STCHK(dalloc(&S.tail, (size_t)4 * kMaxLists * kTailStride));

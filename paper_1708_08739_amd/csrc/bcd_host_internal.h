@@ -96,6 +96,42 @@ inline int default_groups(int64_t n, bool weighted) {
   return (int)g;
 }
 
+// Sizes of a batch workspace of G column groups on an n-vertex graph with H
+// heavy vertices: list and queue capacities as the workspace lays them out, and
+// the device bytes of all its arrays.
+struct BatchSizes {
+  uint64_t GN, n;
+  int G, P;
+  uint64_t capP, capH, hbase, items;     // item lists (BatchState)
+  uint64_t capQ, capQH, qhbase, qsize;   // relaxation queues, weighted graphs
+  uint64_t levels;                       // (level, list) rows
+  BatchSizes(int64_t n_, int G_, uint32_t H) {
+    G = G_;
+    n = (uint64_t)n_;
+    GN = (uint64_t)G * n;
+    P = default_parts(G);
+    const uint64_t parts = (uint64_t)P, per = ((uint64_t)G + parts - 1) / parts;  // groups of a partition
+    capP = (GN * 16 + parts - 1) / parts;
+    // a (group, vertex) is an item at most once per level and on at most 64
+    // levels, so the heavy lists cannot overflow
+    capH = per * H * kLanes;
+    hbase = capP * parts;
+    items = hbase + capH * parts;
+    capQ = per * n;
+    capQH = per * H;
+    qhbase = capQ * parts;
+    qsize = qhbase + capQH * parts;
+    levels = (n + kLevelChunkMax + 4) * kMaxLists;
+  }
+  uint64_t bytes(bool weighted, int64_t m) const {
+    const uint64_t g = (uint64_t)G;
+    uint64_t b = GN * kLanes * 16 + items * 12 + levels * 12 + n * 4;          // counts, psi, items, rows, targets
+    b += g * kLanes * 28 + g * 16 + (uint64_t)kCtrSlots * C_COUNT * 8 + 4096;  // results, staging, counters
+    if (!weighted) return b + GN * M_COUNT * 8;
+    return b + GN * (kLanes * 8 + 64) + qsize * 16 + g * (uint64_t)m * 8 + 4096;  // distances, masks, queues
+  }
+};
+
 struct Graph;
 
 struct Workspace {

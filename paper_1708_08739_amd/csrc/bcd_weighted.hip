@@ -771,11 +771,11 @@ bcd_status Workspace::ensure_weighted() {
   if (weighted_ready && weighted_G == G) return BCD_OK;
   release_weighted();
   const size_t GN = (size_t)G * (size_t)n;
-  const size_t per = (size_t)((G + S.P - 1) / S.P);  // groups of a partition
-  S.capQ = per * (size_t)n;
-  S.capQH = per * S.H;
-  S.qhbase = S.capQ * S.P;
-  S.qsize = S.qhbase + S.capQH * S.P;
+  const BatchSizes B(n, G, S.H);
+  S.capQ = B.capQ;
+  S.capQH = B.capQH;
+  S.qhbase = B.qhbase;
+  S.qsize = B.qsize;
   STCHK(walloc(&S.wd, GN * kLanes));
   STCHK(walloc(&S.wc, GN * kLanes));
   STCHK(walloc(&S.chg, 3 * GN));

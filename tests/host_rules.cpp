@@ -143,4 +143,13 @@ void profile_bytes(int count_bytes, const uint64_t *ctr, double *alg, double *sc
   }
 }
 
+uint64_t workspace_bytes(int64_t n, int64_t m, uint32_t heavy, int weighted, int groups) {
+  Graph g;
+  g.n = n;
+  g.m = m;
+  g.heavy = heavy;
+  g.weighted = weighted != 0;
+  return batch_workspace_bytes(&g, groups);
+}
+
 }  // extern "C"

@@ -175,3 +175,25 @@ def test_server_rmat22_serving_config(B, oracle):
         want, _ = oracle.bc_sampled(g, r, 12, 7 + i)
         got = alone[("s", r)]
         assert abs(got - want) <= 1e-10 * abs(want) and (got == 0) == (want == 0), (r, got, want)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_server_workspaces_take_the_bytes_reported(B, weighted):
+    """Creating a server takes the device memory bcd_server_workspace_bytes
+    reports, to 1 % (allocation granularity, the planner's bitmap and queues)."""
+    import ctypes as C
+    g = gg.rmat(17, 8, seed=9, weighted=weighted, max_weight=50)
+    G = B.Graph.from_digraph(g)
+    hip = C.CDLL(next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln))
+
+    def free():
+        f, t = C.c_size_t(), C.c_size_t()
+        assert hip.hipMemGetInfo(C.byref(f), C.byref(t)) == 0
+        return f.value
+    want = B.Server.workspace_bytes(G, groups=33, workers=2)
+    before = free()
+    with_server = B.Server(G, workers=2, groups=33)
+    taken = before - free()
+    with_server.close()
+    print("workspaces", weighted, want, taken, flush=True)
+    assert abs(taken - want) <= 0.01 * want

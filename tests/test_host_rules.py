@@ -172,3 +172,18 @@ def test_profile_charges_path_counts_as_stored(rules, stored, c):
     assert alg.tolist() == [(24 + c) * fv + 8 * fa + c * fd, (24 + c) * bv + 8 * ba + 8 * bd]
     assert sched.tolist() == [16 * 50 + 4 * 800 + (8 + c) * fv + 4 * fa + c * fd,
                               16 * 40 + 4 * 600 + (8 + c) * bv + 4 * ba + 8 * bd]
+
+
+@pytest.mark.parametrize("n,m,G", [(1 << 20, 1 << 24, 64), (4097, 50_000, 3), (1 << 18, 1 << 22, 5)])
+def test_workspace_bytes_count_the_heavy_lists(rules, n, m, G):
+    """The bytes a server's budget is checked against hold the heavy vertices'
+    item lists (64 items of 12 bytes a group) and queue entries (4 of 4 bytes),
+    and every per-level and per-vertex array."""
+    f = rules.workspace_bytes
+    f.argtypes, f.restype = [C.c_int64, C.c_int64, C.c_uint32, C.c_int, C.c_int], C.c_uint64
+    H = n // 256
+    assert f(n, m, H, 0, G) - f(n, m, 0, 0, G) >= G * H * 64 * 12
+    assert f(n, m, H, 1, G) - f(n, m, 0, 1, G) >= G * H * (64 * 12 + 16)
+    rows = G * n * 64 * 16 + G * n * 16 * 12 + 4 * n * 12 + 4 * n
+    assert rows + 72 * G * n <= f(n, m, 0, 0, G) <= rows + 72 * G * n + (4 << 20)
+    assert rows + G * n * (64 * 8 + 64 + 16) + 8 * G * m <= f(n, m, 0, 1, G)
