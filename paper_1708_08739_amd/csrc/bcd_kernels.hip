@@ -197,11 +197,14 @@ __global__ void k_publish_counts(BatchState S, int level) {
 // TB/s fetched).  A level with two items a step, 64-byte mask records and no
 // heavy list took, summed over the levels of R-MAT 16 / 20 with 1,000 sources,
 // 3.0 / 36 ms; as here 1.9 / 24.
-// 8 waves per SIMD (64 VGPRs): left alone the compiler takes 88 registers for 5
-// (R-MAT 16 exact with narrow rows, 5 / 6 / 7 / 8 waves: 38.7 / 36.6 / 35.9 /
-// 35.4 ms; four or six rows at a time instead of eight 35.5 / 35.9).
+// Narrow rows at 8 waves per SIMD (64 VGPRs, 60 bytes of scratch a lane): left
+// alone the compiler takes 88 registers for 5 (R-MAT 16 exact, 5 / 6 / 7 / 8 waves:
+// 38.7 / 36.6 / 35.9 / 35.4 ms; four or six rows at a time instead of eight 35.5 /
+// 35.9).  64-bit rows at 6 (80 VGPRs, no scratch): on a graph with counts above
+// 2^32, R-MAT 16 exact at 4 / 5 / 6 / 7 / 8 waves 49.7 / 49.8 / 48.6 / 48.5 / 51.2 ms,
+// layers of 30,000 vertices with 1,000 sources 23.8 / 24.0 / 23.6 / 24.3 / 25.2.
 template <int BLOCK, class T>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fwd_level(DevGraph G, BatchState S, int level) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 6, 8))) void k_fwd_level(DevGraph G, BatchState S, int level) {
   constexpr int NW = BLOCK / 64;
   const uint32_t n = (uint32_t)S.n;
   const uint64_t GN = (uint64_t)S.G * n;
