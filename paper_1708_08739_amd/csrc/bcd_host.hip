@@ -9,7 +9,6 @@
 
 #include <algorithm>
 #include <atomic>
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -48,11 +47,6 @@ bcd_status fail_static(bcd_status s, const char *msg) {
 
 bcd_status hip_fail(hipError_t e, const char *what) {
   return fail(BCD_ERR_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
-}
-
-
-static double now_s() {
-  return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
 // ------------------------------------------------------------ device

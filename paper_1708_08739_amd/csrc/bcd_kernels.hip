@@ -147,20 +147,6 @@ static __device__ __forceinline__ ull wave_or(ull x) {
   return out;
 }
 
-// Discovery over one chunk of out-arc lanes: `dag` = the item's lanes not yet
-// seen at head w (0 on lanes without an arc).  One atomicOr marks them seen;
-// the lanes it was the first to set are on the next level, and the first
-// wavefront to flag (g, w) there appends it.  Returns whether this lane's
-// head is to be appended.
-static __device__ __forceinline__ bool discover(ull *seen, ull *next, uint32_t w, ull dag) {
-  bool enq = false;
-  if (dag != 0ull) {
-    const ull fresh = dag & ~atomicOr(&seen[w], dag);
-    if (fresh != 0ull) enq = atomicOr(&next[w], fresh) == 0ull;
-  }
-  return enq;
-}
-
 __global__ void k_publish_counts(BatchState S, int level) {
   const int l = (int)threadIdx.x;
   if (l < S.NL) S.cnt[(uint64_t)level * S.NL + l] = *tail_at(S, level, l);
@@ -210,7 +196,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sizeof(T)
   const uint64_t GN = (uint64_t)S.G * n;
   const int P = S.P, NL = S.NL;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t lrow = (uint64_t)level * NL, nrow = lrow + NL;
+  const uint64_t lrow = (uint64_t)level * NL;
   __shared__ uint32_t stage_all[NW * kStage], hstage_all[NW * kStageHeavy];
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
@@ -529,7 +515,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
   const uint64_t n = (uint64_t)S.n;
   const int P = S.P, NL = S.NL;
   const PartView pv = part_view<BLOCK>(P);
-  const uint64_t lrow = (uint64_t)level * NL, nrow = lrow + NL;
+  const uint64_t lrow = (uint64_t)level * NL;
   __shared__ uint32_t stage_all[(BLOCK / 64) * kStage], hstage_all[(BLOCK / 64) * kStageHeavy];
   const int wv = threadIdx.x >> 6;
   Stage sg = {stage_all + wv * kStage, hstage_all + wv * kStageHeavy, 0, 0};
