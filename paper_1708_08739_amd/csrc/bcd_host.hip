@@ -697,6 +697,7 @@ bcd_status bcd_graph_load_csr(int64_t n, int64_t m, const int64_t *row_ptr, cons
     for (int64_t v = 0; v < n; ++v) {
       deg[(size_t)v] = (uint32_t)(row_ptr[v + 1] - row_ptr[v] + irp[v + 1] - irp[v]);
       top = std::max(top, deg[(size_t)v]);
+      g->longest_row = std::max(g->longest_row, row_ptr[v + 1] - row_ptr[v]);
     }
     std::vector<int64_t> at((size_t)top + 1, 0);  // at[d]: vertices of degree > d, and those of d placed so far
     for (int64_t v = 0; v < n; ++v) at[deg[(size_t)v]]++;

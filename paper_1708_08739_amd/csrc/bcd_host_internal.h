@@ -234,6 +234,7 @@ struct Graph {
   // the same graph in internal ids (DevGraph): rank[v] = internal id of v
   std::vector<int32_t> rank;
   uint32_t heavy = 0;          // internal ids below are heavy
+  int64_t longest_row = 0;     // arcs of the vertex with the most out-arcs
   int64_t *d_prp = nullptr;
   int32_t *d_pcol = nullptr;
   int64_t *d_pirp = nullptr;
@@ -391,6 +392,8 @@ uint64_t batch_workspace_bytes(const Graph *g, int groups);
 // LDS engine (bcd_lds.hip): one workgroup per source at a time, state in LDS.
 size_t lds_bytes_for(int64_t n);
 bool lds_fits(const Graph *g);
+// Whether the LDS engine takes a row's arcs one at a time.
+bool lds_short_rows(const Graph *g);
 // Whether a traversal of at least `levels` levels goes to one workgroup (n < 2^16,
 // visited bits and queue in LDS) instead of a launch per level.
 bool reach_one_workgroup(const Graph *g, int64_t levels);

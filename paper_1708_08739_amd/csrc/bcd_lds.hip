@@ -71,8 +71,16 @@ struct LdsArgs {
 // / 384 / 512: 150 / 140 / 135 / 147 / 170 (five workgroups a CU either way); 2 / 3 /
 // 4 / 6 / 8 arcs at a time at 256: 144 / 142 / 140 / 144 / 156.
 constexpr int kAhead = 4;
+// Where no row has more than kShortRow arcs levels are narrow and bound by their
+// instructions instead: one arc at a time and 256 threads.  Every source, ms, with
+// four at a time / one: a cycle of 1,500 vertices 4.78 / 2.81, a path of 2,000 both
+// ways (rows of 2) 5.50 / 4.76, a binary tree both ways (rows of 3) 0.561 / 0.571, a
+// 3 x 600 grid both ways (rows of 4) 2.36 / 2.88.
+constexpr int64_t kShortRow = 2;
+constexpr int kShortRowBlock = 256;
+bool lds_short_rows(const Graph *g) { return g->longest_row <= kShortRow; }
 
-template <int BLOCK>
+template <int BLOCK, int AHEAD>
 __global__ __launch_bounds__(BLOCK) void k_lds_pass(uint32_t n, const uint32_t *__restrict__ rp,
                                                     const uint16_t *__restrict__ col, LdsArgs A) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -119,32 +127,32 @@ __global__ __launch_bounds__(BLOCK) void k_lds_pass(uint32_t n, const uint32_t *
         const uint32_t e1 = rp[v + 1];
         uint32_t e = rp[v];
         my_m += (uint64_t)(e1 - e);
-        for (; e < e1; e += kAhead) {
-          uint32_t w[kAhead], d[kAhead], old[kAhead];
-          ull o[kAhead];
+        for (; e < e1; e += AHEAD) {
+          uint32_t w[AHEAD], d[AHEAD], old[AHEAD];
+          ull o[AHEAD];
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j) w[j] = col[min(e + j, e1 - 1)];
+          for (int j = 0; j < AHEAD; ++j) w[j] = col[min(e + j, e1 - 1)];
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j) d[j] = e + j < e1 ? dist[w[j]] : 0u;
+          for (int j = 0; j < AHEAD; ++j) d[j] = e + j < e1 ? dist[w[j]] : 0u;
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j) {
+          for (int j = 0; j < AHEAD; ++j) {
             old[j] = 0u;
             if (d[j] == kUnseen) old[j] = atomicCAS(&dist[w[j]], kUnseen, level + 1);
           }
           // claimed here (old unseen), claimed by another arc meanwhile, or
           // found on level + 1 (level + 1 > 0, so a lane without an arc is not)
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j) {
+          for (int j = 0; j < AHEAD; ++j) {
             if (d[j] == kUnseen && old[j] == kUnseen) queue[qe + atomicAdd(add, 1u)] = (uint16_t)w[j];
             if (d[j] == kUnseen) d[j] = level + 1;  // nothing else is claimed in this level
           }
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j) {
+          for (int j = 0; j < AHEAD; ++j) {
             o[j] = 0ull;
             if (d[j] == level + 1) o[j] = atomicAdd(&sig[w[j]], sv);
           }
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j)
+          for (int j = 0; j < AHEAD; ++j)
             if (d[j] == level + 1) {
               my_ovf |= o[j] + sv < o[j];  // the exact sum passed 2^64 - 1
               ++my_a;
@@ -198,18 +206,18 @@ __global__ __launch_bounds__(BLOCK) void k_lds_pass(uint32_t n, const uint32_t *
           const ull sw = sig[v];
           double acc = 0.0;
           const uint32_t e1 = rp[v + 1];
-          for (uint32_t e = rp[v]; e < e1; e += kAhead) {
-            uint32_t w[kAhead], d[kAhead];
-            ull x[kAhead];
+          for (uint32_t e = rp[v]; e < e1; e += AHEAD) {
+            uint32_t w[AHEAD], d[AHEAD];
+            ull x[AHEAD];
 #pragma unroll
-            for (int j = 0; j < kAhead; ++j) w[j] = col[min(e + j, e1 - 1)];
+            for (int j = 0; j < AHEAD; ++j) w[j] = col[min(e + j, e1 - 1)];
 #pragma unroll
-            for (int j = 0; j < kAhead; ++j) {
+            for (int j = 0; j < AHEAD; ++j) {
               d[j] = dist[w[j]];
               x[j] = sig[w[j]];
             }
 #pragma unroll
-            for (int j = 0; j < kAhead; ++j)  // arc order
+            for (int j = 0; j < AHEAD; ++j)  // arc order
               if (e + j < e1 && d[j] == (uint32_t)lv + 1u) acc += __longlong_as_double((long long)x[j]);
           }
           const double sv = (double)sw;
@@ -441,8 +449,10 @@ static bcd_status lds_launch(Graph *g, Workspace *ws, const int32_t *src, int64_
   A.xdel = xdel;
   const size_t shm = lds_bytes_for(g->n);
   // allow dynamic LDS up to the size lds_fits checked (a no-op below 64 KiB)
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_lds_pass<kLdsBlock>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+  const bool short_rows = lds_short_rows(g);
+  const auto kernel = short_rows ? &k_lds_pass<kShortRowBlock, 1> : &k_lds_pass<kLdsBlock, kAhead>;
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
+      hipSuccess)
     (void)hipGetLastError();
   // as many workgroups as fit on the CUs at once (LDS-bound), each taking
   // sources in turn
@@ -450,7 +460,8 @@ static bcd_status lds_launch(Graph *g, Workspace *ws, const int32_t *src, int64_
   const int grid = (int)std::min<int64_t>(k, (int64_t)g->cus * per_cu);
   const bool timed = ms != nullptr;
   if (timed) HIPCHK(hipEventRecord(ws->event_pair(0).first, st));
-  hipLaunchKernelGGL(k_lds_pass<kLdsBlock>, dim3(grid), dim3(kLdsBlock), shm, st, (uint32_t)g->n, g->d_lrp, g->d_lcol, A);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(short_rows ? kShortRowBlock : kLdsBlock), shm, st, (uint32_t)g->n, g->d_lrp,
+                     g->d_lcol, A);
   HIPCHK(hipGetLastError());
   if (timed) HIPCHK(hipEventRecord(ws->event_pair(0).second, st));
   HIPCHK(hipMemcpyAsync(hb, db + in_bytes, out_bytes, hipMemcpyDeviceToHost, st));

@@ -152,4 +152,10 @@ uint64_t workspace_bytes(int64_t n, int64_t m, uint32_t heavy, int weighted, int
   return batch_workspace_bytes(&g, groups);
 }
 
+int short_rows(int64_t longest) {
+  Graph g;
+  g.longest_row = longest;
+  return lds_short_rows(&g);
+}
+
 }  // extern "C"

@@ -1192,3 +1192,32 @@ def test_loaded_arrays_of_every_engine(B, oracle, n, m, wmax):
         for s, w in zip(src, want):
             d, sg, dl = G.source_pass(s)
             assert np.array_equal(d, w[0]) and np.array_equal(sg, w[1]) and close(dl, w[2]), (engine, s)
+
+
+@pytest.mark.parametrize("rows", [1, 2, 3])
+def test_lds_engine_on_short_rows(B, oracle, rows):
+    """The LDS engine on graphs whose longest row has 1, 2 and 3 arcs (a cycle, a
+    path both ways, a tree both ways): passes against the oracle and the batched
+    engine's bits, counters, and an exact score's closed form."""
+    if rows == 1:
+        g = gg.directed_cycle(700)
+    elif rows == 2:
+        g = gg.bidirected_path(700)
+    else:
+        i = np.arange(1, 1023)
+        g = gg.from_arcs(1023, np.concatenate([i, (i - 1) // 2]), np.concatenate([(i - 1) // 2, i]), name="tree")
+    assert int(np.diff(g.row_ptr).max()) == rows
+    G, H = dev(B, g, engine=B.BCD_ENGINE_LDS), dev(B, g)
+    src = [0, 1, g.n // 2, g.n - 1]
+    d, sg, dl = G.multi_source_pass(src)
+    for i, s in enumerate(src):
+        od, osg, odl, _, _ = oracle.source_pass(g, s)
+        assert np.array_equal(d[i], od) and np.array_equal(sg[i], osg) and close(dl[i], odl), (rows, s)
+    assert np.array_equal(dl, H.multi_source_pass(src)[2])
+    every = list(range(g.n))
+    dep, cnt = G.dependencies(3, every, counters=True)
+    hdep, hcnt = H.dependencies(3, every, counters=True)
+    assert np.array_equal(dep, hdep) and np.array_equal(cnt, hcnt)
+    want = {1: (g.n - 1) * (g.n - 2) / 2, 2: 2 * 300 * (g.n - 301), 3: None}[rows]
+    got, _ = G.bc_exact(300)
+    assert got == H.bc_exact(300)[0] and (want is None or got == want)

@@ -187,3 +187,8 @@ def test_workspace_bytes_count_the_heavy_lists(rules, n, m, G):
     rows = G * n * 64 * 16 + G * n * 16 * 12 + 4 * n * 12 + 4 * n
     assert rows + 72 * G * n <= f(n, m, 0, 0, G) <= rows + 72 * G * n + (4 << 20)
     assert rows + G * n * (64 * 8 + 64 + 16) + 8 * G * m <= f(n, m, 0, 1, G)
+
+
+def test_lds_engine_takes_short_rows_alone(rules):
+    """The LDS engine takes arcs one at a time where no row has more than two."""
+    assert [rules.short_rows(C.c_int64(k)) for k in (0, 1, 2, 3, 4, 5000)] == [1, 1, 1, 0, 0, 0]
