@@ -260,7 +260,7 @@ const char *bcd_last_error(void);
 /* ------------------------------------------------------------ profiling
  * When enabled, every launch of the traversal kernels is bracketed by HIP
  * events on its own stream, and the algorithmic byte counts of each launch
- * are accumulated (see DESIGN notes in the source).  kind: 0 = forward
+ * are accumulated.  kind: 0 = forward
  * level kernel, 1 = backward level kernel. */
 typedef struct bcd_kernel_profile {
   int64_t launches;

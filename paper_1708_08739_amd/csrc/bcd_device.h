@@ -269,10 +269,11 @@ static __device__ __forceinline__ PartView part_view(int P) {
 // How a partition's workgroups are dealt between its two lists: the first
 // third takes heavy items (at least one workgroup, when the graph has any; a
 // partition has at least two then), the others light ones, each side striding
-// over its list.  Separate workgroups keep the two loops' registers apart, and
-// with a third of them the heavy items, which take longest, start first and
-// end with the light ones (R-MAT 20, 1,000 sources: an eighth 54.1 ms, half
-// 50.0, a third 48.3).
+// over its list.  A workgroup is on one side only, so that a barrier of a heavy
+// item is met by all its wavefronts; the registers are the kernel's, those of
+// both sides.  With a third of the workgroups the heavy items, which take
+// longest, start first and end with the light ones (R-MAT 20, 1,000 sources: an
+// eighth 54.1 ms, half 50.0, a third 48.3).
 struct ListView {
   bool heavy;            // this workgroup's side
   uint64_t wg, nwg;      // its index among that side's workgroups, and their number

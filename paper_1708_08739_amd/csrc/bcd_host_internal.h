@@ -45,8 +45,12 @@ constexpr int kCtrSlots = 8192;       // max workgroups of a traversal launch
 constexpr int kLevelChunkMax = 64;    // level launches enqueued between host checks
 constexpr int kDefaultItems = 2;      // frontier items per wavefront step, pushed levels
 // Bottom-up threshold denominator of the unweighted forward (0: top-down
-// only).  Bottom-up levels pay on large graphs (R-MAT 20 and 22, acyclic
-// R-MAT 20: +4 to +14 %) and cost a little on small ones (R-MAT 16: -4 %).
+// only).  ms without / with bottom-up levels at 1/4, 1,000 sources: R-MAT 20 32.2 /
+// 28.7, 19 15.7 / 14.0, 18 8.2 / 7.7, 17 5.9 / 4.9, 16 2.46 / 2.58 (exact 36.9 /
+// 32.1), uniform graphs of 500,000 vertices 29.6 / 17.5, of 100,000 7.5 / 4.2, layers
+// of 30,000 vertices (360,000 in all) 23.7 / 24.6.  The line lies where the
+// kernels before these had it (R-MAT 16 then lost 4 %); it is part of the
+// interface's default, so a smaller graph that gains sets bottom_up itself.
 inline int default_bottom_up(int64_t n) { return n >= (int64_t(1) << 19) ? 4 : 0; }
 // Top-down levels of the unweighted forward add path counts along DAG arcs
 // (1) instead of pulling them over in-arcs (0).

@@ -6,7 +6,8 @@
 // Batched engine layout: a column group is 64 sources, one per wavefront
 // lane.  A frontier item is (group g, vertex v) with a 64-bit mask of the
 // lanes for which v sits on the current BFS level; lane b works for source b,
-// so the 64 path counts of v are one coalesced 512-byte row, and testing "has
+// so the 64 path counts of v are one coalesced row of 256 bytes (512 where a
+// count does not fit 32 bits), and testing "has
 // source b already settled w" for all 64 sources reads one 64-bit word per
 // arc.
 #include <algorithm>
@@ -166,8 +167,8 @@ __global__ void k_publish_counts(BatchState S, int level) {
 // found by k_bu_level (which pulled the counts), and step 2 when level+1 will
 // be; the item masks are recorded for the backward either way.
 //
-// Light items: a wavefront takes a block of up to 64, loads their masks and
-// row bounds with a lane per item, then takes them one after the other in
+// Light items: a wavefront takes a block of up to kBlockItems, loads their masks
+// and row bounds with a lane per item, then takes them one after the other in
 // steps of 32 in-arcs (lower half of the wavefront) and 32 out-arcs (upper
 // half), one gather bringing the words of all of them.  The arc ends of the
 // step after next and the words of the next one are loaded while the current
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6, 8))) v
       dn[t] = (read_lane64(dnr, ld) | (is_tgt ? mt[t] : 0ull)) & mt[t];
       sv[t] = ((mt[t] >> lane) & 1ull) ? S.sig[(uint64_t)read_lane(it, ld) * kLanes + lane] : 0ull;
     }
-    // first chunk of every slot's out-arcs: heads, their records, the flags
+    // first chunk of every slot's out-arcs: heads, their masks, the flags
     const int64_t mo = e0 + sl;
     uint32_t w = 0;
     ull push = 0ull;
@@ -928,7 +929,7 @@ struct PsiRows {
 // their lanes.  No atomics: every sum runs in arc order, so results are
 // bit-reproducible.  The masks rotate over three words: written (level), read
 // (level+1) and cleared (level+2).
-// Light items are taken in blocks of up to 64 as in the forward (a lane per
+// Light items are taken in blocks as in the forward (a lane per
 // item loads what is needed of it; items without lanes are passed over), each
 // with the whole wavefront over its out-arcs, the next item's arc ends loaded
 // ahead.  Heavy items are dealt to wavefronts by eight sources, lanes over
@@ -1167,8 +1168,8 @@ __global__ __launch_bounds__(BLOCK) void k_bwd_level(DevGraph G, BatchState S, i
 // reset: every lane's count is written before anything reads it, and only
 // lanes named by a mask are ever read.)  A wavefront per item, lanes over
 // the 64 counts of its row; an item repeated on several levels clears the
-// row again or finds the record already cleared, and either way every
-// settled lane is zeroed by the first wavefront that read the record.
+// row again or finds the masks already cleared, and either way every
+// settled lane is zeroed by the first wavefront that read the masks.
 __global__ void k_batch_cleanup(BatchState S, PartTotals tot) {
   const int lane = lane_id();
   const uint64_t GN = (uint64_t)S.G * (uint64_t)S.n;
