@@ -46,9 +46,9 @@ import numpy as np  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
 
-# HBM bytes per launch measured with rocprofv3 counters (FETCH_SIZE and
-# WRITE_SIZE, each scaled by what it reads for a copy kernel of known size),
-# valid only while the sources of the kernels hash to the recorded value.
+# Bytes per launch between the L2s and memory, measured with rocprofv3 counters
+# (read requests by size, and WRITE_SIZE), valid only while the sources of the
+# kernels hash to the recorded value.  What the Infinity Cache answers is in them.
 TRAFFIC_FILES = {"k_fwd_level": ["profiles/k_fwd_level_rmat16_ef8.md"],
                  "k_fwd_level+k_bu_level": ["profiles/k_fwd_level_rmat22_serving.md",
                                             "profiles/k_fwd_level_rmat20_set.md"],
@@ -72,7 +72,7 @@ def kernel_sources_sha256(kernel: str = "k_fwd_level") -> str:
 
 
 def measured_traffic(kernel: str, workload_name: str, batch_width: int):
-    """Counter-measured HBM bytes per launch of `kernel` on `workload_name` at
+    """Counter-measured memory bytes per launch of `kernel` on `workload_name` at
     `batch_width` sources per batch, or None when none were taken at that
     width or the kernel sources changed since."""
     rec = {}
@@ -99,11 +99,14 @@ def roofline_from_profile(G, fwd: dict, bwd: dict, ename: str, wname: str, batch
     Bytes: the per-source model (24 and a path count per (source, vertex) + 8
     per (source, arc) + a count (backward: 8) per (source, DAG arc); a count has
     4 bytes where it is stored in 4), and the schedule-aware model that counts the graph structure once per work item (64 sources of
-    a column group at one vertex and level).  Time: launches of concurrent
+    a column group at one vertex and level).  The per-source model is no lower
+    bound on what moves: 64 sources share a read of an arc or a record, so
+    `achieved` and `frac` can exceed the memory's bandwidth (`model` says so in
+    the line); what moves is `traffic`.  Time: launches of concurrent
     batches overlap on their streams, so `achieved` and `frac` divide by the
     union of the launch intervals (each instant counted once); the
     per-launch figures divide by the summed durations.  `traffic` is the
-    counter-measured HBM bytes per launch recorded in profiles/ for this
+    counter-measured memory bytes per launch recorded in profiles/ for this
     workload and width, or None.  `probe_gbs` is the measured streaming-read
     bandwidth (the traversal kernels' traffic is mostly reads), the
     achievable reference for the probe-relative fractions."""
@@ -130,6 +133,7 @@ def roofline_from_profile(G, fwd: dict, bwd: dict, ename: str, wname: str, batch
     per_launch_s = dom["total_ms"] * 1e-3 / dom["launches"]
     out = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4),
+           "model": "achieved/frac price each source alone; a batch of 64 shares reads and can exceed 1",
            "traffic": None if traffic is None else round(traffic, 1),
            "kernel": kname,
            "launches": dom["launches"], "avg_launch_us": round(per_launch_s * 1e6, 2),
