@@ -304,6 +304,9 @@ struct SourceRun {
   std::vector<uint64_t> counters;   // [ns][3] when requested
   uint64_t te = 0, reached = 0, dag = 0;
   int32_t width = 0;
+  // sources of the run that this one is a timing sample of (0: none): its second
+  // workspace is then as wide as that run's, so that it is had where that run has it
+  size_t sample_of = 0;
 };
 
 struct TargetMap {
@@ -364,12 +367,15 @@ using StripeFn = std::function<bcd_status(Workspace *ws, size_t first, size_t st
 // Readies a workspace for batches of `groups` column groups.
 using PrepareFn = std::function<bcd_status(Workspace *ws, int groups)>;
 size_t pipelined_batch(const Graph *g, size_t ns, size_t width);
+// Column groups of the second workspace of a run of ns sources, a sample of a run
+// of `sample_of` (0: none), batches at most `width` sources wide; 0: one batch.
+int second_groups(const Graph *g, size_t ns, size_t sample_of, size_t width);
 // Runs `stripe` over the batches of `per` sources each; when the run has more
-// than one and a second workspace can be had (`prepare` readies it, as wide as
-// such a batch), every other batch goes to that workspace on a helper thread,
+// than one and a second workspace of `share` groups (second_groups) can be had
+// (`prepare` readies it), every other batch goes to that workspace on a helper thread,
 // else whole batches run on ws.  The second workspace's counters are added to
 // `tot`; *width receives the sources per batch that ran.
-bcd_status run_pipelined(Graph *g, Workspace *ws, size_t ns, size_t per, const PrepareFn &prepare,
+bcd_status run_pipelined(Graph *g, Workspace *ws, size_t per, int share, const PrepareFn &prepare,
                          const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot, int32_t *width);
 
 // Configurations the autotuner times around `base` (bcd_tune.hip).

@@ -618,13 +618,19 @@ size_t pipelined_batch(const Graph *g, size_t ns, size_t width) {
   return (groups + nb - 1) / nb * kLanes;
 }
 
-bcd_status run_pipelined(Graph *g, Workspace *ws, size_t ns, size_t per, const PrepareFn &prepare,
+int second_groups(const Graph *g, size_t ns, size_t sample_of, size_t width) {
+  const size_t per = pipelined_batch(g, ns, width);
+  if (ns <= per) return 0;
+  const size_t of = sample_of > ns ? pipelined_batch(g, sample_of, width) : per;
+  return (int)((std::max(per, of) + kLanes - 1) / kLanes);
+}
+
+bcd_status run_pipelined(Graph *g, Workspace *ws, size_t per, int share, const PrepareFn &prepare,
                          const StripeFn &stripe, ProfAcc &prof, bool &ovf, uint64_t *tot, int32_t *width) {
   std::unique_ptr<Lease> ls2;
   Workspace *ws2 = nullptr;
   *width = (int32_t)((size_t)ws->G * kLanes);
-  if (ns > per) {
-    int share = (int)((per + kLanes - 1) / kLanes);
+  if (share > 0) {
     ls2.reset(new (std::nothrow) Lease(g, share, ws->G));
     bool room = ls2 && ls2->ok() && (*ls2)->batch_ready && (*ls2)->G >= share && (*ls2)->G <= ws->G &&
                 (!g->weighted || (*ls2)->weighted_ready);
@@ -710,7 +716,8 @@ static bcd_status run_batched(Graph *g, Workspace *ws, const std::vector<int32_t
     auto stripe = [&](Workspace *w, size_t first, size_t stride, ProfAcc &p, bool &o) -> bcd_status {
       return run_batch_stripe(g, w, src, ord, tgt, first, stride, per, out.dep, p, o);
     };
-    STCHK(run_pipelined(g, ws, ns, per, prepare, stripe, prof, ovf, tot, &out.width));
+    STCHK(run_pipelined(g, ws, per, second_groups(g, ns, out.sample_of, G64), prepare, stripe, prof, ovf, tot,
+                        &out.width));
   }
   // counters per source need one source per batch
   TargetMap tm;

@@ -82,6 +82,7 @@ extern "C" bcd_status bcd_autotune(bcd_graph *gh, bcd_vid r, int32_t max_groups,
     if (!ls.ok()) return fail(BCD_ERR_OUT_OF_MEMORY, "workspace allocation failed");
     STCHK(ls->init_common(g));
     SourceRun warm, run;
+    run.sample_of = rv.size();  // a width whose second workspace the device has no room for runs alone here too
     std::vector<int32_t> head(sample.begin(), sample.begin() + std::min<size_t>(sample.size(), 64));
     bcd_status rc = run_sources(g, ls.w.get(), head, tgt, false, warm);
     if (rc == BCD_ERR_OUT_OF_MEMORY) return BCD_OK;

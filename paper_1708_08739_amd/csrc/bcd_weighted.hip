@@ -1031,7 +1031,7 @@ bcd_status run_weighted(Graph *g, Workspace *ws, const std::vector<int32_t> &src
       STCHK(w->ensure_weighted());
       return w->ensure_res((size_t)std::max(ntgt, 1) * (size_t)groups * kLanes);
     };
-    STCHK(run_pipelined(g, ws, ns, two, prepare, stripe, prof, ovf, tot, &out.width));
+    STCHK(run_pipelined(g, ws, two, second_groups(g, ns, out.sample_of, G64), prepare, stripe, prof, ovf, tot, &out.width));
     uint64_t t1[C_COUNT];
     STCHK(wcounters(ws, t1));
     for (int j = 0; j < C_COUNT; ++j) tot[j] += t1[j];

@@ -59,6 +59,14 @@ uint64_t sources_per_batch(int64_t m, int weighted, uint64_t ns, uint64_t width)
   return pipelined_batch(&g, ns, width);
 }
 
+// Groups of a run's second workspace (second_groups).
+int second_workspace_groups(int64_t m, int weighted, uint64_t ns, uint64_t sample_of, uint64_t width) {
+  Graph g;
+  g.m = m;
+  g.weighted = weighted != 0;
+  return second_groups(&g, ns, sample_of, width);
+}
+
 // Width of the pooled workspace a lease takes: pool[0 .. k-1] are the widths of
 // the idle ones; 0 = a new one.  lo = 0: a call's own, else a run's second.
 int leased_width(const int *pool, int k, int lo, int hi) {

@@ -192,3 +192,29 @@ def test_workspace_bytes_count_the_heavy_lists(rules, n, m, G):
 def test_lds_engine_takes_short_rows_alone(rules):
     """The LDS engine takes arcs one at a time where no row has more than two."""
     assert [rules.short_rows(C.c_int64(k)) for k in (0, 1, 2, 3, 4, 5000)] == [1, 1, 1, 0, 0, 0]
+
+
+@pytest.mark.parametrize("weighted,m", [(1, 3938872), (0, 16085068), (0, 1000)])
+def test_timed_samples_take_the_second_workspace_of_their_run(rules, weighted, m):
+    """A run's second workspace holds one of its batches.  A sample that the
+    autotuner times in its place takes one as wide as the run's (its own batches
+    can be narrower), so a width whose pair the device cannot hold is timed on one
+    workspace, as it would run; a run of one batch takes none."""
+    f, per = rules.second_workspace_groups, rules.sources_per_batch
+    f.argtypes, f.restype = [C.c_int64, C.c_int, C.c_uint64, C.c_uint64, C.c_uint64], C.c_int
+    per.argtypes, per.restype = [C.c_int64, C.c_int, C.c_uint64, C.c_uint64], C.c_uint64
+    for groups in (1, 3, 16, 128, 256):
+        width = 64 * groups
+        for ns in (1, 64, 65, 2048, 16384, 150000):
+            own = per(m, weighted, ns, width)
+            alone = 0 if ns <= own else -(-own // 64)
+            assert f(m, weighted, ns, 0, width) == alone
+            assert f(m, weighted, ns, ns, width) == alone
+            for whole in (ns + 1, 130 * 64, 150000):
+                if whole < ns:
+                    continue
+                want = max(own, per(m, weighted, whole, width))
+                assert f(m, weighted, ns, whole, width) == (-(-want // 64) if ns > own else 0)
+    # 16,384 of 150,000 sources at 256 groups: two batches of 128 groups, the run's ten have 235
+    if weighted:
+        assert f(m, 1, 16384, 0, 16384) == 128 and f(m, 1, 16384, 150000, 16384) == -(-2344 // 10)
