@@ -117,19 +117,23 @@ def roofline_from_profile(G, fwd: dict, bwd: dict, ename: str, wname: str, batch
     achieved = dom["alg_bytes"] / (busy_ms * 1e-3) / 1e9
     per_launch = dom["alg_bytes"] / (dom["total_ms"] * 1e-3) / 1e9
     sched = dom.get("sched_bytes", 0.0) or 0.0
+    cfg = G.config()
     if G.info()[2]:
         # weighted engine: the forward is three kernels (relaxation rounds, DAG
         # in-degrees, topological rounds), profiled together
         kname = "k_w_relax+k_w_count+k_w_sigma" if kind == "forward" else "k_w_bwd"
     elif ename == "lds":
         kname = "k_lds_pass"  # both passes in one kernel, timed as the forward
-    elif kind == "forward" and bottom_up:
-        kname = "k_fwd_level+k_bu_level"  # a level found bottom-up runs both, timed as two launches
+    elif kind == "forward":
+        kname = "k_fwd_push" if cfg.push else "k_fwd_level"
+        if bottom_up:
+            kname += "+k_bu_level"  # a level found bottom-up runs both, timed as two launches
     else:
-        kname = f"k_{'fwd' if kind == 'forward' else 'bwd'}_level"
+        kname = "k_bwd_level"
     if batch_width is None:
-        batch_width = 64 * G.config().groups if ename == "batched" else 1
-    traffic = measured_traffic(kname, wname, batch_width)
+        batch_width = 64 * cfg.groups if ename == "batched" else 1
+    # the records are of uncompressed runs; compression runs fewer sources
+    traffic = None if cfg.compress else measured_traffic(kname, wname, batch_width)
     per_launch_s = dom["total_ms"] * 1e-3 / dom["launches"]
     out = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4),

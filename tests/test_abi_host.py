@@ -253,3 +253,36 @@ def test_serving_width_fits_budget_and_splits_evenly():
             g = width(w, budget, start=96)
             assert g >= 1 and (g <= 8 or g % 8 == 0)
             assert g == 1 or g * per_group * w <= (budget << 30) * 85 // 100
+
+
+def test_bench_traffic_is_of_the_form_that_ran(monkeypatch):
+    """Counter traffic taken on pulled, uncompressed runs is not given for a run
+    with pushed path counts (another kernel) or with compression (fewer sources)."""
+    sys.path.insert(0, ROOT)
+    import bench
+
+    class Stub:
+        def __init__(self, **over):
+            self.over = over
+
+        def info(self):
+            return 10, 20, False
+
+        def config(self):
+            return bcd.Config(engine=bcd.BCD_ENGINE_BATCHED, groups=2, block=256, grid_mult=32, items=2, **self.over)
+
+    monkeypatch.setattr(bench, "measured_traffic",
+                        lambda kernel, name, width: 7.0 if kernel in ("k_fwd_level", "k_fwd_level+k_bu_level") else None)
+    p = {"launches": 4, "total_ms": 8.0, "union_ms": 5.0, "alg_bytes": 4e10, "vertex_pairs": 300, "items": 100}
+    q = dict(p, total_ms=1.0)
+
+    def line(bu=False, **over):
+        r = bench.roofline_from_profile(Stub(**over), p, q, "batched", "w", bottom_up=bu)
+        return r["kernel"], r["traffic"], "traffic_achieved" in r
+    assert line() == ("k_fwd_level", 7.0, True)
+    assert line(True) == ("k_fwd_level+k_bu_level", 7.0, True)
+    assert line(push=1) == ("k_fwd_push", None, False)
+    assert line(True, push=1) == ("k_fwd_push+k_bu_level", None, False)
+    assert line(compress=1) == ("k_fwd_level", None, False)
+    back = bench.roofline_from_profile(Stub(push=1), q, p, "batched", "w")
+    assert back["kernel"] == "k_bwd_level"
