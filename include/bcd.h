@@ -195,7 +195,7 @@ bcd_status bcd_rv(const bcd_graph *g, bcd_vid r, bcd_vid *out, int64_t cap, int6
  * harnesses that forbid it).  Same arguments, result and errors as bcd_rv.
  * The traversal's working memory (visited bitmap, two frontier queues,
  * counters: 8 bytes per vertex plus n/8) is one static device array of
- * 34,079,000 bytes that each GPU holds from library load until the process
+ * 34,078,976 bytes that each GPU holds from library load until the process
  * ends; graphs of more than 2^22 vertices return BCD_ERR_UNSUPPORTED.  The
  * graph's device must be current.  Calls in one process are serialized on
  * that array by a lock (they run one at a time); each call clears what it

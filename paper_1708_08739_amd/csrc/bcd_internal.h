@@ -11,7 +11,7 @@ constexpr int kLanes = 64;  // sources per column group = wavefront width on gfx
 
 // Lane masks of the unweighted engine: one 64-bit word per (group, vertex) in
 // each of these arrays, which follow each other in BatchState::msk.  A word
-// array keeps 8 vertices to a 64-byte line, and as internal ids run by falling
+// array keeps 16 vertices to a 128-byte line, and as internal ids run by falling
 // degree, the words of the vertices most arcs lead to are neighbours.
 enum MaskArray {
   M_SEEN = 0,  // lanes settled, or flagged for the level being discovered

@@ -179,9 +179,11 @@ __global__ void k_publish_counts(BatchState S, int level) {
 // share the item's steps and add their partial path counts in LDS.  A
 // wavefront alone walks a hub's thousands of arcs as one serial chain of
 // dependent loads, and every level waits for its largest hub.
-// Bound by the latency and rate of random accesses, not by HBM bandwidth (R-MAT
-// 16, 1,000 sources: 56 % of the cycles of resident waves wait for memory, 1
-// TB/s fetched).  A level with two items a step, 64-byte mask records and no
+// Every random 8-byte read asks memory for 128 bytes.  Wide batches are bound by
+// that traffic (over the time any forward launch runs: R-MAT 16 exact 5.1 TB/s,
+// R-MAT 20 in batches of 4,096 sources 6.6, the streaming read probe 5.7), narrow
+// ones by the latency of their accesses (R-MAT 16, 1,000 sources: 56 % of the
+// cycles of resident waves wait for memory, 2 TB/s).  A level with two items a step, 64-byte mask records and no
 // heavy list took, summed over the levels of R-MAT 16 / 20 with 1,000 sources,
 // 3.0 / 36 ms; as here 1.9 / 24.
 // Narrow rows at 8 waves per SIMD (64 VGPRs, 60 bytes of scratch a lane): left

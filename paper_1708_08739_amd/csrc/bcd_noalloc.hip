@@ -29,7 +29,7 @@ constexpr size_t kCtrBytes = 256;  // counters: four frontiers (ReachCtr) from w
 constexpr int kCtrStride = 4, kListWord = 32;
 constexpr size_t kBitmapBytes = (size_t)(kNoAllocMaxN / 32) * 4;  // visited bits
 constexpr size_t kQueueBytes = (size_t)kNoAllocMaxN * 4;          // one frontier queue (int32 ids)
-constexpr size_t kScratchBytes = kCtrBytes + kBitmapBytes + 2 * kQueueBytes;  // 34,079,000 bytes
+constexpr size_t kScratchBytes = kCtrBytes + kBitmapBytes + 2 * kQueueBytes;  // 34,078,976 bytes
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
