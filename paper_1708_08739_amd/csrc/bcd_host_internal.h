@@ -167,11 +167,12 @@ struct Workspace {
   PlainState P{};
   // reachability
   bool reach_ready = false;
+  uint32_t *rqn = nullptr;  // frontier counters (ReachCtr), a line per level mod 4; then the arrays below
   uint32_t *bitmap = nullptr;
   int32_t *rq[2] = {nullptr, nullptr};
-  uint32_t *rqn = nullptr;  // frontier counters (ReachCtr), a line per level mod 4
   int32_t *d_roots = nullptr;  // several roots of one traversal
   size_t roots_cap = 0;
+  uint32_t *h_reach = nullptr;  // the counters, then the bitmap
   uint32_t *h_bitmap = nullptr;
   // host staging
   uint32_t *h_cnt = nullptr;

@@ -115,7 +115,7 @@ static bcd_status reach_bitmap(Graph *g, Workspace *ws, const int32_t *roots, in
     for (int i = 0; i < chunk; ++i, ++level)
       HIPCHK(launch_reach_level(rp, col, rpo, colo, ws->bitmap, ws->rq[0], ws->rq[1], ctr, d_lev, (int)level, n, bu_arcs,
                                 L, st));
-    uint32_t *h = reinterpret_cast<uint32_t *>(ws->h_misc);
+    uint32_t *h = ws->h_reach;
     HIPCHK(hipMemcpyAsync(h, ctr.c, (size_t)4 * kTailStride * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     have = reach_copies_bitmap(level, chunk, words * sizeof(uint32_t));
     if (have) HIPCHK(hipMemcpyAsync(ws->h_bitmap, ws->bitmap, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));

@@ -1221,3 +1221,20 @@ def test_lds_engine_on_short_rows(B, oracle, rows):
     want = {1: (g.n - 1) * (g.n - 2) / 2, 2: 2 * 300 * (g.n - 301), 3: None}[rows]
     got, _ = G.bc_exact(300)
     assert got == H.bc_exact(300)[0] and (want is None or got == want)
+
+
+@pytest.mark.parametrize("n", [65_536, 65_537, 66_559, 66_560, 66_591])
+def test_reach_arrays_hold_a_full_frontier(B, oracle, n):
+    """A traversal whose one frontier holds every other vertex fills its queue and
+    its bitmap to the last word (the traversal's arrays are one allocation), first
+    from one queue, then from the other, and narrow searches after it still agree."""
+    i = np.arange(2, n)
+    g = gg.from_arcs(n, np.concatenate([i, [1]]), np.concatenate([np.ones(n - 2, np.int64), [0]]), name="in-star")
+    G = dev(B, g)
+    for _ in range(2):
+        for r in (1, 0, n - 1, 0, 1):
+            want = {1: n - 2, 0: n - 1}.get(r, 0)
+            rv = G.rv(r)
+            assert rv.size == want and np.array_equal(rv, oracle.rv(g, r)), r
+    # the same arrays from a run's hub distances on (levels kept) and a reach count
+    assert np.array_equal(G.dependencies(1, list(range(2, 130))), oracle.dependencies(g, 1, list(range(2, 130)))[0])
